@@ -206,7 +206,6 @@ int ckpt_init(const ckpt_config *cfg, ckpt_ctx **out) {
     HIP_TRY(nullptr, hipGetDeviceCount(&ndev));
     if (cfg->device < 0 || cfg->device >= ndev) return fail(CKPT_EINVAL, "config: no such device");
     HIP_TRY(nullptr, hipSetDevice(cfg->device));
-    if ((r = pack_scratch_setup()) != CKPT_OK) return r;   // the static table of ckpt_pack_image_noalloc on this device
 
     std::unique_ptr<ckpt_ctx> c(new ckpt_ctx);
     c->cfg = rc;
@@ -225,6 +224,7 @@ int ckpt_init(const ckpt_config *cfg, ckpt_ctx **out) {
         if ((e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking)) != hipSuccess) return cleanup_fail(CKPT_EHIP, hipGetErrorString(e));
         c->dma.push_back(s);
     }
+    if ((r = pack_image_setup(c->pack_stream)) != CKPT_OK) return cleanup_fail(r, g_last_error);   // the kernels' code is loaded from here on
     trace("init: streams created");
     for (uint64_t i = 0; i < c->n_slots; i++) {
         hipEvent_t ev;

@@ -262,7 +262,7 @@ void tier2_thread_main(ckpt_ctx *c);
 // submit.cpp
 void submit_thread_main(ckpt_ctx *c);
 // pack_image.hip
-int pack_scratch_setup();
+int pack_image_setup(hipStream_t stream);
 // engine.cpp
 int take_async_error(ckpt_ctx *c);
 bool preallocate_file(const std::string &path, uint64_t bytes, int n_threads, bool map_it, bool o_direct, FileSlot *out, std::string *err);

@@ -72,6 +72,25 @@ __device__ __forceinline__ u32x4 keep_bytes(u32x4 v, uint32_t keep) {
 
 // ---------------------------------------------------------------- pack: tensors -> staging
 
+// The 16-byte word that holds a tensor's last bytes: `tail` (1..15) bytes from `addr` on, then zeros. It never comes from
+// an unaligned load (that would read up to 15 bytes past the tensor, possibly into an unmapped page): it is put
+// together from the one or two aligned words that hold those bytes.
+__device__ __forceinline__ u32x4 tail_word(uint64_t addr, uint32_t tail) {
+    const uint32_t sh = uint32_t(addr) & 15, b = sh & 3;
+    const u32x4 *s = reinterpret_cast<const u32x4 *>(addr - sh);
+    u32x4 v = ld16(s);
+    if (sh != 0) {
+        const u32x4 w1 = (sh + tail > 16) ? ld16(s + 1) : u32x4{0, 0, 0, 0};
+        switch (sh >> 2) {
+            case 0: v = funnel<0>(v, w1, b); break;
+            case 1: v = funnel<1>(v, w1, b); break;
+            case 2: v = funnel<2>(v, w1, b); break;
+            default: v = funnel<3>(v, w1, b); break;
+        }
+    }
+    return keep_bytes(v, tail);
+}
+
 // Output word j (16 bytes, aligned) = the 16 bytes at su + 16 j: one group of 64 U words starting at word g, every
 // load of the group issued before its first store. su may have any alignment: the target supports unaligned vector
 // loads (a 16-byte load at a 2-byte-aligned address is a single global_load_dwordx4), and all 16 bytes of every
@@ -135,32 +154,15 @@ __device__ __forceinline__ void pack_range(uint64_t src, u32x4 *dst, uint32_t co
     const uint32_t n_total = total_bytes >> 4;   // 16-byte words to write
     const uint32_t n_full = copy_bytes >> 4;     // of which fully covered by source bytes
     const uint32_t tail = copy_bytes & 15;       // source bytes in word n_full
-    const uint32_t sh = uint32_t(src) & 15;
     if (hi > n_total) hi = n_total;
     if (lo >= hi) return;
     const uint32_t c_hi = hi < n_full ? hi : n_full;            // copy words [lo, c_hi)
     const uint32_t n = c_hi > lo ? c_hi - lo : 0;
     const bool own_tail = tail && lo <= n_full && n_full < hi;  // the range that holds word n_full writes the tail
-    const u32x4 *s = reinterpret_cast<const u32x4 *>(src - sh); // the aligned words that cover the tile's source bytes
-    const uint32_t b = sh & 3;
 
     // the n words that lie wholly inside the tensor, read at the tensor's own (possibly misaligned) addresses
     copy_rolling(reinterpret_cast<const uint8_t *>(src) + 16ull * lo, dst + lo, n, lane);
-    if (own_tail && lane == 0) {
-        // The tail word never comes from an unaligned load (that would read up to 15 bytes past the tensor, possibly
-        // into an unmapped page): aligned word n_full holds source bytes, word n_full + 1 only if sh + tail > 16.
-        u32x4 v = ld16(s + n_full);
-        if (sh != 0) {
-            const u32x4 w1 = (sh + tail > 16) ? ld16(s + n_full + 1) : u32x4{0, 0, 0, 0};
-            switch (sh >> 2) {
-                case 0: v = funnel<0>(v, w1, b); break;
-                case 1: v = funnel<1>(v, w1, b); break;
-                case 2: v = funnel<2>(v, w1, b); break;
-                default: v = funnel<3>(v, w1, b); break;
-            }
-        }
-        st16(dst + n_full, keep_bytes(v, tail));
-    }
+    if (own_tail && lane == 0) st16(dst + n_full, tail_word(src + 16ull * n_full, tail));
     // zero padding after the tensor's last byte
     const uint32_t z0 = n_full + (tail ? 1u : 0u);
     for (uint32_t i = (z0 > lo ? z0 : lo) + lane; i < hi; i += 64) st16(dst + i, u32x4{0, 0, 0, 0});
@@ -182,6 +184,35 @@ __global__ __launch_bounds__(kBlock) void pack_kernel(const ckpt_tile *__restric
     const uint64_t dst_off = uniform_u64(tp->dst_off);
     u32x4 *dst = reinterpret_cast<u32x4 *>(slot_base + (dst_off - slot_data_off));
     pack_range(src, dst, uniform_u32(tp->copy_bytes), uniform_u32(tp->total_bytes), 0, uint32_t(kPackTileBytes / 16), lane);
+}
+
+// The image of up to kPackBatch pieces of tensors without a tile table: the pieces travel in the kernel arguments. The
+// image is a sequence of 4 KiB pages, each of one piece only; a block of ONE wave writes one KiB of one page, 16 bytes
+// per lane, and finds its piece by bisection over the pieces' first pages (scalar loads of the argument segment, nine
+// steps at most, the same cache lines for every wave of a compute unit).
+//
+// HBM-bound. What limits a copy here is the order in which requests reach the memory: with one load and one store per
+// lane and blocks that are handed out in address order, the whole chip sweeps source and image in one narrow front.
+// Measured on MI355X, read + write: 6.76 TB/s on 11 GB of large aligned tensors, 6.5 on 1.7 GB in 592 tensors, 6.1 on
+// 3.7 GB of misaligned fragments, where a wave that walks 32 KiB on its own (pack_kernel, and a kernel that writes its
+// table before it) reaches 5.73, 5.47 and 5.13. More words per lane widen the front and lose (2: 5.3 to 6.1; 4: 5.9 to
+// 6.1), four waves per block lose 5 % on aligned tensors (6.43) and win 1 % on fragments. On small lists the table was
+// the cost: 112 tensors of 0.4 MB took three kernels, 28 us back to back, and take one, 6 us.
+__global__ __launch_bounds__(64) void pack_batch_kernel(PackBatch bt, uint8_t *__restrict__ image) {
+    const uint32_t page = blockIdx.x / 4, at = (blockIdx.x % 4) * 1024 + 16 * threadIdx.x;
+    uint32_t lo = 0, hi = bt.count;
+    if (page >= bt.first_page[hi]) return;
+    while (hi - lo > 1) {
+        const uint32_t mid = (lo + hi) / 2;
+        if (bt.first_page[mid] <= page) lo = mid;
+        else hi = mid;
+    }
+    const uint64_t src = bt.src(lo) + kPackPage * (page - bt.first_page[lo]);
+    const uint32_t copy_bytes = page + 1 == bt.first_page[lo + 1] ? uint32_t(kPackPage) - bt.pad(lo) : uint32_t(kPackPage);
+    u32x4 v = {0, 0, 0, 0};                                    // padding behind the tensor's last byte
+    if (at + 16 <= copy_bytes) v = ld16_unaligned(reinterpret_cast<const uint8_t *>(src + at));
+    else if (at < copy_bytes) v = tail_word(src + at, copy_bytes - at);
+    st16(reinterpret_cast<u32x4 *>(image + kPackPage * page + at), v);
 }
 
 // ---------------------------------------------------------------- scatter: staging -> tensors
@@ -266,7 +297,8 @@ __global__ __launch_bounds__(kBlock) void scatter_kernel(const ckpt_tile *__rest
 // ---------------------------------------------------------------- tile table built on the device
 
 // The tile table of a tensor list, written by the device itself: one block per tensor, one thread per
-// tile. The descriptors travel in the kernel arguments (a batch of up to kTileBatch tensors per
+// tile. ckpt_pack_image used to walk such a table (pack_batch_kernel needs none); it stays as the second, independent
+// construction that the planner's table is compared with. The descriptors travel in the kernel arguments (a batch of up to kTileBatch tensors per
 // launch), so nothing is copied from host memory and the launch can be recorded like any other.
 // Tile i of a tensor whose padded extent is [d0, dend) of the data region: the extent is cut at its
 // start and at every multiple of the tile size, exactly as the host planner cuts it.
@@ -299,6 +331,14 @@ __global__ __launch_bounds__(256) void build_tiles_kernel(TileBatch bt, ckpt_til
 hipError_t launch_build_tiles(const TileBatch &bt, ckpt_tile *dev_table, hipStream_t stream) {
     if (bt.count == 0) return hipSuccess;
     hipLaunchKernelGGL(build_tiles_kernel, dim3(bt.count), dim3(256), 0, stream, bt, dev_table);
+    return hipGetLastError();
+}
+
+// Writes the pieces of `bt` to `image`, which begins with the page of the batch's first piece. A batch without pieces
+// launches one block that finds nothing to do (it makes the runtime load the kernels' code).
+hipError_t launch_pack_batch(const PackBatch &bt, void *image, hipStream_t stream) {
+    const uint32_t pages = bt.first_page[bt.count];
+    hipLaunchKernelGGL(pack_batch_kernel, dim3(pages ? pages * 4 : 1), dim3(64), 0, stream, bt, static_cast<uint8_t *>(image));
     return hipGetLastError();
 }
 
