@@ -5,6 +5,8 @@
 #include <stdio.h>
 #include <stdint.h>
 
+#include <utility>
+
 #include "../../include/ckpt_proxy.h"
 
 namespace {
@@ -12,7 +14,7 @@ namespace {
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 // ------------------------------------------------------------------ counter-based random numbers
@@ -125,128 +127,270 @@ __global__ __launch_bounds__(256) void devcopy_kernel(u32x4 *__restrict__ dst, c
 
 // ------------------------------------------------------------------ bf16 GEMM on the matrix cores
 
-// Block tile (64 T) x (64 T), K step BK, 256 threads = 4 wavefronts in a 2x2 arrangement, each computing a
-// (32 T) x (32 T) sub-tile as T x T MFMA 32x32x16 tiles. Both operands are K-contiguous, so an A or B
-// fragment (8 consecutive K values of one row/column per lane) is one 16-byte LDS read. LDS rows are
-// padded by 16 bytes (80 bytes for BK = 32, 144 for BK = 64), which spreads the 16-byte reads of 16
-// consecutive rows over all banks.
+// Both kernels below compute C = A * B^T tile by tile with MFMA 16x16x32 (the 32x32x16 form does the same work at a
+// higher power: at 8192^3 the card held 1.71 GHz with it at 74 % of the matrix pipe's cycles, and holds 1.76 GHz with
+// this one at 82 %). Operand panels go from memory to LDS without passing through registers (buffer loads to LDS, 16
+// bytes per lane, counted by vmcnt), 64 K values a step, so that every request is a whole 128-byte line.
 //
-// T = 2, BK = 32 (128 x 128 block, 64 accumulator registers per lane, three blocks per CU) is LDS-bound: per
-// MFMA one fragment read, and with the stores of the next tile the LDS pipe is busier than the matrix pipe.
-// T = 4, BK = 64 (256 x 256 block, 144 KiB of LDS, one block per CU, one wave per SIMD, 256 accumulator
-// registers per lane) halves the reads per MFMA: eight fragment reads feed sixteen MFMAs and LDS traffic is
-// about three quarters of the matrix pipe's time. With one wave per SIMD no other wave hides a wait, so the
-// loop is software-pipelined by hand: the fragments of K slice kk+1 are read while the MFMAs of slice kk run,
-// the next tile's LDS stores go under the last slice's MFMAs, and scheduling fences keep that order.
-template <int T, int BK>
-__global__ __launch_bounds__(256) void gemm_bf16_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B,
-                                                       uint16_t *__restrict__ C, int M, int N, int K) {
-    constexpr int BM = 64 * T, BN = 64 * T, WT = 32 * T;   // block tile and one wave's share of it
-    constexpr int LDS_ROW = BK + 8;                        // in bf16 elements: rows padded by 16 bytes (80 or 144 bytes per row)
-    constexpr int PIECES = BK / 8;                         // 16-byte pieces per row of a K step
-    constexpr int ROWS_PER_PASS = 256 / PIECES, PASSES = BM / ROWS_PER_PASS;
-    __shared__ __attribute__((aligned(16))) uint16_t lds_a[2][BM * LDS_ROW];
-    __shared__ __attribute__((aligned(16))) uint16_t lds_b[2][BN * LDS_ROW];
+// LDS layout of a panel: rows of 64 K values, 128 bytes, eight 16-byte pieces; row r keeps piece p at place p ^ f(r), so
+// that the rows a fragment read touches lie in different banks (no conflicts measured). The loads write LDS in lane
+// order, so the permutation is made on the global side: a lane fetches the piece that belongs at its place.
+// A fragments hold 16 consecutive rows, f(r) = bits 1..3 of r. B fragments come in pairs that hold 32 rows as
+// 8 (lane / 4) + lane % 4 and that + 4, f(r) = bits 1, 3, 4: with B as the first operand a lane then ends up with eight
+// consecutive columns of one row of C, one 16-byte store (8-byte stores of 32-byte pieces cost 3 % of the whole).
+#define DSLLM_LDS __attribute__((address_space(3)))
+#define DSLLM_GLB __attribute__((address_space(1)))
 
-    // consecutive block ids go to different XCDs (8 of them, each with its own L2): give each XCD a
-    // contiguous range of tiles, walked in strips 8 tiles tall so that neighbours share A and B panels
-    const int tiles_m = M / BM, tiles_n = N / BN, n_tiles = tiles_m * tiles_n;
+struct GemmTile { int tm, tn; };
+
+// Consecutive block ids go to different XCDs (8 of them, each with its own L2): gives each XCD a contiguous range of
+// tiles, walked in strips 8 tiles tall so that neighbours share A and B panels.
+__device__ __forceinline__ GemmTile gemm_tile(int tiles_m, int tiles_n) {
+    const int n_tiles = tiles_m * tiles_n;
     int bid = blockIdx.x;
     if (n_tiles % 8 == 0) bid = (bid % 8) * (n_tiles / 8) + bid / 8;
     const int strip = 8;
     const int per_strip = strip * tiles_n;
     const int s = bid / per_strip, in_s = bid % per_strip;
     const int rows_here = (tiles_m - s * strip) < strip ? (tiles_m - s * strip) : strip;
-    const int tm = s * strip + in_s % rows_here, tn = in_s / rows_here;
+    return GemmTile{s * strip + in_s % rows_here, in_s / rows_here};
+}
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
-    const uint16_t *a_blk = A + size_t(tm) * BM * K;
-    const uint16_t *b_blk = B + size_t(tn) * BN * K;
+// One wave's eight rows of a panel per instruction; NW waves share a panel. WIDE: 64-bit addresses, for panels that a
+// buffer resource's 32-bit offsets do not span.
+template <int BM, int BN, int NW, bool WIDE>
+struct PanelLoader {
+    static constexpr int LA = BM / 8 / NW, LB = BN / 8 / NW, COUNT = LA + LB;   // instructions per wave and step
+    static_assert(LA * 8 * NW == BM && LB * 8 * NW == BN && NW % 4 == 0, "panels divide among the waves, four waves' rows per 32");
+    const uint16_t *a, *b;
+    __amdgpu_buffer_rsrc_t ra, rb;
+    uint32_t row0, piece_a, piece_b, k, wave;
 
-    // global -> LDS staging: thread t moves 16 bytes of row (t / PIECES + ROWS_PER_PASS * pass), K offset 8 * (t % PIECES)
-    const int ld_row = tid / PIECES, ld_col = (tid % PIECES) * 8;
-    u32x4 ra[PASSES], rb[PASSES];
-    auto load_tile = [&](int kt) {
-#pragma unroll
-        for (int ps = 0; ps < PASSES; ps++) {
-            ra[ps] = *reinterpret_cast<const u32x4 *>(a_blk + size_t(ld_row + ROWS_PER_PASS * ps) * K + kt * BK + ld_col);
-            rb[ps] = *reinterpret_cast<const u32x4 *>(b_blk + size_t(ld_row + ROWS_PER_PASS * ps) * K + kt * BK + ld_col);
+    __device__ __forceinline__ PanelLoader(const uint16_t *a_panel, const uint16_t *b_panel, int K, int lane, int wave_)
+        : a(a_panel), b(b_panel), row0((lane >> 3) + 8 * wave_), piece_a((lane & 7) ^ ((4 * (wave_ & 1) + (lane >> 4)) & 7)),
+          piece_b((lane & 7) ^ (((lane >> 4) & 1) | ((wave_ & 3) << 1))), k(uint32_t(K)), wave(wave_) {
+        if constexpr (!WIDE) {
+            ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(a), 0, uint32_t(BM) * 2u * k, 0x00020000);
+            rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(b), 0, uint32_t(BN) * 2u * k, 0x00020000);
         }
-    };
-    auto store_tile = [&](int buf) {
-#pragma unroll
-        for (int ps = 0; ps < PASSES; ps++) {
-            *reinterpret_cast<u32x4 *>(&lds_a[buf][(ld_row + ROWS_PER_PASS * ps) * LDS_ROW + ld_col]) = ra[ps];
-            *reinterpret_cast<u32x4 *>(&lds_b[buf][(ld_row + ROWS_PER_PASS * ps) * LDS_ROW + ld_col]) = rb[ps];
+    }
+    // instruction i of step kt into the stage at lds (A panel, then B panel)
+    __device__ __forceinline__ void issue(uint16_t *lds, int kt, int i) const {
+        const bool of_a = i < LA;
+        uint16_t *place = lds + (of_a ? 0 : BM * 64) + (of_a ? i : i - LA) * 512 * NW + 512 * wave;
+        const uint32_t piece = of_a ? piece_a : piece_b;
+        const int j = of_a ? i : i - LA;
+        if constexpr (WIDE) {
+            const uint16_t *p = (of_a ? a : b) + size_t(row0 + 8 * NW * j) * k + size_t(kt) * 64 + 8 * piece;
+            __builtin_amdgcn_global_load_lds((const DSLLM_GLB void *)p, (DSLLM_LDS void *)place, 16, 0, 0);
+        } else {
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(of_a ? ra : rb, (DSLLM_LDS void *)place, 16, 2 * (row0 * k + 8 * piece), 16 * NW * j * k + 128 * kt, 0, 0);
         }
+    }
+};
+
+// This wave's loads are in LDS but for the latest N, its LDS reads are over, and every wave of the block is here.
+template <int N>
+__device__ __forceinline__ void wait_loads_and_meet() {
+    static_assert(N >= 0 && N < 64, "vmcnt has six bits");
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
+
+__device__ __forceinline__ void store_columns(uint16_t *c, f32x4 lo, f32x4 hi) {
+    const bf16x4 a = __builtin_convertvector(lo, bf16x4), b = __builtin_convertvector(hi, bf16x4);
+    *reinterpret_cast<bf16x8 *>(c) = __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
+// Small and middle-sized products. A wave computes (16 TM) x (16 TN), WM x WN waves a block tile; KG such groups of
+// waves share the tile, each taking every KG-th step of K, and their sums are added in LDS at the end (in group order:
+// the result does not depend on timing). NST steps are in LDS; the loads of a step go out NST - 1 steps ahead.
+template <int TM, int TN, int WM, int WN, int KG, int NST, bool WIDE = false>
+__global__ __launch_bounds__(64 * WM * WN * KG) void gemm_bf16_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B,
+                                                                     uint16_t *__restrict__ C, int M, int N, int K) {
+    constexpr int BM = 16 * TM * WM, BN = 16 * TN * WN, NW = WM * WN, STEP = (BM + BN) * 64;
+    typedef PanelLoader<BM, BN, NW, WIDE> Loader;
+    static_assert(TN % 2 == 0, "B fragments come in pairs");
+    static_assert((KG - 1) * BM * BN * 4 <= NST * KG * STEP * 2, "the partial sums fit where the panels were");
+    __shared__ __attribute__((aligned(1024))) uint16_t lds[NST * KG * STEP];
+    const GemmTile t = gemm_tile(M / BM, N / BN);
+    const int lane = threadIdx.x & 63, wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wave = wave_all % NW, group = wave_all / NW;
+    const int wm = wave / WN, wn = wave % WN;
+    const Loader load(A + size_t(t.tm) * BM * K, B + size_t(t.tn) * BN * K, K, lane, wave);
+    const int steps64 = K / 64, steps = (steps64 + KG - 1) / KG;
+    const bool in_last = (steps - 1) * KG + group < steps64;      // whether this group has a part of the last step
+    auto issue = [&](int step, int stage) {
+        if (step >= steps || (step == steps - 1 && !in_last)) return;
+#pragma unroll
+        for (int i = 0; i < Loader::COUNT; i++) load.issue(lds + (stage * KG + group) * STEP, step * KG + group, i);
     };
-
-    f32x16 acc[T][T];
+    const int ar = lane & 15, br = 8 * (ar >> 2) + (ar & 3);
+    int at_a[2], at_b[2];
 #pragma unroll
-    for (int i = 0; i < T; i++)
+    for (int h = 0; h < 2; h++) {
+        at_a[h] = (16 * TM * wm + ar) * 64 + 8 * ((4 * h + (lane >> 4)) ^ ((ar >> 1) & 7));
+        at_b[h] = (BM + 16 * TN * wn + br) * 64 + 8 * ((4 * h + (lane >> 4)) ^ (((ar >> 1) & 1) | ((ar >> 2) << 1)));
+    }
+    f32x4 acc[TM][TN];
 #pragma unroll
-        for (int j = 0; j < T; j++)
+    for (int i = 0; i < TM; i++)
 #pragma unroll
-            for (int r = 0; r < 16; r++) acc[i][j][r] = 0.0f;
-
-    const int KT = K / BK;
-    load_tile(0);
-    store_tile(0);
-    __syncthreads();
-    const int frag_row = lane & 31, frag_k = (lane >> 5) * 8;
-    bf16x8 fa[2][T], fb[2][T];          // two sets: the fragments of the next K slice are read while this slice's MFMAs run
-    auto read_frags = [&](int set, int buf, int kk) {
+        for (int j = 0; j < TN; j++) acc[i][j] = f32x4{0, 0, 0, 0};
 #pragma unroll
-        for (int i = 0; i < T; i++) {
-            fa[set][i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(&lds_a[buf][(wm * WT + i * 32 + frag_row) * LDS_ROW + kk * 16 + frag_k]));
-            fb[set][i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(&lds_b[buf][(wn * WT + i * 32 + frag_row) * LDS_ROW + kk * 16 + frag_k]));
+    for (int s = 0; s < NST - 1; s++) issue(s, s);
+    int stage = 0, next = NST - 1;
+    for (int step = 0; step < steps; step++) {
+        // steps step+1 .. step+NST-2 may still be under way; near the end (where a group may lack the last one) nothing may
+        if (steps - 1 - step >= NST - 2 + (KG > 1 ? 1 : 0)) wait_loads_and_meet<(NST - 2) * Loader::COUNT>();
+        else wait_loads_and_meet<0>();
+        issue(step + NST - 1, next);                 // over the stage every wave has just finished reading
+        next = next + 1 == NST ? 0 : next + 1;
+        if (step == steps - 1 && !in_last) break;
+        const uint16_t *p = lds + (stage * KG + group) * STEP;
+        bf16x8 fa[2][TM], fb[2][TN];
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+#pragma unroll
+            for (int j = 0; j < TN; j++) fb[h][j] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(p + at_b[h] + (j >> 1) * 2048 + (j & 1) * 256));
+#pragma unroll
+            for (int i = 0; i < TM; i++) fa[h][i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(p + at_a[h] + i * 1024));
         }
-    };
-    // The scheduler, left alone, sinks every fragment read to just before the MFMA that uses it and waits for it
-    // there: with one wave per SIMD nothing hides that LDS latency. The fences below keep the order written
-    // here: the reads of slice kk+1 are issued, then the MFMAs of slice kk run while those reads are in flight.
-    read_frags(0, 0, 0);
-    for (int kt = 0; kt < KT; kt++) {
-        const int buf = kt & 1;
-        if (kt + 1 < KT) load_tile(kt + 1);
 #pragma unroll
-        for (int kk = 0; kk < BK / 16; kk++) {
-            if (kk + 1 < BK / 16) read_frags((kk + 1) & 1, buf, kk + 1);
-            // the next tile goes to the other LDS buffer (whose readers left at the previous barrier) under the
-            // last slice's MFMAs
-            if (kk + 1 == BK / 16 && kt + 1 < KT) store_tile(buf ^ 1);
-            __builtin_amdgcn_sched_barrier(0);
+        for (int h = 0; h < 2; h++)
 #pragma unroll
-            for (int i = 0; i < T; i++)
+            for (int i = 0; i < TM; i++)
 #pragma unroll
-                for (int j = 0; j < T; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[kk & 1][i], fb[kk & 1][j], acc[i][j], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
+                for (int j = 0; j < TN; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[h][j], fa[h][i], acc[i][j], 0, 0, 0);
+        stage = stage + 1 == NST ? 0 : stage + 1;
+    }
+    if constexpr (KG > 1) {
+        f32x4 *part = reinterpret_cast<f32x4 *>(lds);
+        __syncthreads();
+        if (group > 0) {
+#pragma unroll
+            for (int i = 0; i < TM * TN; i++) part[(((group - 1) * NW + wave) * TM * TN + i) * 64 + lane] = acc[i / TN][i % TN];
         }
         __syncthreads();
-        if (kt + 1 < KT) read_frags(0, buf ^ 1, 0);
+        if (group > 0) return;
+#pragma unroll
+        for (int g = 0; g < KG - 1; g++)
+#pragma unroll
+            for (int i = 0; i < TM * TN; i++) acc[i / TN][i % TN] += part[((g * NW + wave) * TM * TN + i) * 64 + lane];
     }
+    uint16_t *c = C + (size_t(t.tm) * BM + wm * 16 * TM + ar) * N + size_t(t.tn) * BN + wn * 16 * TN + 8 * (lane >> 4);
+#pragma unroll
+    for (int i = 0; i < TM; i++)
+#pragma unroll
+        for (int j = 0; j < TN; j += 2) store_columns(c + size_t(16 * i) * N + 16 * j, acc[i][j], acc[i][j + 1]);
+}
 
-    // accumulator register r of lane l is C[8*(r/4) + 4*(l/32) + r%4][l%32] of its 32x32 tile
-    uint16_t *c_blk = C + size_t(tm) * BM * N + size_t(tn) * BN;
+template <class F, int... I>
+__device__ __forceinline__ void for_each_of(F f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
+
+// Large products: a 256 x 256 block tile, four waves of 128 x 128 each, ONE wave per SIMD: LDS would be the limit
+// otherwise (fragment reads and panel writes take 75 % of its cycles with this split, all of them with eight waves).
+// Nothing hides a wait but the wave's own order, so the order is fixed by hand: a step of 64 K values is 128 MFMAs, and
+// between them, at the places given below, go the 32 fragment reads and the 16 panel loads. Two stages of LDS:
+//   at MFMA 40  every wave has read its second half's fragments of this step: the stage is free, and the loads of
+//               step + 2 into it start, one per four MFMAs (64 bytes a cycle, what a compute unit takes);
+//   at MFMA 96  the loads of step + 1 have landed for all (the fourteen of step + 2 issued so far may be under way), and
+//               the fragments of its first half are read under the rest of this step.
+// A load thus has 2000 cycles and more before it is waited for. The accumulators are named as AGPRs in the MFMA's own
+// operands: left to itself the compiler moves them to and fro between the two register files inside the loop.
+// Measured at 8192^3: 1.08 ms = 1015 TFLOP/s before (one 32x32x16 kernel, panels through registers, a load's latency
+// exposed in every step), 0.72 ms = 1520 now, both sides in turn on one card; 384 registers per lane, which leaves room
+// beside it on a SIMD for two waves of the pack kernel.
+__global__ __launch_bounds__(256) void gemm_bf16_256_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B, uint16_t *__restrict__ C,
+                                                           int M, int N, int K) {
+    constexpr int T = 8, NW = 4, BM = 256, BN = 256, STEP = (BM + BN) * 64, FRAGS = 2 * T, HALF = T * T;
+    constexpr int FREE_AT = 40, LOAD_EVERY = 4, LANDED_AT = 96, READ_EVERY = 2;
+    typedef PanelLoader<BM, BN, NW, false> Loader;
+    constexpr int issued_when_landed = (LANDED_AT - FREE_AT + LOAD_EVERY - 1) / LOAD_EVERY;
+    static_assert((FRAGS - 1) * READ_EVERY < FREE_AT && LANDED_AT + (FRAGS - 1) * READ_EVERY < 2 * HALF, "reads lie inside their half");
+    static_assert(FREE_AT + (Loader::COUNT - 1) * LOAD_EVERY < 2 * HALF && issued_when_landed <= Loader::COUNT, "loads lie inside the step");
+    __shared__ __attribute__((aligned(1024))) uint16_t lds[2 * STEP];
+    const GemmTile t = gemm_tile(M / BM, N / BN);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wm = wave >> 1, wn = wave & 1;
+    const Loader load(A + size_t(t.tm) * BM * K, B + size_t(t.tn) * BN * K, K, lane, wave);
+    const int ar = lane & 15, br = 8 * (ar >> 2) + (ar & 3);
+    int at_a[2], at_b[2];
+#pragma unroll
+    for (int h = 0; h < 2; h++) {
+        at_a[h] = (16 * T * wm + ar) * 64 + 8 * ((4 * h + (lane >> 4)) ^ ((ar >> 1) & 7));
+        at_b[h] = (BM + 16 * T * wn + br) * 64 + 8 * ((4 * h + (lane >> 4)) ^ (((ar >> 1) & 1) | ((ar >> 2) << 1)));
+    }
+    bf16x8 frag[2][FRAGS];      // [half of the step]: B fragments first, then A
+    auto read = [&](int half, int stage, int i) {
+        const uint16_t *p = lds + stage * STEP + (i < T ? at_b[half] + (i >> 1) * 2048 + (i & 1) * 256 : at_a[half] + (i - T) * 1024);
+        frag[half][i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(p));
+    };
+    f32x4 acc[T][T];
 #pragma unroll
     for (int i = 0; i < T; i++)
 #pragma unroll
-        for (int j = 0; j < T; j++) {
-#if defined(__HIP_DEVICE_COMPILE__)
-            asm volatile("" : "+a"(acc[i][j]));      // this tile stays in its accumulator registers up to here
-#endif
+        for (int j = 0; j < T; j++) acc[i][j] = f32x4{0, 0, 0, 0};
+    const int steps = K / 64;
+    asm volatile("s_nop 7");    // accumulators written by ordinary instructions, read by the asm below
 #pragma unroll
-            for (int r = 0; r < 16; r++) {
-                const int row = wm * WT + i * 32 + 8 * (r / 4) + 4 * (lane >> 5) + (r % 4);
-                const int col = wn * WT + j * 32 + (lane & 31);
-                c_blk[size_t(row) * N + col] = bf16_rne(acc[i][j][r]);
-            }
-            // one 32x32 tile at a time: without the pin above and this fence all accumulators are copied out at
-            // once, the kernel then holds 256 + 256 registers per lane and no other wave fits on its SIMD
+    for (int i = 0; i < Loader::COUNT; i++) load.issue(lds, 0, i);
+#pragma unroll
+    for (int i = 0; i < Loader::COUNT; i++) load.issue(lds + STEP, steps > 1 ? 1 : 0, i);
+    wait_loads_and_meet<Loader::COUNT>();
+#pragma unroll
+    for (int i = 0; i < FRAGS; i++) read(0, 0, i);
+    for (int step = 0; step < steps; step++) {
+        const int stage = step & 1;
+        const int ahead = step + 2 < steps ? step + 2 : steps - 1;    // past the end: the last step again, into a stage nothing reads
+        for_each_of([&](auto index) {
+            constexpr int at = index, half = at / HALF, i = at % HALF / T, j = at % T;
+            if constexpr (at == FREE_AT) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            if constexpr (at == LANDED_AT) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(issued_when_landed) : "memory");
+            asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[i][j]) : "v"(frag[half][j]), "v"(frag[half][T + i]));
+            if constexpr (at < HALF && at % READ_EVERY == 0 && at / READ_EVERY < FRAGS) read(1, stage, at / READ_EVERY);
+            if constexpr (at >= LANDED_AT && (at - LANDED_AT) % READ_EVERY == 0 && (at - LANDED_AT) / READ_EVERY < FRAGS)
+                read(0, stage ^ 1, (at - LANDED_AT) / READ_EVERY);
+            if constexpr (at >= FREE_AT && (at - FREE_AT) % LOAD_EVERY == 0 && (at - FREE_AT) / LOAD_EVERY < Loader::COUNT)
+                load.issue(lds + stage * STEP, ahead, (at - FREE_AT) / LOAD_EVERY);
+            __builtin_amdgcn_sched_barrier(0);
+        }, std::make_integer_sequence<int, 2 * HALF>{});
+    }
+    // the last MFMAs' results are readable, and no load to LDS outlives the block
+    asm volatile("s_nop 15\n\ts_nop 15\n\ts_waitcnt vmcnt(0)" ::: "memory");
+    uint16_t *c = C + (size_t(t.tm) * BM + wm * 16 * T + ar) * N + size_t(t.tn) * BN + wn * 16 * T + 8 * (lane >> 4);
+#pragma unroll
+    for (int i = 0; i < T; i++)
+#pragma unroll
+        for (int j = 0; j < T; j += 2) {
+            asm volatile("" : "+a"(acc[i][j]), "+a"(acc[i][j + 1]));      // in their registers up to here: copied out all at once they would spill
+            store_columns(c + size_t(16 * i) * N + 16 * j, acc[i][j], acc[i][j + 1]);
             __builtin_amdgcn_sched_barrier(0);
         }
 }
+
+// Which kernel and tile. Times are for one product on an MI355X, before (128 x 128 tiles with panels through registers,
+// one step ahead) and now.
+//  * 256 x 256 from 192 tiles on (three quarters of the 256 compute units): 3072 x 4096 x 2048 71 -> 48 us (128 x 128: 55);
+//    at 128 tiles 128 x 128 wins (2048 x 4096 x 4096: 63 against 72, 88 before). Below K = 256 its 128 KiB prologue shows.
+//  * 128 x 128 in four waves and 64 KiB of LDS, two blocks per unit, while there are more tiles than units:
+//    1408 x 4608 x 3072 69 -> 48 us.
+//  * one 128 x 128 tile per unit at most: sixteen waves and four steps in LDS, as one block has to hide its own latency:
+//    512 x 5632 x 1536 25 -> 14 us (four waves: 18, 64 x 64 tiles: 16).
+//  * fewer than half as many: 64 x 64, three blocks per unit: 2048 x 1024 x 2048 34 -> 14 us.
+//  * one 64 x 64 tile per unit at most and K long enough to split: two groups of waves along K: 1024^3 16 -> 5.9 us (one
+//    group: 7.1); half as many tiles: four groups on 32 x 64: 512 x 512 x 4096 49 -> 11 us (two groups: 14).
+// WIDE once a panel of 256 rows passes 2 GiB (the offsets of a buffer load are 32 bits wide).
+#define DSLLM_GEMM(BM_, BN_, THREADS, ...) \
+    hipLaunchKernelGGL((__VA_ARGS__), dim3(unsigned((m / (BM_)) * (n / (BN_)))), dim3(THREADS), 0, stream, a, b, c, m, n, k)
+void launch_gemm(const uint16_t *a, const uint16_t *b, uint16_t *c, int m, int n, int k, hipStream_t stream) {
+    const int64_t n64 = int64_t(m / 64) * (n / 64);
+    if (k > (1 << 22)) DSLLM_GEMM(64, 64, 256, gemm_bf16_kernel<2, 2, 2, 2, 1, 3, true>);
+    else if (m % 256 == 0 && n % 256 == 0 && n64 >= 192 * 16 && k >= 256) DSLLM_GEMM(256, 256, 256, gemm_bf16_256_kernel);
+    else if (n64 > 4 * 256) DSLLM_GEMM(128, 128, 256, gemm_bf16_kernel<4, 4, 2, 2, 1, 2>);
+    else if (n64 > 2 * 256) DSLLM_GEMM(128, 128, 1024, gemm_bf16_kernel<2, 2, 4, 4, 1, 4>);
+    else if (n64 > 256 || k < 512) DSLLM_GEMM(64, 64, 256, gemm_bf16_kernel<2, 2, 2, 2, 1, 3>);
+    else if (n64 > 128) DSLLM_GEMM(64, 64, 512, gemm_bf16_kernel<2, 2, 2, 2, 2, 3>);
+    else DSLLM_GEMM(32, 64, 1024, gemm_bf16_kernel<1, 2, 2, 2, 4, 3>);
+}
+#undef DSLLM_GEMM
 
 unsigned blocks_for(uint64_t n, unsigned per_block) {
     uint64_t b = (n + per_block - 1) / per_block;
@@ -263,13 +407,7 @@ extern "C" {
 int proxy_gemm_bf16(const void *a, const void *b, void *c, int32_t m, int32_t n, int32_t k, void *stream) {
     if (!a || !b || !c || m <= 0 || n <= 0 || k <= 0 || m % 128 || n % 128 || k % 64) return -1;
     if ((uint64_t(a) | uint64_t(b) | uint64_t(c)) & 15) return -1;
-    // the 256 x 256 block tile where the shape allows it and there are enough tiles to fill the card
-    if (m % 256 == 0 && n % 256 == 0 && (m / 256) * (n / 256) >= 256)
-        hipLaunchKernelGGL((gemm_bf16_kernel<4, 64>), dim3((m / 256) * (n / 256)), dim3(256), 0, static_cast<hipStream_t>(stream),
-                           static_cast<const uint16_t *>(a), static_cast<const uint16_t *>(b), static_cast<uint16_t *>(c), m, n, k);
-    else
-        hipLaunchKernelGGL((gemm_bf16_kernel<2, 32>), dim3((m / 128) * (n / 128)), dim3(256), 0, static_cast<hipStream_t>(stream),
-                           static_cast<const uint16_t *>(a), static_cast<const uint16_t *>(b), static_cast<uint16_t *>(c), m, n, k);
+    launch_gemm(static_cast<const uint16_t *>(a), static_cast<const uint16_t *>(b), static_cast<uint16_t *>(c), m, n, k, static_cast<hipStream_t>(stream));
     return hip_rc();
 }
 

@@ -1,0 +1,72 @@
+"""Every kernel and tile the proxy's GEMM chooses among, at the edges of its range (fewest steps of K, an odd number of
+them, steps that only some groups of waves have, an odd number of tiles), against the float64 product."""
+import numpy as np
+import pytest
+
+from oracle import proxy_oracle as po
+from paper_2406_10707_amd import binding as B
+from paper_2406_10707_amd import harness
+from tests import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(3072, 4096, 256), (3072, 4096, 320), (4096, 3328, 448),       # 256 x 256 tiles
+          (2176, 2048, 64), (2176, 2048, 192), (128, 67328, 128),        # 128 x 128, two blocks per unit
+          (1536, 2048, 64), (1664, 1920, 320),                           # 128 x 128, sixteen waves
+          (1152, 1024, 64), (1024, 1152, 576), (128, 128, 64), (256, 128, 448),     # 64 x 64
+          (640, 1280, 512), (1024, 1024, 576), (640, 1408, 1088),        # 64 x 64, K split in two
+          (128, 128, 512), (256, 384, 576), (512, 1024, 640), (128, 256, 704)]      # 32 x 64, K split in four
+
+
+@pytest.mark.parametrize("m,n,k", SHAPES)
+def test_gemm_against_float64(m, n, k):
+    print(f"gemm {m}x{n}x{k}", flush=True)
+    rng = np.random.default_rng(m + 3 * n + 7 * k)
+    a = po.bf16_bits(rng.standard_normal((m, k)).astype(np.float32))
+    b = po.bf16_bits(rng.standard_normal((n, k)).astype(np.float32))
+    da, db, dc = harness.DevBuf(2 * m * k), harness.DevBuf(2 * n * k), harness.DevBuf(2 * m * n + 4096)
+    da.upload(a)
+    db.upload(b)
+    ref, ref_abs = po.gemm_bf16(a, b)
+    # f32 sums of K products in any order: K 2^-23 sum |a||b|; one rounding to bf16: 2^-8 |c|
+    bound = k * 2.0 ** -23 * ref_abs + 2.0 ** -8 * np.abs(ref) + 1e-30
+    first = None
+    for _ in range(3):       # the same bits each time: nothing depends on the order in which waves arrive
+        B.proxy_device_fill_async(dc.ptr, 0xEE, dc.nbytes, 0)
+        B.proxy_gemm_bf16(da.ptr, db.ptr, dc.ptr, m, n, k, 0)
+        harness.synchronize()
+        out = gu.download(dc)
+        assert np.all(out[2 * m * n:] == 0xEE)
+        got = po.bf16_to_f64(out[:2 * m * n].view(np.uint16).reshape(m, n))
+        assert np.all(np.abs(got - ref) <= bound), float(np.max(np.abs(got - ref) / bound))
+        assert first is None or np.array_equal(first, out)
+        first = out
+    for x in (da, db, dc):
+        x.free()
+
+
+def test_gemm_with_rows_beyond_32_bit_offsets():
+    """K past 2^22: rows of A and B are zero but for columns at the beginning, in the middle and at the end."""
+    m = n = 128
+    k = (1 << 22) + 64
+    print(f"gemm {m}x{n}x{k}", flush=True)
+    rng = np.random.default_rng(5)
+    at = [0, 63, 64, 1 << 21, (1 << 22) - 1, 1 << 22, k - 1]
+    cols_a = po.bf16_bits(rng.standard_normal((m, len(at))).astype(np.float32))
+    cols_b = po.bf16_bits(rng.standard_normal((n, len(at))).astype(np.float32))
+    bufs = []
+    for cols in (cols_a, cols_b):
+        full = np.zeros((128, k), dtype=np.uint16)
+        full[:, at] = cols
+        d = harness.DevBuf(2 * 128 * k)
+        d.upload(full)
+        bufs.append(d)
+        del full
+    dc = harness.DevBuf(2 * m * n)
+    B.proxy_gemm_bf16(bufs[0].ptr, bufs[1].ptr, dc.ptr, m, n, k, 0)
+    harness.synchronize()
+    got = po.bf16_to_f64(gu.download(dc).view(np.uint16).reshape(m, n))
+    ref, ref_abs = po.gemm_bf16(cols_a, cols_b)
+    assert np.all(np.abs(got - ref) <= len(at) * 2.0 ** -23 * ref_abs + 2.0 ** -8 * np.abs(ref) + 1e-30)
+    for x in bufs + [dc]:
+        x.free()
