@@ -6,7 +6,7 @@
 using namespace dsllm;
 
 static void finish_d2h_stats(ckpt_ctx *c, Snap *s) {
-    // called by the I/O thread that owns the snapshot's last chunk, after all tail events completed
+    // called by the I/O thread that has the first piece of the snapshot's last chunk, after all tail events completed
     double pack_sum = 0, req_d2h = 0, span = 0, req_pack = 0;
     float ms = 0;
     const uint64_t n_sc = s->plan->n_superchunks;
@@ -78,18 +78,16 @@ void dsllm::io_thread_main(ckpt_ctx *c) {
             c->io_q.pop_front();
         }
         if (job.kind == IoJob::STOP) return;
-        uint8_t *slot_ptr = c->ring + job.slot * c->cfg.dma_chunk_bytes;
+        uint8_t *piece = c->ring + job.slot * c->cfg.dma_chunk_bytes + job.slot_off;
         std::string err;
         if (job.kind == IoJob::READ) {
-            uint8_t *piece = slot_ptr + job.slot_off;
             bool ok = c->cfg.o_direct ? (bounce ? direct_read(job.fd, bounce, piece, job.nbytes, job.file_off, &err) : (err = "no bounce buffer", false))
                                       : pread_all(job.fd, piece, job.nbytes, job.file_off, &err);
             if (!ok) c->latch(CKPT_EIO, err);
             std::lock_guard<std::mutex> lk(c->mu);
-            if (--c->slot_reads_left[job.slot] == 0) {   // the chunk's last piece
-                c->slot_state[job.slot] = SLOT_READ_DONE;
-                c->cv_state.notify_all();
-            }
+            c->slot_piece_read[job.slot][job.piece] = 1;
+            if (--c->slot_pieces_left[job.slot] == 0) c->slot_state[job.slot] = SLOT_READ_DONE;   // the chunk's last piece
+            c->cv_state.notify_all();
             continue;
         }
         // WRITE: the chunk's copy must have landed in the slot first
@@ -111,19 +109,23 @@ void dsllm::io_thread_main(ckpt_ctx *c) {
             }
             finish_d2h_stats(c, s);
         }
-        if (s->map) memcpy(s->map + job.file_off, slot_ptr, job.nbytes);   // page-cache/tmpfs sink: parallel across threads
+        if (s->map) memcpy(s->map + job.file_off, piece, job.nbytes);   // page-cache/tmpfs sink: parallel across threads
         else if (s->fd >= 0) {
-            bool ok = c->cfg.o_direct ? (bounce ? direct_write(s->fd, bounce, slot_ptr, job.nbytes, job.file_off, &err) : (err = "no bounce buffer", false))
-                                      : pwrite_all(s->fd, slot_ptr, job.nbytes, job.file_off, &err);
+            bool ok = c->cfg.o_direct ? (bounce ? direct_write(s->fd, bounce, piece, job.nbytes, job.file_off, &err) : (err = "no bounce buffer", false))
+                                      : pwrite_all(s->fd, piece, job.nbytes, job.file_off, &err);
             if (!ok) c->fail_snapshot(s, CKPT_EIO, s->tmp_path + ": " + err);
         }
+        s->io_copy_us += uint64_t(ms_between(tw1, Clock::now()) * 1000.0);
+        bool chunk_written;
         {
             std::lock_guard<std::mutex> lk(c->mu);
-            c->slot_state[job.slot] = SLOT_FREE;
-            c->cv_state.notify_all();
+            chunk_written = --c->slot_pieces_left[job.slot] == 0;
+            if (chunk_written) {
+                c->slot_state[job.slot] = SLOT_FREE;
+                c->cv_state.notify_all();
+            }
         }
-        s->io_copy_us += uint64_t(ms_between(tw1, Clock::now()) * 1000.0);
-        if (s->chunks_left.fetch_sub(1) == 1) {
+        if (chunk_written && s->chunks_left.fetch_sub(1) == 1) {
             // last chunk written: commit. Whether the file gets its final name depends on this snapshot's own
             // record of failures, not on the context-wide latch (a call in between may have taken and cleared that).
             if (s->fd >= 0) {

@@ -38,28 +38,28 @@ static int restore_body(ckpt_ctx *c, int fd, const char *path, hipStream_t strea
     if (p.n_direct)   // these copies write the tensors themselves
         for (size_t k = 0; k < nk; k++) HIP_TRY(c, hipStreamWaitEvent(c->dma[k], c->ev_user, 0));
 
+    const uint64_t piece_bytes = std::min<uint64_t>(kPieceBytes, CH / 8);   // CH is a multiple of 32 KiB: 4 KiB multiples
     uint64_t &issued = *issued_out;   // chunks whose file read has been handed to the I/O threads
     auto issue_reads_upto = [&](uint64_t upto) -> int {
         for (; issued < upto && issued < p.n_chunks; issued++) {
             const uint64_t slot = (base + issued) % c->n_slots;
             if (issued >= c->n_slots) HIP_TRY(c, hipEventSynchronize(c->ev_slot[slot]));   // previous chunk's copy out of the slot
-            // A chunk is read in pieces by as many I/O threads as there are pieces: one thread per whole chunk would
-            // leave a small shard (fewer chunks than threads, or one more) waiting for its slowest read.
-            const uint64_t nbytes = p.chunk_bytes(issued);
-            const uint64_t kReadPieceBytes = CH / kReadPiecesPerChunk;   // CH is a multiple of 32 KiB: pieces are 4 KiB multiples
-            const uint64_t n_pieces = (nbytes + kReadPieceBytes - 1) / kReadPieceBytes;
+            // a chunk is read in pieces, spread over the I/O threads
+            const uint64_t nbytes = p.chunk_bytes(issued), n_pieces = (nbytes + piece_bytes - 1) / piece_bytes;
             {
                 std::lock_guard<std::mutex> lk(c->mu);
                 c->slot_state[slot] = SLOT_BUSY;
-                c->slot_reads_left[slot] = uint32_t(n_pieces);
+                c->slot_pieces_left[slot] = uint32_t(n_pieces);
+                c->slot_piece_read[slot].assign(n_pieces, 0);
                 for (uint64_t q = 0; q < n_pieces; q++) {
                     IoJob job;
                     job.kind = IoJob::READ;
                     job.fd = fd;
                     job.slot = slot;
-                    job.slot_off = q * kReadPieceBytes;
+                    job.piece = uint32_t(q);
+                    job.slot_off = q * piece_bytes;
                     job.file_off = p.header_bytes + issued * CH + job.slot_off;
-                    job.nbytes = std::min<uint64_t>(kReadPieceBytes, nbytes - job.slot_off);
+                    job.nbytes = std::min<uint64_t>(piece_bytes, nbytes - job.slot_off);
                     c->io_q.push_back(job);
                 }
             }
@@ -77,22 +77,46 @@ static int restore_body(ckpt_ctx *c, int fd, const char *path, hipStream_t strea
             int r = issue_reads_upto(ch + c->n_slots);
             if (r != CKPT_OK) return r;
             const uint64_t slot = (base + ch) % c->n_slots;
-            {
-                std::unique_lock<std::mutex> lk(c->mu);
-                c->cv_state.wait(lk, [&] { return c->slot_state[slot] == SLOT_READ_DONE; });
-                if (c->async_code) { g_last_error = c->async_err; return c->async_code; }
-            }
             const size_t k = ch % nk;
             const uint8_t *slot_base = c->ring + slot * CH;
-            for (uint64_t j = p.chunk_first_seg[ch]; j < p.chunk_first_seg[ch + 1]; j++) {
-                const ckpt_segment &sg = p.segs[j];
-                if (sg.kind == CKPT_SEG_ZERO) continue;
-                if (sg.kind == CKPT_SEG_HOST) {   // the slot has been read: host objects are put back by this thread
-                    memcpy(reinterpret_cast<void *>(sg.src), slot_base + (sg.data_off - ch * CH), sg.nbytes);
-                    continue;
+            const uint64_t nbytes = p.chunk_bytes(ch);
+            // Where the copy engines have nothing to do (the first two chunks, and later whenever the file is read more
+            // slowly than the link moves data) the chunk is sent on as its pieces arrive; otherwise as a whole, because
+            // every copy costs the link some ten microseconds.
+            bool in_pieces = ch < 2;
+            if (!in_pieces) {
+                in_pieces = hipEventQuery(c->ev_slot[(base + ch - 1) % c->n_slots]) == hipSuccess;
+                if (!in_pieces) (void)hipGetLastError();   // "not ready" is no error of a later call
+            }
+            uint64_t sent = 0, seg = p.chunk_first_seg[ch];
+            while (sent < nbytes) {
+                uint64_t ready = nbytes;
+                {
+                    std::unique_lock<std::mutex> lk(c->mu);
+                    const std::vector<uint8_t> &got = c->slot_piece_read[slot];
+                    c->cv_state.wait(lk, [&] { return c->slot_state[slot] == SLOT_READ_DONE || (in_pieces && got[sent / piece_bytes]); });
+                    if (c->async_code) { g_last_error = c->async_err; return c->async_code; }
+                    if (c->slot_state[slot] != SLOT_READ_DONE) {
+                        uint64_t q = sent / piece_bytes;
+                        while (q < got.size() && got[q]) q++;
+                        ready = std::min(nbytes, q * piece_bytes);
+                    }
                 }
-                void *dst = sg.kind == CKPT_SEG_DIRECT ? reinterpret_cast<void *>(sg.src) : static_cast<void *>(stage_base + (sg.data_off - sc * SC));
-                HIP_TRY(c, hipMemcpyAsync(dst, slot_base + (sg.data_off - ch * CH), sg.nbytes, hipMemcpyHostToDevice, c->dma[k]));
+                // the parts of the chunk's segments that lie in [sent, ready)
+                for (; seg < p.chunk_first_seg[ch + 1]; seg++) {
+                    const ckpt_segment &sg = p.segs[seg];
+                    const uint64_t at = sg.data_off - ch * CH, lo = std::max(sent, at), hi = std::min(ready, at + sg.nbytes);
+                    if (lo >= ready) break;
+                    const uint64_t into = lo - at;          // bytes of the segment that went before
+                    if (sg.kind == CKPT_SEG_HOST) {         // host objects are put back by this thread
+                        memcpy(reinterpret_cast<uint8_t *>(sg.src) + into, slot_base + lo, hi - lo);
+                    } else if (sg.kind != CKPT_SEG_ZERO) {
+                        void *dst = sg.kind == CKPT_SEG_DIRECT ? reinterpret_cast<uint8_t *>(sg.src) + into : stage_base + (ch * CH + lo - sc * SC);
+                        HIP_TRY(c, hipMemcpyAsync(dst, slot_base + lo, hi - lo, hipMemcpyHostToDevice, c->dma[k]));
+                    }
+                    if (hi < at + sg.nbytes) break;         // the rest of this segment comes with a later piece
+                }
+                sent = ready;
             }
             HIP_TRY(c, hipEventRecord(c->ev_slot[slot], c->dma[k]));
         }

@@ -192,18 +192,23 @@ static void submit_one(ckpt_ctx *c, const std::shared_ptr<Snap> &sp) {
             if (last)
                 for (size_t kk = 0; kk < nk; kk++)
                     if ((e = hipEventRecord(c->ev_job_tail[kk], c->dma[kk])) != hipSuccess) hip_fail("record", e);
-            IoJob job;
-            job.kind = IoJob::WRITE;
-            job.snap = sp;
-            job.slot = slot;
-            job.file_off = p.header_bytes + ch * CH;
-            job.nbytes = nbytes;
-            job.last = last;
+            const uint64_t n_pieces = (nbytes + kPieceBytes - 1) / kPieceBytes;
             {
                 std::lock_guard<std::mutex> lk(c->mu);
-                c->io_q.push_back(std::move(job));
+                c->slot_pieces_left[slot] = uint32_t(n_pieces);
+                for (uint64_t q = 0; q < n_pieces; q++) {
+                    IoJob job;
+                    job.kind = IoJob::WRITE;
+                    job.snap = sp;
+                    job.slot = slot;
+                    job.slot_off = q * kPieceBytes;
+                    job.file_off = p.header_bytes + ch * CH + job.slot_off;
+                    job.nbytes = std::min<uint64_t>(kPieceBytes, nbytes - job.slot_off);
+                    job.last = last && q == 0;
+                    c->io_q.push_back(std::move(job));
+                }
             }
-            c->cv_io.notify_one();
+            c->cv_io.notify_all();
         }
         // The next pack launch goes out one round late, after this super-chunk's copies have been enqueued: its host-side
         // wait is for the copies of the previous super-chunk, and the copy engines have this one's to go on with. The
