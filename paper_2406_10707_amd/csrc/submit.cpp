@@ -4,6 +4,16 @@
 
 using namespace dsllm;
 
+// A data region this small is packed straight into its ring slot over the link: the copy engine's start and the event
+// between kernel and copy cost more than they bring. Request to committed file, staged -> straight: 64 KiB 116 -> 88 us,
+// 1 MiB 156 -> 135, 4 MiB 316 -> 296, 8 MiB 400 -> 385, 16 MiB 586 -> 593 (the kernel's stores reach the copy engines'
+// rate but hold compute units meanwhile, so the line is drawn where the gain is still several per cent). Not under
+// policy PACK, whose window closes with the pack kernel: writing to device memory ends sooner.
+constexpr uint64_t kStraightBytes = 4ull << 20;
+static bool packs_straight_into_ring(const Plan &p, int policy) {
+    return policy == CKPT_WINDOW_D2H && p.n_chunks == 1 && p.data_bytes <= kStraightBytes && p.segs.size() == 1 && p.segs[0].kind == CKPT_SEG_STAGED;
+}
+
 static void submit_one(ckpt_ctx *c, const std::shared_ptr<Snap> &sp) {
     Snap *s = sp.get();
     const uint64_t CH = c->cfg.dma_chunk_bytes, SC = c->cfg.pack_superchunk_bytes;
@@ -114,10 +124,66 @@ static void submit_one(ckpt_ctx *c, const std::shared_ptr<Snap> &sp) {
         s->map = nullptr; s->fd = -1;
     }
 
+    double bp_ms = 0;
+    auto take_slot = [&]() -> uint64_t {      // the next ring slot; waits until it has been written to its file
+        const uint64_t slot = c->ring_next++ % c->n_slots;
+        std::unique_lock<std::mutex> lk(c->mu);
+        if (c->slot_state[slot] != SLOT_FREE) {
+            auto w0 = Clock::now();
+            c->cv_state.wait(lk, [&] { return c->slot_state[slot] == SLOT_FREE; });
+            bp_ms += ms_between(w0, Clock::now());
+        }
+        c->slot_state[slot] = SLOT_BUSY;
+        return slot;
+    };
+    auto hand_to_io = [&](uint64_t ch, uint64_t slot) {      // chunk ch, whose arrival in `slot` is ev_slot[slot], goes to the file
+        const uint64_t nbytes = p.chunk_bytes(ch), n_pieces = (nbytes + kPieceBytes - 1) / kPieceBytes;
+        {
+            std::lock_guard<std::mutex> lk(c->mu);
+            c->slot_pieces_left[slot] = uint32_t(n_pieces);
+            for (uint64_t q = 0; q < n_pieces; q++) {
+                IoJob job;
+                job.kind = IoJob::WRITE;
+                job.snap = sp;
+                job.slot = slot;
+                job.slot_off = q * kPieceBytes;
+                job.file_off = p.header_bytes + ch * CH + job.slot_off;
+                job.nbytes = std::min<uint64_t>(kPieceBytes, nbytes - job.slot_off);
+                job.last = ch + 1 == p.n_chunks && q == 0;
+                c->io_q.push_back(std::move(job));
+            }
+        }
+        if (n_pieces == 1) c->cv_io.notify_one();
+        else c->cv_io.notify_all();
+    };
+    auto all_submitted = [&] {
+        std::vector<uint8_t>().swap(s->host_capture);   // every byte of it is in a ring slot by now
+        std::lock_guard<std::mutex> lk(c->mu);
+        s->backpressure_ms = bp_ms + tier2_wait_ms;
+        s->t_submitted = Clock::now();
+        s->packs_submitted = s->submitted = true;
+        c->prev_job = sp;
+        c->cv_state.notify_all();
+    };
+
+    if (packs_straight_into_ring(p, s->policy)) {
+        // The pack kernel writes the ring slot itself: one launch instead of a launch, an event and a copy behind it.
+        const uint64_t slot = take_slot();
+        if ((e = hipEventRecord(c->ev_first_copy, c->pack_stream)) != hipSuccess) hip_fail("record", e);
+        if ((e = launch_pack(s->dev_tiles, p.tiles.size(), c->ring + slot * CH, 0, c->pack_stream, c->ev_pack_start[0], c->ev_pack_end[0])) != hipSuccess)
+            hip_fail("pack launch", e);
+        if ((e = hipEventRecord(c->ev_packed[0], c->pack_stream)) != hipSuccess) hip_fail("record", e);
+        if ((e = hipEventRecord(c->ev_slot[slot], c->pack_stream)) != hipSuccess) hip_fail("record", e);
+        for (size_t k = 0; k < nk; k++)
+            if ((e = hipEventRecord(c->ev_job_tail[k], c->pack_stream)) != hipSuccess) hip_fail("record", e);
+        hand_to_io(0, slot);
+        all_submitted();
+        return;
+    }
+
     if (p.n_direct)   // these copies read the tensors themselves
         for (size_t k = 0; k < nk; k++)
             if ((e = hipStreamWaitEvent(c->dma[k], s->ev_boundary, 0)) != hipSuccess) hip_fail("wait boundary", e);
-    double bp_ms = 0;
     // Pack launches run ahead of the copies: as far as staging allows when the window closes with the last pack
     // (policy PACK: get the reads of the tensors over with), `ahead` = two staging slots otherwise (under the
     // paper's rule nothing is gained by packing earlier, and a burst of pack kernels would only compete with the
@@ -155,17 +221,7 @@ static void submit_one(ckpt_ctx *c, const std::shared_ptr<Snap> &sp) {
         const uint64_t c1 = std::min<uint64_t>(p.n_chunks, c0 + SC / CH);
         for (uint64_t ch = c0; ch < c1; ch++) {
             const size_t k = ch % nk;
-            const uint64_t slot = c->ring_next++ % c->n_slots;
-            {
-                std::unique_lock<std::mutex> lk(c->mu);
-                if (c->slot_state[slot] != SLOT_FREE) {
-                    auto w0 = Clock::now();
-                    c->cv_state.wait(lk, [&] { return c->slot_state[slot] == SLOT_FREE; });
-                    bp_ms += ms_between(w0, Clock::now());
-                }
-                c->slot_state[slot] = SLOT_BUSY;
-            }
-            const uint64_t nbytes = p.chunk_bytes(ch);
+            const uint64_t slot = take_slot();
             if (ch == 0 && (e = hipEventRecord(c->ev_first_copy, c->dma[k])) != hipSuccess) hip_fail("record", e);
             // the chunk's segments: packed bytes out of staging, large tensors out of their own memory,
             // the padding behind those zero-filled here (the slot belongs to this thread until the copy event)
@@ -192,36 +248,14 @@ static void submit_one(ckpt_ctx *c, const std::shared_ptr<Snap> &sp) {
             if (last)
                 for (size_t kk = 0; kk < nk; kk++)
                     if ((e = hipEventRecord(c->ev_job_tail[kk], c->dma[kk])) != hipSuccess) hip_fail("record", e);
-            const uint64_t n_pieces = (nbytes + kPieceBytes - 1) / kPieceBytes;
-            {
-                std::lock_guard<std::mutex> lk(c->mu);
-                c->slot_pieces_left[slot] = uint32_t(n_pieces);
-                for (uint64_t q = 0; q < n_pieces; q++) {
-                    IoJob job;
-                    job.kind = IoJob::WRITE;
-                    job.snap = sp;
-                    job.slot = slot;
-                    job.slot_off = q * kPieceBytes;
-                    job.file_off = p.header_bytes + ch * CH + job.slot_off;
-                    job.nbytes = std::min<uint64_t>(kPieceBytes, nbytes - job.slot_off);
-                    job.last = last && q == 0;
-                    c->io_q.push_back(std::move(job));
-                }
-            }
-            c->cv_io.notify_all();
+            hand_to_io(ch, slot);
         }
         // The next pack launch goes out one round late, after this super-chunk's copies have been enqueued: its host-side
         // wait is for the copies of the previous super-chunk, and the copy engines have this one's to go on with. The
         // pack of super-chunk sc + 1 was launched a round ago, before the copies above that wait for it.
         if (sc >= 1 && sc - 1 + ahead < p.n_superchunks) enqueue_pack(sc - 1 + ahead);
     }
-    std::vector<uint8_t>().swap(s->host_capture);   // every byte of it is in a ring slot by now
-    std::lock_guard<std::mutex> lk(c->mu);
-    s->backpressure_ms = bp_ms + tier2_wait_ms;
-    s->t_submitted = Clock::now();
-    s->submitted = true;
-    c->prev_job = sp;
-    c->cv_state.notify_all();
+    all_submitted();
 }
 
 void dsllm::submit_thread_main(ckpt_ctx *c) {
