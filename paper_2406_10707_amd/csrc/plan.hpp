@@ -68,6 +68,16 @@ struct Plan {
         uint64_t b = c * cfg.dma_chunk_bytes;
         return data_bytes - b < cfg.dma_chunk_bytes ? data_bytes - b : cfg.dma_chunk_bytes;
     }
+    // first tile of super-chunk sc that lies at or behind data_off (tiles are ordered by offset; chunks are multiples of a tile)
+    uint64_t first_tile_at(uint64_t sc, uint64_t data_off) const {
+        uint64_t lo = sc_first_tile[sc], hi = sc_first_tile[sc + 1];
+        while (lo < hi) {
+            const uint64_t mid = (lo + hi) / 2;
+            if (tiles[mid].dst_off < data_off) lo = mid + 1;
+            else hi = mid;
+        }
+        return lo;
+    }
     uint64_t superchunk_bytes(uint64_t s) const {
         uint64_t b = s * cfg.pack_superchunk_bytes;
         return data_bytes - b < cfg.pack_superchunk_bytes ? data_bytes - b : cfg.pack_superchunk_bytes;

@@ -119,13 +119,13 @@ static int restore_body(ckpt_ctx *c, int fd, const char *path, hipStream_t strea
                 sent = ready;
             }
             HIP_TRY(c, hipEventRecord(c->ev_slot[slot], c->dma[k]));
+            // scattered as soon as it is on the device: what is left to do behind the last copy is one chunk, not a super-chunk
+            const uint64_t t0 = p.first_tile_at(sc, ch * CH), t1 = p.first_tile_at(sc, (ch + 1) * CH);
+            if (t0 < t1) {
+                HIP_TRY(c, hipStreamWaitEvent(c->pack_stream, c->ev_slot[slot], 0));
+                HIP_TRY(c, launch_scatter(dev_tiles + t0, t1 - t0, stage_base, sc * SC, c->pack_stream));
+            }
         }
-        for (size_t k = 0; k < nk; k++) {
-            HIP_TRY(c, hipEventRecord(c->ev_stage_done[stage][k], c->dma[k]));
-            HIP_TRY(c, hipStreamWaitEvent(c->pack_stream, c->ev_stage_done[stage][k], 0));
-        }
-        const uint64_t t0 = p.sc_first_tile[sc], t1 = p.sc_first_tile[sc + 1];
-        HIP_TRY(c, launch_scatter(dev_tiles + t0, t1 - t0, stage_base, sc * SC, c->pack_stream));
         HIP_TRY(c, hipEventRecord(c->ev_packed[sc], c->pack_stream));
     }
     HIP_TRY(c, hipStreamWaitEvent(stream, c->ev_packed[p.n_superchunks - 1], 0));
