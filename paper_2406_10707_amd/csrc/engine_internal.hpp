@@ -264,6 +264,7 @@ inline bool pread_all(int fd, uint8_t *p, uint64_t n, uint64_t off, std::string 
 
 // io_threads.cpp
 void io_thread_main(ckpt_ctx *c);
+void read_piece(ckpt_ctx *c, const IoJob &job, uint8_t *bounce);
 void retire_locked(ckpt_ctx *c, uint64_t iter);
 // second_tier.cpp
 void tier2_offer_locked(ckpt_ctx *c, const std::shared_ptr<Snap> &sp);

@@ -64,6 +64,19 @@ void dsllm::retire_locked(ckpt_ctx *c, uint64_t iter) {
     else sp.close_all();   // somebody removed or replaced the file: drop it
 }
 
+// One piece of a chunk from the file into its ring slot. `bounce`: the thread's aligned buffer for direct I/O.
+void dsllm::read_piece(ckpt_ctx *c, const IoJob &job, uint8_t *bounce) {
+    uint8_t *piece = c->ring + job.slot * c->cfg.dma_chunk_bytes + job.slot_off;
+    std::string err;
+    bool ok = c->cfg.o_direct ? (bounce ? direct_read(job.fd, bounce, piece, job.nbytes, job.file_off, &err) : (err = "no bounce buffer", false))
+                              : pread_all(job.fd, piece, job.nbytes, job.file_off, &err);
+    if (!ok) c->latch(CKPT_EIO, err);
+    std::lock_guard<std::mutex> lk(c->mu);
+    c->slot_piece_read[job.slot][job.piece] = 1;
+    if (--c->slot_pieces_left[job.slot] == 0) c->slot_state[job.slot] = SLOT_READ_DONE;   // the chunk's last piece
+    c->cv_state.notify_all();
+}
+
 void dsllm::io_thread_main(ckpt_ctx *c) {
     (void)hipSetDevice(c->device);
     uint8_t *bounce = nullptr;
@@ -81,13 +94,7 @@ void dsllm::io_thread_main(ckpt_ctx *c) {
         uint8_t *piece = c->ring + job.slot * c->cfg.dma_chunk_bytes + job.slot_off;
         std::string err;
         if (job.kind == IoJob::READ) {
-            bool ok = c->cfg.o_direct ? (bounce ? direct_read(job.fd, bounce, piece, job.nbytes, job.file_off, &err) : (err = "no bounce buffer", false))
-                                      : pread_all(job.fd, piece, job.nbytes, job.file_off, &err);
-            if (!ok) c->latch(CKPT_EIO, err);
-            std::lock_guard<std::mutex> lk(c->mu);
-            c->slot_piece_read[job.slot][job.piece] = 1;
-            if (--c->slot_pieces_left[job.slot] == 0) c->slot_state[job.slot] = SLOT_READ_DONE;   // the chunk's last piece
-            c->cv_state.notify_all();
+            read_piece(c, job, bounce);
             continue;
         }
         // WRITE: the chunk's copy must have landed in the slot first

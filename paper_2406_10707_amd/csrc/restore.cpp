@@ -94,13 +94,26 @@ static int restore_body(ckpt_ctx *c, int fd, const char *path, hipStream_t strea
                 {
                     std::unique_lock<std::mutex> lk(c->mu);
                     const std::vector<uint8_t> &got = c->slot_piece_read[slot];
-                    c->cv_state.wait(lk, [&] { return c->slot_state[slot] == SLOT_READ_DONE || (in_pieces && got[sent / piece_bytes]); });
-                    if (c->async_code) { g_last_error = c->async_err; return c->async_code; }
-                    if (c->slot_state[slot] != SLOT_READ_DONE) {
+                    // pieces read without a gap behind what has been sent; the first one goes at once, later ones four at a time
+                    auto pieces_ready = [&] {
                         uint64_t q = sent / piece_bytes;
                         while (q < got.size() && got[q]) q++;
-                        ready = std::min(nbytes, q * piece_bytes);
+                        return q - sent / piece_bytes;
+                    };
+                    const uint64_t enough = ch == 0 && sent == 0 ? 1 : 4;
+                    auto can_go_on = [&] { return c->slot_state[slot] == SLOT_READ_DONE || (in_pieces && pieces_ready() >= enough); };
+                    // A file that is read more slowly than the link moves data is the rule (one thread reads 15 GB/s): while
+                    // it has nothing to send, this thread reads too, except for direct I/O, which needs a buffer of its own.
+                    while (!can_go_on() && !c->async_code && !c->cfg.o_direct && !c->io_q.empty() && c->io_q.front().kind == IoJob::READ) {
+                        const IoJob job = c->io_q.front();
+                        c->io_q.pop_front();
+                        lk.unlock();
+                        read_piece(c, job, nullptr);
+                        lk.lock();
                     }
+                    c->cv_state.wait(lk, [&] { return can_go_on() || c->async_code; });
+                    if (c->async_code) { g_last_error = c->async_err; return c->async_code; }
+                    if (c->slot_state[slot] != SLOT_READ_DONE) ready = std::min(nbytes, sent + pieces_ready() * piece_bytes);
                 }
                 // the parts of the chunk's segments that lie in [sent, ready)
                 for (; seg < p.chunk_first_seg[ch + 1]; seg++) {
