@@ -114,9 +114,12 @@ __device__ __forceinline__ void copy_group(const uint8_t *su, u32x4 *dst, uint32
 // a hundred registers more. Shorter tiles (the last tile of a tensor, small tensors) go group by group.
 //
 // Measured on MI355X against a shape that keeps the whole tile (32 loads per lane, 138 registers) in flight:
-// alone on the card the two are within 1 % of each other and of a plain table-free copy kernel (0.75 of the HBM
-// peak on aligned tensors, 0.71 on the fragmented workload); beside a matrix kernel that leaves 64 registers per
-// lane free only this one finds room on the SIMDs (0.71 to 0.74 against 0.45 to 0.55).
+// alone on the card the two are within 1 % of each other (0.75 of the HBM peak on aligned tensors, 0.71 on the
+// fragmented workload); beside a matrix kernel that leaves 64 registers per lane free only this one finds room on the
+// SIMDs (0.71 to 0.74 against 0.45 to 0.55). Against a kernel that writes one KiB per wave in address order, as
+// pack_batch_kernel does, it is slower alone (6.02 against 6.66 TB/s aligned, 5.68 against 6.18 fragmented), equal beside a
+// 1300 TFLOP/s GEMM loop on aligned tensors (5.87) and faster there on fragmented ones (5.70 against 4.9): the
+// engine's launches run beside the training step, so they use this one.
 __device__ __forceinline__ void copy_rolling(const uint8_t *su, u32x4 *dst, uint32_t n, uint32_t lane) {
     uint32_t g = 0;
 #pragma unroll 1
