@@ -304,7 +304,8 @@ int ckpt_flush(ckpt_ctx *ctx, uint64_t iter);
  * copied host-to-device into staging, scattered by a kernel (tensors that the hybrid path copies
  * directly are written by the DMA engines straight from the ring slot; host-resident objects by
  * the calling thread). Returns when everything is enqueued (the file has been read by then);
- * `hip_stream` is made to wait for the last scatter kernel and the last copy. The path may lie in
+ * `hip_stream` is made to wait for the last scatter kernel and the last copy. A restore that follows another one
+ * on the context waits until that one's kernels have read staging, i.e. until its stream has got there. The path may lie in
  * either storage tier. iter_out may be NULL. CKPT_ESTATE while a snapshot is in flight. */
 int ckpt_restore(ckpt_ctx *ctx, const char *path, void *hip_stream, uint64_t *iter_out);
 

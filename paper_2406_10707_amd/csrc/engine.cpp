@@ -247,6 +247,7 @@ int ckpt_init(const ckpt_config *cfg, ckpt_ctx **out) {
     if ((e = hipEventCreate(&c->ev_first_copy)) != hipSuccess) return cleanup_fail(CKPT_EHIP, hipGetErrorString(e));
     if ((e = hipEventCreate(&c->ev_user)) != hipSuccess) return cleanup_fail(CKPT_EHIP, hipGetErrorString(e));
     if ((e = hipEventCreate(&c->ev_packed_head)) != hipSuccess) return cleanup_fail(CKPT_EHIP, hipGetErrorString(e));
+    if ((e = hipEventCreate(&c->ev_scattered)) != hipSuccess) return cleanup_fail(CKPT_EHIP, hipGetErrorString(e));
     void *ring = nullptr;
     trace("init: allocating the pinned ring");
     e = hipHostMalloc(&ring, rc.host_ring_bytes, hipHostMallocDefault);
@@ -635,6 +636,7 @@ int ckpt_destroy(ckpt_ctx *c) {
     if (c->ev_first_copy) (void)hipEventDestroy(c->ev_first_copy);
     if (c->ev_user) (void)hipEventDestroy(c->ev_user);
     if (c->ev_packed_head) (void)hipEventDestroy(c->ev_packed_head);
+    if (c->ev_scattered) (void)hipEventDestroy(c->ev_scattered);
     if (c->pack_stream) (void)hipStreamDestroy(c->pack_stream);
     for (auto s : c->dma) (void)hipStreamDestroy(s);
     if (c->staging) (void)hipFree(c->staging);

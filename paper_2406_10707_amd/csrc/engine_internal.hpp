@@ -159,6 +159,7 @@ struct ckpt_ctx {
     std::vector<hipEvent_t> ev_job_tail;                  // per dma stream
     hipEvent_t ev_first_copy = nullptr, ev_user = nullptr;
     hipEvent_t ev_packed_head = nullptr;                  // the first chunk of a snapshot is in staging
+    hipEvent_t ev_scattered = nullptr;                    // restore: what the pack stream held before it has read staging
     uint8_t *hdr_buf = nullptr;                           // 4 KiB-aligned scratch for header writes
     uint64_t ring_next = 0;                               // global chunk counter -> ring slot
     double init_d2h_gbps = -1;                            // one ring slot copied device-to-host at set-up, timed (-1: could not be measured)

@@ -32,6 +32,11 @@ static int restore_body(ckpt_ctx *c, int fd, const char *path, hipStream_t strea
     if (memcmp(hb, p.header.data(), 16) != 0 || memcmp(hb + 24, p.header.data() + 24, p.header_bytes - 24) != 0)
         return fail(CKPT_EMISMATCH, "tensor table differs from the registration");
 
+    // An earlier restore's scatter kernels may still be queued (ckpt_restore does not wait for the caller's stream, which they
+    // come behind): the copies into staging follow them. Recorded ahead of the wait below, so that the copies do not have
+    // to wait for the caller's stream themselves.
+    HIP_TRY(c, hipEventRecord(c->ev_scattered, c->pack_stream));
+    for (size_t k = 0; k < nk; k++) HIP_TRY(c, hipStreamWaitEvent(c->dma[k], c->ev_scattered, 0));
     // earlier work on the caller's stream (which may read or write the tensors) comes first
     HIP_TRY(c, hipEventRecord(c->ev_user, stream));
     HIP_TRY(c, hipStreamWaitEvent(c->pack_stream, c->ev_user, 0));
