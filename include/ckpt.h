@@ -306,7 +306,9 @@ int ckpt_flush(ckpt_ctx *ctx, uint64_t iter);
  * the calling thread). Returns when everything is enqueued (the file has been read by then);
  * `hip_stream` is made to wait for the last scatter kernel and the last copy. A restore that follows another one
  * on the context waits until that one's kernels have read staging, i.e. until its stream has got there. The path may lie in
- * either storage tier. iter_out may be NULL. CKPT_ESTATE while a snapshot is in flight. */
+ * either storage tier. iter_out may be NULL. CKPT_ESTATE while a snapshot is in flight. After a failure in the
+ * middle of the file (CKPT_EIO, CKPT_EHIP) the tensors may hold parts of it, and nothing more is written once the call has returned
+ * (it then waits for the kernels it has enqueued). */
 int ckpt_restore(ckpt_ctx *ctx, const char *path, void *hip_stream, uint64_t *iter_out);
 
 /* The paper's multi-level flush, one level further: out_dir is the fast tier (host memory file system

@@ -305,6 +305,9 @@ int ckpt_restore(ckpt_ctx *c, const char *path, void *stream, uint64_t *iter_out
     if (fd >= 0) close(fd);
     if (rc == CKPT_OK) rc = take_async_error(c);
     else { std::lock_guard<std::mutex> lk(c->mu); c->async_code = 0; c->async_err.clear(); }
+    // A restore that fails on its way has scatter kernels queued, of which the caller's stream knows nothing: after the
+    // error the tensors' memory is the caller's again, to be freed or filled in another way.
+    if (rc != CKPT_OK && issued) (void)hipStreamSynchronize(c->pack_stream);
     return rc;
 }
 

@@ -1,7 +1,8 @@
 // Restores that a caller's stream reaches late, on the CPU model of streams and events (hip/hip_runtime.h). What work the
 // caller enqueues between two restores reads must be the first one's file, whatever the second one has done to the
-// context's staging memory meanwhile. Meant for -fsanitize=thread and -fsanitize=address.
-//   emu_restore <dir> order <reduce> <direct_min>
+// context's staging memory meanwhile; and a restore that fails in the middle of its file has written its last byte when it
+// returns. Meant for -fsanitize=thread and -fsanitize=address.
+//   emu_restore <dir> order|failed <reduce> <direct_min>
 #include <atomic>
 #include <chrono>
 #include <cstdio>
@@ -116,10 +117,40 @@ static void order(const std::string &dir, bool reduce, uint64_t direct_min) {
         }
 }
 
+// The file ends two chunks after its header by the time its data is read: the first chunk's scatter kernel is queued behind
+// the caller's stream when the read of a later one fails. From the return on the tensors' memory is the caller's again.
+static std::string g_cut_file;
+static off_t g_cut_at;
+static std::atomic<bool> g_cut{false};
+
+static void failed(const std::string &dir, bool reduce, uint64_t direct_min) {
+    Run r(dir, reduce, direct_min);
+    State want;
+    want.fill(2, true);
+    g_cut_file = r.snapshot(1, true);
+    const std::string whole = r.snapshot(2, true);
+    ckpt_layout lay;
+    REQUIRE(ckpt_get_layout(r.ctx, &lay) == CKPT_OK);
+    g_cut_at = off_t((reduce ? lay.reduced_header_bytes : lay.header_bytes) + (128 << 10));
+    r.busy();
+    g_cut = true;       // at the restore's first submission: it has looked at the header and the file's size by then
+    g_emu_submit_hook = [](hipStream_t) { if (g_cut.exchange(false)) REQUIRE(truncate(g_cut_file.c_str(), g_cut_at) == 0); };
+    REQUIRE(ckpt_restore(r.ctx, g_cut_file.c_str(), r.compute, nullptr) == CKPT_EIO);
+    g_emu_submit_hook = nullptr;
+    for (auto &t : r.state.t) std::fill(t.begin(), t.end(), 0x77);
+    hipStreamSynchronize(r.compute);
+    std::this_thread::sleep_for(std::chrono::milliseconds(100));
+    for (auto &t : r.state.t) for (uint8_t b : t) REQUIRE(b == 0x77);
+    REQUIRE(ckpt_restore(r.ctx, whole.c_str(), r.compute, nullptr) == CKPT_OK);      // and the context goes on working
+    hipStreamSynchronize(r.compute);
+    for (int j = 0; j < 2 * kParams; j++) REQUIRE(memcmp(r.state.t[j].data(), want.t[j].data(), r.descs[j].nbytes) == 0);
+}
+
 int main(int argc, char **argv) {
     if (argc < 5) return 2;
     const std::string dir = argv[1], what = argv[2];
     if (what == "order") order(dir, atoi(argv[3]) != 0, strtoull(argv[4], nullptr, 10));
+    else if (what == "failed") failed(dir, atoi(argv[3]) != 0, strtoull(argv[4], nullptr, 10));
     else return 2;
     printf("ok %s\n", what.c_str());
     return 0;

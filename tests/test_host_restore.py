@@ -27,3 +27,10 @@ def test_work_between_two_restores_reads_the_first_file(emu, tmp_path, reduce, d
     r = subprocess.run([emu, str(tmp_path), "order", str(reduce), str(direct_min)], capture_output=True, text=True, timeout=300)
     out = r.stdout + r.stderr
     assert r.returncode == 0 and out.strip() == "ok order", out[-6000:]
+
+
+@pytest.mark.parametrize("reduce,direct_min", [(0, 0), (1, 0), (0, 100000)])
+def test_a_failed_restore_writes_nothing_after_it_has_returned(emu, tmp_path, reduce, direct_min):
+    r = subprocess.run([emu, str(tmp_path), "failed", str(reduce), str(direct_min)], capture_output=True, text=True, timeout=300)
+    out = r.stdout + r.stderr
+    assert r.returncode == 0 and out.strip() == "ok failed", out[-6000:]
