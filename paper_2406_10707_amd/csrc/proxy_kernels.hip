@@ -323,7 +323,6 @@ __global__ __launch_bounds__(256) void gemm_bf16_256_kernel(const uint16_t *__re
 #pragma unroll
         for (int j = 0; j < T; j++) acc[i][j] = f32x4{0, 0, 0, 0};
     const int steps = K / 64;
-    asm volatile("s_nop 7");    // accumulators written by ordinary instructions, read by the asm below
 #pragma unroll
     for (int i = 0; i < Loader::COUNT; i++) load.issue(lds, 0, i);
 #pragma unroll
@@ -331,6 +330,14 @@ __global__ __launch_bounds__(256) void gemm_bf16_256_kernel(const uint16_t *__re
     wait_loads_and_meet<Loader::COUNT>();
 #pragma unroll
     for (int i = 0; i < FRAGS; i++) read(0, 0, i);
+    // The accumulators are set by ordinary instructions and read by the asm below, for which the compiler inserts no wait
+    // states: they are in their registers before the fence, which nothing moves across.
+#pragma unroll
+    for (int i = 0; i < T; i++)
+#pragma unroll
+        for (int j = 0; j < T; j++) asm volatile("" : "+a"(acc[i][j]));
+    asm volatile("s_nop 7");
+    __builtin_amdgcn_sched_barrier(0);
     for (int step = 0; step < steps; step++) {
         const int stage = step & 1;
         const int ahead = step + 2 < steps ? step + 2 : steps - 1;    // past the end: the last step again, into a stage nothing reads
