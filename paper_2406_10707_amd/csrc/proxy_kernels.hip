@@ -150,22 +150,25 @@ __device__ __forceinline__ GemmTile gemm_tile(int tiles_m, int tiles_n) {
     return GemmTile{s * strip + in_s % rows_here, in_s / rows_here};
 }
 
-// One wave's eight rows of a panel per instruction; NW waves share a panel. WIDE: 64-bit addresses, for panels that a
-// buffer resource's 32-bit offsets do not span.
+// One wave's eight rows of a panel per instruction; NW waves share a panel. WIDE: 64-bit addresses (the lane's own part
+// made once, the instruction's part uniform), for panels that a buffer resource's 32-bit offsets do not span.
 template <int BM, int BN, int NW, bool WIDE>
 struct PanelLoader {
     static constexpr int LA = BM / 8 / NW, LB = BN / 8 / NW, COUNT = LA + LB;   // instructions per wave and step
     static_assert(LA * 8 * NW == BM && LB * 8 * NW == BN && NW % 4 == 0, "panels divide among the waves, four waves' rows per 32");
-    const uint16_t *a, *b;
+    const uint16_t *lane_a, *lane_b;
     __amdgpu_buffer_rsrc_t ra, rb;
     uint32_t row0, piece_a, piece_b, k, wave;
 
     __device__ __forceinline__ PanelLoader(const uint16_t *a_panel, const uint16_t *b_panel, int K, int lane, int wave_)
-        : a(a_panel), b(b_panel), row0((lane >> 3) + 8 * wave_), piece_a((lane & 7) ^ ((4 * (wave_ & 1) + (lane >> 4)) & 7)),
+        : row0((lane >> 3) + 8 * wave_), piece_a((lane & 7) ^ ((4 * (wave_ & 1) + (lane >> 4)) & 7)),
           piece_b((lane & 7) ^ (((lane >> 4) & 1) | ((wave_ & 3) << 1))), k(uint32_t(K)), wave(wave_) {
-        if constexpr (!WIDE) {
-            ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(a), 0, uint32_t(BM) * 2u * k, 0x00020000);
-            rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(b), 0, uint32_t(BN) * 2u * k, 0x00020000);
+        if constexpr (WIDE) {
+            lane_a = a_panel + size_t(row0) * k + 8 * piece_a;
+            lane_b = b_panel + size_t(row0) * k + 8 * piece_b;
+        } else {
+            ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(a_panel), 0, uint32_t(BM) * 2u * k, 0x00020000);
+            rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(b_panel), 0, uint32_t(BN) * 2u * k, 0x00020000);
         }
     }
     // instruction i of step kt into the stage at lds (A panel, then B panel)
@@ -175,7 +178,7 @@ struct PanelLoader {
         const uint32_t piece = of_a ? piece_a : piece_b;
         const int j = of_a ? i : i - LA;
         if constexpr (WIDE) {
-            const uint16_t *p = (of_a ? a : b) + size_t(row0 + 8 * NW * j) * k + size_t(kt) * 64 + 8 * piece;
+            const uint16_t *p = (of_a ? lane_a : lane_b) + (size_t(8 * NW * j) * k + size_t(kt) * 64);
             __builtin_amdgcn_global_load_lds((const DSLLM_GLB void *)p, (DSLLM_LDS void *)place, 16, 0, 0);
         } else {
             __builtin_amdgcn_raw_ptr_buffer_load_lds(of_a ? ra : rb, (DSLLM_LDS void *)place, 16, 2 * (row0 * k + 8 * piece), 16 * NW * j * k + 128 * kt, 0, 0);
@@ -198,7 +201,7 @@ __device__ __forceinline__ void store_columns(uint16_t *c, f32x4 lo, f32x4 hi) {
 // Small and middle-sized products. A wave computes (16 TM) x (16 TN), WM x WN waves a block tile; KG such groups of
 // waves share the tile, each taking every KG-th step of K, and their sums are added in LDS at the end (in group order:
 // the result does not depend on timing). NST steps are in LDS; the loads of a step go out NST - 1 steps ahead.
-template <int TM, int TN, int WM, int WN, int KG, int NST, bool WIDE = false>
+template <int TM, int TN, int WM, int WN, int KG, int NST, bool WIDE>
 __global__ __launch_bounds__(64 * WM * WN * KG) void gemm_bf16_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B,
                                                                      uint16_t *__restrict__ C, int M, int N, int K) {
     constexpr int BM = 16 * TM * WM, BN = 16 * TN * WN, NW = WM * WN, STEP = (BM + BN) * 64;
@@ -293,11 +296,12 @@ __device__ __forceinline__ void for_each_of(F f, std::integer_sequence<int, I...
 // Measured at 8192^3: 1.08 ms = 1015 TFLOP/s before (one 32x32x16 kernel, panels through registers, a load's latency
 // exposed in every step), 0.72 ms = 1520 now, both sides in turn on one card; 384 registers per lane, which leaves room
 // beside it on a SIMD for two waves of the pack kernel.
+template <bool WIDE>
 __global__ __launch_bounds__(256) void gemm_bf16_256_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B, uint16_t *__restrict__ C,
                                                            int M, int N, int K) {
     constexpr int T = 8, NW = 4, BM = 256, BN = 256, STEP = (BM + BN) * 64, FRAGS = 2 * T, HALF = T * T;
     constexpr int FREE_AT = 40, LOAD_EVERY = 4, LANDED_AT = 96, READ_EVERY = 2;
-    typedef PanelLoader<BM, BN, NW, false> Loader;
+    typedef PanelLoader<BM, BN, NW, WIDE> Loader;
     constexpr int issued_when_landed = (LANDED_AT - FREE_AT + LOAD_EVERY - 1) / LOAD_EVERY;
     static_assert((FRAGS - 1) * READ_EVERY < FREE_AT && LANDED_AT + (FRAGS - 1) * READ_EVERY < 2 * HALF, "reads lie inside their half");
     static_assert(FREE_AT + (Loader::COUNT - 1) * LOAD_EVERY < 2 * HALF && issued_when_landed <= Loader::COUNT, "loads lie inside the step");
@@ -378,18 +382,20 @@ __global__ __launch_bounds__(256) void gemm_bf16_256_kernel(const uint16_t *__re
 //  * fewer than half as many: 64 x 64, three blocks per unit: 2048 x 1024 x 2048 34 -> 14 us.
 //  * one 64 x 64 tile per unit at most and K long enough to split: two groups of waves along K: 1024^3 16 -> 5.9 us (one
 //    group: 7.1); half as many tiles: four groups on 32 x 64: 512 x 512 x 4096 49 -> 11 us (two groups: 14).
-// WIDE once a panel of 256 rows passes 2 GiB (the offsets of a buffer load are 32 bits wide).
+// WIDE once a panel of 256 rows passes 2 GiB (the offsets of a buffer load are 32 bits wide); the rule is the same there:
+// K = 2^22 + 64, 4096 x 4096 160 ms = 880 TFLOP/s, 2048 x 2048 65 ms, 1024 x 1024 18 ms, 128 x 128 13 ms; with 64 x 64 tiles for
+// every size 568, 124, 27 and 23, with the kernels before these 168, 128, 119 and 121.
 #define DSLLM_GEMM(BM_, BN_, THREADS, ...) \
     hipLaunchKernelGGL((__VA_ARGS__), dim3(unsigned((m / (BM_)) * (n / (BN_)))), dim3(THREADS), 0, stream, a, b, c, m, n, k)
+template <bool WIDE>
 void launch_gemm(const uint16_t *a, const uint16_t *b, uint16_t *c, int m, int n, int k, hipStream_t stream) {
     const int64_t n64 = int64_t(m / 64) * (n / 64);
-    if (k > (1 << 22)) DSLLM_GEMM(64, 64, 256, gemm_bf16_kernel<2, 2, 2, 2, 1, 3, true>);
-    else if (m % 256 == 0 && n % 256 == 0 && n64 >= 192 * 16 && k >= 256) DSLLM_GEMM(256, 256, 256, gemm_bf16_256_kernel);
-    else if (n64 > 4 * 256) DSLLM_GEMM(128, 128, 256, gemm_bf16_kernel<4, 4, 2, 2, 1, 2>);
-    else if (n64 > 2 * 256) DSLLM_GEMM(128, 128, 1024, gemm_bf16_kernel<2, 2, 4, 4, 1, 4>);
-    else if (n64 > 256 || k < 512) DSLLM_GEMM(64, 64, 256, gemm_bf16_kernel<2, 2, 2, 2, 1, 3>);
-    else if (n64 > 128) DSLLM_GEMM(64, 64, 512, gemm_bf16_kernel<2, 2, 2, 2, 2, 3>);
-    else DSLLM_GEMM(32, 64, 1024, gemm_bf16_kernel<1, 2, 2, 2, 4, 3>);
+    if (m % 256 == 0 && n % 256 == 0 && n64 >= 192 * 16 && k >= 256) DSLLM_GEMM(256, 256, 256, gemm_bf16_256_kernel<WIDE>);
+    else if (n64 > 4 * 256) DSLLM_GEMM(128, 128, 256, gemm_bf16_kernel<4, 4, 2, 2, 1, 2, WIDE>);
+    else if (n64 > 2 * 256) DSLLM_GEMM(128, 128, 1024, gemm_bf16_kernel<2, 2, 4, 4, 1, 4, WIDE>);
+    else if (n64 > 256 || k < 512) DSLLM_GEMM(64, 64, 256, gemm_bf16_kernel<2, 2, 2, 2, 1, 3, WIDE>);
+    else if (n64 > 128) DSLLM_GEMM(64, 64, 512, gemm_bf16_kernel<2, 2, 2, 2, 2, 3, WIDE>);
+    else DSLLM_GEMM(32, 64, 1024, gemm_bf16_kernel<1, 2, 2, 2, 4, 3, WIDE>);
 }
 #undef DSLLM_GEMM
 
@@ -408,7 +414,8 @@ extern "C" {
 int proxy_gemm_bf16(const void *a, const void *b, void *c, int32_t m, int32_t n, int32_t k, void *stream) {
     if (!a || !b || !c || m <= 0 || n <= 0 || k <= 0 || m % 128 || n % 128 || k % 64) return -1;
     if ((uint64_t(a) | uint64_t(b) | uint64_t(c)) & 15) return -1;
-    launch_gemm(static_cast<const uint16_t *>(a), static_cast<const uint16_t *>(b), static_cast<uint16_t *>(c), m, n, k, static_cast<hipStream_t>(stream));
+    const auto launch = k > (1 << 22) ? launch_gemm<true> : launch_gemm<false>;
+    launch(static_cast<const uint16_t *>(a), static_cast<const uint16_t *>(b), static_cast<uint16_t *>(c), m, n, k, static_cast<hipStream_t>(stream));
     return hip_rc();
 }
 

@@ -70,3 +70,37 @@ def test_gemm_with_rows_beyond_32_bit_offsets():
     assert np.all(np.abs(got - ref) <= len(at) * 2.0 ** -23 * ref_abs + 2.0 ** -8 * np.abs(ref) + 1e-30)
     for x in bufs + [dc]:
         x.free()
+
+
+# one shape for every kernel and tile, as above, with the fewest tiles of its range
+@pytest.mark.parametrize("m,n", [(3072, 4096), (2176, 2048), (1536, 2048), (1152, 1024), (640, 1280), (256, 384)])
+def test_gemm_tiles_with_rows_beyond_32_bit_offsets(m, n):
+    """K past 2^22: rows of A and B are zero but for eight columns in each of a few places, that of the first, of the last
+    and of an odd step of K among them."""
+    k = (1 << 22) + 64
+    print(f"gemm {m}x{n}x{k}", flush=True)
+    rng = np.random.default_rng(m + n)
+    at = [0, 5 * 64 + 24, (1 << 21) + 8, (1 << 22) - 8, (1 << 22) + 56]
+    cols, bufs = [], []
+    for rows in (m, n):
+        c = po.bf16_bits(rng.standard_normal((rows, 8 * len(at))).astype(np.float32))
+        d = harness.DevBuf(2 * rows * k)
+        B.proxy_device_fill_async(d.ptr, 0, d.nbytes, 0)
+        harness.synchronize()
+        for r in range(rows):
+            for i, col in enumerate(at):
+                B.proxy_copy_h2d(d.ptr + 2 * (r * k + col), c[r, 8 * i:].ctypes.data, 16)
+        cols.append(c)
+        bufs.append(d)
+    dc = harness.DevBuf(2 * m * n + 4096)
+    B.proxy_device_fill_async(dc.ptr, 0xEE, dc.nbytes, 0)
+    B.proxy_gemm_bf16(bufs[0].ptr, bufs[1].ptr, dc.ptr, m, n, k, 0)
+    harness.synchronize()
+    out = gu.download(dc)
+    assert np.all(out[2 * m * n:] == 0xEE)
+    got = po.bf16_to_f64(out[:2 * m * n].view(np.uint16).reshape(m, n))
+    ref, ref_abs = po.gemm_bf16(*cols)
+    # f32 sums of 40 products that are not zero; one rounding to bf16
+    assert np.all(np.abs(got - ref) <= 40 * 2.0 ** -23 * ref_abs + 2.0 ** -8 * np.abs(ref) + 1e-30)
+    for x in bufs + [dc]:
+        x.free()
