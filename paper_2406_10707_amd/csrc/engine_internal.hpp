@@ -34,8 +34,9 @@ namespace dsllm {
 hipError_t launch_pack(const ckpt_tile *dev_tiles, uint64_t n_tiles, void *slot_base, uint64_t slot_data_off, hipStream_t stream,
                        hipEvent_t t_start = nullptr, hipEvent_t t_stop = nullptr);
 hipError_t launch_scatter(const ckpt_tile *dev_tiles, uint64_t n_tiles, const void *slot_base, uint64_t slot_data_off, hipStream_t stream);
-hipError_t launch_verify_pairs(const PairTile *dev_tiles, uint64_t n_tiles, uint32_t *dev_flag, hipStream_t stream);
-hipError_t launch_derive_pairs(const PairTile *dev_tiles, uint64_t n_tiles, hipStream_t stream);
+// n_blocks: how many of the n_tiles are not small (they come first)
+hipError_t launch_verify_pairs(const PairTile *dev_tiles, uint64_t n_blocks, uint64_t n_tiles, uint32_t *dev_flag, hipStream_t stream);
+hipError_t launch_derive_pairs(const PairTile *dev_tiles, uint64_t n_blocks, uint64_t n_tiles, hipStream_t stream);
 }  // namespace dsllm
 
 using namespace dsllm;

@@ -1,5 +1,6 @@
 #include "plan.hpp"
 
+#include <algorithm>
 #include <cstring>
 
 namespace dsllm {
@@ -121,6 +122,8 @@ int build_plan(const ckpt_tensor_desc *descs, size_t n, const ResolvedConfig &cf
                 p.n_derived++; p.derived_bytes += t.nbytes;
             }
         }
+        p.n_pair_blocks = uint64_t(std::stable_partition(p.pair_tiles.begin(), p.pair_tiles.end(), [](const PairTile &t) { return t.count > kPairSmallElems; }) -
+                                   p.pair_tiles.begin());
     }
     if (p.version == 2) table += 5ull * n;     // enc u8 + ref u32 at the end of every entry
     p.header_bytes = align_up(kFixedHeader + table, kAlign);

@@ -27,8 +27,9 @@ struct TensorInfo {
     uint32_t source = 0;
 };
 
-// One work item of the derivation kernels: `count` elements of an f32 tensor and of its bf16 copy.
-constexpr uint32_t kPairTileElems = 8192;
+// One work item of the derivation kernels: `count` elements of an f32 tensor and of its bf16 copy. A block of the kernels
+// takes one, or several of at most kPairSmallElems (one per wave).
+constexpr uint32_t kPairTileElems = 4096, kPairSmallElems = 512;
 struct PairTile {
     uint64_t f32_addr;
     uint64_t bf16_addr;
@@ -61,7 +62,8 @@ struct Plan {
     uint64_t n_host = 0, host_bytes = 0, host_data_bytes = 0;
     uint32_t version = 1;                 // file format version this plan writes: 2 when tensors are derived
     uint64_t n_derived = 0, derived_bytes = 0;   // tensors described but not stored, and their payload
-    std::vector<PairTile> pair_tiles;     // the declared pairs cut into work items (filled in both plans of a registration)
+    std::vector<PairTile> pair_tiles;     // the declared pairs cut into work items (filled in both plans of a registration), the small ones last
+    uint64_t n_pair_blocks = 0;           // how many of them are not small
 
     uint64_t file_bytes() const { return header_bytes + data_bytes; }
     uint64_t chunk_bytes(uint64_t c) const {      // last chunk may be short (still a 4 KiB multiple)

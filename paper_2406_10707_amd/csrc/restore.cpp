@@ -157,7 +157,7 @@ static int restore_body(ckpt_ctx *c, int fd, const char *path, hipStream_t strea
         // their direct copies): the derived tensors are then recomputed from their sources
         if (p.n_direct)
             for (size_t k = 0; k < nk; k++) HIP_TRY(c, hipStreamWaitEvent(c->pack_stream, c->ev_job_tail[k], 0));
-        HIP_TRY(c, launch_derive_pairs(c->dev_pairs, c->plan.pair_tiles.size(), c->pack_stream));
+        HIP_TRY(c, launch_derive_pairs(c->dev_pairs, c->plan.n_pair_blocks, c->plan.pair_tiles.size(), c->pack_stream));
         HIP_TRY(c, hipEventRecord(c->ev_derived, c->pack_stream));
         HIP_TRY(c, hipStreamWaitEvent(stream, c->ev_derived, 0));
     }

@@ -58,7 +58,7 @@ static void submit_one(ckpt_ctx *c, const std::shared_ptr<Snap> &sp) {
     if (c->have_rplan) {
         bool launched = true;
         if ((e = hipEventRecord(c->ev_verify_start, c->pack_stream)) != hipSuccess) { hip_fail("record", e); launched = false; }
-        if (launched && (e = launch_verify_pairs(c->dev_pairs, c->plan.pair_tiles.size(), c->dev_flag, c->pack_stream)) != hipSuccess) { hip_fail("verify launch", e); launched = false; }
+        if (launched && (e = launch_verify_pairs(c->dev_pairs, c->plan.n_pair_blocks, c->plan.pair_tiles.size(), c->dev_flag, c->pack_stream)) != hipSuccess) { hip_fail("verify launch", e); launched = false; }
         if (launched && (e = hipMemcpyAsync(c->host_flag, c->dev_flag, sizeof(uint32_t), hipMemcpyDeviceToHost, c->pack_stream)) != hipSuccess) { hip_fail("verdict copy", e); launched = false; }
         if (launched && (e = hipEventRecord(c->ev_verify_done, c->pack_stream)) != hipSuccess) { hip_fail("record", e); launched = false; }
         if (launched && (e = hipEventSynchronize(c->ev_verify_done)) != hipSuccess) { hip_fail("verdict sync", e); launched = false; }

@@ -12,12 +12,14 @@ from tests import gpu_util as gu
 
 pytestmark = pytest.mark.gpu
 COUNTS = [1, 3, 4, 5, 7, 1023, 1024, 1025, 4095, 4096, 4097, 8191, 8192, 8193, 12289, 20003]
+# around a wave's share, small work items in a number that four does not divide
+SMALL = [2, 255, 256, 257, 259, 508, 511, 512, 513, 516, 4608, 4609, 8192 + 511]
 
 
-def _state(shift):
+def _state(shift, counts):
     """Tensors p0, m0, p1, m1, ... in two flat buffers, starts shifted element-wise by up to 15."""
     tensors, off = [], [0, 0]
-    for k, n in enumerate(COUNTS):
+    for k, n in enumerate(counts):
         for b, (role, code, es) in enumerate((("p_bf16", B.CKPT_BF16, 2), ("master", B.CKPT_F32, 4))):
             off[b] += es * ((k * 5 + shift) % 16)
             tensors.append(shards.TensorSpec(f"t{k}.{role}", code, (n,), buffer=b, offset=off[b], role="raw"))
@@ -25,16 +27,17 @@ def _state(shift):
     return shards.ShardSpec("pairs", 7, tensors, flat_buffers=[(o + 255) // 256 * 256 + 256 for o in off])
 
 
+@pytest.mark.parametrize("counts", [COUNTS, SMALL], ids=["counts", "small"])
 @pytest.mark.parametrize("shift", [0, 1, 2, 3])
-def test_check_and_regeneration(tmp_path, shift):
+def test_check_and_regeneration(tmp_path, shift, counts):
     print(f"pairs unaligned, shift {shift}", flush=True)
-    shard, stream = harness.DeviceShard(_state(shift)), harness.Stream()
+    shard, stream = harness.DeviceShard(_state(shift, counts)), harness.Stream()
     rng = np.random.default_rng(shift)
     for f in shard.flat:
         B.proxy_device_fill_async(f.ptr, 0x5A, f.nbytes, stream.handle)
     stream.synchronize()
     bits = []
-    for k, n in enumerate(COUNTS):
+    for k, n in enumerate(counts):
         m = (rng.standard_normal(n, dtype=np.float32) * np.float32(0.02))
         special = np.array([0x7FC00001, 0xFFC12345, 0x80000000, 0x00000001, 0x807FFFFF, 0xFFFFFFFF, 0x7F800000, 0x3F808000, 0x3F818000], dtype=np.uint32)
         u = m.view(np.uint32).copy()
@@ -44,7 +47,7 @@ def test_check_and_regeneration(tmp_path, shift):
         B.proxy_copy_h2d(shard.ptrs[2 * k], p.ctypes.data, p.nbytes)
         B.proxy_copy_h2d(shard.ptrs[2 * k + 1], u.ctypes.data, u.nbytes)
     ck = B.Checkpointer(B.make_config(out_dir=str(tmp_path), dma_chunk_bytes=64 << 10, pack_superchunk_bytes=256 << 10, host_ring_bytes=256 << 10))
-    ck.declare_derived([(2 * k, 2 * k + 1) for k in range(len(COUNTS))])
+    ck.declare_derived([(2 * k, 2 * k + 1) for k in range(len(counts))])
     ck.register_tensors(shard.descs())
     it = 0
 
@@ -59,7 +62,7 @@ def test_check_and_regeneration(tmp_path, shift):
     assert snapshot() == 2
     whole = [gu.download(f) for f in shard.flat]
     good = ck.file_name(it)
-    for k, n in enumerate(COUNTS):
+    for k, n in enumerate(counts):
         p = bits[k][0]
         for e in sorted({0, n - 1, n // 4 * 4 - 1, min(n - 1, n // 4 * 4), min(n, 4096) - 1, min(n - 1, 4096), min(n, 8192) - 1, min(n - 1, 8192)}):
             if e < 0:
@@ -69,7 +72,7 @@ def test_check_and_regeneration(tmp_path, shift):
             assert snapshot() == 1, (k, n, e)
             B.proxy_copy_h2d(shard.ptrs[2 * k] + 2 * e, p[e:e + 1].ctypes.data, 2)
     assert snapshot() == 2
-    for k, n in enumerate(COUNTS):      # the stored state stays, the derived one is lost; the guards keep their bytes
+    for k, n in enumerate(counts):      # the stored state stays, the derived one is lost; the guards keep their bytes
         junk = np.full(n, 0xABCD, dtype=np.uint16)
         B.proxy_copy_h2d(shard.ptrs[2 * k], junk.ctypes.data, junk.nbytes)
         zeros = np.zeros(n, dtype=np.uint32)
