@@ -377,6 +377,9 @@ __global__ __launch_bounds__(256) void gemm_bf16_256_kernel(const uint16_t *__re
 //    at 128 tiles 128 x 128 wins (2048 x 4096 x 4096: 63 against 72, 88 before). Below K = 256 its 128 KiB prologue shows.
 //  * 128 x 128 in four waves and 64 KiB of LDS, two blocks per unit, while there are more tiles than units:
 //    1408 x 4608 x 3072 69 -> 48 us.
+//    With two to three tiles per unit and K from 16384 on the sixteen-wave form below instead: the second round's blocks, one
+//    to a unit, run against two to a unit, and along a long K they no longer share panels in L2. 1408 x 8064 x 26816 905 -> 787
+//    us (two blocks per unit: 961 to 988), 1152 x 7808 x 53568 1759 -> 1533 (1775); at K = 14000 the two are even.
 //  * one 128 x 128 tile per unit at most: sixteen waves and four steps in LDS, as one block has to hide its own latency:
 //    512 x 5632 x 1536 25 -> 14 us (four waves: 18, 64 x 64 tiles: 16).
 //  * fewer than half as many: 64 x 64, three blocks per unit: 2048 x 1024 x 2048 34 -> 14 us.
@@ -391,7 +394,7 @@ template <bool WIDE>
 void launch_gemm(const uint16_t *a, const uint16_t *b, uint16_t *c, int m, int n, int k, hipStream_t stream) {
     const int64_t n64 = int64_t(m / 64) * (n / 64);
     if (m % 256 == 0 && n % 256 == 0 && n64 >= 192 * 16 && k >= 256) DSLLM_GEMM(256, 256, 256, gemm_bf16_256_kernel<WIDE>);
-    else if (n64 > 4 * 256) DSLLM_GEMM(128, 128, 256, gemm_bf16_kernel<4, 4, 2, 2, 1, 2, WIDE>);
+    else if (n64 > 4 * 256 && (k < (1 << 14) || n64 <= 8 * 256 || n64 > 12 * 256)) DSLLM_GEMM(128, 128, 256, gemm_bf16_kernel<4, 4, 2, 2, 1, 2, WIDE>);
     else if (n64 > 2 * 256) DSLLM_GEMM(128, 128, 1024, gemm_bf16_kernel<2, 2, 4, 4, 1, 4, WIDE>);
     else if (n64 > 256 || k < 512) DSLLM_GEMM(64, 64, 256, gemm_bf16_kernel<2, 2, 2, 2, 1, 3, WIDE>);
     else if (n64 > 128) DSLLM_GEMM(64, 64, 512, gemm_bf16_kernel<2, 2, 2, 2, 2, 3, WIDE>);

@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 SHAPES = [(3072, 4096, 256), (3072, 4096, 320), (4096, 3328, 448),       # 256 x 256 tiles
           (2176, 2048, 64), (2176, 2048, 192), (128, 67328, 128),        # 128 x 128, two blocks per unit
-          (1536, 2048, 64), (1664, 1920, 320),                           # 128 x 128, sixteen waves
+          (1536, 2048, 64), (1664, 1920, 320), (2432, 3456, 16384),      # 128 x 128, sixteen waves
           (1152, 1024, 64), (1024, 1152, 576), (128, 128, 64), (256, 128, 448),     # 64 x 64
           (640, 1280, 512), (1024, 1024, 576), (640, 1408, 1088),        # 64 x 64, K split in two
           (128, 128, 512), (256, 384, 576), (512, 1024, 640), (128, 256, 704)]      # 32 x 64, K split in four
