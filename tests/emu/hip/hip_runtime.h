@@ -147,8 +147,20 @@ inline hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind
     emu_submit(st, [=] { memcpy(d, s, n); });
     return hipSuccess;
 }
-inline hipError_t hipPointerGetAttributes(hipPointerAttribute_t *a, const void *) { a->type = hipMemoryTypeDevice; a->device = 0; return hipSuccess; }
-inline hipError_t hipMemGetAddressRange(hipDeviceptr_t *, size_t *, hipDeviceptr_t) { return hipErrorNotSupported; }
+// a test may say what allocations there are (base and size of the one that holds an address, false if none does) and count the queries
+inline std::atomic<bool (*)(const void *, void **, size_t *)> g_emu_allocation_of{nullptr};
+inline std::atomic<int> g_emu_pointer_queries{0};
+inline hipError_t hipPointerGetAttributes(hipPointerAttribute_t *a, const void *p) {
+    g_emu_pointer_queries++;
+    void *base; size_t size;
+    if (auto of = g_emu_allocation_of.load()) if (!of(p, &base, &size)) return hipErrorInvalidValue;
+    a->type = hipMemoryTypeDevice; a->device = 0;
+    return hipSuccess;
+}
+inline hipError_t hipMemGetAddressRange(hipDeviceptr_t *base, size_t *size, hipDeviceptr_t p) {
+    auto of = g_emu_allocation_of.load();
+    return of && of(p, base, size) ? hipSuccess : hipErrorNotSupported;
+}
 
 inline hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { *s = new EmuStream; return hipSuccess; }
 inline hipError_t hipStreamDestroy(hipStream_t s) { delete s; return hipSuccess; }
