@@ -247,6 +247,8 @@ int ckpt_init(const ckpt_config *cfg, ckpt_ctx **out) {
     if ((e = hipEventCreate(&c->ev_first_copy)) != hipSuccess) return cleanup_fail(CKPT_EHIP, hipGetErrorString(e));
     if ((e = hipEventCreate(&c->ev_user)) != hipSuccess) return cleanup_fail(CKPT_EHIP, hipGetErrorString(e));
     if ((e = hipEventCreate(&c->ev_packed_head)) != hipSuccess) return cleanup_fail(CKPT_EHIP, hipGetErrorString(e));
+    if ((e = hipEventCreate(&c->ev_head_end)) != hipSuccess) return cleanup_fail(CKPT_EHIP, hipGetErrorString(e));
+    if ((e = hipEventCreate(&c->ev_rest_start)) != hipSuccess) return cleanup_fail(CKPT_EHIP, hipGetErrorString(e));
     if ((e = hipEventCreate(&c->ev_scattered)) != hipSuccess) return cleanup_fail(CKPT_EHIP, hipGetErrorString(e));
     void *ring = nullptr;
     trace("init: allocating the pinned ring");
@@ -636,6 +638,8 @@ int ckpt_destroy(ckpt_ctx *c) {
     if (c->ev_first_copy) (void)hipEventDestroy(c->ev_first_copy);
     if (c->ev_user) (void)hipEventDestroy(c->ev_user);
     if (c->ev_packed_head) (void)hipEventDestroy(c->ev_packed_head);
+    if (c->ev_head_end) (void)hipEventDestroy(c->ev_head_end);
+    if (c->ev_rest_start) (void)hipEventDestroy(c->ev_rest_start);
     if (c->ev_scattered) (void)hipEventDestroy(c->ev_scattered);
     if (c->pack_stream) (void)hipStreamDestroy(c->pack_stream);
     for (auto s : c->dma) (void)hipStreamDestroy(s);

@@ -96,6 +96,7 @@ struct Snap {
     std::atomic<uint64_t> io_wait_us{0}, io_copy_us{0};   // summed over the I/O threads
     double pack_ms_sum = -1, req_to_d2h_end_ms = -1, d2h_span_ms = -1, req_to_pack_end_ms = -1;
     std::vector<uint8_t> host_capture;      // the host-resident objects as they were when the snapshot was requested
+    bool head_apart = false;                // the first super-chunk was packed in two launches (its first chunk, the rest)
     int policy = CKPT_WINDOW_D2H;           // window policy in force when the snapshot was requested
     int tier2_state = CKPT_TIER2_NONE;      // ckpt_tier2_state
     double tier2_ms = -1;                   // host: copy to the second tier, open to rename
@@ -160,6 +161,7 @@ struct ckpt_ctx {
     std::vector<hipEvent_t> ev_job_tail;                  // per dma stream
     hipEvent_t ev_first_copy = nullptr, ev_user = nullptr;
     hipEvent_t ev_packed_head = nullptr;                  // the first chunk of a snapshot is in staging
+    hipEvent_t ev_head_end = nullptr, ev_rest_start = nullptr;   // timing of the first super-chunk's two launches, between ev_pack_start[0] and ev_pack_end[0]
     hipEvent_t ev_scattered = nullptr;                    // restore: what the pack stream held before it has read staging
     uint8_t *hdr_buf = nullptr;                           // 4 KiB-aligned scratch for header writes
     uint64_t ring_next = 0;                               // global chunk counter -> ring slot

@@ -10,8 +10,12 @@ static void finish_d2h_stats(ckpt_ctx *c, Snap *s) {
     double pack_sum = 0, req_d2h = 0, span = 0, req_pack = 0;
     float ms = 0;
     const uint64_t n_sc = s->plan->n_superchunks;
-    for (uint64_t i = 0; i < n_sc; i++)
-        if (hipEventElapsedTime(&ms, c->ev_pack_start[i], c->ev_pack_end[i]) == hipSuccess) pack_sum += ms;
+    auto add_launch = [&](hipEvent_t start, hipEvent_t end) { if (hipEventElapsedTime(&ms, start, end) == hipSuccess) pack_sum += ms; };
+    for (uint64_t i = 0; i < n_sc; i++) {
+        const bool parts = i == 0 && s->head_apart;   // two launches
+        if (parts) add_launch(c->ev_pack_start[0], c->ev_head_end);
+        add_launch(parts ? c->ev_rest_start : c->ev_pack_start[i], c->ev_pack_end[i]);
+    }
     for (size_t k = 0; k < c->dma.size(); k++) {
         if (hipEventElapsedTime(&ms, s->ev_boundary, c->ev_job_tail[k]) == hipSuccess && ms > req_d2h) req_d2h = ms;
         if (hipEventElapsedTime(&ms, c->ev_first_copy, c->ev_job_tail[k]) == hipSuccess && ms > span) span = ms;

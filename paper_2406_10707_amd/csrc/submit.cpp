@@ -192,6 +192,7 @@ static void submit_one(ckpt_ctx *c, const std::shared_ptr<Snap> &sp) {
     const uint64_t ahead = s->policy == CKPT_WINDOW_PACK ? c->n_stage : std::min<uint64_t>(c->n_stage, 2);
     // whether the first super-chunk has tiles both in its first chunk and behind it
     const bool head_apart = p.n_chunks > 1 && SC > CH && p.sc_first_tile[0] < p.first_tile_at(0, CH) && p.first_tile_at(0, CH) < p.sc_first_tile[1];
+    s->head_apart = head_apart;
     auto enqueue_pack = [&](uint64_t sc) {
         const uint64_t stage = sc % c->n_stage;
         if (sc >= ahead)
@@ -205,14 +206,14 @@ static void submit_one(ckpt_ctx *c, const std::shared_ptr<Snap> &sp) {
         uint64_t t0 = p.sc_first_tile[sc];
         const uint64_t t1 = p.sc_first_tile[sc + 1];
         hipEvent_t start = c->ev_pack_start[sc];
-        if (head_apart && sc == 0) {
+        if (head_apart && sc == 0) {   // each of the two launches has its own start and end, as the pack time is the sum of the launches'
             // The first chunk's tiles go in a launch of their own: the link starts when they are in staging and not when a
             // whole super-chunk is (0.18 ms per GiB of aligned tensors, twice that beside a GEMM).
             const uint64_t tc = p.first_tile_at(0, CH);
-            if ((e = launch_pack(s->dev_tiles + t0, tc - t0, c->staging, 0, c->pack_stream, start, nullptr)) != hipSuccess) hip_fail("pack launch", e);
+            if ((e = launch_pack(s->dev_tiles + t0, tc - t0, c->staging, 0, c->pack_stream, start, c->ev_head_end)) != hipSuccess) hip_fail("pack launch", e);
             if ((e = hipEventRecord(c->ev_packed_head, c->pack_stream)) != hipSuccess) hip_fail("record", e);
             t0 = tc;
-            start = nullptr;
+            start = c->ev_rest_start;
         }
         if ((e = launch_pack(s->dev_tiles + t0, t1 - t0, c->staging + stage * SC, sc * SC, c->pack_stream, start, c->ev_pack_end[sc])) != hipSuccess)
             hip_fail("pack launch", e);
