@@ -34,9 +34,12 @@ static int restore_body(ckpt_ctx *c, int fd, const char *path, hipStream_t strea
 
     // An earlier restore's scatter kernels may still be queued (ckpt_restore does not wait for the caller's stream, which they
     // come behind): the copies into staging follow them. Recorded ahead of the wait below, so that the copies do not have
-    // to wait for the caller's stream themselves.
-    HIP_TRY(c, hipEventRecord(c->ev_scattered, c->pack_stream));
-    for (size_t k = 0; k < nk; k++) HIP_TRY(c, hipStreamWaitEvent(c->dma[k], c->ev_scattered, 0));
+    // to wait for the caller's stream themselves; not at all when nothing is queued (20 of 105 us on a 256 KiB shard).
+    if (hipStreamQuery(c->pack_stream) != hipSuccess) {
+        (void)hipGetLastError();   // "not ready" is no error of a later call
+        HIP_TRY(c, hipEventRecord(c->ev_scattered, c->pack_stream));
+        for (size_t k = 0; k < nk; k++) HIP_TRY(c, hipStreamWaitEvent(c->dma[k], c->ev_scattered, 0));
+    }
     // earlier work on the caller's stream (which may read or write the tensors) comes first
     HIP_TRY(c, hipEventRecord(c->ev_user, stream));
     HIP_TRY(c, hipStreamWaitEvent(c->pack_stream, c->ev_user, 0));
