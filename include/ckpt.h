@@ -182,7 +182,7 @@ typedef struct {
     uint64_t iter;
     uint64_t payload_bytes, data_bytes, file_bytes;
     int32_t d2h_done, committed;      /* 1 once the last copy has landed / the file has its final name */
-    int32_t pack_launches;            /* super-chunks packed: a launch each, but two for the first of several chunks (its first chunk goes ahead) */
+    int32_t pack_launches;            /* super-chunks packed: a launch each, but two for a large first one (its first chunk goes ahead) */
     int32_t tier2_state;              /* ckpt_tier2_state */
     double pack_ms_sum;               /* sum over all pack launches of (end - start) on the pack stream */
     double request_to_d2h_end_ms;     /* boundary event on the caller's stream -> last copy done */

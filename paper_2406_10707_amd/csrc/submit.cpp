@@ -14,6 +14,15 @@ static bool packs_straight_into_ring(const Plan &p, int policy) {
     return policy == CKPT_WINDOW_D2H && p.n_chunks == 1 && p.data_bytes <= kStraightBytes && p.segs.size() == 1 && p.segs[0].kind == CKPT_SEG_STAGED;
 }
 
+// The tiles of a snapshot's first chunk go in a launch of their own where at least so many are left behind them in the super-chunk
+// (32 MiB of whole tiles): the link then starts when the first chunk is in staging and not when the whole super-chunk is
+// (0.18 ms per GiB of aligned tensors, twice that beside a GEMM). The second launch and its events cost the snapshot
+// 10 to 20 us: window of a 20 MiB shard in chunks of 4 MiB 540 us apart, 531 together; 60 MiB 1374, 1381; 250 MiB (chunks of
+// 16 MiB) 4895, 4970.
+#ifndef DSLLM_HEAD_APART_TILES
+#define DSLLM_HEAD_APART_TILES 1024
+#endif
+
 static void submit_one(ckpt_ctx *c, const std::shared_ptr<Snap> &sp) {
     Snap *s = sp.get();
     const uint64_t CH = c->cfg.dma_chunk_bytes, SC = c->cfg.pack_superchunk_bytes;
@@ -190,8 +199,8 @@ static void submit_one(ckpt_ctx *c, const std::shared_ptr<Snap> &sp) {
     // forward pass). Pack sc needs the staging slot that the copies of super-chunk sc - ahead read (ahead <= n_stage,
     // copies are in order): this thread waits for those copies on the host and launches the pack then.
     const uint64_t ahead = s->policy == CKPT_WINDOW_PACK ? c->n_stage : std::min<uint64_t>(c->n_stage, 2);
-    // whether the first super-chunk has tiles both in its first chunk and behind it
-    const bool head_apart = p.n_chunks > 1 && SC > CH && p.sc_first_tile[0] < p.first_tile_at(0, CH) && p.first_tile_at(0, CH) < p.sc_first_tile[1];
+    const uint64_t behind_head = p.first_tile_at(0, CH);      // first tile that is not the first chunk's
+    const bool head_apart = p.n_chunks > 1 && SC > CH && p.sc_first_tile[0] < behind_head && behind_head + DSLLM_HEAD_APART_TILES <= p.sc_first_tile[1];
     s->head_apart = head_apart;
     auto enqueue_pack = [&](uint64_t sc) {
         const uint64_t stage = sc % c->n_stage;
@@ -207,12 +216,9 @@ static void submit_one(ckpt_ctx *c, const std::shared_ptr<Snap> &sp) {
         const uint64_t t1 = p.sc_first_tile[sc + 1];
         hipEvent_t start = c->ev_pack_start[sc];
         if (head_apart && sc == 0) {   // each of the two launches has its own start and end, as the pack time is the sum of the launches'
-            // The first chunk's tiles go in a launch of their own: the link starts when they are in staging and not when a
-            // whole super-chunk is (0.18 ms per GiB of aligned tensors, twice that beside a GEMM).
-            const uint64_t tc = p.first_tile_at(0, CH);
-            if ((e = launch_pack(s->dev_tiles + t0, tc - t0, c->staging, 0, c->pack_stream, start, c->ev_head_end)) != hipSuccess) hip_fail("pack launch", e);
+            if ((e = launch_pack(s->dev_tiles + t0, behind_head - t0, c->staging, 0, c->pack_stream, start, c->ev_head_end)) != hipSuccess) hip_fail("pack launch", e);
             if ((e = hipEventRecord(c->ev_packed_head, c->pack_stream)) != hipSuccess) hip_fail("record", e);
-            t0 = tc;
+            t0 = behind_head;
             start = c->ev_rest_start;
         }
         if ((e = launch_pack(s->dev_tiles + t0, t1 - t0, c->staging + stage * SC, sc * SC, c->pack_stream, start, c->ev_pack_end[sc])) != hipSuccess)

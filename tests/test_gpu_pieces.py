@@ -21,6 +21,7 @@ MIB = 1 << 20
     ([3, 16 * MIB, 20 * MIB + 7, 11, 33 * MIB], 16 * MIB, {"keep_last": 1, "prealloc_files": 2, "n_io_threads": 1}),
     ([3, 16 * MIB, 20 * MIB + 7, 11, 33 * MIB], 16 * MIB, {"direct_min_bytes": 4 * MIB}),
     ([70 * MIB + 13, 1], 64 * MIB, {"n_io_threads": 7}),
+    ([3, 16 * MIB, 20 * MIB + 7, 11, 33 * MIB], 16 * MIB, {"pack_superchunk_bytes": 64 * MIB}),       # the first chunk packed apart
 ])
 def test_snapshot_and_restore(tmp_path, sizes, chunk, options):
     print(f"pieces {sizes} chunk {chunk} {options}", flush=True)
@@ -30,7 +31,7 @@ def test_snapshot_and_restore(tmp_path, sizes, chunk, options):
         off += n + 2 * k + 1
     shard = harness.DeviceShard(shards.ShardSpec("pieces", 3, tensors, flat_buffers=[(off + 255) // 256 * 256]))
     stream = harness.Stream()
-    ck = B.Checkpointer(B.make_config(out_dir=str(tmp_path), dma_chunk_bytes=chunk, pack_superchunk_bytes=2 * chunk, host_ring_bytes=2 * chunk, **options))
+    ck = B.Checkpointer(B.make_config(**{"out_dir": str(tmp_path), "dma_chunk_bytes": chunk, "pack_superchunk_bytes": 2 * chunk, "host_ring_bytes": 2 * chunk, **options}))
     ck.register_tensors(shard.descs())
     shard.fill_device(stream)
     for it in (1, 2, 3):

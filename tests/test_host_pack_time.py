@@ -15,7 +15,7 @@ def test_pack_time_is_that_of_the_launches(tmp_path):
         pytest.skip("ROCm clang not present")
     exe = str(tmp_path / "emu_pack_time")
     subprocess.run([CLANG, "-x", "c++", "-std=c++17", "-O1", "-g", "-fsanitize=thread", "-fno-omit-frame-pointer", "-pthread",
-                    "-I", os.path.join(ROOT, "tests", "emu"), "-o", exe, os.path.join(ROOT, "tests", "emu", "emu_pack_time.cpp"),
+                    "-DDSLLM_HEAD_APART_TILES=1", "-I", os.path.join(ROOT, "tests", "emu"), "-o", exe, os.path.join(ROOT, "tests", "emu", "emu_pack_time.cpp"),
                     *[os.path.join(ROOT, "paper_2406_10707_amd", "csrc", f) for f in SOURCES]], check=True, cwd=os.path.join(ROOT, "tests", "emu"))
     r = subprocess.run([exe, str(tmp_path)], capture_output=True, text=True, timeout=300)
     out = r.stdout + r.stderr
