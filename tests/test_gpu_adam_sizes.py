@@ -1,5 +1,7 @@
 """The Adam step where its grid ends: one lane, the last lane of a block, one beyond it, a tail behind whole quads; nothing
 outside the tensors is touched. Against the float64 oracle."""
+import zlib
+
 import numpy as np
 import pytest
 
@@ -40,3 +42,28 @@ def test_adam_at_the_edges_of_its_grid(numel):
     assert np.max(np.abs(gv - ov)) <= 1e-5 * np.max(np.abs(ov)) + 1e-18
     assert np.all(np.abs(gw - ow) <= 1e-5 * (np.abs(w0) + np.abs(ow - w0)) + 1e-12)
     assert np.array_equal(gp, po.bf16_bits(gw))
+
+
+def _after_three_steps(n):
+    """Outputs of three steps from states whose elements depend on their index alone."""
+    u = ((np.arange(3 * 65538, dtype=np.uint64) * np.uint64(2654435761)) & np.uint64(0xFFFFFFFF)).astype(np.uint32).reshape(3, -1)[:, :n] >> 8
+    state = [u[k].astype(np.float32) * np.float32(s) for k, s in enumerate((2.0 ** -29, -2.0 ** -31, 2.0 ** -44))]
+    bufs = [harness.DevBuf(es * n) for es in (2, 4, 4, 4)]
+    for b, x in zip(bufs[1:], state):
+        b.upload(x)
+    harness.synchronize()
+    for step in (1, 2, 3):
+        B.proxy_adam_step(*[b.ptr for b in bufs], n, 11, 2, step, 0)
+    harness.synchronize()
+    return [gu.download(b) for b in bufs]
+
+
+def test_adam_bits():
+    """The bits that the grid-stride form of this kernel gave (checksums taken from it), and the same bits whether an element
+    falls into a whole quad or into the tail."""
+    print("adam bits", flush=True)
+    whole = _after_three_steps(65538)
+    assert [zlib.crc32(x.tobytes()) for x in whole] == [0x62b7252e, 0x2ce87695, 0x81f84e75, 0x81b6bda4]
+    for n in (1, 3, 255, 1027, 65537):
+        for part, all_, es in zip(_after_three_steps(n), whole, (2, 4, 4, 4)):
+            assert np.array_equal(part, all_[:es * n]), n
