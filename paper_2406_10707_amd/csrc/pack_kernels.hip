@@ -297,45 +297,7 @@ __global__ __launch_bounds__(kBlock) void scatter_kernel(const ckpt_tile *__rest
     if (lane < tail) dst[done + lane] = src[done + lane];
 }
 
-// ---------------------------------------------------------------- tile table built on the device
-
-// The tile table of a tensor list, written by the device itself: one block per tensor, one thread per
-// tile. ckpt_pack_image used to walk such a table (pack_batch_kernel needs none); it stays as the second, independent
-// construction that the planner's table is compared with. The descriptors travel in the kernel arguments (a batch of up to kTileBatch tensors per
-// launch), so nothing is copied from host memory and the launch can be recorded like any other.
-// Tile i of a tensor whose padded extent is [d0, dend) of the data region: the extent is cut at its
-// start and at every multiple of the tile size, exactly as the host planner cuts it.
-__global__ __launch_bounds__(256) void build_tiles_kernel(TileBatch bt, ckpt_tile *__restrict__ table) {
-    const uint32_t k = blockIdx.x;
-    if (k >= bt.count) return;
-    const uint64_t T = kPackTileBytes;
-    const uint64_t d0 = bt.data_off[k], nbytes = bt.nbytes[k], src = bt.src[k];
-    const uint64_t dend = d0 + (nbytes + 4095) / 4096 * 4096;
-    const uint32_t n = bt.first_tile[k + 1] - bt.first_tile[k];
-    ckpt_tile *out = table + bt.first_tile[k];
-    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) {
-        const uint64_t start = i == 0 ? d0 : (d0 / T + i) * T;
-        uint64_t stop = (d0 / T + i + 1) * T;
-        if (stop > dend) stop = dend;
-        const uint64_t rel = start - d0;
-        const uint64_t left = rel >= nbytes ? 0 : nbytes - rel;
-        ckpt_tile t;
-        t.src = src + rel;
-        t.dst_off = start;
-        t.copy_bytes = uint32_t(left < stop - start ? left : stop - start);
-        t.total_bytes = uint32_t(stop - start);
-        t.reserved = 0;
-        out[i] = t;
-    }
-}
-
 // ---------------------------------------------------------------- launchers (host)
-
-hipError_t launch_build_tiles(const TileBatch &bt, ckpt_tile *dev_table, hipStream_t stream) {
-    if (bt.count == 0) return hipSuccess;
-    hipLaunchKernelGGL(build_tiles_kernel, dim3(bt.count), dim3(256), 0, stream, bt, dev_table);
-    return hipGetLastError();
-}
 
 // Writes the pieces of `bt` to `image`, which begins with the page of the batch's first piece. A batch without pieces
 // launches one block that finds nothing to do (it makes the runtime load the kernels' code).

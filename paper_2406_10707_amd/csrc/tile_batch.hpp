@@ -1,5 +1,4 @@
-// Batches of tensor descriptors small enough to travel in a kernel's arguments (under 4 KiB): PackBatch is what
-// pack_batch_kernel packs, TileBatch what build_tiles_kernel turns into entries of a tile table.
+// A batch of tensor descriptors small enough to travel in a kernel's arguments (under 4 KiB).
 #pragma once
 #include <cstdint>
 
@@ -10,17 +9,6 @@
 #endif
 
 namespace dsllm {
-
-constexpr int kTileBatch = 96;
-
-struct TileBatch {
-    uint64_t src[kTileBatch];          // device address of the tensor's first byte
-    uint64_t data_off[kTileBatch];     // offset of the tensor in the data region (a multiple of 4096)
-    uint64_t nbytes[kTileBatch];
-    uint32_t first_tile[kTileBatch + 1];   // index of the tensor's first tile in the table; [count] = one past the batch's last
-    uint32_t count;
-};
-static_assert(sizeof(TileBatch) <= 3072, "must fit the kernel argument segment with room to spare");
 
 // What pack_batch_kernel works through: pieces of tensors, in image order, compact so that many fit the kernel arguments
 // (12 bytes each). Every piece fills whole 4 KiB pages of the image; all but a tensor's last piece are multiples of 4 KiB.

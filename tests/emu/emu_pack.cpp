@@ -11,6 +11,7 @@
 
 #include "../../paper_2406_10707_amd/csrc/pack_kernels.hip"
 #include "../../paper_2406_10707_amd/csrc/plan.hpp"
+#include "build_tiles.hpp"
 
 thread_local dim3 threadIdx, blockIdx, blockDim, gridDim;
 ssize_t emu_pwrite(int, const void *, size_t, off_t) { return -1; }   // no file is written here
@@ -71,7 +72,7 @@ int main(int argc, char **argv) {
     if (build_plan(descs.data(), descs.size(), rc, &p, &err)) { printf("plan: %s\n", err.c_str()); return 2; }
     const uint64_t SC = rc.pack_superchunk_bytes;
 
-    // the tile table as the device builds it (batches of descriptors in the kernel arguments) must be the planner's
+    // the tile table as the second construction has it must be the planner's
     {
         std::vector<ckpt_tile> table(p.tiles.size());
         TileBatch bt;
@@ -90,7 +91,7 @@ int main(int argc, char **argv) {
         for (size_t i = 0; i < table.size(); i++) {
             const ckpt_tile &a = table[i], &b = p.tiles[i];
             if (a.src != b.src || a.dst_off != b.dst_off || a.copy_bytes != b.copy_bytes || a.total_bytes != b.total_bytes || a.reserved != 0) {
-                printf("device-built tile %zu differs from the planner's\n", i);
+                printf("tile %zu of the second construction differs from the planner's\n", i);
                 return 1;
             }
         }

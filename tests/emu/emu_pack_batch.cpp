@@ -1,6 +1,6 @@
 // Host emulation of pack_batch_kernel under AddressSanitizer (see hip/hip_runtime.h here): the image of random tensor
 // lists must be the concatenation of the tensors, each padded with zeros to 4 KiB, and the one the tile-table path
-// (build_tiles_kernel + pack_kernel) writes. Compiled with a small DSLLM_PACK_BATCH_PAGES, so that batches end for
+// (build_tiles.hpp + pack_kernel) writes. Compiled with a small DSLLM_PACK_BATCH_PAGES, so that batches end for
 // either reason (pieces, pages) and tensors are split across launches. Every tensor sits in a buffer of exactly the
 // 16-byte lines it touches, so a read past them is reported.
 #include <cstdio>
@@ -10,6 +10,7 @@
 
 #include "../../paper_2406_10707_amd/csrc/pack_kernels.hip"
 #include "../../paper_2406_10707_amd/csrc/plan.hpp"
+#include "build_tiles.hpp"
 
 thread_local dim3 threadIdx, blockIdx, blockDim, gridDim;
 ssize_t emu_pwrite(int, const void *, size_t, off_t) { return -1; }   // no file is written here

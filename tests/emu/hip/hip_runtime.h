@@ -41,8 +41,6 @@ extern thread_local dim3 threadIdx, blockIdx, blockDim, gridDim;
 // one "thread" runs at a time per launch, and launches of different streams may run at the same time: LDS of the
 // model belongs to the host thread that runs the launch (only kernels whose lanes read back what they wrote themselves)
 #define __shared__ static thread_local
-#define __align__(n) __attribute__((aligned(n)))
-#define HIP_SYMBOL(x) x
 
 typedef int hipError_t;
 static const hipError_t hipSuccess = 0, hipErrorInvalidValue = 1, hipErrorOutOfMemory = 2, hipErrorNotSupported = 801;
@@ -136,7 +134,6 @@ inline void emu_submit(hipStream_t s, std::function<void()> f) {
 
 inline hipError_t hipSetDevice(int) { return hipSuccess; }
 inline hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
-template <class T> inline hipError_t hipGetSymbolAddress(void **p, T &symbol) { *p = &symbol; return hipSuccess; }   // the model has one "device"
 inline hipError_t hipGetDeviceCount(int *n) { *n = 1; return hipSuccess; }
 inline hipError_t hipMalloc(void **p, size_t n) { *p = aligned_alloc(256, (n + 255) / 256 * 256); return *p ? hipSuccess : hipErrorOutOfMemory; }
 inline hipError_t hipFree(void *p) { free(p); return hipSuccess; }
