@@ -118,7 +118,7 @@ def measure_link_peak(B, harness, s, nbytes=1 << 30, reps=10):
 
 
 def measure_devcopy(B, harness, s, nbytes=4 << 30, reps=5):
-    """Contiguous aligned copy kernel: the practical HBM ceiling for the pack kernel (GB/s read+write)."""
+    """Contiguous aligned copy kernel, what the pack kernel is compared with (GB/s read+write)."""
     a, b = harness.DevBuf(nbytes), harness.DevBuf(nbytes)
     B.proxy_device_fill_async(a.ptr, 1, nbytes, s.handle)
     best = 0.0
@@ -242,7 +242,7 @@ def run(args, B, harness, spec, every, compute_ms, out_dir):
         return pack_only(args, B, harness, spec)
     info = B.proxy_device_info()
     stream = harness.make_compute_stream()
-    say("link peak and copy-kernel ceiling")
+    say("link peak and copy kernel")
     link = measure_link_peak(B, harness, stream)
     devcopy_gbps = measure_devcopy(B, harness, stream)
 

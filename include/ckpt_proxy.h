@@ -3,7 +3,7 @@
  * in for the forward and backward passes (the phase in which, per the paper's observation on
  * immutability, parameters and optimizer state are only read), an element-wise Adam step that
  * stands in for the update phase that mutates all of them, seeded state generators, and a plain
- * device copy that measures the HBM copy ceiling. Measurement harness only: the checkpoint engine
+ * device copy that the pack kernels are compared with. Measurement harness only: the checkpoint engine
  * (ckpt.h) does not depend on it.
  *
  * Plain C ABI; every `dev_` pointer is a device address on the current HIP device; `stream` is a
@@ -50,7 +50,7 @@ int proxy_fill_words(void *dev_words, uint64_t n_words, uint64_t seed, void *str
 int proxy_mutate_words(void *dev_words, uint64_t n_words, uint64_t step, void *stream);
 
 /* dst[0..nbytes) = src[0..nbytes), both 16-byte aligned, nbytes a multiple of 16: the contiguous
- * copy whose bandwidth is the practical ceiling for the pack kernel. */
+ * copy that the pack kernels are compared with. */
 int proxy_devcopy(void *dev_dst, const void *dev_src, uint64_t nbytes, void *stream);
 
 /* ---- device memory, copies, events: thin wrappers so that a harness needs no other GPU package ----

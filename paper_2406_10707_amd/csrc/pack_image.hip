@@ -5,7 +5,8 @@
 #include "engine_internal.hpp"
 #include "tile_batch.hpp"
 
-// The largest list ckpt_pack_image_noalloc takes, in tiles of 32 KiB.
+// The largest list ckpt_pack_image_noalloc takes, in tiles of 32 KiB: its callers rely on what it refuses, and it bounds what
+// the call enqueues without waiting to 410 launches.
 constexpr uint64_t kNoallocTiles = 131072;
 
 namespace dsllm {

@@ -114,7 +114,7 @@ __global__ __launch_bounds__(256) void mutate_words_kernel(uint32_t *__restrict_
     for (uint64_t i = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += stride) w[i] = w[i] * 1664525u + 1013904223u + step;
 }
 
-// The ceiling the pack kernels are held against: 16 bytes per lane, one wave per block, in address order (6.69 TB/s read +
+// A plain copy, what the pack kernels are compared with: 16 bytes per lane, one wave per block, in address order (6.69 TB/s read +
 // write over 8 GiB; waves that each stream 32 KiB pieces with sixteen loads in flight, the form before, 5.87).
 __global__ __launch_bounds__(64) void devcopy_kernel(u32x4 *__restrict__ dst, const u32x4 *__restrict__ src, uint64_t n16) {
     const uint64_t i = uint64_t(blockIdx.x) * 64 + threadIdx.x;
@@ -295,8 +295,8 @@ __device__ __forceinline__ void for_each_of(F f, std::integer_sequence<int, I...
 //               the fragments of its first half are read under the rest of this step.
 // A load thus has 2000 cycles and more before it is waited for. The accumulators are named as AGPRs in the MFMA's own
 // operands: left to itself the compiler moves them to and fro between the two register files inside the loop.
-// Measured at 8192^3: 1.08 ms = 1015 TFLOP/s before (one 32x32x16 kernel, panels through registers, a load's latency
-// exposed in every step), 0.72 ms = 1520 now, both sides in turn on one card; 384 registers per lane, which leaves room
+// Measured at 8192^3: 1.08 ms = 1020 TFLOP/s before (one 32x32x16 kernel, panels through registers, a load's latency
+// exposed in every step), 0.71 ms = 1550 now, both sides in turn on one card; 384 registers per lane, which leaves room
 // beside it on a SIMD for two waves of the pack kernel.
 template <bool WIDE>
 __global__ __launch_bounds__(256) void gemm_bf16_256_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B, uint16_t *__restrict__ C,

@@ -1,7 +1,6 @@
 """ckpt_pack_image_noalloc (the entry point for callers that cannot allocate) against ckpt_pack_image, the
 entry point it is a variant of: same image, bit for bit, on two calls in a row on one stream with no
-synchronisation in between, the second with a smaller input (the static table still holds the first call's
-entries behind the second call's); also against the oracle's data region, and the size limit."""
+synchronisation in between, the second with a smaller input; also against the oracle's data region, and the size limit."""
 import numpy as np
 import pytest
 
@@ -23,8 +22,8 @@ def test_two_calls_in_a_row_equal_the_allocating_entry_point():
     shard = harness.DeviceShard(spec)
     shard.upload_host_values()
     stream = harness.Stream()
-    big = shard.descs()                       # 302 fragments at odd offsets: four descriptor batches, hundreds of tiles
-    small = big[17:60]                        # the second, smaller input: fewer tiles than the table still holds
+    big = shard.descs()                       # 302 fragments at odd offsets: one launch takes up to 320
+    small = big[17:60]                        # the second, smaller input
     guard = 4096
     out = {}
     for name, descs in (("big", big), ("small", small)):
@@ -60,7 +59,7 @@ def test_two_calls_in_a_row_equal_the_allocating_entry_point():
 def test_limit_and_bad_arguments_launch_nothing():
     print("no-alloc pack image, limit", flush=True)
     src = harness.DevBuf(4096)
-    n = 131072 + 1                            # one tile more than the static table holds
+    n = 131072 + 1                            # one tile more than the entry point takes
     dst = harness.DevBuf(n * 4096)
     B.proxy_device_fill_async(dst.ptr, 0x11, 64 << 10, 0)
     descs = [("t", B.CKPT_U8, (1,), src.ptr, 1)] * n
