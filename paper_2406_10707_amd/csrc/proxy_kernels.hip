@@ -124,8 +124,8 @@ __global__ __launch_bounds__(64) void devcopy_kernel(u32x4 *__restrict__ dst, co
 // ------------------------------------------------------------------ bf16 GEMM on the matrix cores
 
 // Both kernels below compute C = A * B^T tile by tile with MFMA 16x16x32 (the 32x32x16 form does the same work at a
-// higher power: at 8192^3 the card held 1.71 GHz with it at 74 % of the matrix pipe's cycles, and holds 1.76 GHz with
-// this one at 82 %). Operand panels go from memory to LDS without passing through registers (buffer loads to LDS, 16
+// higher power: at 8192^3 the card held 1.71 GHz with it at 74 % of the matrix pipe's cycles, and holds 1.73 GHz with
+// this one at 84 %). Operand panels go from memory to LDS without passing through registers (buffer loads to LDS, 16
 // bytes per lane, counted by vmcnt), 64 K values a step, so that every request is a whole 128-byte line.
 //
 // LDS layout of a panel: rows of 64 K values, 128 bytes, eight 16-byte pieces; row r keeps piece p at place p ^ f(r), so
@@ -295,8 +295,8 @@ __device__ __forceinline__ void for_each_of(F f, std::integer_sequence<int, I...
 //               the fragments of its first half are read under the rest of this step.
 // A load thus has 2000 cycles and more before it is waited for. The accumulators are named as AGPRs in the MFMA's own
 // operands: left to itself the compiler moves them to and fro between the two register files inside the loop.
-// Measured at 8192^3: 1.08 ms = 1020 TFLOP/s before (one 32x32x16 kernel, panels through registers, a load's latency
-// exposed in every step), 0.71 ms = 1550 now, both sides in turn on one card; 384 registers per lane, which leaves room
+// Measured at 8192^3: 1.07 ms = 1030 TFLOP/s before (one 32x32x16 kernel, panels through registers, a load's latency
+// exposed in every step), 0.70 ms = 1570 now, both sides in turn on one card; 384 registers per lane, which leaves room
 // beside it on a SIMD for two waves of the pack kernel.
 template <bool WIDE>
 __global__ __launch_bounds__(256) void gemm_bf16_256_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B, uint16_t *__restrict__ C,
