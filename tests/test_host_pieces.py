@@ -17,7 +17,7 @@ def test_engine_scenarios_with_chunks_in_several_pieces(tmp_path, sanitizer, pie
         pytest.skip("ROCm clang not present")
     exe = str(tmp_path / "emu_engine")
     subprocess.run([CLANG, "-x", "c++", "-std=c++17", "-O1", "-g", "-fsanitize=" + sanitizer, "-fno-omit-frame-pointer", "-pthread",
-                    "-DDSLLM_PIECE_BYTES=%dull" % piece, "-DDSLLM_HEAD_APART_TILES=1", "-I", os.path.join(ROOT, "tests", "emu"), "-o", exe, os.path.join(ROOT, "tests", "emu", "emu_engine.cpp"),
+                    "-DDSLLM_PIECE_BYTES=%dull" % piece, "-DDSLLM_HEAD_APART_TILES=1", "-DDSLLM_SCATTER_BYTES=%dull" % (1 if piece == 8192 else 128 << 10), "-I", os.path.join(ROOT, "tests", "emu"), "-o", exe, os.path.join(ROOT, "tests", "emu", "emu_engine.cpp"),
                     *[os.path.join(ROOT, "paper_2406_10707_amd", "csrc", f) for f in SOURCES]], check=True, cwd=os.path.join(ROOT, "tests", "emu"))
     work = tmp_path / "files"
     work.mkdir()

@@ -11,13 +11,14 @@ SOURCES = ("engine.cpp", "submit.cpp", "io_threads.cpp", "restore.cpp", "second_
            "derive_kernels.hip")
 
 
-@pytest.fixture(scope="module", params=["thread", "address,undefined"])
+# chunks sent in pieces and scattered one by one, and sent whole and scattered together, two at a time and all of a super-chunk
+@pytest.fixture(scope="module", params=[("thread", 1), ("thread", 128 << 10), ("address,undefined", 1), ("address,undefined", 8 << 20)])
 def emu(request, tmp_path_factory):
     if not os.path.exists(CLANG):
         pytest.skip("ROCm clang not present")
     exe = str(tmp_path_factory.mktemp("emu") / "emu_restore")
-    subprocess.run([CLANG, "-x", "c++", "-std=c++17", "-O1", "-g", "-fsanitize=" + request.param, "-fno-omit-frame-pointer", "-pthread",
-                    "-I", os.path.join(ROOT, "tests", "emu"), "-o", exe, os.path.join(ROOT, "tests", "emu", "emu_restore.cpp"),
+    subprocess.run([CLANG, "-x", "c++", "-std=c++17", "-O1", "-g", "-fsanitize=" + request.param[0], "-fno-omit-frame-pointer", "-pthread",
+                    "-DDSLLM_SCATTER_BYTES=%dull" % request.param[1], "-I", os.path.join(ROOT, "tests", "emu"), "-o", exe, os.path.join(ROOT, "tests", "emu", "emu_restore.cpp"),
                     *[os.path.join(ROOT, "paper_2406_10707_amd", "csrc", f) for f in SOURCES]], check=True, cwd=os.path.join(ROOT, "tests", "emu"))
     return exe
 
