@@ -123,7 +123,7 @@ __global__ __launch_bounds__(64) void devcopy_kernel(u32x4 *__restrict__ dst, co
 
 // ------------------------------------------------------------------ bf16 GEMM on the matrix cores
 
-// Both kernels below compute C = A * B^T tile by tile with MFMA 16x16x32 (the 32x32x16 form does the same work at a
+// The kernels below compute C = A * B^T tile by tile with MFMA 16x16x32 (the 32x32x16 form does the same work at a
 // higher power: at 8192^3 the card held 1.71 GHz with it at 74 % of the matrix pipe's cycles, and holds 1.73 GHz with
 // this one at 84 %). Operand panels go from memory to LDS without passing through registers (buffer loads to LDS, 16
 // bytes per lane, counted by vmcnt), 64 K values a step, so that every request is a whole 128-byte line.
@@ -140,11 +140,13 @@ __global__ __launch_bounds__(64) void devcopy_kernel(u32x4 *__restrict__ dst, co
 struct GemmTile { int tm, tn; };
 
 // Consecutive block ids go to different XCDs (8 of them, each with its own L2): gives each XCD a contiguous range of
-// tiles, walked in strips 8 tiles tall so that neighbours share A and B panels.
+// tiles, walked in strips 8 tiles tall so that neighbours share A and B panels. ALWAYS: also where 8 does not divide the
+// number of tiles. With a short K the stores of C are what counts, and those go better in block order (7808 x 3968 x 128
+// 18.2 us, by XCD 18.9).
+template <bool ALWAYS>
 __device__ __forceinline__ GemmTile gemm_tile(int tiles_m, int tiles_n) {
-    const int n_tiles = tiles_m * tiles_n;
-    int bid = blockIdx.x;
-    if (n_tiles % 8 == 0) bid = (bid % 8) * (n_tiles / 8) + bid / 8;
+    const int n_tiles = tiles_m * tiles_n, xcd = blockIdx.x % 8, each = n_tiles / 8, more = n_tiles % 8;    // the first `more` XCDs have one tile more
+    const int bid = !ALWAYS && more ? blockIdx.x : xcd * each + (xcd < more ? xcd : more) + blockIdx.x / 8;
     const int strip = 8;
     const int per_strip = strip * tiles_n;
     const int s = bid / per_strip, in_s = bid % per_strip;
@@ -152,15 +154,18 @@ __device__ __forceinline__ GemmTile gemm_tile(int tiles_m, int tiles_n) {
     return GemmTile{s * strip + in_s % rows_here, in_s / rows_here};
 }
 
-// One wave's eight rows of a panel per instruction; NW waves share a panel. WIDE: 64-bit addresses (the lane's own part
-// made once, the instruction's part uniform), for panels that a buffer resource's 32-bit offsets do not span.
-template <int BM, int BN, int NW, bool WIDE>
+// One wave's eight rows of a panel per instruction; NW waves share a panel. KEPT: a lane's offset for each instruction stays in
+// a register of its own; otherwise the instruction's part is a scalar addition for every load, which is issued in the shadow
+// of a matrix instruction. Where that shadow is short the registers are faster (128 x 128 tiles: 3 %), with 256 x 256 tiles
+// slower (2 %). WIDE: 64-bit addresses (the lane's own part made once, the instruction's part uniform), for panels that a
+// buffer resource's 32-bit offsets do not span.
+template <int BM, int BN, int NW, bool KEPT, bool WIDE>
 struct PanelLoader {
     static constexpr int LA = BM / 8 / NW, LB = BN / 8 / NW, COUNT = LA + LB;   // instructions per wave and step
     static_assert(LA * 8 * NW == BM && LB * 8 * NW == BN && NW % 4 == 0, "panels divide among the waves, four waves' rows per 32");
     const uint16_t *lane_a, *lane_b;
     __amdgpu_buffer_rsrc_t ra, rb;
-    uint32_t row0, piece_a, piece_b, k, wave;
+    uint32_t row0, piece_a, piece_b, k, wave, lane_off[COUNT];
 
     __device__ __forceinline__ PanelLoader(const uint16_t *a_panel, const uint16_t *b_panel, int K, int lane, int wave_)
         : row0((lane >> 3) + 8 * wave_), piece_a((lane & 7) ^ ((4 * (wave_ & 1) + (lane >> 4)) & 7)),
@@ -171,6 +176,9 @@ struct PanelLoader {
         } else {
             ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(a_panel), 0, uint32_t(BM) * 2u * k, 0x00020000);
             rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(b_panel), 0, uint32_t(BN) * 2u * k, 0x00020000);
+            if constexpr (KEPT)
+#pragma unroll
+                for (int i = 0; i < COUNT; i++) lane_off[i] = 2 * ((row0 + 8 * NW * (i < LA ? i : i - LA)) * k + 8 * (i < LA ? piece_a : piece_b));
         }
     }
     // instruction i of step kt into the stage at lds (A panel, then B panel)
@@ -182,6 +190,8 @@ struct PanelLoader {
         if constexpr (WIDE) {
             const uint16_t *p = (of_a ? lane_a : lane_b) + (size_t(8 * NW * j) * k + size_t(kt) * 64);
             __builtin_amdgcn_global_load_lds((const DSLLM_GLB void *)p, (DSLLM_LDS void *)place, 16, 0, 0);
+        } else if constexpr (KEPT) {
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(of_a ? ra : rb, (DSLLM_LDS void *)place, 16, lane_off[i], 128 * kt, 0, 0);
         } else {
             __builtin_amdgcn_raw_ptr_buffer_load_lds(of_a ? ra : rb, (DSLLM_LDS void *)place, 16, 2 * (row0 * k + 8 * piece), 16 * NW * j * k + 128 * kt, 0, 0);
         }
@@ -200,18 +210,19 @@ __device__ __forceinline__ void store_columns(uint16_t *c, f32x4 lo, f32x4 hi) {
     *reinterpret_cast<bf16x8 *>(c) = __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
-// Small and middle-sized products. A wave computes (16 TM) x (16 TN), WM x WN waves a block tile; KG such groups of
-// waves share the tile, each taking every KG-th step of K, and their sums are added in LDS at the end (in group order:
-// the result does not depend on timing). NST steps are in LDS; the loads of a step go out NST - 1 steps ahead.
+// Products with a short K or a small C; the order inside a step is the compiler's. A wave computes (16 TM) x (16 TN),
+// WM x WN waves a block tile, which M and N are multiples of; KG such groups of waves share the tile, each taking every
+// KG-th step of K, and their sums are added in LDS at the end (in group order: the result does not depend on timing).
+// NST steps are in LDS; the loads of a step go out NST - 1 steps ahead.
 template <int TM, int TN, int WM, int WN, int KG, int NST, bool WIDE>
 __global__ __launch_bounds__(64 * WM * WN * KG) void gemm_bf16_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B,
                                                                      uint16_t *__restrict__ C, int M, int N, int K) {
     constexpr int BM = 16 * TM * WM, BN = 16 * TN * WN, NW = WM * WN, STEP = (BM + BN) * 64;
-    typedef PanelLoader<BM, BN, NW, WIDE> Loader;
+    typedef PanelLoader<BM, BN, NW, false, WIDE> Loader;
     static_assert(TN % 2 == 0, "B fragments come in pairs");
     static_assert((KG - 1) * BM * BN * 4 <= NST * KG * STEP * 2, "the partial sums fit where the panels were");
     __shared__ __attribute__((aligned(1024))) uint16_t lds[NST * KG * STEP];
-    const GemmTile t = gemm_tile(M / BM, N / BN);
+    const GemmTile t = gemm_tile<(KG > 1)>(M / BM, N / BN);
     const int lane = threadIdx.x & 63, wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wave = wave_all % NW, group = wave_all / NW;
     const int wm = wave / WN, wn = wave % WN;
     const Loader load(A + size_t(t.tm) * BM * K, B + size_t(t.tn) * BN * K, K, lane, wave);
@@ -285,124 +296,238 @@ __global__ __launch_bounds__(64 * WM * WN * KG) void gemm_bf16_kernel(const uint
 template <class F, int... I>
 __device__ __forceinline__ void for_each_of(F f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
 
-// Large products: a 256 x 256 block tile, four waves of 128 x 128 each, ONE wave per SIMD: LDS would be the limit
-// otherwise (fragment reads and panel writes take 75 % of its cycles with this split, all of them with eight waves).
-// Nothing hides a wait but the wave's own order, so the order is fixed by hand: a step of 64 K values is 128 MFMAs, and
-// between them, at the places given below, go the 32 fragment reads and the 16 panel loads. Two stages of LDS:
-//   at MFMA 40  every wave has read its second half's fragments of this step: the stage is free, and the loads of
-//               step + 2 into it start, one per four MFMAs (64 bytes a cycle, what a compute unit takes);
-//   at MFMA 96  the loads of step + 1 have landed for all (the fourteen of step + 2 issued so far may be under way), and
-//               the fragments of its first half are read under the rest of this step.
-// A load thus has 2000 cycles and more before it is waited for. The accumulators are named as AGPRs in the MFMA's own
-// operands: left to itself the compiler moves them to and fro between the two register files inside the loop.
-// Measured at 8192^3: 1.07 ms = 1030 TFLOP/s before (one 32x32x16 kernel, panels through registers, a load's latency
-// exposed in every step), 0.70 ms = 1570 now, both sides in turn on one card; 384 registers per lane, which leaves room
-// beside it on a SIMD for two waves of the pack kernel.
-template <bool WIDE>
-__global__ __launch_bounds__(256) void gemm_bf16_256_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B, uint16_t *__restrict__ C,
-                                                           int M, int N, int K) {
-    constexpr int T = 8, NW = 4, BM = 256, BN = 256, STEP = (BM + BN) * 64, FRAGS = 2 * T, HALF = T * T;
-    constexpr int FREE_AT = 40, LOAD_EVERY = 4, LANDED_AT = 96, READ_EVERY = 2;
-    typedef PanelLoader<BM, BN, NW, WIDE> Loader;
-    constexpr int issued_when_landed = (LANDED_AT - FREE_AT + LOAD_EVERY - 1) / LOAD_EVERY;
-    static_assert((FRAGS - 1) * READ_EVERY < FREE_AT && LANDED_AT + (FRAGS - 1) * READ_EVERY < 2 * HALF, "reads lie inside their half");
-    static_assert(FREE_AT + (Loader::COUNT - 1) * LOAD_EVERY < 2 * HALF && issued_when_landed <= Loader::COUNT, "loads lie inside the step");
-    __shared__ __attribute__((aligned(1024))) uint16_t lds[2 * STEP];
-    const GemmTile t = gemm_tile(M / BM, N / BN);
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wm = wave >> 1, wn = wave & 1;
-    const Loader load(A + size_t(t.tm) * BM * K, B + size_t(t.tn) * BN * K, K, lane, wave);
+// The other products: WM x WN waves, each computing (16 TM) x (16 TN) of the block's tile, ONE wave per SIMD or two. Nothing
+// hides a wait but the wave's own order, so the order is fixed by hand: a step of 64 K values is 2 TM TN MFMAs, and
+// between them, at the places given below, go the 2 (TM + TN) fragment reads and the panel loads. The fragments of one half
+// of a step (32 K values) are read under the MFMAs of the half before, READS a MFMA or (negative) one in -READS MFMAs; the
+// panel loads go out one every LOAD_EVERY MFMAs (64 bytes a cycle is what a compute unit takes, 44 to 58 what it was
+// seen to take). STAGES steps are in LDS:
+//   two     once every wave has read its second half's fragments of this step the stage is free, and the loads of step + 2
+//           into it start; three quarters into the step the loads of step + 1 have landed for all (those of step + 2 issued
+//           so far may be under way), and the fragments of its first half are read under the rest of this step;
+//   more    both in one meeting at the beginning of the second half. The loads that this frees the stage for go on
+//           into the next step, up to its meeting.
+// A load thus has most of a step and more before it is waited for. Tiles of more than 128 x 128 per SIMD pair name the
+// accumulators as AGPRs in the MFMA's own operands: left to itself the compiler moves them to and fro between the two
+// register files inside the loop.
+// MFMAs go to and fro along B's fragments, so that two in a row always share an operand (8192^3 686 -> 684 us).
+// M is at least BM and N at least BN, both multiples of 32. The last tile of a row or column ends at the edge of C: it
+// starts inside the one before it where BM or BN does not divide, and both write the same bits there.
+//
+// What bounds it: the power, with 256 x 256 tiles (1.76 GHz at 92 % of the matrix pipe's cycles in the loop; 8192^3 in
+// 0.70 ms = 1570 TFLOP/s, where one 32x32x16 kernel with panels through registers took 1.07), and towards small tiles
+// more and more what a wave issues between its MFMAs and the panel loads (BM + BN rows a step): 128 x 128 takes 820 cycles a step,
+// of which the MFMAs are 512 and the loads at 58 bytes a cycle 565. Four waves of 64 x 64 instead of sixteen of 32 x 32
+// and a hand-made order made of 1024 x 3072 x 768 9.9 -> 7.5 us.
+template <int WM, int WN, int TM, int TN, int STAGES, int READS, int LOAD_EVERY, bool WIDE>
+__device__ __forceinline__ void gemm_bf16_tile(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B, uint16_t *__restrict__ C, int M, int N, int K) {
+    constexpr int NW = WM * WN, BM = 16 * TM * WM, BN = 16 * TN * WN, STEP = (BM + BN) * 64, FRAGS = TM + TN, HALF = TM * TN;
+    constexpr bool NAMED = TM * TN > 32, TWO = STAGES == 2;
+    typedef PanelLoader<BM, BN, NW, !NAMED, WIDE> Loader;
+    constexpr int COUNT = Loader::COUNT;
+    static_assert(TN % 2 == 0 && STAGES >= 2, "B fragments come in pairs");
+    // fragment i of a half is read behind MFMA at_read(i) of the half before it (of what is left of that behind the second meeting)
+    constexpr int PACE = READS > 0 ? READS : 1, AT_ONCE = READS > 0 ? 1 : -READS;
+    constexpr int READ_SPAN = (FRAGS + AT_ONCE - 1) / AT_ONCE * PACE;
+    constexpr int FREE_AT = TWO ? (READ_SPAN + 8 < HALF ? READ_SPAN + 8 : READ_SPAN + 4 < HALF ? READ_SPAN + 4 : HALF) : HALF + 2;
+    constexpr int LANDED_AT = TWO ? HALF + HALF / 2 : HALF + 2;
+    constexpr int FITTING = (2 * HALF - FREE_AT + LOAD_EVERY - 1) / LOAD_EVERY;       // loads that go out in the step that frees their stage
+    constexpr int NOW = TWO || FITTING > COUNT ? COUNT : FITTING;
+    constexpr int GONE = (LANDED_AT - FREE_AT + LOAD_EVERY - 1) / LOAD_EVERY;         // two stages: those of them out at the second meeting
+    constexpr int UNDER_WAY = TWO ? (GONE < COUNT ? GONE : COUNT) : (STAGES - 2) * COUNT;
+    static_assert(READ_SPAN <= HALF && FREE_AT <= HALF + 2 && LANDED_AT < 2 * HALF, "the reads of a half lie inside the half before");
+    static_assert(TWO || FREE_AT + (COUNT - 1) * LOAD_EVERY - 2 * HALF < LANDED_AT, "a step's loads are out before the next one's");
+    __shared__ __attribute__((aligned(1024))) uint16_t lds[STAGES * STEP];
+    const GemmTile t = gemm_tile<true>(M / BM + (M % BM != 0), N / BN + (N % BN != 0));
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wm = wave / WN, wn = wave % WN;
+    const int row = min(t.tm * BM, M - BM), col = min(t.tn * BN, N - BN);
+    const Loader load(A + size_t(row) * K, B + size_t(col) * K, K, lane, wave);
     const int ar = lane & 15, br = 8 * (ar >> 2) + (ar & 3);
     int at_a[2], at_b[2];
 #pragma unroll
     for (int h = 0; h < 2; h++) {
-        at_a[h] = (16 * T * wm + ar) * 64 + 8 * ((4 * h + (lane >> 4)) ^ ((ar >> 1) & 7));
-        at_b[h] = (BM + 16 * T * wn + br) * 64 + 8 * ((4 * h + (lane >> 4)) ^ (((ar >> 1) & 1) | ((ar >> 2) << 1)));
+        at_a[h] = (16 * TM * wm + ar) * 64 + 8 * ((4 * h + (lane >> 4)) ^ ((ar >> 1) & 7));
+        at_b[h] = (BM + 16 * TN * wn + br) * 64 + 8 * ((4 * h + (lane >> 4)) ^ (((ar >> 1) & 1) | ((ar >> 2) << 1)));
     }
     bf16x8 frag[2][FRAGS];      // [half of the step]: B fragments first, then A
     auto read = [&](int half, int stage, int i) {
-        const uint16_t *p = lds + stage * STEP + (i < T ? at_b[half] + (i >> 1) * 2048 + (i & 1) * 256 : at_a[half] + (i - T) * 1024);
+        const uint16_t *p = lds + stage * STEP + (i < TN ? at_b[half] + (i >> 1) * 2048 + (i & 1) * 256 : at_a[half] + (i - TN) * 1024);
         frag[half][i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(p));
     };
-    f32x4 acc[T][T];
+    f32x4 acc[TM][TN];
 #pragma unroll
-    for (int i = 0; i < T; i++)
+    for (int i = 0; i < TM; i++)
 #pragma unroll
-        for (int j = 0; j < T; j++) acc[i][j] = f32x4{0, 0, 0, 0};
+        for (int j = 0; j < TN; j++) acc[i][j] = f32x4{0, 0, 0, 0};
     const int steps = K / 64;
+    // Past the end the last step is loaded again, into a stage nothing reads.
 #pragma unroll
-    for (int i = 0; i < Loader::COUNT; i++) load.issue(lds, 0, i);
+    for (int s = 0; s < STAGES; s++)
 #pragma unroll
-    for (int i = 0; i < Loader::COUNT; i++) load.issue(lds + STEP, steps > 1 ? 1 : 0, i);
-    wait_loads_and_meet<Loader::COUNT>();
+        for (int i = 0; i < (s == STAGES - 1 ? NOW : COUNT); i++) load.issue(lds + s * STEP, s < steps ? s : steps - 1, i);
+    wait_loads_and_meet<(STAGES - 2) * COUNT + NOW>();
 #pragma unroll
     for (int i = 0; i < FRAGS; i++) read(0, 0, i);
-    // The accumulators are set by ordinary instructions and read by the asm below, for which the compiler inserts no wait
-    // states: they are in their registers before the fence, which nothing moves across.
+    if constexpr (NAMED) {
+        // The accumulators are set by ordinary instructions and read by the asm below, for which the compiler inserts no wait
+        // states: they are in their registers before the fence, which nothing moves across.
 #pragma unroll
-    for (int i = 0; i < T; i++)
+        for (int i = 0; i < TM; i++)
 #pragma unroll
-        for (int j = 0; j < T; j++) asm volatile("" : "+a"(acc[i][j]));
-    asm volatile("s_nop 7");
+            for (int j = 0; j < TN; j++) asm volatile("" : "+a"(acc[i][j]));
+        asm volatile("s_nop 7");
+    }
     __builtin_amdgcn_sched_barrier(0);
+    int in_turn = 0;
     for (int step = 0; step < steps; step++) {
-        const int stage = step & 1;
-        const int ahead = step + 2 < steps ? step + 2 : steps - 1;    // past the end: the last step again, into a stage nothing reads
+        const int stage = TWO ? step & 1 : in_turn, next = TWO ? stage ^ 1 : stage + 1 == STAGES ? 0 : stage + 1;
+        const int before = stage == 0 ? STAGES - 1 : stage - 1;
+        const int ahead = step + STAGES < steps ? step + STAGES : steps - 1, late = step + STAGES - 1 < steps ? step + STAGES - 1 : steps - 1;
         for_each_of([&](auto index) {
-            constexpr int at = index, half = at / HALF, i = at % HALF / T, j = at % T;
-            if constexpr (at == FREE_AT) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-            if constexpr (at == LANDED_AT) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(issued_when_landed) : "memory");
-            asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[i][j]) : "v"(frag[half][j]), "v"(frag[half][T + i]));
-            if constexpr (at < HALF && at % READ_EVERY == 0 && at / READ_EVERY < FRAGS) read(1, stage, at / READ_EVERY);
-            if constexpr (at >= LANDED_AT && (at - LANDED_AT) % READ_EVERY == 0 && (at - LANDED_AT) / READ_EVERY < FRAGS)
-                read(0, stage ^ 1, (at - LANDED_AT) / READ_EVERY);
-            if constexpr (at >= FREE_AT && (at - FREE_AT) % LOAD_EVERY == 0 && (at - FREE_AT) / LOAD_EVERY < Loader::COUNT)
+            constexpr int at = index, half = at / HALF, i = at % HALF / TN, j = i & 1 ? TN - 1 - at % TN : at % TN;
+            if constexpr (TWO && at == FREE_AT) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            if constexpr (at == LANDED_AT && TWO) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(UNDER_WAY) : "memory");
+            if constexpr (at == LANDED_AT && !TWO) wait_loads_and_meet<UNDER_WAY>();
+            if constexpr (NAMED) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[i][j]) : "v"(frag[half][j]), "v"(frag[half][TN + i]));
+            else acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag[half][j], frag[half][TN + i], acc[i][j], 0, 0, 0);
+#pragma unroll
+            for (int q = 0; q < AT_ONCE; q++) {
+                if (at < HALF && at % PACE == 0 && at / PACE * AT_ONCE + q < FRAGS) read(1, stage, at / PACE * AT_ONCE + q);
+                if (at >= LANDED_AT && (at - LANDED_AT) % PACE == 0 && (at - LANDED_AT) / PACE * AT_ONCE + q < FRAGS)
+                    read(0, next, (at - LANDED_AT) / PACE * AT_ONCE + q);
+            }
+            if constexpr (at >= FREE_AT && (at - FREE_AT) % LOAD_EVERY == 0 && (at - FREE_AT) / LOAD_EVERY < COUNT)
                 load.issue(lds + stage * STEP, ahead, (at - FREE_AT) / LOAD_EVERY);
+            constexpr int since = at + 2 * HALF - FREE_AT;      // MFMAs since the stage of the step before was free
+            if constexpr (NOW < COUNT && at < LANDED_AT && since % LOAD_EVERY == 0 && since / LOAD_EVERY < COUNT)
+                load.issue(lds + before * STEP, late, since / LOAD_EVERY);
             __builtin_amdgcn_sched_barrier(0);
         }, std::make_integer_sequence<int, 2 * HALF>{});
+        // what there was no MFMA left for
+#pragma unroll
+        for (int i = FITTING; i < NOW; i++) load.issue(lds + stage * STEP, ahead, i);
+#pragma unroll
+        for (int i = (2 * HALF - LANDED_AT + PACE - 1) / PACE * AT_ONCE; i < FRAGS; i++) read(0, next, i);
+        __builtin_amdgcn_sched_barrier(0);
+        in_turn = next;
     }
     // the last MFMAs' results are readable, and no load to LDS outlives the block
     asm volatile("s_nop 15\n\ts_nop 15\n\ts_waitcnt vmcnt(0)" ::: "memory");
-    uint16_t *c = C + (size_t(t.tm) * BM + wm * 16 * T + ar) * N + size_t(t.tn) * BN + wn * 16 * T + 8 * (lane >> 4);
+    uint16_t *c = C + size_t(row + wm * 16 * TM + ar) * N + col + wn * 16 * TN + 8 * (lane >> 4);
 #pragma unroll
-    for (int i = 0; i < T; i++)
+    for (int i = 0; i < TM; i++)
 #pragma unroll
-        for (int j = 0; j < T; j += 2) {
-            asm volatile("" : "+a"(acc[i][j]), "+a"(acc[i][j + 1]));      // in their registers up to here: copied out all at once they would spill
+        for (int j = 0; j < TN; j += 2) {
+            // in their registers up to here: copied out all at once they would spill
+            if constexpr (NAMED) asm volatile("" : "+a"(acc[i][j]), "+a"(acc[i][j + 1]));
             store_columns(c + size_t(16 * i) * N + 16 * j, acc[i][j], acc[i][j + 1]);
             __builtin_amdgcn_sched_barrier(0);
         }
 }
 
-// Which kernel and tile. Times are for one product on an MI355X, before (128 x 128 tiles with panels through registers,
-// one step ahead) and now.
-//  * 256 x 256 from 192 tiles on (three quarters of the 256 compute units): 3072 x 4096 x 2048 71 -> 48 us (128 x 128: 55);
-//    at 128 tiles 128 x 128 wins (2048 x 4096 x 4096: 63 against 72, 88 before). Below K = 256 its 128 KiB prologue shows.
-//  * 128 x 128 in four waves and 64 KiB of LDS, two blocks per unit, while there are more tiles than units:
-//    1408 x 4608 x 3072 69 -> 48 us.
-//    With two to three tiles per unit and K from 16384 on the sixteen-wave form below instead: the second round's blocks, one
-//    to a unit, run against two to a unit, and along a long K they no longer share panels in L2. 1408 x 8064 x 26816 905 -> 787
-//    us (two blocks per unit: 961 to 988), 1152 x 7808 x 53568 1759 -> 1533 (1775); at K = 14000 the two are even.
-//  * one 128 x 128 tile per unit at most: sixteen waves and four steps in LDS, as one block has to hide its own latency:
-//    512 x 5632 x 1536 25 -> 14 us (four waves: 18, 64 x 64 tiles: 16).
-//  * fewer than half as many: 64 x 64, three blocks per unit: 2048 x 1024 x 2048 34 -> 14 us.
-//  * one 64 x 64 tile per unit at most and K long enough to split: two groups of waves along K: 1024^3 16 -> 5.9 us (one
-//    group: 7.1); half as many tiles: four groups on 32 x 64: 512 x 512 x 4096 49 -> 11 us (two groups: 14).
-// WIDE once a panel of 256 rows passes 2 GiB (the offsets of a buffer load are 32 bits wide); the rule is the same there:
-// K = 2^22 + 64, 4096 x 4096 160 ms = 880 TFLOP/s, 2048 x 2048 65 ms, 1024 x 1024 18 ms, 128 x 128 13 ms; with 64 x 64 tiles for
-// every size 568, 124, 27 and 23, with the kernels before these 168, 128, 119 and 121.
-#define DSLLM_GEMM(BM_, BN_, THREADS, ...) \
-    hipLaunchKernelGGL((__VA_ARGS__), dim3(unsigned((m / (BM_)) * (n / (BN_)))), dim3(THREADS), 0, stream, a, b, c, m, n, k)
+// TOGETHER blocks share a compute unit. The bodies are the device's only: the host's pass needs no more than the names.
+template <int TOGETHER, int WM, int WN, int TM, int TN, int STAGES, int READS, int LOAD_EVERY, bool WIDE>
+__global__ __launch_bounds__(256, TOGETHER) void gemm_bf16_tile_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B,
+                                                                      uint16_t *__restrict__ C, int M, int N, int K) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    gemm_bf16_tile<WM, WN, TM, TN, STAGES, READS, LOAD_EVERY, WIDE>(A, B, C, M, N, K);
+#endif
+}
+template <bool WIDE>
+__global__ __launch_bounds__(256) void gemm_bf16_256_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B, uint16_t *__restrict__ C, int M,
+                                                           int N, int K) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    gemm_bf16_tile<2, 2, 8, 8, 2, 2, 4, WIDE>(A, B, C, M, N, K);
+#endif
+}
+
+// Which kernel and tile: the one of these that is expected to be done first. Up to K = 192 it is the first lines of launch_gemm
+// that decide, as a product is then little more than a launch and the stores of C (the hand-made order's prologue costs 0.5 us
+// more than the other kernel's: 2432 x 4992 x 64 8.8 us against 10.0).
+//
+// What a form is expected to take, in us: `start`, and then for the compute unit with the most blocks, which takes them in
+// rounds of up to `together`, block[n - 1] + step[n - 1] * (K / 64) for every round of n; and for all blocks together, as a
+// full card clocks lower and shares memory, (spread_block + spread_step * (K / 64)) * blocks / 256. The figures are fitted to times
+// of every form on 560 products on an MI355X, M and N multiples of 128 up to 8192 and K of 64 up to 8192, each spread over the
+// logarithm of its range: 2 to 3 % off in the mean, 4 to 9 % at the ninth decile. The choice by them is 1.1 % slower in the
+// mean than the best form for each product, and 17 % faster than a rule on the number of tiles over two 128 x 128, two 64 x 64, one
+// 32 x 64 kernel and 256 x 256 where both sizes are its multiples. Where that lost most:
+//   6272 x 7808 x 6592 685 -> 462 us     sizes not multiples of 256, formerly 128 x 128 for all
+//   1920 x 7936 x 3456 127 -> 76
+//   768 x 5632 x 3392 46 -> 34           a few 128 x 128 tiles more than there are units
+//   384 x 5248 x 960 12.1 -> 6.9
+//   1024 x 3072 x 768 9.9 -> 7.6         fewer 128 x 128 tiles than units: 128 x 96 fills them
+// WIDE once a panel of 256 rows passes 2 GiB (the offsets of a buffer load are 32 bits wide); the choice is the same there.
+struct GemmForm {
+    int rows, cols, together;
+    float start, block[3], step[3], spread_block, spread_step;
+
+    float expected(int m, int n, int k) const {
+        if (m < rows || n < cols) return INFINITY;
+        const float steps = float(k / 64), blocks = float(m / rows + (m % rows != 0)) * float(n / cols + (n % cols != 0));
+        const float per_unit = ceilf(blocks / 256), rounds = floorf(per_unit / float(together));
+        const int rest = int(per_unit - rounds * float(together));
+        float us = start + rounds * (block[together - 1] + step[together - 1] * steps) + (spread_block + spread_step * steps) * blocks / 256;
+        if (rest) us += block[rest - 1] + step[rest - 1] * steps;
+        return us;
+    }
+};
+const GemmForm kGemmForms[] = {     // in the order of launch_gemm's switch
+    {256, 256, 1, 2.43f, {3.90f, 0.00f, 0.00f}, {0.9122f, 0.0000f, 0.0000f}, 4.56f, 0.2758f},
+    {224, 256, 1, 1.94f, {3.93f, 0.00f, 0.00f}, {0.7984f, 0.0000f, 0.0000f}, 3.95f, 0.2545f},
+    {256, 192, 1, 1.71f, {3.74f, 0.00f, 0.00f}, {0.6975f, 0.0000f, 0.0000f}, 3.20f, 0.2218f},
+    {160, 256, 1, 1.24f, {3.91f, 0.00f, 0.00f}, {0.5994f, 0.0000f, 0.0000f}, 2.76f, 0.1911f},
+    {192, 128, 2, 2.94f, {1.14f, 2.09f, 0.00f}, {0.4599f, 0.8657f, 0.0000f}, 1.45f, 0.1007f},
+    {160, 128, 1, 1.35f, {2.72f, 0.00f, 0.00f}, {0.3502f, 0.0000f, 0.0000f}, 0.69f, 0.1319f},
+    {128, 128, 1, 1.26f, {2.39f, 0.00f, 0.00f}, {0.3033f, 0.0000f, 0.0000f}, 0.39f, 0.1069f},
+    {128, 128, 2, 2.56f, {0.84f, 1.66f, 0.00f}, {0.3865f, 0.6772f, 0.0000f}, 0.94f, 0.0625f},
+    {128, 96, 1, 1.28f, {1.93f, 0.00f, 0.00f}, {0.2641f, 0.0000f, 0.0000f}, 0.25f, 0.0856f},
+    {64, 128, 2, 1.75f, {1.02f, 1.53f, 0.00f}, {0.2244f, 0.4022f, 0.0000f}, 0.20f, 0.0705f},
+    {96, 64, 2, 1.73f, {1.01f, 1.32f, 0.00f}, {0.1853f, 0.3621f, 0.0000f}, 0.23f, 0.0407f},
+    {64, 64, 2, 1.80f, {0.67f, 0.89f, 0.00f}, {0.1494f, 0.2870f, 0.0000f}, 0.18f, 0.0281f},
+    {64, 64, 3, 2.07f, {0.17f, 0.58f, 1.24f}, {0.1521f, 0.2266f, 0.3086f}, 0.00f, 0.0740f},
+    {32, 64, 1, 1.37f, {1.66f, 0.00f, 0.00f}, {0.1244f, 0.0000f, 0.0000f}, 0.17f, 0.0134f},
+    {128, 128, 2, 2.24f, {0.55f, 1.81f, 0.00f}, {0.5691f, 0.6548f, 0.0000f}, 0.76f, 0.1264f},
+};
+
 template <bool WIDE>
 void launch_gemm(const uint16_t *a, const uint16_t *b, uint16_t *c, int m, int n, int k, hipStream_t stream) {
-    const int64_t n64 = int64_t(m / 64) * (n / 64);
-    if (m % 256 == 0 && n % 256 == 0 && n64 >= 192 * 16 && k >= 256) DSLLM_GEMM(256, 256, 256, gemm_bf16_256_kernel<WIDE>);
-    else if (n64 > 4 * 256 && (k < (1 << 14) || n64 <= 8 * 256 || n64 > 12 * 256)) DSLLM_GEMM(128, 128, 256, gemm_bf16_kernel<4, 4, 2, 2, 1, 2, WIDE>);
-    else if (n64 > 2 * 256) DSLLM_GEMM(128, 128, 1024, gemm_bf16_kernel<2, 2, 4, 4, 1, 4, WIDE>);
-    else if (n64 > 256 || k < 512) DSLLM_GEMM(64, 64, 256, gemm_bf16_kernel<2, 2, 2, 2, 1, 3, WIDE>);
-    else if (n64 > 128) DSLLM_GEMM(64, 64, 512, gemm_bf16_kernel<2, 2, 2, 2, 2, 3, WIDE>);
-    else DSLLM_GEMM(32, 64, 1024, gemm_bf16_kernel<1, 2, 2, 2, 4, 3, WIDE>);
+    auto go = [&](auto kernel, int rows, int cols, int threads) {
+        const uint64_t blocks = uint64_t(m / rows + (m % rows != 0)) * uint64_t(n / cols + (n % cols != 0));
+        hipLaunchKernelGGL(kernel, dim3(unsigned(blocks)), dim3(threads), 0, stream, a, b, c, m, n, k);
+    };
+    if (k <= 192) {
+        const int64_t n64 = int64_t(m / 64) * (n / 64);
+        if (n64 > 4 * 256) go(gemm_bf16_kernel<4, 4, 2, 2, 1, 2, WIDE>, 128, 128, 256);
+        else if (n64 > 3 * 256) go(gemm_bf16_kernel<2, 2, 4, 4, 1, 4, WIDE>, 128, 128, 1024);      // more than the three of 64 x 64 that share a unit
+        else go(gemm_bf16_kernel<2, 2, 2, 2, 1, 3, WIDE>, 64, 64, 256);
+        return;
+    }
+    int best = 0;
+    float us = kGemmForms[0].expected(m, n, k);
+    for (int f = 1; f < int(sizeof kGemmForms / sizeof kGemmForms[0]); f++) {
+        const float t = kGemmForms[f].expected(m, n, k);
+        if (t < us) { us = t; best = f; }
+    }
+    const GemmForm &form = kGemmForms[best];
+    switch (best) {
+        case 0: go(gemm_bf16_256_kernel<WIDE>, form.rows, form.cols, 256); break;
+        case 1: go(gemm_bf16_tile_kernel<1, 2, 2, 7, 8, 2, 2, 4, WIDE>, form.rows, form.cols, 256); break;
+        case 2: go(gemm_bf16_tile_kernel<1, 2, 2, 8, 6, 2, 2, 4, WIDE>, form.rows, form.cols, 256); break;
+        case 3: go(gemm_bf16_tile_kernel<1, 2, 2, 5, 8, 3, 2, 4, WIDE>, form.rows, form.cols, 256); break;
+        case 4: go(gemm_bf16_tile_kernel<2, 2, 2, 6, 4, 2, 1, 2, WIDE>, form.rows, form.cols, 256); break;
+        case 5: go(gemm_bf16_tile_kernel<1, 2, 2, 5, 4, 3, 1, 4, WIDE>, form.rows, form.cols, 256); break;
+        case 6: go(gemm_bf16_tile_kernel<1, 2, 2, 4, 4, 3, 1, 4, WIDE>, form.rows, form.cols, 256); break;
+        case 7: go(gemm_bf16_tile_kernel<2, 2, 2, 4, 4, 2, -2, 1, WIDE>, form.rows, form.cols, 256); break;
+        case 8: go(gemm_bf16_tile_kernel<1, 4, 1, 2, 6, 3, 1, 3, WIDE>, form.rows, form.cols, 256); break;
+        case 9: go(gemm_bf16_tile_kernel<2, 2, 2, 2, 4, 3, 1, 2, WIDE>, form.rows, form.cols, 256); break;
+        case 10: go(gemm_bf16_tile_kernel<2, 2, 2, 3, 2, 4, -2, 1, WIDE>, form.rows, form.cols, 256); break;
+        case 11: go(gemm_bf16_tile_kernel<2, 2, 2, 2, 2, 4, -2, 1, WIDE>, form.rows, form.cols, 256); break;
+        case 12: go(gemm_bf16_tile_kernel<3, 2, 2, 2, 2, 3, -2, 1, WIDE>, form.rows, form.cols, 256); break;
+        case 13: go(gemm_bf16_kernel<1, 2, 2, 2, 4, 3, WIDE>, form.rows, form.cols, 1024); break;
+        default: go(gemm_bf16_kernel<4, 4, 2, 2, 1, 2, WIDE>, form.rows, form.cols, 256); break;
+    }
 }
-#undef DSLLM_GEMM
 
 unsigned blocks_for(uint64_t n, unsigned per_block) {
     uint64_t b = (n + per_block - 1) / per_block;

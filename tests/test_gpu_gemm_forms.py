@@ -1,0 +1,56 @@
+"""Every form that the proxy's GEMM chooses among, with tiles that end at the edge of C and tiles that reach over it in
+either direction, against the float64 product. K is as short as the form is chosen for, in steps that its stages in LDS
+divide and do not divide."""
+import numpy as np
+import pytest
+
+from oracle import proxy_oracle as po
+from paper_2406_10707_amd import binding as B
+from paper_2406_10707_amd import harness
+from tests import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(2816, 5120, 256), (4736, 2944, 256),                          # 256 x 256
+          (4480, 2816, 256), (3328, 3840, 256), (2816, 4480, 320),       # 224 x 256
+          (2048, 4992, 256), (3072, 3200, 320), (2176, 4736, 320),       # 256 x 192
+          (2560, 3328, 256), (4736, 1792, 320), (2432, 3456, 256),       # 160 x 256
+          (1152, 4224, 256), (2944, 1792, 320),                          # 192 x 128, two to a unit
+          (2560, 1664, 256), (4736, 896, 320),                           # 160 x 128
+          (4992, 640, 256), (640, 4992, 320),                            # 128 x 128
+          (4480, 1408, 448),                                             # 128 x 128, two to a unit
+          (2816, 768, 256), (1664, 1280, 320),                           # 128 x 96
+          (512, 2816, 320), (512, 2816, 448),                            # 64 x 128
+          (768, 1408, 256), (640, 1664, 320),                            # 96 x 64
+          (128, 1664, 1472), (128, 128, 256), (256, 384, 320),           # 64 x 64, two and three to a unit
+          (384, 256, 2048 + 64),                                         # 32 x 64, K split in four
+          (4480, 1408, 256), (2304, 1152, 192), (1152, 1024, 192)]       # the order left to the compiler
+
+
+@pytest.mark.parametrize("m,n,k", SHAPES)
+def test_gemm_form_against_float64(m, n, k):
+    print(f"gemm {m}x{n}x{k}", flush=True)
+    rng = np.random.default_rng(m + 3 * n + 7 * k)
+    a = po.bf16_bits(rng.standard_normal((m, k)).astype(np.float32))
+    b = po.bf16_bits(rng.standard_normal((n, k)).astype(np.float32))
+    # rows behind the operands' last are there and are no numbers: whatever a tile over the edge reads is not stored
+    nan = np.full((256, k), 0x7FC0, dtype=np.uint16)
+    da, db, dc = harness.DevBuf(2 * (m + 256) * k), harness.DevBuf(2 * (n + 256) * k), harness.DevBuf(2 * m * n + 4096)
+    da.upload(np.concatenate([a, nan]))
+    db.upload(np.concatenate([b, nan]))
+    ref, ref_abs = po.gemm_bf16(a, b)
+    # f32 sums of K products in any order: K 2^-23 sum |a||b|; one rounding to bf16: 2^-8 |c|
+    bound = k * 2.0 ** -23 * ref_abs + 2.0 ** -8 * np.abs(ref) + 1e-30
+    first = None
+    for _ in range(2):       # the same bits each time: nothing depends on the order in which waves arrive
+        B.proxy_device_fill_async(dc.ptr, 0xEE, dc.nbytes, 0)
+        B.proxy_gemm_bf16(da.ptr, db.ptr, dc.ptr, m, n, k, 0)
+        harness.synchronize()
+        out = gu.download(dc)
+        assert np.all(out[2 * m * n:] == 0xEE)
+        got = po.bf16_to_f64(out[:2 * m * n].view(np.uint16).reshape(m, n))
+        assert np.all(np.abs(got - ref) <= bound), float(np.max(np.abs(got - ref) / bound))
+        assert first is None or np.array_equal(first, out)
+        first = out
+    for x in (da, db, dc):
+        x.free()
