@@ -201,8 +201,16 @@ __global__ __launch_bounds__(kBlock) void pack_kernel(const ckpt_tile *__restric
 // table before it) reaches 5.73, 5.47 and 5.13. More words per lane widen the front and lose (2: 5.3 to 6.1; 4: 5.9 to
 // 6.1), four waves per block lose 5 % on aligned tensors (6.43) and win 1 % on fragments. On small lists the table was
 // the cost: 112 tensors of 0.4 MB took three kernels, 28 us back to back, and take one, 6 us.
+//
+// RUNS: of every 64 KiB, each XCD takes eight in a row instead of every eighth (consecutive blocks go to the eight XCDs in
+// turn). Of a tensor that does not start on a 128-byte line every wave's KiB ends in the middle of one, which the next wave
+// reads again; on the same XCD it finds it in that XCD's L2. Measured on MI355X: 3.7 GB of misaligned fragments 1399 -> 1362 us, 0.6
+// GB of smaller ones 574 -> 553 (runs of 4: 1384, 562; of 16: 1390, 553). Aligned tensors share no lines and lose by the
+// wider front: 1321 -> 1339 us, 11 GB of large ones 3368 -> 3525.
+template <bool RUNS>
 __global__ __launch_bounds__(64) void pack_batch_kernel(PackBatch bt, uint8_t *__restrict__ image) {
-    const uint32_t page = blockIdx.x / 4, at = (blockIdx.x % 4) * 1024 + 16 * threadIdx.x;
+    const uint32_t turn = blockIdx.x % 64, kib = RUNS ? blockIdx.x - turn + turn % 8 * 8 + turn / 8 : blockIdx.x;
+    const uint32_t page = kib / 4, at = (kib % 4) * 1024 + 16 * threadIdx.x;
     uint32_t lo = 0, hi = bt.count;
     if (page >= bt.first_page[hi]) return;
     while (hi - lo > 1) {
@@ -299,11 +307,23 @@ __global__ __launch_bounds__(kBlock) void scatter_kernel(const ckpt_tile *__rest
 
 // ---------------------------------------------------------------- launchers (host)
 
+// A launch of fewer pages takes little more than a launch, whatever the order (see pack_batch_kernel).
+#ifndef DSLLM_PACK_RUNS_FROM
+#define DSLLM_PACK_RUNS_FROM 2048
+#endif
+
 // Writes the pieces of `bt` to `image`, which begins with the page of the batch's first piece. A batch without pieces
-// launches one block that finds nothing to do (it makes the runtime load the kernels' code).
+// launches one block of either kernel that finds nothing to do (it makes the runtime load the kernels' code).
 hipError_t launch_pack_batch(const PackBatch &bt, void *image, hipStream_t stream) {
     const uint32_t pages = bt.first_page[bt.count];
-    hipLaunchKernelGGL(pack_batch_kernel, dim3(pages ? pages * 4 : 1), dim3(64), 0, stream, bt, static_cast<uint8_t *>(image));
+    uint32_t off_lines = 0;      // pages of tensors that do not start on a 128-byte line
+    if (pages >= DSLLM_PACK_RUNS_FROM)
+        for (uint32_t k = 0; k < bt.count; k++)
+            if (bt.src(k) % 128) off_lines += bt.first_page[k + 1] - bt.first_page[k];
+    if (off_lines > pages / 2 || !pages)
+        hipLaunchKernelGGL(pack_batch_kernel<true>, dim3(pages ? (pages * 4 + 63) / 64 * 64 : 1), dim3(64), 0, stream, bt, static_cast<uint8_t *>(image));
+    if (off_lines <= pages / 2)
+        hipLaunchKernelGGL(pack_batch_kernel<false>, dim3(pages ? pages * 4 : 1), dim3(64), 0, stream, bt, static_cast<uint8_t *>(image));
     return hipGetLastError();
 }
 
