@@ -232,6 +232,16 @@ int ckpt_init(const ckpt_config *cfg, ckpt_ctx **out) {
         if ((e = hipEventCreateWithFlags(&ev, hipEventBlockingSync)) != hipSuccess) return cleanup_fail(CKPT_EHIP, hipGetErrorString(e));
         c->ev_slot.push_back(ev);
     }
+    for (auto *events : {&c->ev_sent, &c->ev_part}) {
+        const bool sent = events == &c->ev_sent;
+        events->resize(rc.n_dma_streams + (sent ? 0 : 1));
+        for (auto &v : *events)
+            for (uint64_t i = 0; i < (sent ? c->n_slots : (rc.dma_chunk_bytes + kPartBytes - 1) / kPartBytes); i++) {
+                hipEvent_t ev;
+                if ((e = hipEventCreateWithFlags(&ev, hipEventDisableTiming | hipEventBlockingSync)) != hipSuccess) return cleanup_fail(CKPT_EHIP, hipGetErrorString(e));
+                v.push_back(ev);
+            }
+    }
     trace("init: slot events created");
     for (int k = 0; k < rc.n_dma_streams; k++) {
         hipEvent_t ev;
@@ -630,6 +640,8 @@ int ckpt_destroy(ckpt_ctx *c) {
     for (auto &kv : c->snaps) if (kv.second->ev_boundary) (void)hipEventDestroy(kv.second->ev_boundary);
     for (auto ev : c->ev_boundary_free) (void)hipEventDestroy(ev);
     for (auto ev : c->ev_slot) (void)hipEventDestroy(ev);
+    for (auto &v : c->ev_sent) for (auto ev : v) (void)hipEventDestroy(ev);
+    for (auto &v : c->ev_part) for (auto ev : v) (void)hipEventDestroy(ev);
     for (auto ev : c->ev_pack_start) (void)hipEventDestroy(ev);
     for (auto ev : c->ev_packed) (void)hipEventDestroy(ev);
     for (auto ev : c->ev_pack_end) (void)hipEventDestroy(ev);

@@ -113,7 +113,8 @@ struct IoJob {
     int fd = -1;                  // READ
     uint64_t slot = 0, file_off = 0, nbytes = 0;
     uint64_t slot_off = 0;        // where in the slot this piece of the chunk lies
-    bool last = false;            // WRITE: first piece of the snapshot's last chunk
+    bool last = false;            // WRITE: of the snapshot's last chunk, the piece that lands last (the first one if all land together)
+    hipEvent_t landed = nullptr;  // WRITE: the copy that brings this piece
     uint32_t piece = 0;           // READ: number of the piece in its chunk
 };
 
@@ -125,6 +126,13 @@ struct IoJob {
 #define DSLLM_PIECE_BYTES (4ull << 20)   // a multiple of 4 KiB
 #endif
 constexpr uint64_t kPieceBytes = DSLLM_PIECE_BYTES;
+// On restore pieces are a quarter of that, except for direct I/O: the link waits for the first one, and four threads that read
+// 4 MiB each bring none for 0.3 ms and then four at once.
+constexpr uint64_t kReadPieceBytes = kPieceBytes / 4 < 4096 ? 4096 : kPieceBytes / 4 / 4096 * 4096;
+// What one copy between ring and device moves where a chunk is shared among the copy streams. One stream loses some 10 us per
+// copy, two hide that from each other: 57.0 GB/s to the device in pieces of 4 MiB (one stream 50.4, whole chunks 57.6), 56.4 to the
+// host in parts of 16 MiB (55.1, 57.1).
+constexpr uint64_t kSendBytes = kPieceBytes, kPartBytes = 4 * kPieceBytes;
 constexpr int kBoundaryEvents = 8;          // boundary events created at set-up (snapshots in flight at a time)
 constexpr size_t kMaxSnapRecords = 1024;   // per-snapshot records (measurements, states) kept per context
 
@@ -155,7 +163,9 @@ struct ckpt_ctx {
     hipEvent_t ev_verify_start = nullptr, ev_verify_done = nullptr, ev_derived = nullptr;
     hipStream_t pack_stream = nullptr;
     std::vector<hipStream_t> dma;
-    std::vector<hipEvent_t> ev_slot;                      // per ring slot: copy into/out of the slot done
+    std::vector<hipEvent_t> ev_slot;                      // per ring slot: snapshot's copy into the slot done
+    std::vector<std::vector<hipEvent_t>> ev_sent;         // restore, [dma stream][slot]: what the stream had to copy when the slot's chunk was sent
+    std::vector<std::vector<hipEvent_t>> ev_part;         // [chunks from the end][part]: part of one of a snapshot's last chunks
     std::vector<hipEvent_t> ev_pack_start, ev_pack_end, ev_packed;   // per super-chunk: the kernel's start and end (timing), its completion in the pack stream (ordering)
     std::vector<std::vector<hipEvent_t>> ev_stage_done;   // [stage slot][dma stream]
     std::vector<hipEvent_t> ev_job_tail;                  // per dma stream

@@ -6,7 +6,7 @@
 using namespace dsllm;
 
 static void finish_d2h_stats(ckpt_ctx *c, Snap *s) {
-    // called by the I/O thread that has the first piece of the snapshot's last chunk, after all tail events completed
+    // called by the I/O thread that has the piece of the snapshot that lands last, after all tail events completed
     double pack_sum = 0, req_d2h = 0, span = 0, req_pack = 0;
     float ms = 0;
     const uint64_t n_sc = s->plan->n_superchunks;
@@ -101,10 +101,10 @@ void dsllm::io_thread_main(ckpt_ctx *c) {
             read_piece(c, job, bounce);
             continue;
         }
-        // WRITE: the chunk's copy must have landed in the slot first
+        // WRITE: the copy that brings the piece must have landed in the slot first
         Snap *s = job.snap.get();
         auto tw0 = Clock::now();
-        hipError_t he = hipEventSynchronize(c->ev_slot[job.slot]);
+        hipError_t he = hipEventSynchronize(job.landed);
         auto tw1 = Clock::now();
         s->io_wait_us += uint64_t(ms_between(tw0, tw1) * 1000.0);
         if (he != hipSuccess) c->fail_snapshot(s, CKPT_EHIP, std::string("copy event: ") + hipGetErrorString(he));

@@ -54,12 +54,20 @@ static int restore_body(ckpt_ctx *c, int fd, const char *path, hipStream_t strea
     if (p.n_direct)   // these copies write the tensors themselves
         for (size_t k = 0; k < nk; k++) HIP_TRY(c, hipStreamWaitEvent(c->dma[k], c->ev_user, 0));
 
-    const uint64_t piece_bytes = std::min<uint64_t>(kPieceBytes, CH / 8);   // CH is a multiple of 32 KiB: 4 KiB multiples
+    const uint64_t piece_bytes = std::min<uint64_t>(c->cfg.o_direct ? kPieceBytes : kReadPieceBytes, CH / 8);   // CH is a multiple of 32 KiB: 4 KiB multiples
+    const uint64_t send_pieces = std::max<uint64_t>(kSendBytes / piece_bytes, 1);
+    uint64_t sends = 0;             // copies enqueued, for the copy streams in turn
+    // A large chunk is sent on as its pieces arrive, over the copy streams in turn (one alone would lose time between the
+    // copies); a small one as a whole, on one stream, whose event is then the only one to be recorded and waited for.
+    const bool in_pieces = CH >= DSLLM_SCATTER_BYTES;
+    auto sent_on = [&](uint64_t ch, size_t k) { return in_pieces || k == ch % nk; };
     uint64_t &issued = *issued_out;   // chunks whose file read has been handed to the I/O threads
     auto issue_reads_upto = [&](uint64_t upto) -> int {
         for (; issued < upto && issued < p.n_chunks; issued++) {
             const uint64_t slot = (base + issued) % c->n_slots;
-            if (issued >= c->n_slots) HIP_TRY(c, hipEventSynchronize(c->ev_slot[slot]));   // previous chunk's copy out of the slot
+            if (issued >= c->n_slots)
+                for (size_t k = 0; k < nk; k++)
+                    if (sent_on(issued - c->n_slots, k)) HIP_TRY(c, hipEventSynchronize(c->ev_sent[k][slot]));   // previous chunk's copies out of the slot
             // a chunk is read in pieces, spread over the I/O threads
             const uint64_t nbytes = p.chunk_bytes(issued), n_pieces = (nbytes + piece_bytes - 1) / piece_bytes;
             {
@@ -94,30 +102,23 @@ static int restore_body(ckpt_ctx *c, int fd, const char *path, hipStream_t strea
             int r = issue_reads_upto(ch + c->n_slots);
             if (r != CKPT_OK) return r;
             const uint64_t slot = (base + ch) % c->n_slots;
-            const size_t k = ch % nk;
             const uint8_t *slot_base = c->ring + slot * CH;
             const uint64_t nbytes = p.chunk_bytes(ch);
-            // Where the copy engines have nothing to do (the first two chunks, and later whenever the file is read more
-            // slowly than the link moves data) the chunk is sent on as its pieces arrive; otherwise as a whole, because
-            // every copy costs the link some ten microseconds.
-            bool in_pieces = CH >= DSLLM_SCATTER_BYTES && ch < 2;
-            if (CH >= DSLLM_SCATTER_BYTES && !in_pieces) {
-                in_pieces = hipEventQuery(c->ev_slot[(base + ch - 1) % c->n_slots]) == hipSuccess;
-                if (!in_pieces) (void)hipGetLastError();   // "not ready" is no error of a later call
-            }
             uint64_t sent = 0, seg = p.chunk_first_seg[ch];
             while (sent < nbytes) {
                 uint64_t ready = nbytes;
                 {
                     std::unique_lock<std::mutex> lk(c->mu);
                     const std::vector<uint8_t> &got = c->slot_piece_read[slot];
-                    // pieces read without a gap behind what has been sent; the first one goes at once, later ones four at a time
+                    // pieces read without a gap behind what has been sent; the first one goes at once, later ones some at a time
                     auto pieces_ready = [&] {
                         uint64_t q = sent / piece_bytes;
                         while (q < got.size() && got[q]) q++;
                         return q - sent / piece_bytes;
                     };
-                    const uint64_t enough = ch == 0 && sent == 0 ? 1 : 4;
+                    // (at the ends little, as the link or the caller waits for it; in between more, to have the link busy while
+                    // this thread reads)
+                    const uint64_t enough = ch == 0 && sent == 0 ? 1 : ch < 2 || ch + 1 == p.n_chunks ? send_pieces : 4 * send_pieces;
                     auto can_go_on = [&] { return c->slot_state[slot] == SLOT_READ_DONE || (in_pieces && pieces_ready() >= enough); };
                     // A file that is read more slowly than the link moves data is the rule (one thread reads 15 GB/s): while
                     // it has nothing to send, this thread reads too, except for direct I/O, which needs a buffer of its own.
@@ -130,8 +131,10 @@ static int restore_body(ckpt_ctx *c, int fd, const char *path, hipStream_t strea
                     }
                     c->cv_state.wait(lk, [&] { return can_go_on() || c->async_code; });
                     if (c->async_code) { g_last_error = c->async_err; return c->async_code; }
-                    if (c->slot_state[slot] != SLOT_READ_DONE) ready = std::min(nbytes, sent + pieces_ready() * piece_bytes);
+                    // not too much, or one stream would have the link for itself for long
+                    if (in_pieces) ready = std::min(nbytes, sent + std::min(pieces_ready(), 4 * send_pieces) * piece_bytes);
                 }
+                const size_t k = in_pieces ? sends++ % nk : ch % nk;
                 // the parts of the chunk's segments that lie in [sent, ready)
                 for (; seg < p.chunk_first_seg[ch + 1]; seg++) {
                     const ckpt_segment &sg = p.segs[seg];
@@ -148,14 +151,16 @@ static int restore_body(ckpt_ctx *c, int fd, const char *path, hipStream_t strea
                 }
                 sent = ready;
             }
-            HIP_TRY(c, hipEventRecord(c->ev_slot[slot], c->dma[k]));
+            for (size_t k = 0; k < nk; k++)
+                if (sent_on(ch, k)) HIP_TRY(c, hipEventRecord(c->ev_sent[k][slot], c->dma[k]));
             // scattered as soon as it is on the device: what is left to do behind the last copy is one chunk, not a super-chunk
             if (ch + 1 < c1 && (ch + 1 - group) * CH < DSLLM_SCATTER_BYTES) continue;
             const uint64_t t1 = p.first_tile_at(sc, (ch + 1) * CH);
             if (t0 < t1) {
-                // every copy stream's latest chunk of the group (a slot that has been filled again since: the older copy was waited for)
-                for (uint64_t g = std::max(group, ch + 1 - std::min<uint64_t>(ch + 1, nk)); g <= ch; g++)
-                    HIP_TRY(c, hipStreamWaitEvent(c->pack_stream, c->ev_slot[(base + g) % c->n_slots], 0));
+                // every copy stream's latest event of the group (a slot that has been filled again since: the older copy was waited for)
+                for (uint64_t g = in_pieces ? ch : std::max(group, ch + 1 - std::min<uint64_t>(ch + 1, nk)); g <= ch; g++)
+                    for (size_t k = 0; k < nk; k++)
+                        if (sent_on(g, k)) HIP_TRY(c, hipStreamWaitEvent(c->pack_stream, c->ev_sent[k][(base + g) % c->n_slots], 0));
                 HIP_TRY(c, launch_scatter(dev_tiles + t0, t1 - t0, stage_base, sc * SC, c->pack_stream));
             }
             group = ch + 1;

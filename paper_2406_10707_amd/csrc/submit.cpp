@@ -145,7 +145,8 @@ static void submit_one(ckpt_ctx *c, const std::shared_ptr<Snap> &sp) {
         c->slot_state[slot] = SLOT_BUSY;
         return slot;
     };
-    auto hand_to_io = [&](uint64_t ch, uint64_t slot) {      // chunk ch, whose arrival in `slot` is ev_slot[slot], goes to the file
+    // chunk ch goes to the file; its arrival in `slot` is ev_slot[slot], or part by part the events in `parts`
+    auto hand_to_io = [&](uint64_t ch, uint64_t slot, const hipEvent_t *parts = nullptr) {
         const uint64_t nbytes = p.chunk_bytes(ch), n_pieces = (nbytes + kPieceBytes - 1) / kPieceBytes;
         {
             std::lock_guard<std::mutex> lk(c->mu);
@@ -158,7 +159,8 @@ static void submit_one(ckpt_ctx *c, const std::shared_ptr<Snap> &sp) {
                 job.slot_off = q * kPieceBytes;
                 job.file_off = p.header_bytes + ch * CH + job.slot_off;
                 job.nbytes = std::min<uint64_t>(kPieceBytes, nbytes - job.slot_off);
-                job.last = ch + 1 == p.n_chunks && q == 0;
+                job.last = ch + 1 == p.n_chunks && q == (parts ? n_pieces - 1 : 0);
+                job.landed = parts ? parts[job.slot_off / kPartBytes] : c->ev_slot[slot];
                 c->io_q.push_back(std::move(job));
             }
         }
@@ -230,12 +232,22 @@ static void submit_one(ckpt_ctx *c, const std::shared_ptr<Snap> &sp) {
             c->cv_state.notify_all();
         }
     };
+    // The last chunks are shared among the copy streams, part by part in turn, and written part by part. The streams otherwise
+    // end with a chunk each, and the last ones land together: 1.2 ms of writing behind the last copy with two of 64 MiB, 0.3 in parts.
+    // One chunk more than there are streams, so that the I/O threads have caught up when the last one lands. The events
+    // are the context's: they must not be in use for the snapshot before, which a slow disk may still be writing.
+    uint64_t shared = 0;
+    if (nk > 1 && CH > kPartBytes && p.n_chunks > 1) {
+        std::lock_guard<std::mutex> lk(c->mu);
+        if (!c->prev_job || c->prev_job->committed) shared = std::min<uint64_t>(p.n_chunks, nk + 1);
+    }
     for (uint64_t sc = 0; sc < std::min<uint64_t>(ahead, p.n_superchunks); sc++) enqueue_pack(sc);
     for (uint64_t sc = 0; sc < p.n_superchunks; sc++) {
         const uint64_t stage = sc % c->n_stage;
         uint8_t *stage_base = c->staging + stage * SC;
         auto wait_packed = [&](size_t k, hipEvent_t packed) { if ((e = hipStreamWaitEvent(c->dma[k], packed, 0)) != hipSuccess) hip_fail("wait packed", e); };
         const bool head = head_apart && sc == 0;
+        bool only_head = head;       // the first copy stream has waited for the first chunk's launch alone
         if (head) wait_packed(0, c->ev_packed_head);
         for (size_t k = head ? 1 : 0; k < nk; k++) wait_packed(k, c->ev_packed[sc]);
 
@@ -243,15 +255,20 @@ static void submit_one(ckpt_ctx *c, const std::shared_ptr<Snap> &sp) {
         const uint64_t c1 = std::min<uint64_t>(p.n_chunks, c0 + SC / CH);
         for (uint64_t ch = c0; ch < c1; ch++) {
             const size_t k = ch % nk;
-            if (head && ch == nk) wait_packed(0, c->ev_packed[0]);   // the first copy stream's second chunk
+            const bool in_parts = ch + shared >= p.n_chunks;
+            if (only_head && ch > 0 && (in_parts || k == 0)) { wait_packed(0, c->ev_packed[0]); only_head = false; }
             const uint64_t slot = take_slot();
             if (ch == 0 && (e = hipEventRecord(c->ev_first_copy, c->dma[k])) != hipSuccess) hip_fail("record", e);
             // the chunk's segments: packed bytes out of staging, large tensors out of their own memory,
             // the padding behind those zero-filled here (the slot belongs to this thread until the copy event)
             uint8_t *slot_base = c->ring + slot * CH;
+            const uint64_t part_bytes = in_parts ? kPartBytes : CH;
+            uint64_t part = 0;
+            const hipEvent_t *parts = in_parts ? c->ev_part[p.n_chunks - 1 - ch].data() : nullptr;
             for (uint64_t j = p.chunk_first_seg[ch]; j < p.chunk_first_seg[ch + 1]; j++) {
                 const ckpt_segment &sg = p.segs[j];
-                uint8_t *dst = slot_base + (sg.data_off - ch * CH);
+                const uint64_t at = sg.data_off - ch * CH;
+                uint8_t *dst = slot_base + at;
                 if (sg.kind == CKPT_SEG_ZERO) { memset(dst, 0, sg.nbytes); continue; }
                 if (sg.kind == CKPT_SEG_HOST) {   // from the copy taken at the request
                     const TensorInfo &ti = p.tensors[sg.tensor];
@@ -260,10 +277,19 @@ static void submit_one(ckpt_ctx *c, const std::shared_ptr<Snap> &sp) {
                 }
                 const void *src = sg.kind == CKPT_SEG_DIRECT ? reinterpret_cast<const void *>(sg.src)
                                                              : static_cast<const void *>(stage_base + (sg.data_off - sc * SC));
-                e = hipMemcpyAsync(dst, src, sg.nbytes, hipMemcpyDeviceToHost, c->dma[k]);
-                if (e != hipSuccess) hip_fail("hipMemcpyAsync D2H", e);
+                for (uint64_t done = 0; done < sg.nbytes;) {
+                    for (; part < (at + done) / part_bytes; part++)      // every copy of an earlier part is enqueued
+                        if ((e = hipEventRecord(parts[part], c->dma[(k + part) % nk])) != hipSuccess) hip_fail("record", e);
+                    const uint64_t n = std::min(sg.nbytes - done, (part + 1) * part_bytes - (at + done));
+                    e = hipMemcpyAsync(dst + done, static_cast<const uint8_t *>(src) + done, n, hipMemcpyDeviceToHost, c->dma[(k + part) % nk]);
+                    if (e != hipSuccess) hip_fail("hipMemcpyAsync D2H", e);
+                    done += n;
+                }
             }
-            if ((e = hipEventRecord(c->ev_slot[slot], c->dma[k])) != hipSuccess) hip_fail("record", e);
+            if (in_parts) {
+                for (; part * part_bytes < p.chunk_bytes(ch); part++)
+                    if ((e = hipEventRecord(parts[part], c->dma[(k + part) % nk])) != hipSuccess) hip_fail("record", e);
+            } else if ((e = hipEventRecord(c->ev_slot[slot], c->dma[k])) != hipSuccess) hip_fail("record", e);
             const bool last = ch + 1 == p.n_chunks;
             if (ch + 1 == c1)
                 for (size_t kk = 0; kk < nk; kk++)
@@ -271,7 +297,7 @@ static void submit_one(ckpt_ctx *c, const std::shared_ptr<Snap> &sp) {
             if (last)
                 for (size_t kk = 0; kk < nk; kk++)
                     if ((e = hipEventRecord(c->ev_job_tail[kk], c->dma[kk])) != hipSuccess) hip_fail("record", e);
-            hand_to_io(ch, slot);
+            hand_to_io(ch, slot, parts);
         }
         // The next pack launch goes out one round late, after this super-chunk's copies have been enqueued: its host-side
         // wait is for the copies of the previous super-chunk, and the copy engines have this one's to go on with. The
