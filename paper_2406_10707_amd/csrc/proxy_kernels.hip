@@ -159,7 +159,7 @@ __device__ __forceinline__ GemmTile gemm_tile(int tiles_m, int tiles_n) {
 // of a matrix instruction. Where that shadow is short the registers are faster (128 x 128 tiles: 3 %), with 256 x 256 tiles
 // slower (2 %). WIDE: 64-bit addresses (the lane's own part made once, the instruction's part uniform), for panels that a
 // buffer resource's 32-bit offsets do not span.
-template <int BM, int BN, int NW, bool KEPT, bool WIDE>
+template <int BM, int BN, int NW, bool PAIRS, bool KEPT, bool WIDE>
 struct PanelLoader {
     static constexpr int LA = BM / 8 / NW, LB = BN / 8 / NW, COUNT = LA + LB;   // instructions per wave and step
     static_assert(LA * 8 * NW == BM && LB * 8 * NW == BN && NW % 4 == 0, "panels divide among the waves, four waves' rows per 32");
@@ -169,7 +169,7 @@ struct PanelLoader {
 
     __device__ __forceinline__ PanelLoader(const uint16_t *a_panel, const uint16_t *b_panel, int K, int lane, int wave_)
         : row0((lane >> 3) + 8 * wave_), piece_a((lane & 7) ^ ((4 * (wave_ & 1) + (lane >> 4)) & 7)),
-          piece_b((lane & 7) ^ (((lane >> 4) & 1) | ((wave_ & 3) << 1))), k(uint32_t(K)), wave(wave_) {
+          piece_b(PAIRS ? (lane & 7) ^ (((lane >> 4) & 1) | ((wave_ & 3) << 1)) : piece_a), k(uint32_t(K)), wave(wave_) {
         if constexpr (WIDE) {
             lane_a = a_panel + size_t(row0) * k + 8 * piece_a;
             lane_b = b_panel + size_t(row0) * k + 8 * piece_b;
@@ -213,13 +213,18 @@ __device__ __forceinline__ void store_columns(uint16_t *c, f32x4 lo, f32x4 hi) {
 // Products with a short K or a small C; the order inside a step is the compiler's. A wave computes (16 TM) x (16 TN),
 // WM x WN waves a block tile, which M and N are multiples of; KG such groups of waves share the tile, each taking every
 // KG-th step of K, and their sums are added in LDS at the end (in group order: the result does not depend on timing).
-// NST steps are in LDS; the loads of a step go out NST - 1 steps ahead.
+// NST steps are in LDS; the loads of a step go out NST - 1 steps ahead. With 32 x 32 tiles a wave has one fragment of each side
+// (and stores half a piece a row): what bounds a block of a long K is the panels' bytes at some 50 a cycle, and where 32 x 64
+// tiles leave half of the compute units or more without one, tiles of half the size have a third less to load each:
+// 256 x 512 x 7808 20.0 -> 13.8 us, 128 x 128 x 5120 12.8 -> 9.6, 256 x 384 x 1664 6.3 -> 5.2. (Fragments straight from memory, with K
+// split among the waves of a block, take twice as long: sixteen rows a request.)
 template <int TM, int TN, int WM, int WN, int KG, int NST, bool WIDE>
 __global__ __launch_bounds__(64 * WM * WN * KG) void gemm_bf16_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B,
                                                                      uint16_t *__restrict__ C, int M, int N, int K) {
     constexpr int BM = 16 * TM * WM, BN = 16 * TN * WN, NW = WM * WN, STEP = (BM + BN) * 64;
-    typedef PanelLoader<BM, BN, NW, false, WIDE> Loader;
-    static_assert(TN % 2 == 0, "B fragments come in pairs");
+    constexpr bool PAIRS = TN % 2 == 0;
+    typedef PanelLoader<BM, BN, NW, PAIRS, false, WIDE> Loader;
+    static_assert(PAIRS || TN == 1, "B fragments come in pairs, or there is one");
     static_assert((KG - 1) * BM * BN * 4 <= NST * KG * STEP * 2, "the partial sums fit where the panels were");
     __shared__ __attribute__((aligned(1024))) uint16_t lds[NST * KG * STEP];
     const GemmTile t = gemm_tile<(KG > 1)>(M / BM, N / BN);
@@ -233,12 +238,12 @@ __global__ __launch_bounds__(64 * WM * WN * KG) void gemm_bf16_kernel(const uint
 #pragma unroll
         for (int i = 0; i < Loader::COUNT; i++) load.issue(lds + (stage * KG + group) * STEP, step * KG + group, i);
     };
-    const int ar = lane & 15, br = 8 * (ar >> 2) + (ar & 3);
+    const int ar = lane & 15, br = PAIRS ? 8 * (ar >> 2) + (ar & 3) : ar;
     int at_a[2], at_b[2];
 #pragma unroll
     for (int h = 0; h < 2; h++) {
         at_a[h] = (16 * TM * wm + ar) * 64 + 8 * ((4 * h + (lane >> 4)) ^ ((ar >> 1) & 7));
-        at_b[h] = (BM + 16 * TN * wn + br) * 64 + 8 * ((4 * h + (lane >> 4)) ^ (((ar >> 1) & 1) | ((ar >> 2) << 1)));
+        at_b[h] = (BM + 16 * TN * wn + br) * 64 + 8 * ((4 * h + (lane >> 4)) ^ (PAIRS ? ((ar >> 1) & 1) | ((ar >> 2) << 1) : (ar >> 1) & 7));
     }
     f32x4 acc[TM][TN];
 #pragma unroll
@@ -286,11 +291,14 @@ __global__ __launch_bounds__(64 * WM * WN * KG) void gemm_bf16_kernel(const uint
 #pragma unroll
             for (int i = 0; i < TM * TN; i++) acc[i / TN][i % TN] += part[((g * NW + wave) * TM * TN + i) * 64 + lane];
     }
-    uint16_t *c = C + (size_t(t.tm) * BM + wm * 16 * TM + ar) * N + size_t(t.tn) * BN + wn * 16 * TN + 8 * (lane >> 4);
+    uint16_t *c = C + (size_t(t.tm) * BM + wm * 16 * TM + ar) * N + size_t(t.tn) * BN + wn * 16 * TN + (PAIRS ? 8 : 4) * (lane >> 4);
 #pragma unroll
-    for (int i = 0; i < TM; i++)
+    for (int i = 0; i < TM; i++) {
+        if constexpr (!PAIRS) *reinterpret_cast<bf16x4 *>(c + size_t(16 * i) * N) = __builtin_convertvector(acc[i][0], bf16x4);
+        else
 #pragma unroll
-        for (int j = 0; j < TN; j += 2) store_columns(c + size_t(16 * i) * N + 16 * j, acc[i][j], acc[i][j + 1]);
+            for (int j = 0; j < TN; j += 2) store_columns(c + size_t(16 * i) * N + 16 * j, acc[i][j], acc[i][j + 1]);
+    }
 }
 
 template <class F, int... I>
@@ -323,7 +331,7 @@ template <int WM, int WN, int TM, int TN, int STAGES, int READS, int LOAD_EVERY,
 __device__ __forceinline__ void gemm_bf16_tile(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B, uint16_t *__restrict__ C, int M, int N, int K) {
     constexpr int NW = WM * WN, BM = 16 * TM * WM, BN = 16 * TN * WN, STEP = (BM + BN) * 64, FRAGS = TM + TN, HALF = TM * TN;
     constexpr bool NAMED = TM * TN > 32, TWO = STAGES == 2;
-    typedef PanelLoader<BM, BN, NW, !NAMED, WIDE> Loader;
+    typedef PanelLoader<BM, BN, NW, true, !NAMED, WIDE> Loader;
     constexpr int COUNT = Loader::COUNT;
     static_assert(TN % 2 == 0 && STAGES >= 2, "B fragments come in pairs");
     // fragment i of a half is read behind MFMA at_read(i) of the half before it (of what is left of that behind the second meeting)
@@ -487,6 +495,7 @@ const GemmForm kGemmForms[] = {     // in the order of launch_gemm's switch
     {64, 64, 2, 1.80f, {0.67f, 0.89f, 0.00f}, {0.1494f, 0.2870f, 0.0000f}, 0.18f, 0.0281f},
     {64, 64, 3, 2.07f, {0.17f, 0.58f, 1.24f}, {0.1521f, 0.2266f, 0.3086f}, 0.00f, 0.0740f},
     {32, 64, 1, 1.37f, {1.66f, 0.00f, 0.00f}, {0.1244f, 0.0000f, 0.0000f}, 0.17f, 0.0134f},
+    {32, 32, 1, 1.25f, {1.74f, 0.00f, 0.00f}, {0.0820f, 0.0000f, 0.0000f}, 0.08f, 0.0071f},
     {128, 128, 2, 2.24f, {0.55f, 1.81f, 0.00f}, {0.5691f, 0.6548f, 0.0000f}, 0.76f, 0.1264f},
 };
 
@@ -525,6 +534,7 @@ void launch_gemm(const uint16_t *a, const uint16_t *b, uint16_t *c, int m, int n
         case 11: go(gemm_bf16_tile_kernel<2, 2, 2, 2, 2, 4, -2, 1, WIDE>, form.rows, form.cols, 256); break;
         case 12: go(gemm_bf16_tile_kernel<3, 2, 2, 2, 2, 3, -2, 1, WIDE>, form.rows, form.cols, 256); break;
         case 13: go(gemm_bf16_kernel<1, 2, 2, 2, 4, 3, WIDE>, form.rows, form.cols, 1024); break;
+        case 14: go(gemm_bf16_kernel<1, 1, 2, 2, 4, 3, WIDE>, form.rows, form.cols, 1024); break;
         default: go(gemm_bf16_kernel<4, 4, 2, 2, 1, 2, WIDE>, form.rows, form.cols, 256); break;
     }
 }
