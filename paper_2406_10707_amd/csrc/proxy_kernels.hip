@@ -139,19 +139,47 @@ __global__ __launch_bounds__(64) void devcopy_kernel(u32x4 *__restrict__ dst, co
 
 struct GemmTile { int tm, tn; };
 
-// Consecutive block ids go to different XCDs (8 of them, each with its own L2): gives each XCD a contiguous range of
-// tiles, walked in strips 8 tiles tall so that neighbours share A and B panels. ALWAYS: also where 8 does not divide the
-// number of tiles. With a short K the stores of C are what counts, and those go better in block order (7808 x 3968 x 128
-// 18.2 us, by XCD 18.9).
-template <bool ALWAYS>
-__device__ __forceinline__ GemmTile gemm_tile(int tiles_m, int tiles_n) {
-    const int n_tiles = tiles_m * tiles_n, xcd = blockIdx.x % 8, each = n_tiles / 8, more = n_tiles % 8;    // the first `more` XCDs have one tile more
-    const int bid = !ALWAYS && more ? blockIdx.x : xcd * each + (xcd < more ? xcd : more) + blockIdx.x / 8;
-    const int strip = 8;
-    const int per_strip = strip * tiles_n;
-    const int s = bid / per_strip, in_s = bid % per_strip;
-    const int rows_here = (tiles_m - s * strip) < strip ? (tiles_m - s * strip) : strip;
-    return GemmTile{s * strip + in_s % rows_here, in_s / rows_here};
+// Which tile a block computes. Consecutive block ids go to different XCDs (8 of them, each with its own L2): each XCD is given
+// a contiguous range of tiles, walked in strips 8 tiles tall so that neighbours share A and B panels. With a short K the
+// stores of C are what counts, and those go better in block order where 8 does not divide the number of tiles (7808 x 3968 x
+// 128 18.2 us, by XCD 18.9).
+// The host prepares the divisions: three of them, on scalars, were 90 of the 150 instructions in front of a block's first load
+// (and a branch costs some 40 cycles, so there is none). Products of 4 to 6 us take 4 % less than with divisions in the kernel, of
+// 6 to 10 us 2 %, of 10 to 20 us 1 % (300 products; 1024 x 3072 x 768 7.7 -> 7.5 us, 896 x 3072 x 64 4.1 -> 3.5); those of
+// 3 us are bound by the launches.
+struct TileOrder {
+    uint32_t xcd_bits, xcd_shift;            // of a block id: its XCD, what is left of it (0, 0: tiles go in the blocks' own order)
+    uint32_t each, more;                     // tiles of every XCD; how many XCDs have one tile more
+    uint32_t per_strip, strip_inverse;       // tiles of a full strip
+    uint32_t full_strips, last_rows, last_inverse;       // the last strip may be less than 8 tall
+
+    static uint32_t inverse(uint32_t d) { return 0xFFFFFFFFu / d; }
+    // x / d: the upper half of x times the inverse is that or one less
+    static __host__ __device__ __forceinline__ uint32_t divided(uint32_t x, uint32_t d, uint32_t inverse) {
+        const uint32_t q = uint32_t((uint64_t(x) * inverse) >> 32);
+        return x - q * d >= d ? q + 1 : q;
+    }
+    TileOrder(uint32_t tiles_m, uint32_t tiles_n, bool by_xcd) {
+        const uint32_t n = tiles_m * tiles_n;
+        const bool in_order = !by_xcd && n % 8;
+        xcd_bits = in_order ? 0 : 7;
+        xcd_shift = in_order ? 0 : 3;
+        each = n / 8;
+        more = n % 8;
+        per_strip = 8 * tiles_n;
+        strip_inverse = inverse(per_strip);
+        full_strips = tiles_m / 8;
+        last_rows = tiles_m % 8 ? tiles_m % 8 : 8;
+        last_inverse = inverse(last_rows);
+    }
+};
+
+__device__ __forceinline__ GemmTile gemm_tile(const TileOrder &o) {
+    const uint32_t xcd = blockIdx.x & o.xcd_bits, tile = xcd * o.each + min(xcd, o.more) + (blockIdx.x >> o.xcd_shift);
+    const uint32_t s = TileOrder::divided(tile, o.per_strip, o.strip_inverse), in_s = tile - s * o.per_strip;
+    const uint32_t rows_here = s < o.full_strips ? 8 : o.last_rows;
+    const uint32_t col = TileOrder::divided(in_s, rows_here, s < o.full_strips ? 1u << 29 : o.last_inverse);
+    return GemmTile{int(8 * s + in_s - col * rows_here), int(col)};
 }
 
 // One wave's eight rows of a panel per instruction; NW waves share a panel. KEPT: a lane's offset for each instruction stays in
@@ -220,14 +248,14 @@ __device__ __forceinline__ void store_columns(uint16_t *c, f32x4 lo, f32x4 hi) {
 // split among the waves of a block, take twice as long: sixteen rows a request.)
 template <int TM, int TN, int WM, int WN, int KG, int NST, bool WIDE>
 __global__ __launch_bounds__(64 * WM * WN * KG) void gemm_bf16_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B,
-                                                                     uint16_t *__restrict__ C, int M, int N, int K) {
+                                                                     uint16_t *__restrict__ C, int N, int K, TileOrder order) {
     constexpr int BM = 16 * TM * WM, BN = 16 * TN * WN, NW = WM * WN, STEP = (BM + BN) * 64;
     constexpr bool PAIRS = TN % 2 == 0;
     typedef PanelLoader<BM, BN, NW, PAIRS, false, WIDE> Loader;
     static_assert(PAIRS || TN == 1, "B fragments come in pairs, or there is one");
     static_assert((KG - 1) * BM * BN * 4 <= NST * KG * STEP * 2, "the partial sums fit where the panels were");
     __shared__ __attribute__((aligned(1024))) uint16_t lds[NST * KG * STEP];
-    const GemmTile t = gemm_tile<(KG > 1)>(M / BM, N / BN);
+    const GemmTile t = gemm_tile(order);
     const int lane = threadIdx.x & 63, wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wave = wave_all % NW, group = wave_all / NW;
     const int wm = wave / WN, wn = wave % WN;
     const Loader load(A + size_t(t.tm) * BM * K, B + size_t(t.tn) * BN * K, K, lane, wave);
@@ -326,9 +354,10 @@ __device__ __forceinline__ void for_each_of(F f, std::integer_sequence<int, I...
 // 0.70 ms = 1570 TFLOP/s, where one 32x32x16 kernel with panels through registers took 1.07), and towards small tiles
 // more and more what a wave issues between its MFMAs and the panel loads (BM + BN rows a step): 128 x 128 takes 820 cycles a step,
 // of which the MFMAs are 512 and the loads at 58 bytes a cycle 565. Four waves of 64 x 64 instead of sixteen of 32 x 32
-// and a hand-made order made of 1024 x 3072 x 768 9.9 -> 7.5 us.
+// and a hand-made order made of 1024 x 3072 x 768 10.0 -> 7.5 us, launched in a row.
 template <int WM, int WN, int TM, int TN, int STAGES, int READS, int LOAD_EVERY, bool WIDE>
-__device__ __forceinline__ void gemm_bf16_tile(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B, uint16_t *__restrict__ C, int M, int N, int K) {
+__device__ __forceinline__ void gemm_bf16_tile(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B, uint16_t *__restrict__ C, int M, int N, int K,
+                                               const TileOrder &order) {
     constexpr int NW = WM * WN, BM = 16 * TM * WM, BN = 16 * TN * WN, STEP = (BM + BN) * 64, FRAGS = TM + TN, HALF = TM * TN;
     constexpr bool NAMED = TM * TN > 32, TWO = STAGES == 2;
     typedef PanelLoader<BM, BN, NW, true, !NAMED, WIDE> Loader;
@@ -346,7 +375,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const uint16_t *__restrict__ A, c
     static_assert(READ_SPAN <= HALF && FREE_AT <= HALF + 2 && LANDED_AT < 2 * HALF, "the reads of a half lie inside the half before");
     static_assert(TWO || FREE_AT + (COUNT - 1) * LOAD_EVERY - 2 * HALF < LANDED_AT, "a step's loads are out before the next one's");
     __shared__ __attribute__((aligned(1024))) uint16_t lds[STAGES * STEP];
-    const GemmTile t = gemm_tile<true>(M / BM + (M % BM != 0), N / BN + (N % BN != 0));
+    const GemmTile t = gemm_tile(order);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wm = wave / WN, wn = wave % WN;
     const int row = min(t.tm * BM, M - BM), col = min(t.tn * BN, N - BN);
     const Loader load(A + size_t(row) * K, B + size_t(col) * K, K, lane, wave);
@@ -436,16 +465,16 @@ __device__ __forceinline__ void gemm_bf16_tile(const uint16_t *__restrict__ A, c
 // TOGETHER blocks share a compute unit. The bodies are the device's only: the host's pass needs no more than the names.
 template <int TOGETHER, int WM, int WN, int TM, int TN, int STAGES, int READS, int LOAD_EVERY, bool WIDE>
 __global__ __launch_bounds__(256, TOGETHER) void gemm_bf16_tile_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B,
-                                                                      uint16_t *__restrict__ C, int M, int N, int K) {
+                                                                      uint16_t *__restrict__ C, int M, int N, int K, TileOrder order) {
 #if defined(__HIP_DEVICE_COMPILE__)
-    gemm_bf16_tile<WM, WN, TM, TN, STAGES, READS, LOAD_EVERY, WIDE>(A, B, C, M, N, K);
+    gemm_bf16_tile<WM, WN, TM, TN, STAGES, READS, LOAD_EVERY, WIDE>(A, B, C, M, N, K, order);
 #endif
 }
 template <bool WIDE>
 __global__ __launch_bounds__(256) void gemm_bf16_256_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B, uint16_t *__restrict__ C, int M,
-                                                           int N, int K) {
+                                                           int N, int K, TileOrder order) {
 #if defined(__HIP_DEVICE_COMPILE__)
-    gemm_bf16_tile<2, 2, 8, 8, 2, 2, 4, WIDE>(A, B, C, M, N, K);
+    gemm_bf16_tile<2, 2, 8, 8, 2, 2, 4, WIDE>(A, B, C, M, N, K, order);
 #endif
 }
 
@@ -457,14 +486,14 @@ __global__ __launch_bounds__(256) void gemm_bf16_256_kernel(const uint16_t *__re
 // rounds of up to `together`, block[n - 1] + step[n - 1] * (K / 64) for every round of n; and for all blocks together, as a
 // full card clocks lower and shares memory, (spread_block + spread_step * (K / 64)) * blocks / 256. The figures are fitted to times
 // of every form on 560 products on an MI355X, M and N multiples of 128 up to 8192 and K of 64 up to 8192, each spread over the
-// logarithm of its range: 2 to 3 % off in the mean, 4 to 9 % at the ninth decile. The choice by them is 1.1 % slower in the
-// mean than the best form for each product, and 17 % faster than a rule on the number of tiles over two 128 x 128, two 64 x 64, one
-// 32 x 64 kernel and 256 x 256 where both sizes are its multiples. Where that lost most:
+// logarithm of its range (32 x 32: on 75 of them): 2 to 3 % off in the mean, 4 to 9 % at the ninth decile. The choice by them is 1.1 % slower in the
+// mean than the best form for each product, and over 300 other products 14 % faster than a rule on the number of tiles over two 128 x 128, two
+// 64 x 64, one 32 x 64 kernel and 256 x 256 where both sizes are its multiples. Where that lost most:
 //   6272 x 7808 x 6592 685 -> 462 us     sizes not multiples of 256, formerly 128 x 128 for all
 //   1920 x 7936 x 3456 127 -> 76
 //   768 x 5632 x 3392 46 -> 34           a few 128 x 128 tiles more than there are units
 //   384 x 5248 x 960 12.1 -> 6.9
-//   1024 x 3072 x 768 9.9 -> 7.6         fewer 128 x 128 tiles than units: 128 x 96 fills them
+//   1024 x 3072 x 768 10.0 -> 7.5        fewer 128 x 128 tiles than units: 128 x 96 fills them
 // WIDE once a panel of 256 rows passes 2 GiB (the offsets of a buffer load are 32 bits wide); the choice is the same there.
 struct GemmForm {
     int rows, cols, together;
@@ -501,15 +530,21 @@ const GemmForm kGemmForms[] = {     // in the order of launch_gemm's switch
 
 template <bool WIDE>
 void launch_gemm(const uint16_t *a, const uint16_t *b, uint16_t *c, int m, int n, int k, hipStream_t stream) {
-    auto go = [&](auto kernel, int rows, int cols, int threads) {
-        const uint64_t blocks = uint64_t(m / rows + (m % rows != 0)) * uint64_t(n / cols + (n % cols != 0));
-        hipLaunchKernelGGL(kernel, dim3(unsigned(blocks)), dim3(threads), 0, stream, a, b, c, m, n, k);
+    // `simple`: the kernels whose order is the compiler's; `by_xcd`: see TileOrder
+    auto tiles = [](int size, int tile) { return (unsigned(size) + unsigned(tile) - 1) / unsigned(tile); };
+    auto simple = [&](auto kernel, int rows, int cols, int threads, bool by_xcd) {
+        const unsigned tm = tiles(m, rows), tn = tiles(n, cols);
+        hipLaunchKernelGGL(kernel, dim3(tm * tn), dim3(threads), 0, stream, a, b, c, n, k, TileOrder(tm, tn, by_xcd));
+    };
+    auto go = [&](auto kernel, int rows, int cols) {
+        const unsigned tm = tiles(m, rows), tn = tiles(n, cols);
+        hipLaunchKernelGGL(kernel, dim3(tm * tn), dim3(256), 0, stream, a, b, c, m, n, k, TileOrder(tm, tn, true));
     };
     if (k <= 192) {
         const int64_t n64 = int64_t(m / 64) * (n / 64);
-        if (n64 > 4 * 256) go(gemm_bf16_kernel<4, 4, 2, 2, 1, 2, WIDE>, 128, 128, 256);
-        else if (n64 > 3 * 256) go(gemm_bf16_kernel<2, 2, 4, 4, 1, 4, WIDE>, 128, 128, 1024);      // more than the three of 64 x 64 that share a unit
-        else go(gemm_bf16_kernel<2, 2, 2, 2, 1, 3, WIDE>, 64, 64, 256);
+        if (n64 > 4 * 256) simple(gemm_bf16_kernel<4, 4, 2, 2, 1, 2, WIDE>, 128, 128, 256, false);
+        else if (n64 > 3 * 256) simple(gemm_bf16_kernel<2, 2, 4, 4, 1, 4, WIDE>, 128, 128, 1024, false);      // more than the three of 64 x 64 that share a unit
+        else simple(gemm_bf16_kernel<2, 2, 2, 2, 1, 3, WIDE>, 64, 64, 256, false);
         return;
     }
     int best = 0;
@@ -520,22 +555,22 @@ void launch_gemm(const uint16_t *a, const uint16_t *b, uint16_t *c, int m, int n
     }
     const GemmForm &form = kGemmForms[best];
     switch (best) {
-        case 0: go(gemm_bf16_256_kernel<WIDE>, form.rows, form.cols, 256); break;
-        case 1: go(gemm_bf16_tile_kernel<1, 2, 2, 7, 8, 2, 2, 4, WIDE>, form.rows, form.cols, 256); break;
-        case 2: go(gemm_bf16_tile_kernel<1, 2, 2, 8, 6, 2, 2, 4, WIDE>, form.rows, form.cols, 256); break;
-        case 3: go(gemm_bf16_tile_kernel<1, 2, 2, 5, 8, 3, 2, 4, WIDE>, form.rows, form.cols, 256); break;
-        case 4: go(gemm_bf16_tile_kernel<2, 2, 2, 6, 4, 2, 1, 2, WIDE>, form.rows, form.cols, 256); break;
-        case 5: go(gemm_bf16_tile_kernel<1, 2, 2, 5, 4, 3, 1, 4, WIDE>, form.rows, form.cols, 256); break;
-        case 6: go(gemm_bf16_tile_kernel<1, 2, 2, 4, 4, 3, 1, 4, WIDE>, form.rows, form.cols, 256); break;
-        case 7: go(gemm_bf16_tile_kernel<2, 2, 2, 4, 4, 2, -2, 1, WIDE>, form.rows, form.cols, 256); break;
-        case 8: go(gemm_bf16_tile_kernel<1, 4, 1, 2, 6, 3, 1, 3, WIDE>, form.rows, form.cols, 256); break;
-        case 9: go(gemm_bf16_tile_kernel<2, 2, 2, 2, 4, 3, 1, 2, WIDE>, form.rows, form.cols, 256); break;
-        case 10: go(gemm_bf16_tile_kernel<2, 2, 2, 3, 2, 4, -2, 1, WIDE>, form.rows, form.cols, 256); break;
-        case 11: go(gemm_bf16_tile_kernel<2, 2, 2, 2, 2, 4, -2, 1, WIDE>, form.rows, form.cols, 256); break;
-        case 12: go(gemm_bf16_tile_kernel<3, 2, 2, 2, 2, 3, -2, 1, WIDE>, form.rows, form.cols, 256); break;
-        case 13: go(gemm_bf16_kernel<1, 2, 2, 2, 4, 3, WIDE>, form.rows, form.cols, 1024); break;
-        case 14: go(gemm_bf16_kernel<1, 1, 2, 2, 4, 3, WIDE>, form.rows, form.cols, 1024); break;
-        default: go(gemm_bf16_kernel<4, 4, 2, 2, 1, 2, WIDE>, form.rows, form.cols, 256); break;
+        case 0: go(gemm_bf16_256_kernel<WIDE>, form.rows, form.cols); break;
+        case 1: go(gemm_bf16_tile_kernel<1, 2, 2, 7, 8, 2, 2, 4, WIDE>, form.rows, form.cols); break;
+        case 2: go(gemm_bf16_tile_kernel<1, 2, 2, 8, 6, 2, 2, 4, WIDE>, form.rows, form.cols); break;
+        case 3: go(gemm_bf16_tile_kernel<1, 2, 2, 5, 8, 3, 2, 4, WIDE>, form.rows, form.cols); break;
+        case 4: go(gemm_bf16_tile_kernel<2, 2, 2, 6, 4, 2, 1, 2, WIDE>, form.rows, form.cols); break;
+        case 5: go(gemm_bf16_tile_kernel<1, 2, 2, 5, 4, 3, 1, 4, WIDE>, form.rows, form.cols); break;
+        case 6: go(gemm_bf16_tile_kernel<1, 2, 2, 4, 4, 3, 1, 4, WIDE>, form.rows, form.cols); break;
+        case 7: go(gemm_bf16_tile_kernel<2, 2, 2, 4, 4, 2, -2, 1, WIDE>, form.rows, form.cols); break;
+        case 8: go(gemm_bf16_tile_kernel<1, 4, 1, 2, 6, 3, 1, 3, WIDE>, form.rows, form.cols); break;
+        case 9: go(gemm_bf16_tile_kernel<2, 2, 2, 2, 4, 3, 1, 2, WIDE>, form.rows, form.cols); break;
+        case 10: go(gemm_bf16_tile_kernel<2, 2, 2, 3, 2, 4, -2, 1, WIDE>, form.rows, form.cols); break;
+        case 11: go(gemm_bf16_tile_kernel<2, 2, 2, 2, 2, 4, -2, 1, WIDE>, form.rows, form.cols); break;
+        case 12: go(gemm_bf16_tile_kernel<3, 2, 2, 2, 2, 3, -2, 1, WIDE>, form.rows, form.cols); break;
+        case 13: simple(gemm_bf16_kernel<1, 2, 2, 2, 4, 3, WIDE>, form.rows, form.cols, 1024, true); break;
+        case 14: simple(gemm_bf16_kernel<1, 1, 2, 2, 4, 3, WIDE>, form.rows, form.cols, 1024, true); break;
+        default: simple(gemm_bf16_kernel<4, 4, 2, 2, 1, 2, WIDE>, form.rows, form.cols, 256, false); break;
     }
 }
 

@@ -25,7 +25,8 @@ SHAPES = [(2816, 5120, 256), (4736, 2944, 256),                          # 256 x
           (128, 1664, 1472), (128, 128, 256), (256, 384, 320),           # 64 x 64, two and three to a unit
           (384, 768, 1408), (256, 1536, 2048 + 64),                      # 32 x 64, K split in four
           (384, 256, 2048 + 64), (128, 128, 1024), (512, 512, 1664), (128, 640, 1152),     # 32 x 32, K split in four
-          (4480, 1408, 256), (2304, 1152, 192), (1152, 1024, 192)]       # the order left to the compiler
+          (4480, 1408, 256), (2304, 1152, 192), (1152, 1024, 192),       # the order left to the compiler
+          (128, 128, 64), (384, 640, 64), (640, 1664, 128), (1408, 640, 192), (1920, 896, 64), (2176, 3200, 64)]     # strips of 1 to 7 rows of tiles
 
 
 @pytest.mark.parametrize("m,n,k", SHAPES)
