@@ -480,7 +480,13 @@ __global__ __launch_bounds__(256) void gemm_bf16_256_kernel(const uint16_t *__re
 
 // Which kernel and tile: the one of these that is expected to be done first. Up to K = 192 it is the first lines of launch_gemm
 // that decide, as a product is then little more than a launch and the stores of C (the hand-made order's prologue costs 0.5 us
-// more than the other kernel's: 2432 x 4992 x 64 8.8 us against 10.0).
+// more than the other kernel's: 2432 x 4992 x 64 8.8 us against 10.0). 64 x 64 tiles as long as they are all under way at once,
+// three to a unit. Then what counts is how many rounds of blocks there are: a round of 64 x 128 tiles, three to a unit, is
+// three quarters of the data of one of 128 x 128, two to a unit, and takes about 0.8 of its time. Four waves a 128 x 128 tile in a single round
+// or with K = 64; else eight, in the XCDs' order, as panels are then read again by other rounds. Over 225 products
+// 2.9 % faster than 64 x 64, sixteen-wave 128 x 128 and four-wave 128 x 128 tiles by their number alone, and none slower:
+//   896 x 3456 x 64 4.76 -> 4.33         640 x 6784 x 64 5.76 -> 4.86      7040 x 1280 x 128 9.4 -> 8.2
+//   1792 x 7808 x 192 14.2 -> 12.8       3456 x 7808 x 192 26.1 -> 20.2
 //
 // What a form is expected to take, in us: `start`, and then for the compute unit with the most blocks, which takes them in
 // rounds of up to `together`, block[n - 1] + step[n - 1] * (K / 64) for every round of n; and for all blocks together, as a
@@ -540,11 +546,13 @@ void launch_gemm(const uint16_t *a, const uint16_t *b, uint16_t *c, int m, int n
         const unsigned tm = tiles(m, rows), tn = tiles(n, cols);
         hipLaunchKernelGGL(kernel, dim3(tm * tn), dim3(256), 0, stream, a, b, c, m, n, k, TileOrder(tm, tn, true));
     };
-    if (k <= 192) {
+    if (!WIDE && k <= 192) {
         const int64_t n64 = int64_t(m / 64) * (n / 64);
-        if (n64 > 4 * 256) simple(gemm_bf16_kernel<4, 4, 2, 2, 1, 2, WIDE>, 128, 128, 256, false);
-        else if (n64 > 3 * 256) simple(gemm_bf16_kernel<2, 2, 4, 4, 1, 4, WIDE>, 128, 128, 1024, false);      // more than the three of 64 x 64 that share a unit
-        else simple(gemm_bf16_kernel<2, 2, 2, 2, 1, 3, WIDE>, 64, 64, 256, false);
+        const int64_t rounds_of_half = (n64 / 2 + 3 * 256 - 1) / (3 * 256), rounds_of_128 = (n64 / 4 + 2 * 256 - 1) / (2 * 256);
+        if (n64 <= 3 * 256) simple(gemm_bf16_kernel<2, 2, 2, 2, 1, 3, false>, 64, 64, 256, false);
+        else if (4 * rounds_of_half <= 5 * rounds_of_128) simple(gemm_bf16_kernel<2, 4, 2, 2, 1, 2, false>, 64, 128, 256, false);
+        else if (k == 64 || rounds_of_128 == 1) simple(gemm_bf16_kernel<4, 4, 2, 2, 1, 2, false>, 128, 128, 256, false);
+        else simple(gemm_bf16_kernel<2, 4, 4, 2, 1, 2, false>, 128, 128, 512, true);
         return;
     }
     int best = 0;

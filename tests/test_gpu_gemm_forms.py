@@ -26,7 +26,9 @@ SHAPES = [(2816, 5120, 256), (4736, 2944, 256),                          # 256 x
           (384, 768, 1408), (256, 1536, 2048 + 64),                      # 32 x 64, K split in four
           (384, 256, 2048 + 64), (128, 128, 1024), (512, 512, 1664), (128, 640, 1152),     # 32 x 32, K split in four
           (4480, 1408, 256), (2304, 1152, 192), (1152, 1024, 192),       # the order left to the compiler
-          (128, 128, 64), (384, 640, 64), (640, 1664, 128), (1408, 640, 192), (1920, 896, 64), (2176, 3200, 64)]     # strips of 1 to 7 rows of tiles
+          (128, 128, 64), (384, 640, 64), (640, 1664, 128), (1408, 640, 192), (1920, 896, 64), (2176, 3200, 64),     # strips of 1 to 7 rows of tiles
+          (1024, 3072, 64), (128, 25088, 128), (1664, 3584, 192), (3072, 4096, 64),        # K to 192: the most tiles of 64 x 64; 64 x 128
+          (3072, 2176, 192), (2048, 4096, 64), (2944, 4736, 128), (3072, 4224, 192)]       # 128 x 128, four waves and eight
 
 
 @pytest.mark.parametrize("m,n,k", SHAPES)
