@@ -54,8 +54,11 @@ static int restore_body(ckpt_ctx *c, int fd, const char *path, hipStream_t strea
     if (p.n_direct)   // these copies write the tensors themselves
         for (size_t k = 0; k < nk; k++) HIP_TRY(c, hipStreamWaitEvent(c->dma[k], c->ev_user, 0));
 
-    const uint64_t piece_bytes = std::min<uint64_t>(c->cfg.o_direct ? kPieceBytes : kReadPieceBytes, CH / 8);   // CH is a multiple of 32 KiB: 4 KiB multiples
-    const uint64_t send_pieces = std::max<uint64_t>(kSendBytes / piece_bytes, 1);
+    // Chunks of more than 64 MiB but the first two and the last: large pieces again, as they mostly go on as a whole (below).
+    auto in_between = [&](uint64_t ch) { return CH > 4 * kPartBytes && ch >= 2 && ch + 1 < p.n_chunks; };
+    auto piece_of = [&](uint64_t ch) {       // CH is a multiple of 32 KiB: 4 KiB multiples
+        return std::min<uint64_t>(c->cfg.o_direct || in_between(ch) ? kPieceBytes : kReadPieceBytes, CH / 8);
+    };
     uint64_t sends = 0;             // copies enqueued, for the copy streams in turn
     // A large chunk is sent on as its pieces arrive, over the copy streams in turn (one alone would lose time between the
     // copies); a small one as a whole, on one stream, whose event is then the only one to be recorded and waited for.
@@ -69,7 +72,7 @@ static int restore_body(ckpt_ctx *c, int fd, const char *path, hipStream_t strea
                 for (size_t k = 0; k < nk; k++)
                     if (sent_on(issued - c->n_slots, k)) HIP_TRY(c, hipEventSynchronize(c->ev_sent[k][slot]));   // previous chunk's copies out of the slot
             // a chunk is read in pieces, spread over the I/O threads
-            const uint64_t nbytes = p.chunk_bytes(issued), n_pieces = (nbytes + piece_bytes - 1) / piece_bytes;
+            const uint64_t nbytes = p.chunk_bytes(issued), piece_bytes = piece_of(issued), n_pieces = (nbytes + piece_bytes - 1) / piece_bytes;
             {
                 std::lock_guard<std::mutex> lk(c->mu);
                 c->slot_state[slot] = SLOT_BUSY;
@@ -103,7 +106,14 @@ static int restore_body(ckpt_ctx *c, int fd, const char *path, hipStream_t strea
             if (r != CKPT_OK) return r;
             const uint64_t slot = (base + ch) % c->n_slots;
             const uint8_t *slot_base = c->ring + slot * CH;
-            const uint64_t nbytes = p.chunk_bytes(ch);
+            const uint64_t nbytes = p.chunk_bytes(ch), piece_bytes = piece_of(ch), send_pieces = std::max<uint64_t>(kSendBytes / piece_bytes, 1);
+            // A chunk of more than 64 MiB behind which there are others goes as a whole while the copies before it keep the link
+            // busy: every copy costs the link some ten microseconds under some runtimes (40 GB in runs of 16 MiB 54.0 GB/s, in whole chunks 55.6).
+            bool whole = !in_pieces;
+            if (in_pieces && in_between(ch)) {
+                whole = hipEventQuery(c->ev_sent[(sends - 1) % nk][(base + ch - 1) % c->n_slots]) != hipSuccess;
+                if (whole) (void)hipGetLastError();   // "not ready" is no error of a later call
+            }
             uint64_t sent = 0, seg = p.chunk_first_seg[ch];
             while (sent < nbytes) {
                 uint64_t ready = nbytes;
@@ -119,7 +129,7 @@ static int restore_body(ckpt_ctx *c, int fd, const char *path, hipStream_t strea
                     // (at the ends little, as the link or the caller waits for it; in between more, to have the link busy while
                     // this thread reads)
                     const uint64_t enough = ch == 0 && sent == 0 ? 1 : ch < 2 || ch + 1 == p.n_chunks ? send_pieces : 4 * send_pieces;
-                    auto can_go_on = [&] { return c->slot_state[slot] == SLOT_READ_DONE || (in_pieces && pieces_ready() >= enough); };
+                    auto can_go_on = [&] { return c->slot_state[slot] == SLOT_READ_DONE || (!whole && pieces_ready() >= enough); };
                     // A file that is read more slowly than the link moves data is the rule (one thread reads 15 GB/s): while
                     // it has nothing to send, this thread reads too, except for direct I/O, which needs a buffer of its own.
                     while (!can_go_on() && !c->async_code && !c->cfg.o_direct && !c->io_q.empty() && c->io_q.front().kind == IoJob::READ) {
@@ -132,7 +142,7 @@ static int restore_body(ckpt_ctx *c, int fd, const char *path, hipStream_t strea
                     c->cv_state.wait(lk, [&] { return can_go_on() || c->async_code; });
                     if (c->async_code) { g_last_error = c->async_err; return c->async_code; }
                     // not too much, or one stream would have the link for itself for long
-                    if (in_pieces) ready = std::min(nbytes, sent + std::min(pieces_ready(), 4 * send_pieces) * piece_bytes);
+                    if (!whole) ready = std::min(nbytes, sent + std::min(pieces_ready(), 4 * send_pieces) * piece_bytes);
                 }
                 const size_t k = in_pieces ? sends++ % nk : ch % nk;
                 // the parts of the chunk's segments that lie in [sent, ready)

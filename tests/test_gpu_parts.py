@@ -57,3 +57,31 @@ def test_snapshots_and_restore(tmp_path, sizes, chunk, options):
         assert all(np.array_equal(a, b) for a, b in zip(wants[6], gu.readback_all(shard)))
     ck.destroy()
     shard.free()
+
+
+def test_many_chunks_of_more_than_64_mib(tmp_path):
+    """Eight chunks of 72 MiB: the last ones are not shared, and a restore sends those in between as a whole while the link is busy."""
+    print("eight chunks of 72 MiB", flush=True)
+    sizes = [200 * MIB + 5, 3, 150 * MIB, 180 * MIB + 4097]
+    tensors, off = [], 0
+    for k, n in enumerate(sizes):
+        tensors.append(shards.TensorSpec(f"t{k}", shards.U8, (n,), buffer=0, offset=off, role="raw"))
+        off += n + 2 * k + 1
+    shard = harness.DeviceShard(shards.ShardSpec("parts", 4, tensors, flat_buffers=[(off + 255) // 256 * 256]))
+    stream = harness.Stream()
+    ck = B.Checkpointer(B.make_config(out_dir=str(tmp_path), dma_chunk_bytes=72 * MIB, pack_superchunk_bytes=144 * MIB, host_ring_bytes=288 * MIB))
+    ck.register_tensors(shard.descs())
+    shard.fill_device(stream)
+    ck.snapshot_async(1, stream.cuda_stream)
+    ck.wait_immutable_window_end(stream.cuda_stream)
+    stream.synchronize()
+    want = gu.readback_all(shard)
+    ck.flush(1)
+    assert oracle.compare_file(shard.oracle_tensors(want), 1, ck.file_name(1)) is None
+    for _ in range(2):
+        shard.poison()
+        assert ck.restore(ck.file_name(1), stream.cuda_stream) == 1
+        stream.synchronize()
+        assert all(np.array_equal(a, b) for a, b in zip(want, gu.readback_all(shard)))
+    ck.destroy()
+    shard.free()
