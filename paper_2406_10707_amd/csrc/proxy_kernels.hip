@@ -9,6 +9,9 @@
 #include <utility>
 
 #include "../../include/ckpt_proxy.h"
+#include "gemm_forms.hpp"
+
+using namespace dsllm;
 
 namespace {
 
@@ -478,107 +481,39 @@ __global__ __launch_bounds__(256) void gemm_bf16_256_kernel(const uint16_t *__re
 #endif
 }
 
-// Which kernel and tile: the one of these that is expected to be done first. Up to K = 192 it is the first lines of launch_gemm
-// that decide, as a product is then little more than a launch and the stores of C (the hand-made order's prologue costs 0.5 us
-// more than the other kernel's: 2432 x 4992 x 64 8.8 us against 10.0). 64 x 64 tiles as long as they are all under way at once,
-// three to a unit. Then what counts is how many rounds of blocks there are: a round of 64 x 128 tiles, three to a unit, is
-// three quarters of the data of one of 128 x 128, two to a unit, and takes about 0.8 of its time. Four waves a 128 x 128 tile in a single round
-// or with K = 64; else eight, in the XCDs' order, as panels are then read again by other rounds. Over 225 products
-// 2.9 % faster than 64 x 64, sixteen-wave 128 x 128 and four-wave 128 x 128 tiles by their number alone, and none slower:
-//   896 x 3456 x 64 4.76 -> 4.33         640 x 6784 x 64 5.76 -> 4.86      7040 x 1280 x 128 9.4 -> 8.2
-//   1792 x 7808 x 192 14.2 -> 12.8       3456 x 7808 x 192 26.1 -> 20.2
-//
-// What a form is expected to take, in us: `start`, and then for the compute unit with the most blocks, which takes them in
-// rounds of up to `together`, block[n - 1] + step[n - 1] * (K / 64) for every round of n; and for all blocks together, as a
-// full card clocks lower and shares memory, (spread_block + spread_step * (K / 64)) * blocks / 256. The figures are fitted to times
-// of every form on 560 products on an MI355X, M and N multiples of 128 up to 8192 and K of 64 up to 8192, each spread over the
-// logarithm of its range (32 x 32: on 75 of them): 2 to 3 % off in the mean, 4 to 9 % at the ninth decile. The choice by them is 1.1 % slower in the
-// mean than the best form for each product, and over 300 other products 14 % faster than a rule on the number of tiles over two 128 x 128, two
-// 64 x 64, one 32 x 64 kernel and 256 x 256 where both sizes are its multiples. Where that lost most:
-//   6272 x 7808 x 6592 685 -> 462 us     sizes not multiples of 256, formerly 128 x 128 for all
-//   1920 x 7936 x 3456 127 -> 76
-//   768 x 5632 x 3392 46 -> 34           a few 128 x 128 tiles more than there are units
-//   384 x 5248 x 960 12.1 -> 6.9
-//   1024 x 3072 x 768 10.0 -> 7.5        fewer 128 x 128 tiles than units: 128 x 96 fills them
-// WIDE once a panel of 256 rows passes 2 GiB (the offsets of a buffer load are 32 bits wide); the choice is the same there.
-struct GemmForm {
-    int rows, cols, together;
-    float start, block[3], step[3], spread_block, spread_step;
-
-    float expected(int m, int n, int k) const {
-        if (m < rows || n < cols) return INFINITY;
-        const float steps = float(k / 64), blocks = float(m / rows + (m % rows != 0)) * float(n / cols + (n % cols != 0));
-        const float per_unit = ceilf(blocks / 256), rounds = floorf(per_unit / float(together));
-        const int rest = int(per_unit - rounds * float(together));
-        float us = start + rounds * (block[together - 1] + step[together - 1] * steps) + (spread_block + spread_step * steps) * blocks / 256;
-        if (rest) us += block[rest - 1] + step[rest - 1] * steps;
-        return us;
-    }
-};
-const GemmForm kGemmForms[] = {     // in the order of launch_gemm's switch
-    {256, 256, 1, 2.43f, {3.90f, 0.00f, 0.00f}, {0.9122f, 0.0000f, 0.0000f}, 4.56f, 0.2758f},
-    {224, 256, 1, 1.94f, {3.93f, 0.00f, 0.00f}, {0.7984f, 0.0000f, 0.0000f}, 3.95f, 0.2545f},
-    {256, 192, 1, 1.71f, {3.74f, 0.00f, 0.00f}, {0.6975f, 0.0000f, 0.0000f}, 3.20f, 0.2218f},
-    {160, 256, 1, 1.24f, {3.91f, 0.00f, 0.00f}, {0.5994f, 0.0000f, 0.0000f}, 2.76f, 0.1911f},
-    {192, 128, 2, 2.94f, {1.14f, 2.09f, 0.00f}, {0.4599f, 0.8657f, 0.0000f}, 1.45f, 0.1007f},
-    {160, 128, 1, 1.35f, {2.72f, 0.00f, 0.00f}, {0.3502f, 0.0000f, 0.0000f}, 0.69f, 0.1319f},
-    {128, 128, 1, 1.26f, {2.39f, 0.00f, 0.00f}, {0.3033f, 0.0000f, 0.0000f}, 0.39f, 0.1069f},
-    {128, 128, 2, 2.56f, {0.84f, 1.66f, 0.00f}, {0.3865f, 0.6772f, 0.0000f}, 0.94f, 0.0625f},
-    {128, 96, 1, 1.28f, {1.93f, 0.00f, 0.00f}, {0.2641f, 0.0000f, 0.0000f}, 0.25f, 0.0856f},
-    {64, 128, 2, 1.75f, {1.02f, 1.53f, 0.00f}, {0.2244f, 0.4022f, 0.0000f}, 0.20f, 0.0705f},
-    {96, 64, 2, 1.73f, {1.01f, 1.32f, 0.00f}, {0.1853f, 0.3621f, 0.0000f}, 0.23f, 0.0407f},
-    {64, 64, 2, 1.80f, {0.67f, 0.89f, 0.00f}, {0.1494f, 0.2870f, 0.0000f}, 0.18f, 0.0281f},
-    {64, 64, 3, 2.07f, {0.17f, 0.58f, 1.24f}, {0.1521f, 0.2266f, 0.3086f}, 0.00f, 0.0740f},
-    {32, 64, 1, 1.37f, {1.66f, 0.00f, 0.00f}, {0.1244f, 0.0000f, 0.0000f}, 0.17f, 0.0134f},
-    {32, 32, 1, 1.25f, {1.74f, 0.00f, 0.00f}, {0.0820f, 0.0000f, 0.0000f}, 0.08f, 0.0071f},
-    {128, 128, 2, 2.24f, {0.55f, 1.81f, 0.00f}, {0.5691f, 0.6548f, 0.0000f}, 0.76f, 0.1264f},
-};
-
 template <bool WIDE>
 void launch_gemm(const uint16_t *a, const uint16_t *b, uint16_t *c, int m, int n, int k, hipStream_t stream) {
+    const int choice = gemm_form(m, n, k);
+    const GemmForm &form = kGemmForms[choice];
+    const unsigned tm = form.tiles_m(m), tn = form.tiles_n(n);
     // `simple`: the kernels whose order is the compiler's; `by_xcd`: see TileOrder
-    auto tiles = [](int size, int tile) { return (unsigned(size) + unsigned(tile) - 1) / unsigned(tile); };
-    auto simple = [&](auto kernel, int rows, int cols, int threads, bool by_xcd) {
-        const unsigned tm = tiles(m, rows), tn = tiles(n, cols);
-        hipLaunchKernelGGL(kernel, dim3(tm * tn), dim3(threads), 0, stream, a, b, c, n, k, TileOrder(tm, tn, by_xcd));
+    auto simple = [&](auto kernel, bool by_xcd) {
+        hipLaunchKernelGGL(kernel, dim3(tm * tn), dim3(form.threads), 0, stream, a, b, c, n, k, TileOrder(tm, tn, by_xcd));
     };
-    auto go = [&](auto kernel, int rows, int cols) {
-        const unsigned tm = tiles(m, rows), tn = tiles(n, cols);
-        hipLaunchKernelGGL(kernel, dim3(tm * tn), dim3(256), 0, stream, a, b, c, m, n, k, TileOrder(tm, tn, true));
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(tm * tn), dim3(form.threads), 0, stream, a, b, c, m, n, k, TileOrder(tm, tn, true));
     };
-    if (!WIDE && k <= 192) {
-        const int64_t n64 = int64_t(m / 64) * (n / 64);
-        const int64_t rounds_of_half = (n64 / 2 + 3 * 256 - 1) / (3 * 256), rounds_of_128 = (n64 / 4 + 2 * 256 - 1) / (2 * 256);
-        if (n64 <= 3 * 256) simple(gemm_bf16_kernel<2, 2, 2, 2, 1, 3, false>, 64, 64, 256, false);
-        else if (4 * rounds_of_half <= 5 * rounds_of_128) simple(gemm_bf16_kernel<2, 4, 2, 2, 1, 2, false>, 64, 128, 256, false);
-        else if (k == 64 || rounds_of_128 == 1) simple(gemm_bf16_kernel<4, 4, 2, 2, 1, 2, false>, 128, 128, 256, false);
-        else simple(gemm_bf16_kernel<2, 4, 4, 2, 1, 2, false>, 128, 128, 512, true);
-        return;
-    }
-    int best = 0;
-    float us = kGemmForms[0].expected(m, n, k);
-    for (int f = 1; f < int(sizeof kGemmForms / sizeof kGemmForms[0]); f++) {
-        const float t = kGemmForms[f].expected(m, n, k);
-        if (t < us) { us = t; best = f; }
-    }
-    const GemmForm &form = kGemmForms[best];
-    switch (best) {
-        case 0: go(gemm_bf16_256_kernel<WIDE>, form.rows, form.cols); break;
-        case 1: go(gemm_bf16_tile_kernel<1, 2, 2, 7, 8, 2, 2, 4, WIDE>, form.rows, form.cols); break;
-        case 2: go(gemm_bf16_tile_kernel<1, 2, 2, 8, 6, 2, 2, 4, WIDE>, form.rows, form.cols); break;
-        case 3: go(gemm_bf16_tile_kernel<1, 2, 2, 5, 8, 3, 2, 4, WIDE>, form.rows, form.cols); break;
-        case 4: go(gemm_bf16_tile_kernel<2, 2, 2, 6, 4, 2, 1, 2, WIDE>, form.rows, form.cols); break;
-        case 5: go(gemm_bf16_tile_kernel<1, 2, 2, 5, 4, 3, 1, 4, WIDE>, form.rows, form.cols); break;
-        case 6: go(gemm_bf16_tile_kernel<1, 2, 2, 4, 4, 3, 1, 4, WIDE>, form.rows, form.cols); break;
-        case 7: go(gemm_bf16_tile_kernel<2, 2, 2, 4, 4, 2, -2, 1, WIDE>, form.rows, form.cols); break;
-        case 8: go(gemm_bf16_tile_kernel<1, 4, 1, 2, 6, 3, 1, 3, WIDE>, form.rows, form.cols); break;
-        case 9: go(gemm_bf16_tile_kernel<2, 2, 2, 2, 4, 3, 1, 2, WIDE>, form.rows, form.cols); break;
-        case 10: go(gemm_bf16_tile_kernel<2, 2, 2, 3, 2, 4, -2, 1, WIDE>, form.rows, form.cols); break;
-        case 11: go(gemm_bf16_tile_kernel<2, 2, 2, 2, 2, 4, -2, 1, WIDE>, form.rows, form.cols); break;
-        case 12: go(gemm_bf16_tile_kernel<3, 2, 2, 2, 2, 3, -2, 1, WIDE>, form.rows, form.cols); break;
-        case 13: simple(gemm_bf16_kernel<1, 2, 2, 2, 4, 3, WIDE>, form.rows, form.cols, 1024, true); break;
-        case 14: simple(gemm_bf16_kernel<1, 1, 2, 2, 4, 3, WIDE>, form.rows, form.cols, 1024, true); break;
-        default: simple(gemm_bf16_kernel<4, 4, 2, 2, 1, 2, WIDE>, form.rows, form.cols, 256, false); break;
+    switch (choice) {
+        case 0: go(gemm_bf16_256_kernel<WIDE>); break;
+        case 1: go(gemm_bf16_tile_kernel<1, 2, 2, 7, 8, 2, 2, 4, WIDE>); break;
+        case 2: go(gemm_bf16_tile_kernel<1, 2, 2, 8, 6, 2, 2, 4, WIDE>); break;
+        case 3: go(gemm_bf16_tile_kernel<1, 2, 2, 5, 8, 3, 2, 4, WIDE>); break;
+        case 4: go(gemm_bf16_tile_kernel<2, 2, 2, 6, 4, 2, 1, 2, WIDE>); break;
+        case 5: go(gemm_bf16_tile_kernel<1, 2, 2, 5, 4, 3, 1, 4, WIDE>); break;
+        case 6: go(gemm_bf16_tile_kernel<1, 2, 2, 4, 4, 3, 1, 4, WIDE>); break;
+        case 7: go(gemm_bf16_tile_kernel<2, 2, 2, 4, 4, 2, -2, 1, WIDE>); break;
+        case 8: go(gemm_bf16_tile_kernel<1, 4, 1, 2, 6, 3, 1, 3, WIDE>); break;
+        case 9: go(gemm_bf16_tile_kernel<2, 2, 2, 2, 4, 3, 1, 2, WIDE>); break;
+        case 10: go(gemm_bf16_tile_kernel<2, 2, 2, 3, 2, 4, -2, 1, WIDE>); break;
+        case 11: go(gemm_bf16_tile_kernel<2, 2, 2, 2, 2, 4, -2, 1, WIDE>); break;
+        case 12: go(gemm_bf16_tile_kernel<3, 2, 2, 2, 2, 3, -2, 1, WIDE>); break;
+        case 13: simple(gemm_bf16_kernel<1, 2, 2, 2, 4, 3, WIDE>, true); break;
+        case 14: simple(gemm_bf16_kernel<1, 1, 2, 2, 4, 3, WIDE>, true); break;
+        case 15: simple(gemm_bf16_kernel<4, 4, 2, 2, 1, 2, WIDE>, false); break;
+        // K up to 192
+        case 16: if constexpr (!WIDE) simple(gemm_bf16_kernel<2, 2, 2, 2, 1, 3, false>, false); break;
+        case 17: if constexpr (!WIDE) simple(gemm_bf16_kernel<2, 4, 2, 2, 1, 2, false>, false); break;
+        default: if constexpr (!WIDE) simple(gemm_bf16_kernel<2, 4, 4, 2, 1, 2, false>, true); break;
     }
 }
 
@@ -597,7 +532,7 @@ extern "C" {
 int proxy_gemm_bf16(const void *a, const void *b, void *c, int32_t m, int32_t n, int32_t k, void *stream) {
     if (!a || !b || !c || m <= 0 || n <= 0 || k <= 0 || m % 128 || n % 128 || k % 64) return -1;
     if ((uint64_t(a) | uint64_t(b) | uint64_t(c)) & 15) return -1;
-    const auto launch = k > (1 << 22) ? launch_gemm<true> : launch_gemm<false>;
+    const auto launch = gemm_wide(k) ? launch_gemm<true> : launch_gemm<false>;
     launch(static_cast<const uint16_t *>(a), static_cast<const uint16_t *>(b), static_cast<uint16_t *>(c), m, n, k, static_cast<hipStream_t>(stream));
     return hip_rc();
 }

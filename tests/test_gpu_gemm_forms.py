@@ -11,27 +11,33 @@ from tests import gpu_util as gu
 
 pytestmark = pytest.mark.gpu
 
-SHAPES = [(2816, 5120, 256), (4736, 2944, 256),                          # 256 x 256
-          (4480, 2816, 256), (3328, 3840, 256), (2816, 4480, 320),       # 224 x 256
-          (2048, 4992, 256), (3072, 3200, 320), (2176, 4736, 320),       # 256 x 192
-          (2560, 3328, 256), (4736, 1792, 320), (2432, 3456, 256),       # 160 x 256
-          (1152, 4224, 256), (2944, 1792, 320),                          # 192 x 128, two to a unit
-          (2560, 1664, 256), (4736, 896, 320),                           # 160 x 128
-          (4992, 640, 256), (640, 4992, 320),                            # 128 x 128
-          (4480, 1408, 448),                                             # 128 x 128, two to a unit
-          (2816, 768, 256), (1664, 1280, 320),                           # 128 x 96
-          (512, 2816, 320), (512, 2816, 448),                            # 64 x 128
-          (768, 1408, 256), (640, 1664, 320),                            # 96 x 64
-          (128, 1664, 1472), (128, 128, 256), (256, 384, 320),           # 64 x 64, two and three to a unit
-          (384, 768, 1408), (256, 1536, 2048 + 64),                      # 32 x 64, K split in four
-          (384, 256, 2048 + 64), (128, 128, 1024), (512, 512, 1664), (128, 640, 1152),     # 32 x 32, K split in four
-          (4480, 1408, 256), (2304, 1152, 192), (1152, 1024, 192),       # the order left to the compiler
-          (128, 128, 64), (384, 640, 64), (640, 1664, 128), (1408, 640, 192), (1920, 896, 64), (2176, 3200, 64),     # strips of 1 to 7 rows of tiles
-          (1024, 3072, 64), (128, 25088, 128), (1664, 3584, 192), (3072, 4096, 64),        # K to 192: the most tiles of 64 x 64; 64 x 128
-          (3072, 2176, 192), (2048, 4096, 64), (2944, 4736, 128), (3072, 4224, 192)]       # 128 x 128, four waves and eight
+# by the form that they take (tests/test_host_gemm_forms.py asks the choice itself)
+FORMS = {
+    "256x256": [(2816, 5120, 256), (4736, 2944, 256), (2816, 5120, 1472)],
+    "224x256": [(4480, 2816, 256), (3328, 3840, 256), (2816, 4480, 320)],
+    "256x192": [(2048, 4992, 256), (3072, 3200, 320), (2176, 4736, 320)],
+    "160x256": [(2560, 3328, 256), (4736, 1792, 320), (2432, 3456, 256)],
+    "192x128 by 2": [(1152, 4224, 256), (2944, 1792, 320)],
+    "160x128": [(2560, 1664, 256), (4736, 896, 320)],
+    "128x128": [(4992, 640, 256), (640, 4992, 320)],
+    "128x128 by 2": [(4480, 1408, 448)],
+    "128x96": [(2816, 768, 256), (1664, 1280, 320)],
+    "64x128 by 2": [(512, 2816, 320), (512, 2816, 448)],
+    "96x64 by 2": [(768, 1408, 256), (640, 1664, 320)],
+    "64x64 by 2": [(384, 768, 1408), (640, 1408, 1088)],
+    "64x64 by 3": [(128, 128, 256), (256, 384, 320)],
+    "32x64 K/4": [(256, 1536, 2048 + 64)],
+    "32x32 K/4": [(384, 256, 2048 + 64), (128, 128, 1024), (512, 512, 1664), (128, 640, 1152), (128, 1664, 1472)],
+    # the order left to the compiler, four waves a tile: a few steps of K, and up to K = 192 a single round of blocks or K = 64
+    "128x128 compiled": [(4480, 1408, 256), (2176, 3200, 64), (3072, 2176, 192), (2048, 4096, 64)],
+    # K up to 192; strips of 1 to 7 rows of tiles; the most tiles of 64 x 64
+    "64x64 short": [(2304, 1152, 192), (1152, 1024, 192), (128, 128, 64), (384, 640, 64), (640, 1664, 128), (1408, 640, 192), (1920, 896, 64), (1024, 3072, 64)],
+    "64x128 short": [(128, 25088, 128), (1664, 3584, 192), (3072, 4096, 64)],
+    "128x128 short, eight waves": [(2944, 4736, 128), (3072, 4224, 192)],
+}
 
 
-@pytest.mark.parametrize("m,n,k", SHAPES)
+@pytest.mark.parametrize("m,n,k", [shape for shapes in FORMS.values() for shape in shapes])
 def test_gemm_form_against_float64(m, n, k):
     print(f"gemm {m}x{n}x{k}", flush=True)
     rng = np.random.default_rng(m + 3 * n + 7 * k)

@@ -1,5 +1,6 @@
-"""Every kernel and tile the proxy's GEMM chooses among, at the edges of its range (fewest steps of K, an odd number of
-them, steps that only some groups of waves have, an odd number of tiles), against the float64 product."""
+"""The proxy's GEMM over its range (the fewest steps of K, an odd number of them, steps that only some groups of waves have, an
+odd number of tiles, a long K, many tiles of a flat C), against the float64 product. Every form that it chooses among:
+test_gpu_gemm_forms.py."""
 import numpy as np
 import pytest
 
@@ -10,12 +11,12 @@ from tests import gpu_util as gu
 
 pytestmark = pytest.mark.gpu
 
-SHAPES = [(3072, 4096, 256), (3072, 4096, 320), (4096, 3328, 448),       # 256 x 256 tiles
-          (2176, 2048, 64), (2176, 2048, 192), (128, 67328, 128),        # 128 x 128, two blocks per unit
-          (1536, 2048, 64), (1664, 1920, 320), (2432, 3456, 16384),      # 128 x 128, sixteen waves
-          (1152, 1024, 64), (1024, 1152, 576), (128, 128, 64), (256, 128, 448),     # 64 x 64
-          (640, 1280, 512), (1024, 1024, 576), (640, 1408, 1088),        # 64 x 64, K split in two
-          (128, 128, 512), (256, 384, 576), (512, 1024, 640), (128, 256, 704)]      # 32 x 64, K split in four
+SHAPES = [(3072, 4096, 256), (3072, 4096, 320), (4096, 3328, 448),       # about 200 and more of the largest tiles
+          (2176, 2048, 64), (2176, 2048, 192), (128, 67328, 128),        # more 64 x 64 tiles than are under way at once, short K
+          (1536, 2048, 64), (1664, 1920, 320), (2432, 3456, 16384),
+          (1152, 1024, 64), (1024, 1152, 576), (128, 128, 64), (256, 128, 448),     # fewer tiles
+          (640, 1280, 512), (1024, 1024, 576), (640, 1408, 1088),
+          (128, 128, 512), (256, 384, 576), (512, 1024, 640), (128, 256, 704)]      # a small C
 
 
 @pytest.mark.parametrize("m,n,k", SHAPES)

@@ -1,0 +1,32 @@
+"""Which form the proxy's GEMM takes, asked of the choice itself (csrc/gemm_forms.hpp): the shapes of the GPU tests take the
+forms that they stand for, and there is one for every form."""
+import os
+import re
+import subprocess
+
+import pytest
+
+from tests.test_gpu_gemm_forms import FORMS
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def forms(tmp_path_factory):
+    """forms(shapes) -> [(name, blocks, threads of a block)]"""
+    exe = str(tmp_path_factory.mktemp("forms") / "gemm_form")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-o", exe, os.path.join(ROOT, "tests", "emu", "gemm_form.cpp")], check=True)
+
+    def ask(shapes):
+        out = subprocess.run([exe], input="".join("%d %d %d\n" % s for s in shapes), capture_output=True, text=True, check=True).stdout
+        return [(name, int(blocks), int(threads)) for name, blocks, threads in (line.rsplit(",", 2) for line in out.splitlines())]
+
+    return ask
+
+
+def test_every_form_has_shapes_that_take_it(forms):
+    with open(os.path.join(ROOT, "paper_2406_10707_amd", "csrc", "gemm_forms.hpp")) as f:
+        names = re.findall(r'^    \{"([^"]+)", ', f.read(), re.M)
+    assert len(names) == 19 and names == list(FORMS)
+    for name, shapes in FORMS.items():
+        assert shapes and [taken for taken, _, _ in forms(shapes)] == [name] * len(shapes)
