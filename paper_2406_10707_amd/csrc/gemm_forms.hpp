@@ -78,7 +78,8 @@ inline int gemm_form(int m, int n, int k) {
         const int64_t rounds_of_half = (n64 / 2 + 3 * 256 - 1) / (3 * 256), rounds_of_128 = (n64 / 4 + 2 * 256 - 1) / (2 * 256);
         if (n64 <= 3 * 256) return 16;
         if (4 * rounds_of_half <= 5 * rounds_of_128) return 17;
-        return k == 64 || rounds_of_128 == 1 ? 15 : 18;
+        // (eight waves a tile only where the grid has fewer than 2^32 work-items, as it must: below 2^37 elements of C)
+        return k == 64 || rounds_of_128 == 1 || n64 / 4 >= 1 << 23 ? 15 : 18;
     }
     int best = 0;
     float us = kGemmForms[0].expected(m, n, k);

@@ -30,3 +30,17 @@ def test_every_form_has_shapes_that_take_it(forms):
     assert len(names) == 19 and names == list(FORMS)
     for name, shapes in FORMS.items():
         assert shapes and [taken for taken, _, _ in forms(shapes)] == [name] * len(shapes)
+
+
+@pytest.mark.parametrize("k", [64, 128, 192, 256, 320, 1024])
+def test_a_grid_has_fewer_work_items_than_32_bits_count(forms, k):
+    """Up to a C of 288 GB, square and flat."""
+    shapes = []
+    for rows in (128, 1 << 14, 1 << 16, 1 << 18, 128 * 2897):
+        for elements in (1 << 35, 1 << 36, (1 << 37) - (1 << 30), 1 << 37, 144 * 10 ** 9):
+            cols = -(-elements // rows // 128) * 128
+            if cols < 1 << 31:
+                shapes.append((rows, cols, k))
+    assert len(shapes) >= 20
+    for shape, (name, blocks, threads) in zip(shapes, forms(shapes)):
+        assert blocks * threads < 1 << 32, (shape, name)
