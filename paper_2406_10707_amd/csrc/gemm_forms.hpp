@@ -27,10 +27,13 @@ namespace dsllm {
 //   768 x 5632 x 3392 46 -> 34           a few 128 x 128 tiles more than there are units
 //   384 x 5248 x 960 12.1 -> 6.9
 //   1024 x 3072 x 768 10.0 -> 7.5        fewer 128 x 128 tiles than units: 128 x 96 fills them
-// WIDE once a panel of 256 rows passes 2 GiB (the offsets of a buffer load are 32 bits wide); the choice is the same there.
+// WIDE once a panel of 256 rows passes 2 GiB (the offsets of a buffer load are 32 bits wide). The choice is the same there, but for
+// three forms, which aren't built for it: two were never chosen, and 128 x 128 by 2 for ten pairs of sizes among those whose
+// operands fit the card (20608..21760 x 384; 20608 x 384 takes 122 to 127 ms with it and 123 to 130 without).
 struct GemmForm {
     const char *name;        // tile; "by n": n blocks share a compute unit
     int rows, cols, threads, together;
+    bool wide;               // built for K above 2^22 too
     float start, block[3], step[3], spread_block, spread_step;
 
     unsigned tiles_m(int m) const { return (unsigned(m) + unsigned(rows) - 1) / unsigned(rows); }
@@ -46,26 +49,26 @@ struct GemmForm {
     }
 };
 constexpr GemmForm kGemmForms[] = {     // in the order of launch_gemm's switch
-    {"256x256", 256, 256, 256, 1, 2.43f, {3.90f, 0.00f, 0.00f}, {0.9122f, 0.0000f, 0.0000f}, 4.56f, 0.2758f},
-    {"224x256", 224, 256, 256, 1, 1.94f, {3.93f, 0.00f, 0.00f}, {0.7984f, 0.0000f, 0.0000f}, 3.95f, 0.2545f},
-    {"256x192", 256, 192, 256, 1, 1.71f, {3.74f, 0.00f, 0.00f}, {0.6975f, 0.0000f, 0.0000f}, 3.20f, 0.2218f},
-    {"160x256", 160, 256, 256, 1, 1.24f, {3.91f, 0.00f, 0.00f}, {0.5994f, 0.0000f, 0.0000f}, 2.76f, 0.1911f},
-    {"192x128 by 2", 192, 128, 256, 2, 2.94f, {1.14f, 2.09f, 0.00f}, {0.4599f, 0.8657f, 0.0000f}, 1.45f, 0.1007f},
-    {"160x128", 160, 128, 256, 1, 1.35f, {2.72f, 0.00f, 0.00f}, {0.3502f, 0.0000f, 0.0000f}, 0.69f, 0.1319f},
-    {"128x128", 128, 128, 256, 1, 1.26f, {2.39f, 0.00f, 0.00f}, {0.3033f, 0.0000f, 0.0000f}, 0.39f, 0.1069f},
-    {"128x128 by 2", 128, 128, 256, 2, 2.56f, {0.84f, 1.66f, 0.00f}, {0.3865f, 0.6772f, 0.0000f}, 0.94f, 0.0625f},
-    {"128x96", 128, 96, 256, 1, 1.28f, {1.93f, 0.00f, 0.00f}, {0.2641f, 0.0000f, 0.0000f}, 0.25f, 0.0856f},
-    {"64x128 by 2", 64, 128, 256, 2, 1.75f, {1.02f, 1.53f, 0.00f}, {0.2244f, 0.4022f, 0.0000f}, 0.20f, 0.0705f},
-    {"96x64 by 2", 96, 64, 256, 2, 1.73f, {1.01f, 1.32f, 0.00f}, {0.1853f, 0.3621f, 0.0000f}, 0.23f, 0.0407f},
-    {"64x64 by 2", 64, 64, 256, 2, 1.80f, {0.67f, 0.89f, 0.00f}, {0.1494f, 0.2870f, 0.0000f}, 0.18f, 0.0281f},
-    {"64x64 by 3", 64, 64, 256, 3, 2.07f, {0.17f, 0.58f, 1.24f}, {0.1521f, 0.2266f, 0.3086f}, 0.00f, 0.0740f},
-    {"32x64 K/4", 32, 64, 1024, 1, 1.37f, {1.66f, 0.00f, 0.00f}, {0.1244f, 0.0000f, 0.0000f}, 0.17f, 0.0134f},
-    {"32x32 K/4", 32, 32, 1024, 1, 1.25f, {1.74f, 0.00f, 0.00f}, {0.0820f, 0.0000f, 0.0000f}, 0.08f, 0.0071f},
-    {"128x128 compiled", 128, 128, 256, 2, 2.24f, {0.55f, 1.81f, 0.00f}, {0.5691f, 0.6548f, 0.0000f}, 0.76f, 0.1264f},
+    {"256x256", 256, 256, 256, 1, true, 2.43f, {3.90f, 0.00f, 0.00f}, {0.9122f, 0.0000f, 0.0000f}, 4.56f, 0.2758f},
+    {"224x256", 224, 256, 256, 1, true, 1.94f, {3.93f, 0.00f, 0.00f}, {0.7984f, 0.0000f, 0.0000f}, 3.95f, 0.2545f},
+    {"256x192", 256, 192, 256, 1, true, 1.71f, {3.74f, 0.00f, 0.00f}, {0.6975f, 0.0000f, 0.0000f}, 3.20f, 0.2218f},
+    {"160x256", 160, 256, 256, 1, true, 1.24f, {3.91f, 0.00f, 0.00f}, {0.5994f, 0.0000f, 0.0000f}, 2.76f, 0.1911f},
+    {"192x128 by 2", 192, 128, 256, 2, true, 2.94f, {1.14f, 2.09f, 0.00f}, {0.4599f, 0.8657f, 0.0000f}, 1.45f, 0.1007f},
+    {"160x128", 160, 128, 256, 1, true, 1.35f, {2.72f, 0.00f, 0.00f}, {0.3502f, 0.0000f, 0.0000f}, 0.69f, 0.1319f},
+    {"128x128", 128, 128, 256, 1, true, 1.26f, {2.39f, 0.00f, 0.00f}, {0.3033f, 0.0000f, 0.0000f}, 0.39f, 0.1069f},
+    {"128x128 by 2", 128, 128, 256, 2, false, 2.56f, {0.84f, 1.66f, 0.00f}, {0.3865f, 0.6772f, 0.0000f}, 0.94f, 0.0625f},
+    {"128x96", 128, 96, 256, 1, true, 1.28f, {1.93f, 0.00f, 0.00f}, {0.2641f, 0.0000f, 0.0000f}, 0.25f, 0.0856f},
+    {"64x128 by 2", 64, 128, 256, 2, true, 1.75f, {1.02f, 1.53f, 0.00f}, {0.2244f, 0.4022f, 0.0000f}, 0.20f, 0.0705f},
+    {"96x64 by 2", 96, 64, 256, 2, true, 1.73f, {1.01f, 1.32f, 0.00f}, {0.1853f, 0.3621f, 0.0000f}, 0.23f, 0.0407f},
+    {"64x64 by 2", 64, 64, 256, 2, true, 1.80f, {0.67f, 0.89f, 0.00f}, {0.1494f, 0.2870f, 0.0000f}, 0.18f, 0.0281f},
+    {"64x64 by 3", 64, 64, 256, 3, false, 2.07f, {0.17f, 0.58f, 1.24f}, {0.1521f, 0.2266f, 0.3086f}, 0.00f, 0.0740f},
+    {"32x64 K/4", 32, 64, 1024, 1, true, 1.37f, {1.66f, 0.00f, 0.00f}, {0.1244f, 0.0000f, 0.0000f}, 0.17f, 0.0134f},
+    {"32x32 K/4", 32, 32, 1024, 1, true, 1.25f, {1.74f, 0.00f, 0.00f}, {0.0820f, 0.0000f, 0.0000f}, 0.08f, 0.0071f},
+    {"128x128 compiled", 128, 128, 256, 2, false, 2.24f, {0.55f, 1.81f, 0.00f}, {0.5691f, 0.6548f, 0.0000f}, 0.76f, 0.1264f},
     // up to K = 192 only: no model
-    {"64x64 short", 64, 64, 256, 3, INFINITY, {}, {}, 0, 0},
-    {"64x128 short", 64, 128, 256, 3, INFINITY, {}, {}, 0, 0},
-    {"128x128 short, eight waves", 128, 128, 512, 2, INFINITY, {}, {}, 0, 0},
+    {"64x64 short", 64, 64, 256, 3, false, INFINITY, {}, {}, 0, 0},
+    {"64x128 short", 64, 128, 256, 3, false, INFINITY, {}, {}, 0, 0},
+    {"128x128 short, eight waves", 128, 128, 512, 2, false, INFINITY, {}, {}, 0, 0},
 };
 constexpr int kModelledForms = 16;
 
@@ -84,6 +87,7 @@ inline int gemm_form(int m, int n, int k) {
     int best = 0;
     float us = kGemmForms[0].expected(m, n, k);
     for (int f = 1; f < kModelledForms; f++) {
+        if (gemm_wide(k) && !kGemmForms[f].wide) continue;
         const float t = kGemmForms[f].expected(m, n, k);
         if (t < us) { us = t; best = f; }
     }

@@ -501,16 +501,16 @@ void launch_gemm(const uint16_t *a, const uint16_t *b, uint16_t *c, int m, int n
         case 4: go(gemm_bf16_tile_kernel<2, 2, 2, 6, 4, 2, 1, 2, WIDE>); break;
         case 5: go(gemm_bf16_tile_kernel<1, 2, 2, 5, 4, 3, 1, 4, WIDE>); break;
         case 6: go(gemm_bf16_tile_kernel<1, 2, 2, 4, 4, 3, 1, 4, WIDE>); break;
-        case 7: go(gemm_bf16_tile_kernel<2, 2, 2, 4, 4, 2, -2, 1, WIDE>); break;
+        case 7: if constexpr (!WIDE) go(gemm_bf16_tile_kernel<2, 2, 2, 4, 4, 2, -2, 1, false>); break;
         case 8: go(gemm_bf16_tile_kernel<1, 4, 1, 2, 6, 3, 1, 3, WIDE>); break;
         case 9: go(gemm_bf16_tile_kernel<2, 2, 2, 2, 4, 3, 1, 2, WIDE>); break;
         case 10: go(gemm_bf16_tile_kernel<2, 2, 2, 3, 2, 4, -2, 1, WIDE>); break;
         case 11: go(gemm_bf16_tile_kernel<2, 2, 2, 2, 2, 4, -2, 1, WIDE>); break;
-        case 12: go(gemm_bf16_tile_kernel<3, 2, 2, 2, 2, 3, -2, 1, WIDE>); break;
+        case 12: if constexpr (!WIDE) go(gemm_bf16_tile_kernel<3, 2, 2, 2, 2, 3, -2, 1, false>); break;
         case 13: simple(gemm_bf16_kernel<1, 2, 2, 2, 4, 3, WIDE>, true); break;
         case 14: simple(gemm_bf16_kernel<1, 1, 2, 2, 4, 3, WIDE>, true); break;
-        case 15: simple(gemm_bf16_kernel<4, 4, 2, 2, 1, 2, WIDE>, false); break;
-        // K up to 192
+        case 15: if constexpr (!WIDE) simple(gemm_bf16_kernel<4, 4, 2, 2, 1, 2, false>, false); break;
+        // up to K = 192
         case 16: if constexpr (!WIDE) simple(gemm_bf16_kernel<2, 2, 2, 2, 1, 3, false>, false); break;
         case 17: if constexpr (!WIDE) simple(gemm_bf16_kernel<2, 4, 2, 2, 1, 2, false>, false); break;
         default: if constexpr (!WIDE) simple(gemm_bf16_kernel<2, 4, 4, 2, 1, 2, false>, true); break;

@@ -73,12 +73,30 @@ def test_gemm_with_rows_beyond_32_bit_offsets():
         x.free()
 
 
-# one shape for every kernel and tile, as above, with the fewest tiles of its range
-@pytest.mark.parametrize("m,n", [(3072, 4096), (2176, 2048), (1536, 2048), (1152, 1024), (640, 1280), (256, 384)])
+# with 64-bit addresses, by the form that they take (tests/test_host_gemm_forms.py asks the choice itself)
+WIDE_K = (1 << 22) + 64
+WIDE_FORMS = {
+    "256x256": [(3840, 3712)],
+    "224x256": [(3072, 4096)],
+    "256x192": [(3072, 3200)],
+    "160x256": [(2432, 2560)],
+    "192x128 by 2": [(1792, 2816)],
+    "160x128": [(2176, 2048)],
+    "128x128": [(1536, 2048)],
+    "128x96": [(1280, 1664)],
+    "64x128 by 2": [(896, 1664)],
+    "96x64 by 2": [(1152, 1024)],
+    "64x64 by 2": [(640, 1280)],
+    "32x64 K/4": [(384, 768)],
+    "32x32 K/4": [(256, 384)],
+}
+
+
+@pytest.mark.parametrize("m,n", [shape for shapes in WIDE_FORMS.values() for shape in shapes])
 def test_gemm_tiles_with_rows_beyond_32_bit_offsets(m, n):
     """K past 2^22: rows of A and B are zero but for eight columns in each of a few places, that of the first, of the last
     and of an odd step of K among them."""
-    k = (1 << 22) + 64
+    k = WIDE_K
     print(f"gemm {m}x{n}x{k}", flush=True)
     rng = np.random.default_rng(m + n)
     at = [0, 5 * 64 + 24, (1 << 21) + 8, (1 << 22) - 8, (1 << 22) + 56]

@@ -7,6 +7,7 @@ import subprocess
 import pytest
 
 from tests.test_gpu_gemm_forms import FORMS
+from tests.test_gpu_gemm_shapes import WIDE_FORMS, WIDE_K
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -24,12 +25,29 @@ def forms(tmp_path_factory):
     return ask
 
 
-def test_every_form_has_shapes_that_take_it(forms):
+@pytest.fixture(scope="module")
+def table():
+    """[(name, built for 64-bit addresses too)]"""
     with open(os.path.join(ROOT, "paper_2406_10707_amd", "csrc", "gemm_forms.hpp")) as f:
-        names = re.findall(r'^    \{"([^"]+)", ', f.read(), re.M)
-    assert len(names) == 19 and names == list(FORMS)
+        return [(name, wide == "true") for name, wide in re.findall(r'^    \{"([^"]+)", \d+, \d+, \d+, \d, (true|false), ', f.read(), re.M)]
+
+
+def test_every_form_has_shapes_that_take_it(forms, table):
+    assert len(table) == 19 and [name for name, _ in table] == list(FORMS)
     for name, shapes in FORMS.items():
         assert shapes and [taken for taken, _, _ in forms(shapes)] == [name] * len(shapes)
+
+
+def test_every_form_with_64_bit_addresses_has_a_shape_that_takes_it(forms, table):
+    assert [name for name, wide in table if wide] == list(WIDE_FORMS)
+    for name, shapes in WIDE_FORMS.items():
+        assert shapes and [taken for taken, _, _ in forms([(m, n, WIDE_K) for m, n in shapes])] == [name] * len(shapes)
+
+
+def test_only_forms_built_for_64_bit_addresses_are_taken_with_them(forms, table):
+    sizes = [128, 256, 384, 640, 1024, 1408, 2048, 4480, 8192, 16384, 20608, 21760, 33280]
+    shapes = [(m, n, k) for m in sizes for n in sizes for k in (WIDE_K, 1 << 26, (1 << 31) - 64)]
+    assert {name for name, _, _ in forms(shapes)} <= {name for name, wide in table if wide}
 
 
 @pytest.mark.parametrize("k", [64, 128, 192, 256, 320, 1024])
