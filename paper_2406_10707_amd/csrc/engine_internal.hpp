@@ -88,6 +88,7 @@ struct Snap {
     uint8_t *map = nullptr;
     std::string tmp_path, final_path;
     std::atomic<uint64_t> chunks_left{0};
+    std::atomic<bool> copies_over{false};   // one of the I/O threads has seen it
     hipEvent_t ev_boundary = nullptr;
     bool submitted = false, packs_submitted = false, d2h_done = false, committed = false, window_closed = false;
     Clock::time_point t_request, t_submitted, t_committed, t_first_chunk;
@@ -113,7 +114,8 @@ struct IoJob {
     int fd = -1;                  // READ
     uint64_t slot = 0, file_off = 0, nbytes = 0;
     uint64_t slot_off = 0;        // where in the slot this piece of the chunk lies
-    bool last = false;            // WRITE: of the snapshot's last chunk, the piece that lands last (the first one if all land together)
+    bool ends = false;            // WRITE: after it has landed the snapshot's copies may be over (pieces of the last chunk)
+    bool last = false;            // WRITE: after it has landed they are waited for (of these the last one, the first if all land together)
     hipEvent_t landed = nullptr;  // WRITE: the copy that brings this piece
     uint32_t piece = 0;           // READ: number of the piece in its chunk
 };

@@ -6,7 +6,7 @@
 using namespace dsllm;
 
 static void finish_d2h_stats(ckpt_ctx *c, Snap *s) {
-    // called by the I/O thread that has the piece of the snapshot that lands last, after all tail events completed
+    // called by one I/O thread, after all tail events completed
     double pack_sum = 0, req_d2h = 0, span = 0, req_pack = 0;
     float ms = 0;
     const uint64_t n_sc = s->plan->n_superchunks;
@@ -113,12 +113,18 @@ void dsllm::io_thread_main(ckpt_ctx *c) {
             s->t_first_chunk = Clock::now();
             s->have_first_chunk = true;
         }
-        if (job.last) {
-            for (size_t k = 0; k < c->dma.size(); k++) {
-                he = hipEventSynchronize(c->ev_job_tail[k]);
-                if (he != hipSuccess) c->fail_snapshot(s, CKPT_EHIP, std::string("tail event: ") + hipGetErrorString(he));
+        // The first thread to see the end of the copies says so: the next snapshot's submit waits for it, and behind a sink slower than the
+        // link the last chunk is then still to be written.
+        if (job.ends && !s->copies_over) {
+            bool over = true;
+            for (size_t k = 0; over && k < c->dma.size(); k++) {
+                he = job.last ? hipEventSynchronize(c->ev_job_tail[k]) : hipEventQuery(c->ev_job_tail[k]);
+                if (he == hipSuccess) continue;
+                if (job.last) c->fail_snapshot(s, CKPT_EHIP, std::string("tail event: ") + hipGetErrorString(he));
+                else over = false;                 // not yet, or an error that the last piece will report
+                (void)hipGetLastError();
             }
-            finish_d2h_stats(c, s);
+            if (over && !s->copies_over.exchange(true)) finish_d2h_stats(c, s);
         }
         if (s->map) memcpy(s->map + job.file_off, piece, job.nbytes);   // page-cache/tmpfs sink: parallel across threads
         else if (s->fd >= 0) {

@@ -160,6 +160,7 @@ static void submit_one(ckpt_ctx *c, const std::shared_ptr<Snap> &sp) {
                 job.file_off = p.header_bytes + ch * CH + job.slot_off;
                 job.nbytes = std::min<uint64_t>(kPieceBytes, nbytes - job.slot_off);
                 job.last = ch + 1 == p.n_chunks && q == (parts ? n_pieces - 1 : 0);
+                job.ends = ch + 1 == p.n_chunks && (parts || job.last);
                 job.landed = parts ? parts[job.slot_off / kPartBytes] : c->ev_slot[slot];
                 c->io_q.push_back(std::move(job));
             }

@@ -1,0 +1,33 @@
+"""Snapshots in parts (tests/emu/emu_parts.cpp), on the CPU model of streams and events,
+under ThreadSanitizer and AddressSanitizer."""
+import os
+import subprocess
+
+import pytest
+
+from tests.test_host_restore import CLANG, ROOT, SOURCES
+
+
+def _build(tmp_path_factory, sanitizer, *sizes):
+    if not os.path.exists(CLANG):
+        pytest.skip("ROCm clang not present")
+    exe = str(tmp_path_factory.mktemp("emu") / "emu_parts")
+    subprocess.run([CLANG, "-x", "c++", "-std=c++17", "-O1", "-g", "-fsanitize=" + sanitizer, "-fno-omit-frame-pointer", "-pthread", *sizes, "-I", os.path.join(ROOT, "tests", "emu"), "-o", exe,
+                    os.path.join(ROOT, "tests", "emu", "emu_parts.cpp"), *[os.path.join(ROOT, "paper_2406_10707_amd", "csrc", f) for f in SOURCES]],
+                   check=True, cwd=os.path.join(ROOT, "tests", "emu"))
+    return exe
+
+
+@pytest.fixture(scope="module", params=["thread", "address,undefined"])
+def emu(request, tmp_path_factory):
+    return _build(tmp_path_factory, request.param, "-DDSLLM_PIECE_BYTES=4096ull", "-DDSLLM_SCATTER_BYTES=1ull")
+
+
+def _run(emu, *args):
+    r = subprocess.run([emu, *map(str, args)], capture_output=True, text=True, timeout=300)
+    out = r.stdout + r.stderr
+    assert r.returncode == 0 and out.strip() == "ok " + args[1], out[-6000:]
+
+
+def test_the_end_of_the_copies_is_seen_before_the_last_chunk_is_written(emu, tmp_path):
+    _run(emu, tmp_path, "end")
