@@ -102,7 +102,7 @@ static int restore_body(ckpt_ctx *c, int fd, const char *path, hipStream_t strea
         const uint64_t c0 = sc * (SC / CH), c1 = std::min<uint64_t>(p.n_chunks, c0 + SC / CH);
         uint64_t group = c0, t0 = p.sc_first_tile[sc];      // first chunk and first tile not yet scattered
         for (uint64_t ch = c0; ch < c1; ch++) {
-            int r = issue_reads_upto(ch + c->n_slots);
+            int r = issue_reads_upto(ch ? ch + 1 : c->n_slots);
             if (r != CKPT_OK) return r;
             const uint64_t slot = (base + ch) % c->n_slots;
             const uint8_t *slot_base = c->ring + slot * CH;
@@ -164,17 +164,21 @@ static int restore_body(ckpt_ctx *c, int fd, const char *path, hipStream_t strea
             for (size_t k = 0; k < nk; k++)
                 if (sent_on(ch, k)) HIP_TRY(c, hipEventRecord(c->ev_sent[k][slot], c->dma[k]));
             // scattered as soon as it is on the device: what is left to do behind the last copy is one chunk, not a super-chunk
-            if (ch + 1 < c1 && (ch + 1 - group) * CH < DSLLM_SCATTER_BYTES) continue;
-            const uint64_t t1 = p.first_tile_at(sc, (ch + 1) * CH);
-            if (t0 < t1) {
-                // every copy stream's latest event of the group (a slot that has been filled again since: the older copy was waited for)
-                for (uint64_t g = in_pieces ? ch : std::max(group, ch + 1 - std::min<uint64_t>(ch + 1, nk)); g <= ch; g++)
-                    for (size_t k = 0; k < nk; k++)
-                        if (sent_on(g, k)) HIP_TRY(c, hipStreamWaitEvent(c->pack_stream, c->ev_sent[k][(base + g) % c->n_slots], 0));
-                HIP_TRY(c, launch_scatter(dev_tiles + t0, t1 - t0, stage_base, sc * SC, c->pack_stream));
+            if (ch + 1 == c1 || (ch + 1 - group) * CH >= DSLLM_SCATTER_BYTES) {
+                const uint64_t t1 = p.first_tile_at(sc, (ch + 1) * CH);
+                if (t0 < t1) {
+                    // every copy stream's latest event of the group (a slot that has been filled again since: the older copy was waited for)
+                    for (uint64_t g = in_pieces ? ch : std::max(group, ch + 1 - std::min<uint64_t>(ch + 1, nk)); g <= ch; g++)
+                        for (size_t k = 0; k < nk; k++)
+                            if (sent_on(g, k)) HIP_TRY(c, hipStreamWaitEvent(c->pack_stream, c->ev_sent[k][(base + g) % c->n_slots], 0));
+                    HIP_TRY(c, launch_scatter(dev_tiles + t0, t1 - t0, stage_base, sc * SC, c->pack_stream));
+                }
+                group = ch + 1;
+                t0 = t1;
             }
-            group = ch + 1;
-            t0 = t1;
+            // The slot of the chunk before is filled again: this waits for that chunk's copies, with this one's handed over behind them.
+            r = issue_reads_upto(ch + c->n_slots);
+            if (r != CKPT_OK) return r;
         }
         HIP_TRY(c, hipEventRecord(c->ev_packed[sc], c->pack_stream));
     }

@@ -1,12 +1,16 @@
-// Snapshots in parts, on the CPU model of streams and events (hip/hip_runtime.h).
+// Snapshots in parts and restores of files larger than the ring, on the CPU model of streams and events (hip/hip_runtime.h).
 //   end      a slow sink: once its copies have landed, a snapshot says so, and the next one starts, while its last chunk is
 //            still being written
-//   emu_parts <dir> end
+//   restore  a restore hands a chunk's copies to the device while those of the chunk before it are under way, also when the
+//            ring's slots come round again
+//   emu_parts <dir> end|restore [<chunk bytes> <ring slots>]
 #include <atomic>
 #include <chrono>
 #include <cstdio>
 #include <cstdlib>
 #include <functional>
+#include <map>
+#include <mutex>
 #include <string>
 #include <thread>
 #include <vector>
@@ -114,10 +118,51 @@ static void end_of_copies(const std::string &dir) {
     r.restored(2);
 }
 
+// A copy is held until one of the next chunk has been handed over. In between the ends, chunks of more than sixteen pieces go as a
+// whole then: one copy each.
+static std::mutex g_copies;
+static uint64_t g_chunk = 0, g_handed = 0;
+static std::map<const void *, uint64_t> g_chunk_of;
+static std::vector<int> g_copies_of;
+static std::atomic<bool> g_alone{false};
+
+static void on_copy(const void *src, size_t n, hipMemcpyKind kind, bool starts) {
+    if (kind != hipMemcpyHostToDevice) return;
+    std::unique_lock<std::mutex> lk(g_copies);
+    if (!starts) {
+        g_chunk_of[src] = g_handed / g_chunk;
+        g_copies_of[g_handed / g_chunk]++;
+        g_handed += n;
+        return;
+    }
+    const uint64_t ch = g_chunk_of[src];
+    lk.unlock();
+    if (ch + 1 < g_copies_of.size() && !g_alone && !comes_true([&] { std::lock_guard<std::mutex> l(g_copies); return g_handed > (ch + 1) * g_chunk; })) g_alone = true;
+}
+
+static void restore(const std::string &dir, uint64_t chunk, uint64_t slots) {
+    Run r(dir, {3 * chunk + 777, 100, 5 * chunk, 2 * chunk + 4097}, chunk, slots, 3);
+    r.snapshot(1);
+    REQUIRE(ckpt_wait_immutable_window_end(r.ctx, r.compute, 0) == CKPT_OK);
+    REQUIRE(ckpt_flush(r.ctx, 1) == CKPT_OK);
+    for (int rep = 0; rep < 2; rep++) {
+        g_chunk = chunk;
+        g_handed = 0;
+        g_copies_of.assign(r.lay.n_chunks, 0);
+        g_emu_copy_hook = on_copy;
+        r.restored(1);
+        g_emu_copy_hook = nullptr;
+        REQUIRE(!g_alone && g_handed == r.lay.data_bytes);
+        for (uint64_t ch = 0; ch < r.lay.n_chunks; ch++)
+            REQUIRE(g_copies_of[ch] >= 1 && (chunk <= 16 * DSLLM_PIECE_BYTES || ch < 2 || ch + 1 == r.lay.n_chunks || g_copies_of[ch] == 1));
+    }
+}
+
 int main(int argc, char **argv) {
     if (argc < 3) return 2;
     const std::string dir = argv[1], what = argv[2];
     if (what == "end") end_of_copies(dir);
+    else if (what == "restore" && argc > 4) restore(dir, strtoull(argv[3], nullptr, 10), strtoull(argv[4], nullptr, 10));
     else return 2;
     printf("ok %s\n", what.c_str());
     return 0;

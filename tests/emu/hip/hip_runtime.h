@@ -140,8 +140,14 @@ inline hipError_t hipFree(void *p) { free(p); return hipSuccess; }
 inline hipError_t hipHostMalloc(void **p, size_t n, unsigned) { *p = aligned_alloc(4096, (n + 4095) / 4096 * 4096); return *p ? hipSuccess : hipErrorOutOfMemory; }
 inline hipError_t hipHostFree(void *p) { free(p); return hipSuccess; }
 inline hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) { memcpy(d, s, n); return hipSuccess; }
-inline hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t st) {
-    emu_submit(st, [=] { memcpy(d, s, n); });
+// a test may watch asynchronous copies: as one is handed over (starts: false) and on its stream right before it is made
+inline std::atomic<void (*)(const void *src, size_t n, hipMemcpyKind kind, bool starts)> g_emu_copy_hook{nullptr};
+inline hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind kind, hipStream_t st) {
+    if (auto hook = g_emu_copy_hook.load()) hook(s, n, kind, false);
+    emu_submit(st, [=] {
+        if (auto hook = g_emu_copy_hook.load()) hook(s, n, kind, true);
+        memcpy(d, s, n);
+    });
     return hipSuccess;
 }
 // a test may say what allocations there are (base and size of the one that holds an address, false if none does) and count the queries

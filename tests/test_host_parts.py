@@ -1,4 +1,4 @@
-"""Snapshots in parts (tests/emu/emu_parts.cpp), on the CPU model of streams and events,
+"""Snapshots in parts and restores of files larger than the ring (tests/emu/emu_parts.cpp), on the CPU model of streams and events,
 under ThreadSanitizer and AddressSanitizer."""
 import os
 import subprocess
@@ -31,3 +31,9 @@ def _run(emu, *args):
 
 def test_the_end_of_the_copies_is_seen_before_the_last_chunk_is_written(emu, tmp_path):
     _run(emu, tmp_path, "end")
+
+
+# chunks sent in pieces, and (more than sixteen pieces) as a whole in between
+@pytest.mark.parametrize("chunk,slots", [(64 << 10, 2), (64 << 10, 3), (128 << 10, 2), (128 << 10, 3), (128 << 10, 20)])
+def test_a_restore_keeps_two_chunks_under_way(emu, tmp_path, chunk, slots):
+    _run(emu, tmp_path, "restore", chunk, slots)
