@@ -128,8 +128,8 @@ struct IoJob {
 #define DSLLM_PIECE_BYTES (4ull << 20)   // a multiple of 4 KiB
 #endif
 constexpr uint64_t kPieceBytes = DSLLM_PIECE_BYTES;
-// On restore pieces are a quarter of that, except for direct I/O: the link waits for the first one, and four threads that read
-// 4 MiB each bring none for 0.3 ms and then four at once.
+// On restore, where the copy streams take pieces in turn, pieces are a quarter of that, except for direct I/O: the link waits for the
+// first one, and four threads that read 4 MiB each bring none for 0.3 ms and then four at once.
 constexpr uint64_t kReadPieceBytes = kPieceBytes / 4 < 4096 ? 4096 : kPieceBytes / 4 / 4096 * 4096;
 // What one copy between ring and device moves where a chunk is shared among the copy streams. One stream loses some 10 us per
 // copy, two hide that from each other: 57.0 GB/s to the device in pieces of 4 MiB (one stream 50.4, whole chunks 57.6), 56.4 to the

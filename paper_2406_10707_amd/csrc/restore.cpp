@@ -54,16 +54,17 @@ static int restore_body(ckpt_ctx *c, int fd, const char *path, hipStream_t strea
     if (p.n_direct)   // these copies write the tensors themselves
         for (size_t k = 0; k < nk; k++) HIP_TRY(c, hipStreamWaitEvent(c->dma[k], c->ev_user, 0));
 
-    // Chunks of more than 64 MiB but the first two and the last: large pieces again, as they mostly go on as a whole (below).
-    auto in_between = [&](uint64_t ch) { return CH > 4 * kPartBytes && ch >= 2 && ch + 1 < p.n_chunks; };
-    auto piece_of = [&](uint64_t ch) {       // CH is a multiple of 32 KiB: 4 KiB multiples
-        return std::min<uint64_t>(c->cfg.o_direct || in_between(ch) ? kPieceBytes : kReadPieceBytes, CH / 8);
-    };
+    // Chunks of 8 MiB and more are sent on as their pieces arrive: up to 64 MiB, or if there is little in all, over the copy streams in turn
+    // (one alone would lose time between the copies), else on one stream each, in runs of 16 MiB or, behind the first two, as a whole
+    // while the copies before it keep the link busy: every copy costs the link some ten microseconds under some runtimes. 8 GB in
+    // chunks of 256 MiB through a ring of eight 154.4 ms, with the chunks at both ends on the streams in turn 155.4, with all of
+    // them 158.1; chunks of 128 MiB 153.7, 154.9 and 158.1. In one chunk 32 MB 1.22 ms, in turn 0.93, 100 MB 2.74 and 2.32, 250 MB 5.72 and 5.34;
+    // 400 MB in two are even. Small chunks go as a whole, on one stream, whose event is then the only one to be recorded and waited for.
+    const bool in_pieces = CH >= DSLLM_SCATTER_BYTES, in_turn = in_pieces && (CH <= 4 * kPartBytes || p.data_bytes <= 16 * kPartBytes);
+    const uint64_t piece_bytes = std::min<uint64_t>(c->cfg.o_direct || !in_turn ? kPieceBytes : kReadPieceBytes, CH / 8);   // CH is a multiple of 32 KiB: 4 KiB multiples
+    const uint64_t send_pieces = std::max<uint64_t>(kSendBytes / piece_bytes, 1);
     uint64_t sends = 0;             // copies enqueued, for the copy streams in turn
-    // A large chunk is sent on as its pieces arrive, over the copy streams in turn (one alone would lose time between the
-    // copies); a small one as a whole, on one stream, whose event is then the only one to be recorded and waited for.
-    const bool in_pieces = CH >= DSLLM_SCATTER_BYTES;
-    auto sent_on = [&](uint64_t ch, size_t k) { return in_pieces || k == ch % nk; };
+    auto sent_on = [&](uint64_t ch, size_t k) { return in_turn || k == ch % nk; };
     uint64_t &issued = *issued_out;   // chunks whose file read has been handed to the I/O threads
     auto issue_reads_upto = [&](uint64_t upto) -> int {
         for (; issued < upto && issued < p.n_chunks; issued++) {
@@ -72,7 +73,7 @@ static int restore_body(ckpt_ctx *c, int fd, const char *path, hipStream_t strea
                 for (size_t k = 0; k < nk; k++)
                     if (sent_on(issued - c->n_slots, k)) HIP_TRY(c, hipEventSynchronize(c->ev_sent[k][slot]));   // previous chunk's copies out of the slot
             // a chunk is read in pieces, spread over the I/O threads
-            const uint64_t nbytes = p.chunk_bytes(issued), piece_bytes = piece_of(issued), n_pieces = (nbytes + piece_bytes - 1) / piece_bytes;
+            const uint64_t nbytes = p.chunk_bytes(issued), n_pieces = (nbytes + piece_bytes - 1) / piece_bytes;
             {
                 std::lock_guard<std::mutex> lk(c->mu);
                 c->slot_state[slot] = SLOT_BUSY;
@@ -106,12 +107,11 @@ static int restore_body(ckpt_ctx *c, int fd, const char *path, hipStream_t strea
             if (r != CKPT_OK) return r;
             const uint64_t slot = (base + ch) % c->n_slots;
             const uint8_t *slot_base = c->ring + slot * CH;
-            const uint64_t nbytes = p.chunk_bytes(ch), piece_bytes = piece_of(ch), send_pieces = std::max<uint64_t>(kSendBytes / piece_bytes, 1);
-            // A chunk of more than 64 MiB behind which there are others goes as a whole while the copies before it keep the link
-            // busy: every copy costs the link some ten microseconds under some runtimes (40 GB in runs of 16 MiB 54.0 GB/s, in whole chunks 55.6).
+            const uint64_t nbytes = p.chunk_bytes(ch);
+            const bool end = ch < 2 || ch + 1 == p.n_chunks;
             bool whole = !in_pieces;
-            if (in_pieces && in_between(ch)) {
-                whole = hipEventQuery(c->ev_sent[(sends - 1) % nk][(base + ch - 1) % c->n_slots]) != hipSuccess;
+            if (in_pieces && !in_turn && !end) {
+                whole = hipEventQuery(c->ev_sent[(ch - 1) % nk][(base + ch - 1) % c->n_slots]) != hipSuccess;
                 if (whole) (void)hipGetLastError();   // "not ready" is no error of a later call
             }
             uint64_t sent = 0, seg = p.chunk_first_seg[ch];
@@ -126,9 +126,9 @@ static int restore_body(ckpt_ctx *c, int fd, const char *path, hipStream_t strea
                         while (q < got.size() && got[q]) q++;
                         return q - sent / piece_bytes;
                     };
-                    // (at the ends little, as the link or the caller waits for it; in between more, to have the link busy while
-                    // this thread reads)
-                    const uint64_t enough = ch == 0 && sent == 0 ? 1 : ch < 2 || ch + 1 == p.n_chunks ? send_pieces : 4 * send_pieces;
+                    // (on streams in turn little at the ends, as the link or the caller waits for it; else more, to have the link busy
+                    // while this thread reads)
+                    const uint64_t enough = ch == 0 && sent == 0 ? 1 : in_turn && end ? send_pieces : 4 * send_pieces;
                     auto can_go_on = [&] { return c->slot_state[slot] == SLOT_READ_DONE || (!whole && pieces_ready() >= enough); };
                     // A file that is read more slowly than the link moves data is the rule (one thread reads 15 GB/s): while
                     // it has nothing to send, this thread reads too, except for direct I/O, which needs a buffer of its own.
@@ -144,7 +144,7 @@ static int restore_body(ckpt_ctx *c, int fd, const char *path, hipStream_t strea
                     // not too much, or one stream would have the link for itself for long
                     if (!whole) ready = std::min(nbytes, sent + std::min(pieces_ready(), 4 * send_pieces) * piece_bytes);
                 }
-                const size_t k = in_pieces ? sends++ % nk : ch % nk;
+                const size_t k = in_turn ? sends++ % nk : ch % nk;
                 // the parts of the chunk's segments that lie in [sent, ready)
                 for (; seg < p.chunk_first_seg[ch + 1]; seg++) {
                     const ckpt_segment &sg = p.segs[seg];
@@ -168,7 +168,7 @@ static int restore_body(ckpt_ctx *c, int fd, const char *path, hipStream_t strea
                 const uint64_t t1 = p.first_tile_at(sc, (ch + 1) * CH);
                 if (t0 < t1) {
                     // every copy stream's latest event of the group (a slot that has been filled again since: the older copy was waited for)
-                    for (uint64_t g = in_pieces ? ch : std::max(group, ch + 1 - std::min<uint64_t>(ch + 1, nk)); g <= ch; g++)
+                    for (uint64_t g = in_turn ? ch : std::max(group, ch + 1 - std::min<uint64_t>(ch + 1, nk)); g <= ch; g++)
                         for (size_t k = 0; k < nk; k++)
                             if (sent_on(g, k)) HIP_TRY(c, hipStreamWaitEvent(c->pack_stream, c->ev_sent[k][(base + g) % c->n_slots], 0));
                     HIP_TRY(c, launch_scatter(dev_tiles + t0, t1 - t0, stage_base, sc * SC, c->pack_stream));
