@@ -232,16 +232,19 @@ int ckpt_init(const ckpt_config *cfg, ckpt_ctx **out) {
         if ((e = hipEventCreateWithFlags(&ev, hipEventBlockingSync)) != hipSuccess) return cleanup_fail(CKPT_EHIP, hipGetErrorString(e));
         c->ev_slot.push_back(ev);
     }
-    for (auto *events : {&c->ev_sent, &c->ev_part}) {
-        const bool sent = events == &c->ev_sent;
-        events->resize(rc.n_dma_streams + (sent ? 0 : 1));
-        for (auto &v : *events)
-            for (uint64_t i = 0; i < (sent ? c->n_slots : (rc.dma_chunk_bytes + kPartBytes - 1) / kPartBytes); i++) {
+    auto create_events = [&](std::vector<std::vector<hipEvent_t>> &events, size_t n, uint64_t of_each) {
+        events.resize(n);
+        for (auto &v : events)
+            for (uint64_t i = 0; i < of_each; i++) {
                 hipEvent_t ev;
-                if ((e = hipEventCreateWithFlags(&ev, hipEventDisableTiming | hipEventBlockingSync)) != hipSuccess) return cleanup_fail(CKPT_EHIP, hipGetErrorString(e));
+                if ((e = hipEventCreateWithFlags(&ev, hipEventDisableTiming | hipEventBlockingSync)) != hipSuccess) return false;
                 v.push_back(ev);
             }
-    }
+        return true;
+    };
+    if (rc.dma_chunk_bytes >= DSLLM_SCATTER_BYTES && !create_events(c->ev_sent, c->dma.size() - 1, c->n_slots)) return cleanup_fail(CKPT_EHIP, hipGetErrorString(e));
+    if (c->shares_last_chunks() && !create_events(c->ev_part, c->dma.size() + 1, (rc.dma_chunk_bytes + kPartBytes - 1) / kPartBytes))
+        return cleanup_fail(CKPT_EHIP, hipGetErrorString(e));
     trace("init: slot events created");
     for (int k = 0; k < rc.n_dma_streams; k++) {
         hipEvent_t ev;

@@ -135,6 +135,13 @@ constexpr uint64_t kReadPieceBytes = kPieceBytes / 4 < 4096 ? 4096 : kPieceBytes
 // copy, two hide that from each other: 57.0 GB/s to the device in pieces of 4 MiB (one stream 50.4, whole chunks 57.6), 56.4 to the
 // host in parts of 16 MiB (55.1, 57.1).
 constexpr uint64_t kSendBytes = kPieceBytes, kPartBytes = 4 * kPieceBytes;
+// On restore, chunks of at least this size are sent to the device piece by piece, and each is scattered by a launch of its own as soon as it
+// is there. Smaller ones are sent whole and scattered together up to this size: a launch and its wait cost the
+// calling thread as much as the copy of a MiB takes. 250 MiB restored in chunks of 256 KiB 25.2 -> 17.2 ms, of 1 MiB 7.7 -> 6.4
+// (with a launch for each super-chunk 17.0 and 7.3); from 8 MiB on the two are even.
+#ifndef DSLLM_SCATTER_BYTES
+#define DSLLM_SCATTER_BYTES (8ull << 20)
+#endif
 constexpr int kBoundaryEvents = 8;          // boundary events created at set-up (snapshots in flight at a time)
 constexpr size_t kMaxSnapRecords = 1024;   // per-snapshot records (measurements, states) kept per context
 
@@ -165,9 +172,12 @@ struct ckpt_ctx {
     hipEvent_t ev_verify_start = nullptr, ev_verify_done = nullptr, ev_derived = nullptr;
     hipStream_t pack_stream = nullptr;
     std::vector<hipStream_t> dma;
-    std::vector<hipEvent_t> ev_slot;                      // per ring slot: snapshot's copy into the slot done
-    std::vector<std::vector<hipEvent_t>> ev_sent;         // restore, [dma stream][slot]: what the stream had to copy when the slot's chunk was sent
+    std::vector<hipEvent_t> ev_slot;                      // per ring slot: copy into or out of the slot done
+    std::vector<std::vector<hipEvent_t>> ev_sent;         // restore in chunks that may be sent on several streams, [dma stream - 1][slot]: the other streams' copies
     std::vector<std::vector<hipEvent_t>> ev_part;         // [chunks from the end][part]: part of one of a snapshot's last chunks
+    // restore: what the stream had to copy when the slot's chunk was sent (whichever stream that is, if it is always one)
+    hipEvent_t sent_event(size_t stream, uint64_t slot) const { return stream == 0 || ev_sent.empty() ? ev_slot[slot] : ev_sent[stream - 1][slot]; }
+    bool shares_last_chunks() const { return dma.size() > 1 && cfg.dma_chunk_bytes > dsllm::kPartBytes; }
     std::vector<hipEvent_t> ev_pack_start, ev_pack_end, ev_packed;   // per super-chunk: the kernel's start and end (timing), its completion in the pack stream (ordering)
     std::vector<std::vector<hipEvent_t>> ev_stage_done;   // [stage slot][dma stream]
     std::vector<hipEvent_t> ev_job_tail;                  // per dma stream

@@ -3,14 +3,6 @@
 
 using namespace dsllm;
 
-// Chunks of at least this size are sent to the device piece by piece where that helps, and each is scattered by a launch of its own
-// as soon as it is there. Smaller ones are sent whole and scattered together up to this size: a launch and its wait cost the
-// calling thread as much as the copy of a MiB takes. 250 MiB restored in chunks of 256 KiB 25.2 -> 17.2 ms, of 1 MiB 7.7 -> 6.4
-// (with a launch for each super-chunk 17.0 and 7.3); from 8 MiB on the two are even.
-#ifndef DSLLM_SCATTER_BYTES
-#define DSLLM_SCATTER_BYTES (8ull << 20)
-#endif
-
 static int restore_body(ckpt_ctx *c, int fd, const char *path, hipStream_t stream, uint64_t base, uint64_t *issued_out, uint64_t *iter_out) {
     const uint64_t CH = c->cfg.dma_chunk_bytes, SC = c->cfg.pack_superchunk_bytes;
     const size_t nk = c->dma.size();
@@ -71,7 +63,7 @@ static int restore_body(ckpt_ctx *c, int fd, const char *path, hipStream_t strea
             const uint64_t slot = (base + issued) % c->n_slots;
             if (issued >= c->n_slots)
                 for (size_t k = 0; k < nk; k++)
-                    if (sent_on(issued - c->n_slots, k)) HIP_TRY(c, hipEventSynchronize(c->ev_sent[k][slot]));   // previous chunk's copies out of the slot
+                    if (sent_on(issued - c->n_slots, k)) HIP_TRY(c, hipEventSynchronize(c->sent_event(k, slot)));   // previous chunk's copies out of the slot
             // a chunk is read in pieces, spread over the I/O threads
             const uint64_t nbytes = p.chunk_bytes(issued), n_pieces = (nbytes + piece_bytes - 1) / piece_bytes;
             {
@@ -111,7 +103,7 @@ static int restore_body(ckpt_ctx *c, int fd, const char *path, hipStream_t strea
             const bool end = ch < 2 || ch + 1 == p.n_chunks;
             bool whole = !in_pieces;
             if (in_pieces && !in_turn && !end) {
-                whole = hipEventQuery(c->ev_sent[(ch - 1) % nk][(base + ch - 1) % c->n_slots]) != hipSuccess;
+                whole = hipEventQuery(c->sent_event((ch - 1) % nk, (base + ch - 1) % c->n_slots)) != hipSuccess;
                 if (whole) (void)hipGetLastError();   // "not ready" is no error of a later call
             }
             uint64_t sent = 0, seg = p.chunk_first_seg[ch];
@@ -162,7 +154,7 @@ static int restore_body(ckpt_ctx *c, int fd, const char *path, hipStream_t strea
                 sent = ready;
             }
             for (size_t k = 0; k < nk; k++)
-                if (sent_on(ch, k)) HIP_TRY(c, hipEventRecord(c->ev_sent[k][slot], c->dma[k]));
+                if (sent_on(ch, k)) HIP_TRY(c, hipEventRecord(c->sent_event(k, slot), c->dma[k]));
             // scattered as soon as it is on the device: what is left to do behind the last copy is one chunk, not a super-chunk
             if (ch + 1 == c1 || (ch + 1 - group) * CH >= DSLLM_SCATTER_BYTES) {
                 const uint64_t t1 = p.first_tile_at(sc, (ch + 1) * CH);
@@ -170,7 +162,7 @@ static int restore_body(ckpt_ctx *c, int fd, const char *path, hipStream_t strea
                     // every copy stream's latest event of the group (a slot that has been filled again since: the older copy was waited for)
                     for (uint64_t g = in_turn ? ch : std::max(group, ch + 1 - std::min<uint64_t>(ch + 1, nk)); g <= ch; g++)
                         for (size_t k = 0; k < nk; k++)
-                            if (sent_on(g, k)) HIP_TRY(c, hipStreamWaitEvent(c->pack_stream, c->ev_sent[k][(base + g) % c->n_slots], 0));
+                            if (sent_on(g, k)) HIP_TRY(c, hipStreamWaitEvent(c->pack_stream, c->sent_event(k, (base + g) % c->n_slots), 0));
                     HIP_TRY(c, launch_scatter(dev_tiles + t0, t1 - t0, stage_base, sc * SC, c->pack_stream));
                 }
                 group = ch + 1;

@@ -240,7 +240,7 @@ static void submit_one(ckpt_ctx *c, const std::shared_ptr<Snap> &sp) {
     // chunks of more than 64 MiB: beside the training step every copy more costs the system runtime some 40 us (1.74 GB in chunks of
     // 256 MiB, the last three in parts: copies at 55.8 GB/s instead of 56.6), and the end is little of the whole there.
     uint64_t shared = 0;
-    if (nk > 1 && CH > kPartBytes && p.n_chunks > 1 && (CH <= 4 * kPartBytes || p.n_chunks <= 2 * (nk + 1))) {
+    if (c->shares_last_chunks() && p.n_chunks > 1 && (CH <= 4 * kPartBytes || p.n_chunks <= 2 * (nk + 1))) {
         std::lock_guard<std::mutex> lk(c->mu);
         if (!c->prev_job || c->prev_job->committed) shared = std::min<uint64_t>(p.n_chunks, nk + 1);
     }

@@ -3,7 +3,8 @@
 //            still being written
 //   restore  a restore hands a chunk's copies to the device while those of the chunk before it are under way, also when the
 //            ring's slots come round again
-//   emu_parts <dir> end|restore [<chunk bytes> <ring slots>]
+//   events   a context has the events that its chunks and streams need
+//   emu_parts <dir> end|restore|events [<chunk bytes> <ring slots>]
 #include <atomic>
 #include <chrono>
 #include <cstdio>
@@ -28,6 +29,9 @@ ssize_t emu_pwrite(int fd, const void *buf, size_t n, off_t off) {
     struct iovec iov = {const_cast<void *>(buf), n};
     return pwritev(fd, &iov, 1, off);
 }
+#ifndef DSLLM_PIECE_BYTES
+#define DSLLM_PIECE_BYTES (4ull << 20)
+#endif
 #define REQUIRE(x) do { if (!(x)) { printf("FAILED line %d: %s (%s)\n", __LINE__, #x, ckpt_last_error()); exit(1); } } while (0)
 
 // waits until it holds, five seconds at most: no wait here can hang the test
@@ -158,11 +162,37 @@ static void restore(const std::string &dir, uint64_t chunk, uint64_t slots) {
     }
 }
 
+static int events_of(const std::string &dir, uint64_t chunk, uint64_t slots, int streams) {
+    ckpt_config cfg{};
+    cfg.out_dir = dir.c_str();
+    cfg.host_ring_bytes = slots * chunk;
+    cfg.dma_chunk_bytes = chunk;
+    cfg.pack_superchunk_bytes = 2 * chunk;
+    cfg.n_dma_streams = streams;
+    ckpt_ctx *ctx = nullptr;
+    const int before = g_emu_events_created;
+    REQUIRE(ckpt_init(&cfg, &ctx) == CKPT_OK);
+    const int made = g_emu_events_created - before;
+    REQUIRE(ckpt_destroy(ctx) == CKPT_OK);
+    return made;
+}
+
+// with the library's own piece sizes
+static void events(const std::string &dir) {
+    for (int streams : {1, 2, 3}) {
+        REQUIRE(events_of(dir, 256 << 10, 96, streams) - events_of(dir, 256 << 10, 32, streams) == 64);          // one for every slot
+        REQUIRE(events_of(dir, 8 << 20, 6, streams) - events_of(dir, 8 << 20, 2, streams) == 4 * streams);       // sent on several streams
+    }
+    REQUIRE(events_of(dir, 40 << 20, 2, 1) == events_of(dir, 256 << 10, 2, 1));                                  // parts of the last chunks:
+    REQUIRE(events_of(dir, 40 << 20, 2, 2) - events_of(dir, 16 << 20, 2, 2) == 3 * 3);                           // three chunks, three parts
+}
+
 int main(int argc, char **argv) {
     if (argc < 3) return 2;
     const std::string dir = argv[1], what = argv[2];
     if (what == "end") end_of_copies(dir);
     else if (what == "restore" && argc > 4) restore(dir, strtoull(argv[3], nullptr, 10), strtoull(argv[4], nullptr, 10));
+    else if (what == "events") events(dir);
     else return 2;
     printf("ok %s\n", what.c_str());
     return 0;

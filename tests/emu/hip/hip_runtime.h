@@ -174,7 +174,8 @@ inline hipError_t hipStreamQuery(hipStream_t s) {
     return s->done >= s->enqueued ? hipSuccess : 600;   // hipErrorNotReady
 }
 
-inline hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { *e = new EmuEvent; return hipSuccess; }
+inline std::atomic<int> g_emu_events_created{0};
+inline hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { g_emu_events_created++; *e = new EmuEvent; return hipSuccess; }
 inline hipError_t hipEventCreate(hipEvent_t *e) { return hipEventCreateWithFlags(e, 0); }
 inline hipError_t hipEventDestroy(hipEvent_t e) { delete e; return hipSuccess; }
 inline hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {

@@ -37,3 +37,7 @@ def test_the_end_of_the_copies_is_seen_before_the_last_chunk_is_written(emu, tmp
 @pytest.mark.parametrize("chunk,slots", [(64 << 10, 2), (64 << 10, 3), (128 << 10, 2), (128 << 10, 3), (128 << 10, 20)])
 def test_a_restore_keeps_two_chunks_under_way(emu, tmp_path, chunk, slots):
     _run(emu, tmp_path, "restore", chunk, slots)
+
+
+def test_a_context_has_the_events_that_it_uses(tmp_path_factory, tmp_path):
+    _run(_build(tmp_path_factory, "address,undefined"), tmp_path, "events")
