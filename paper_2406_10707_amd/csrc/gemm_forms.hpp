@@ -20,13 +20,16 @@ namespace dsllm {
 // full card clocks lower and shares memory, (spread_block + spread_step * (K / 64)) * blocks / 256. The figures are fitted to times
 // of every form on 560 products on an MI355X, M and N multiples of 128 up to 8192 and K of 64 up to 8192, each spread over the
 // logarithm of its range (32 x 32: on 75 of them): 2 to 3 % off in the mean, 4 to 9 % at the ninth decile. The choice by them is 1.1 % slower in the
-// mean than the best form for each product, and over 300 other products 14 % faster than a rule on the number of tiles over two 128 x 128, two
-// 64 x 64, one 32 x 64 kernel and 256 x 256 where both sizes are its multiples. Where that lost most:
-//   6272 x 7808 x 6592 685 -> 462 us     sizes not multiples of 256, formerly 128 x 128 for all
+// mean than the best form for each product. Against a rule on the number of tiles over two 128 x 128, two 64 x 64, one 32 x 64 kernel and
+// 256 x 256 where both sizes are its multiples, 300 other products of these ranges take 16 % less time in the mean, and 40 with K of 8192 to
+// 131072, for which nothing was fitted, 19 % (none of either more than 2 % longer). Where the rule lost most:
+//   1152 x 7808 x 53568 1511 -> 747 us
+//   6272 x 7808 x 6592 686 -> 479        sizes not multiples of 256, formerly 128 x 128 for all
 //   1920 x 7936 x 3456 127 -> 76
 //   768 x 5632 x 3392 46 -> 34           a few 128 x 128 tiles more than there are units
 //   384 x 5248 x 960 12.1 -> 6.9
-//   1024 x 3072 x 768 10.0 -> 7.5        fewer 128 x 128 tiles than units: 128 x 96 fills them
+//   1024 x 3072 x 768 9.8 -> 7.4         fewer 128 x 128 tiles than units: 128 x 96 fills them
+// One product was found that loses more than that: 7040 x 2688 x 256 17.8 -> 18.5 (of 400 more with K of 256 to 512 none).
 // WIDE once a panel of 256 rows passes 2 GiB (the offsets of a buffer load are 32 bits wide). The choice is the same there, but for
 // three forms, which aren't built for it: two were never chosen, and 128 x 128 by 2 for ten pairs of sizes among those whose
 // operands fit the card (20608..21760 x 384; 20608 x 384 takes 122 to 127 ms with it and 123 to 130 without).

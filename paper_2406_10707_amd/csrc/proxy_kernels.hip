@@ -349,15 +349,15 @@ __device__ __forceinline__ void for_each_of(F f, std::integer_sequence<int, I...
 // A load thus has most of a step and more before it is waited for. Tiles of more than 128 x 128 per SIMD pair name the
 // accumulators as AGPRs in the MFMA's own operands: left to itself the compiler moves them to and fro between the two
 // register files inside the loop.
-// MFMAs go to and fro along B's fragments, so that two in a row always share an operand (8192^3 686 -> 684 us).
+// MFMAs go to and fro along B's fragments, so that two in a row always share an operand (0.3 % at 8192^3).
 // M is at least BM and N at least BN, both multiples of 32. The last tile of a row or column ends at the edge of C: it
 // starts inside the one before it where BM or BN does not divide, and both write the same bits there.
 //
 // What bounds it: the power, with 256 x 256 tiles (1.76 GHz at 92 % of the matrix pipe's cycles in the loop; 8192^3 in
-// 0.70 ms = 1570 TFLOP/s, where one 32x32x16 kernel with panels through registers took 1.07), and towards small tiles
+// 0.69 to 0.72 ms = 1590 to 1530 TFLOP/s, where one 32x32x16 kernel with panels through registers took 1.07), and towards small tiles
 // more and more what a wave issues between its MFMAs and the panel loads (BM + BN rows a step): 128 x 128 takes 820 cycles a step,
 // of which the MFMAs are 512 and the loads at 58 bytes a cycle 565. Four waves of 64 x 64 instead of sixteen of 32 x 32
-// and a hand-made order made of 1024 x 3072 x 768 10.0 -> 7.5 us, launched in a row.
+// and a hand-made order made of 1024 x 3072 x 768 9.8 -> 7.4 us, launched in a row.
 template <int WM, int WN, int TM, int TN, int STAGES, int READS, int LOAD_EVERY, bool WIDE>
 __device__ __forceinline__ void gemm_bf16_tile(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B, uint16_t *__restrict__ C, int M, int N, int K,
                                                const TileOrder &order) {
