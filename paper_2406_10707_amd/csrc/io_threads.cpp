@@ -117,7 +117,7 @@ void dsllm::io_thread_main(ckpt_ctx *c) {
         // link the last chunk is then still to be written.
         if (job.ends && !s->copies_over) {
             bool over = true;
-            for (size_t k = 0; over && k < c->dma.size(); k++) {
+            for (size_t k = 0; over && !s->copies_over && k < c->dma.size(); k++) {   // (once another thread has seen it the events may be the next one's)
                 he = job.last ? hipEventSynchronize(c->ev_job_tail[k]) : hipEventQuery(c->ev_job_tail[k]);
                 if (he == hipSuccess) continue;
                 if (job.last) c->fail_snapshot(s, CKPT_EHIP, std::string("tail event: ") + hipGetErrorString(he));
