@@ -67,24 +67,23 @@ __global__ __launch_bounds__(256) void fill_state_kernel(uint16_t *__restrict__ 
 
 struct AdamArgs { float lr, beta1, beta2, eps, inv_bc1, inv_bc2; };
 
-__device__ __forceinline__ void adam_one(float &w, float &m, float &v, uint16_t &p, uint64_t key, uint64_t i, const AdamArgs &a) {
+__device__ __forceinline__ void adam_one(float &w, float &m, float &v, uint64_t key, uint64_t i, const AdamArgs &a) {
     const uint64_t r = mix(key ^ mix(i));
-    const float g = 0.001f * (2.0f * (float(uint32_t(r >> 40)) * (1.0f / 16777216.0f)) - 1.0f);
+    const float g = 0.001f * (float(uint32_t(r >> 32) >> 8) * (1.0f / 8388608.0f) - 1.0f);     // the generator's 24 upper bits to -1 .. 1
     m = a.beta1 * m + (1.0f - a.beta1) * g;
     v = a.beta2 * v + (1.0f - a.beta2) * (g * g);
     const float mhat = m * a.inv_bc1, vhat = v * a.inv_bc2;
     w = w - a.lr * (mhat / (sqrtf(vhat) + a.eps));
-    p = bf16_rne(w);
 }
 
 // Four elements per lane: 16-byte accesses to master, m, v and 8-byte ones to the bf16 copy, one wave per block, each
-// element by one lane of the grid, nothing in a loop. HBM-bound (28 bytes an element, four streams read and four
-// written). Blocks of one wave handed out in address order keep the chip in one narrow front of each stream, and
-// non-temporal accesses keep the streams from displacing each other in L2: on 202 M elements 0.87 ms = 6.5 TB/s, where
-// 4096 blocks of four waves striding over the tensor with ordinary accesses took 1.06 to 1.13 ms = 5.0 to 5.3 TB/s (blocks of
-// four waves: 6.1; ordinary accesses: 6.0; two quads per lane: 6.1). The price: one tensor of 2.5 to 16 M elements whose
-// state stays in the memory-side cache from step to step is 2 to 8 % slower (10 M: 41.4 -> 43.1 us); out of memory, as in a
-// larger state, it is faster (52.2 -> 44.7), and ordinary accesses cost 27 tensors of 1.6 M 292 us instead of 234.
+// element by one lane of the grid, nothing in a loop. HBM-bound (12 bytes an element read, 14 written). Blocks of one wave handed
+// out in address order and non-temporal accesses keep the chip in a narrow front of each of the seven streams: 4096 blocks of four waves striding over
+// the tensor with ordinary accesses took 1.06 to 1.13 ms for 202 M elements, this 0.88 with as many waves as there is room for.
+// Those are more than the memory needs, and the more there are the wider the front: with twelve to a compute unit
+// (kAdamLds, which nothing uses, holds off the others) it takes 0.80 ms = 6.6 TB/s; with 16, 14, 11, 10 and 8: 0.81, 0.80, 0.80, 0.82 and 0.91. (A plain
+// copy, with one load a wave, is fastest with all it can have.) The rounding to bf16 is one instruction for two elements, which gives
+// the bits of bf16_rne for every f32 pattern, in place of two masked branches an element: 1 M elements 5.9 -> 5.6 us.
 __global__ __launch_bounds__(64) void adam_kernel(uint16_t *__restrict__ p, float *__restrict__ master, float *__restrict__ m,
                                                  float *__restrict__ v, uint64_t numel, uint64_t first_quad, uint64_t key, AdamArgs a) {
     const uint64_t n4 = numel >> 2, q = first_quad + uint64_t(blockIdx.x) * 64 + threadIdx.x;
@@ -92,18 +91,24 @@ __global__ __launch_bounds__(64) void adam_kernel(uint16_t *__restrict__ p, floa
         const f32x4 w4 = __builtin_nontemporal_load(reinterpret_cast<f32x4 *>(master) + q), m4 = __builtin_nontemporal_load(reinterpret_cast<f32x4 *>(m) + q),
                     v4 = __builtin_nontemporal_load(reinterpret_cast<f32x4 *>(v) + q);
         float w[4] = {w4.x, w4.y, w4.z, w4.w}, mm[4] = {m4.x, m4.y, m4.z, m4.w}, vv[4] = {v4.x, v4.y, v4.z, v4.w};
-        uint16_t pb[4];
 #pragma unroll
-        for (int j = 0; j < 4; j++) adam_one(w[j], mm[j], vv[j], pb[j], key, 4 * q + j, a);
-        __builtin_nontemporal_store(f32x4{w[0], w[1], w[2], w[3]}, reinterpret_cast<f32x4 *>(master) + q);
+        for (int j = 0; j < 4; j++) adam_one(w[j], mm[j], vv[j], key, 4 * q + j, a);
+        const f32x4 w_new{w[0], w[1], w[2], w[3]};
+        __builtin_nontemporal_store(w_new, reinterpret_cast<f32x4 *>(master) + q);
         __builtin_nontemporal_store(f32x4{mm[0], mm[1], mm[2], mm[3]}, reinterpret_cast<f32x4 *>(m) + q);
         __builtin_nontemporal_store(f32x4{vv[0], vv[1], vv[2], vv[3]}, reinterpret_cast<f32x4 *>(v) + q);
-        __builtin_nontemporal_store(u32x2{uint32_t(pb[0]) | (uint32_t(pb[1]) << 16), uint32_t(pb[2]) | (uint32_t(pb[3]) << 16)}, reinterpret_cast<u32x2 *>(p) + q);
+        __builtin_nontemporal_store(__builtin_bit_cast(u32x2, __builtin_convertvector(w_new, bf16x4)), reinterpret_cast<u32x2 *>(p) + q);
     }
     // ragged tail (numel not a multiple of 4)
     const uint64_t t = (n4 << 2) + q;
-    if (t < numel) adam_one(master[t], m[t], v[t], p[t], key, t, a);
+    if (t < numel) {
+        adam_one(master[t], m[t], v[t], key, t, a);
+        p[t] = bf16_rne(master[t]);
+    }
 }
+// Shared memory of a block that has room for twelve beside each other (160 KiB a compute unit, handed out in pieces of 1280 bytes); only
+// for grids that don't fit the chip's 256 x 32 wave slots at once, as it costs those that do (1 M elements 5.6 -> 6.5 us; 2.5 M 13.6 -> 12.8).
+constexpr unsigned kAdamLds = 12800, kAdamFreeBlocks = 256 * 32;
 
 // ------------------------------------------------------------------ flat-buffer words, copy
 
@@ -554,10 +559,12 @@ int proxy_adam_step(void *p, void *master, void *m, void *v, uint64_t numel, uin
     a.inv_bc1 = float(1.0 / (1.0 - pow(double(beta1), double(step))));
     a.inv_bc2 = float(1.0 / (1.0 - pow(double(beta2), double(step))));
     const uint64_t quads = (numel + 3) / 4, most = 1ull << 31;     // a grid has fewer than 2^32 work-items
-    for (uint64_t first = 0; first < quads; first += most)
-        hipLaunchKernelGGL(adam_kernel, dim3(unsigned((std::min(quads - first, most) + 63) / 64)), dim3(64), 0, static_cast<hipStream_t>(stream),
+    for (uint64_t first = 0; first < quads; first += most) {
+        const unsigned blocks = unsigned((std::min(quads - first, most) + 63) / 64);
+        hipLaunchKernelGGL(adam_kernel, dim3(blocks), dim3(64), blocks > kAdamFreeBlocks ? kAdamLds : 0, static_cast<hipStream_t>(stream),
                            static_cast<uint16_t *>(p), static_cast<float *>(master), static_cast<float *>(m), static_cast<float *>(v), numel, first,
                            stream_key(seed + step, tensor, 3), a);
+    }
     return hip_rc();
 }
 
