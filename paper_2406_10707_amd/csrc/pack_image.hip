@@ -10,7 +10,7 @@
 constexpr uint64_t kNoallocTiles = 131072;
 
 namespace dsllm {
-hipError_t launch_pack_batch(const PackBatch &bt, void *image, hipStream_t stream);
+hipError_t launch_pack_batch(PackBatch &bt, void *image, hipStream_t stream);
 }
 
 using namespace dsllm;
@@ -71,7 +71,7 @@ int enqueue_pack_image(const ckpt_tensor_desc *tensors, size_t n, void *dev_dst,
     uint8_t *image = static_cast<uint8_t *>(dev_dst);
     auto launch = [&]() -> int {
         HIP_TRY(nullptr, launch_pack_batch(bt, image, stream));
-        image += kPackPage * bt.first_page[bt.count];
+        image += kPackPage * bt.pages;
         bt.clear();
         return CKPT_OK;
     };

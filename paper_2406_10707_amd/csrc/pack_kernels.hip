@@ -189,40 +189,32 @@ __global__ __launch_bounds__(kBlock) void pack_kernel(const ckpt_tile *__restric
     pack_range(src, dst, uniform_u32(tp->copy_bytes), uniform_u32(tp->total_bytes), 0, uint32_t(kPackTileBytes / 16), lane);
 }
 
-// The image of up to kPackBatch pieces of tensors without a tile table: the pieces travel in the kernel arguments. The
+// The image of a batch of pieces of tensors without a tile table: the pieces travel in the kernel arguments. The
 // image is a sequence of 4 KiB pages, each of one piece only; a block of ONE wave writes one KiB of one page, 16 bytes
-// per lane, and finds its piece by bisection over the pieces' first pages (scalar loads of the argument segment, nine
-// steps at most, the same cache lines for every wave of a compute unit).
+// per lane, and finds its piece through scalar loads of the arguments (the same cache lines for every wave of a compute unit).
 //
 // HBM-bound. What limits a copy here is the order in which requests reach the memory: with one load and one store per
 // lane and blocks that are handed out in address order, the whole chip sweeps source and image in one narrow front.
-// Measured on MI355X, read + write: 6.76 TB/s on 11 GB of large aligned tensors, 6.5 on 1.7 GB in 592 tensors, 6.1 on
+// Measured on MI355X, read + write: 6.76 TB/s on 11 GB of large aligned tensors, 6.6 on 1.7 GB in 592 tensors, 6.2 on
 // 3.7 GB of misaligned fragments, where a wave that walks 32 KiB on its own (pack_kernel, and a kernel that writes its
 // table before it) reaches 5.73, 5.47 and 5.13. More words per lane widen the front and lose (2: 5.3 to 6.1; 4: 5.9 to
 // 6.1), four waves per block lose 5 % on aligned tensors (6.43) and win 1 % on fragments. On small lists the table was
-// the cost: 112 tensors of 0.4 MB took three kernels, 28 us back to back, and take one, 6 us.
+// the cost: 112 tensors of 0.4 MB took three kernels, 28 us back to back.
 //
 // RUNS: of every 64 KiB, each XCD takes eight in a row instead of every eighth (consecutive blocks go to the eight XCDs in
 // turn). Of a tensor that does not start on a 128-byte line every wave's KiB ends in the middle of one, which the next wave
 // reads again; on the same XCD it finds it in that XCD's L2. Measured on MI355X: 3.7 GB of misaligned fragments 1399 -> 1362 us, 0.6
 // GB of smaller ones 574 -> 553 (runs of 4: 1384, 562; of 16: 1390, 553). Aligned tensors share no lines and lose by the
 // wider front: 1321 -> 1339 us, 11 GB of large ones 3368 -> 3525.
-template <bool RUNS>
-__global__ __launch_bounds__(64) void pack_batch_kernel(PackBatch bt, uint8_t *__restrict__ image) {
+template <bool RUNS, int N>
+__global__ __launch_bounds__(64) void pack_batch_kernel(PackArgs<N> args, uint8_t *__restrict__ image) {
     const uint32_t turn = blockIdx.x % 64, kib = RUNS ? blockIdx.x - turn + turn % 8 * 8 + turn / 8 : blockIdx.x;
     const uint32_t page = kib / 4, at = (kib % 4) * 1024 + 16 * threadIdx.x;
-    uint32_t lo = 0, hi = bt.count;
-    if (page >= bt.first_page[hi]) return;
-    while (hi - lo > 1) {
-        const uint32_t mid = (lo + hi) / 2;
-        if (bt.first_page[mid] <= page) lo = mid;
-        else hi = mid;
-    }
-    const uint64_t src = bt.src(lo) + kPackPage * (page - bt.first_page[lo]);
-    const uint32_t copy_bytes = page + 1 == bt.first_page[lo + 1] ? uint32_t(kPackPage) - bt.pad(lo) : uint32_t(kPackPage);
+    if (page >= args.pages) return;
+    const PackSource s = args.of(page);
     u32x4 v = {0, 0, 0, 0};                                    // padding behind the tensor's last byte
-    if (at + 16 <= copy_bytes) v = ld16_unaligned(reinterpret_cast<const uint8_t *>(src + at));
-    else if (at < copy_bytes) v = tail_word(src + at, copy_bytes - at);
+    if (at + 16 <= s.bytes) v = ld16_unaligned(reinterpret_cast<const uint8_t *>(s.src + at));
+    else if (at < s.bytes) v = tail_word(s.src + at, s.bytes - at);
     st16(reinterpret_cast<u32x4 *>(image + kPackPage * page + at), v);
 }
 
@@ -312,18 +304,34 @@ __global__ __launch_bounds__(kBlock) void scatter_kernel(const ckpt_tile *__rest
 #define DSLLM_PACK_RUNS_FROM 2048
 #endif
 
+// Groups of pages are made from 4 MiB on: 592 tensors of 50 MB 23.8 -> 20.9 us, 288 of 250 MB 94.9 -> 92.3, 2400 of 4.3 GB (misaligned)
+// 1384 -> 1368; with fewer pages the host takes longer than the kernel (316 tensors of 3.7 MB 4.7 us either way). Not for pieces of
+// more than 16 MiB in the mean: 144 tensors of 11.3 GB take 3369 us without and 3400 with them (why was not established); 72 of 1.9 GB 578 and 575,
+// 400 of 9.7 GB 2879 and 2893.
+#ifndef DSLLM_PACK_GROUPS_FROM
+#define DSLLM_PACK_GROUPS_FROM 1024
+#endif
+constexpr uint32_t kMostPagesEach = 4096;
+
 // Writes the pieces of `bt` to `image`, which begins with the page of the batch's first piece. A batch without pieces
-// launches one block of either kernel that finds nothing to do (it makes the runtime load the kernels' code).
-hipError_t launch_pack_batch(const PackBatch &bt, void *image, hipStream_t stream) {
-    const uint32_t pages = bt.first_page[bt.count];
+// launches one block of every kernel that finds nothing to do (it makes the runtime load the kernels' code). The arguments
+// have three sizes, as a launch takes the host longer with more bytes of them: 12 tensors 3.4 us with 4 KB, 3.1 with 0.5.
+hipError_t launch_pack_batch(PackBatch &bt, void *image, hipStream_t stream) {
+    const uint32_t pages = bt.pages;
     uint32_t off_lines = 0;      // pages of tensors that do not start on a 128-byte line
     if (pages >= DSLLM_PACK_RUNS_FROM)
         for (uint32_t k = 0; k < bt.count; k++)
             if (bt.src(k) % 128) off_lines += bt.first_page[k + 1] - bt.first_page[k];
-    if (off_lines > pages / 2 || !pages)
-        hipLaunchKernelGGL(pack_batch_kernel<true>, dim3(pages ? (pages * 4 + 63) / 64 * 64 : 1), dim3(64), 0, stream, bt, static_cast<uint8_t *>(image));
-    if (off_lines <= pages / 2)
-        hipLaunchKernelGGL(pack_batch_kernel<false>, dim3(pages ? pages * 4 : 1), dim3(64), 0, stream, bt, static_cast<uint8_t *>(image));
+    bt.make_groups(DSLLM_PACK_GROUPS_FROM, kMostPagesEach);
+    const bool runs = off_lines > pages / 2 || !pages, in_order = off_lines <= pages / 2;
+    auto launch = [&](const auto &args, auto runs_kernel, auto kernel) {
+        const unsigned kib = pages ? pages * 4 : 1;
+        if (runs) hipLaunchKernelGGL(runs_kernel, dim3((kib + 63) / 64 * 64), dim3(64), 0, stream, args, static_cast<uint8_t *>(image));
+        if (in_order) hipLaunchKernelGGL(kernel, dim3(kib), dim3(64), 0, stream, args, static_cast<uint8_t *>(image));
+    };
+    if (bt.count <= 32) launch(bt.shorter<32>(), pack_batch_kernel<true, 32>, pack_batch_kernel<false, 32>);
+    if ((bt.count > 32 && bt.count <= 128) || !pages) launch(bt.shorter<128>(), pack_batch_kernel<true, 128>, pack_batch_kernel<false, 128>);
+    if (bt.count > 128 || !pages) launch(static_cast<const PackArgs<kPackBatch> &>(bt), pack_batch_kernel<true, kPackBatch>, pack_batch_kernel<false, kPackBatch>);
     return hipGetLastError();
 }
 

@@ -19,28 +19,76 @@ constexpr uint64_t kPackPage = 4096;                  // the file format's align
 #endif
 constexpr uint32_t kPackBatchPages = DSLLM_PACK_BATCH_PAGES;
 
-struct PackBatch {
-    uint64_t src_pad[kPackBatch];          // address of the piece's first byte (48 bits), zero bytes behind its last one << 48
-    uint32_t first_page[kPackBatch + 1];   // page of the batch's image that the piece begins with; [count] = one past its last
-    uint32_t count;
+// A list of up to N pieces as a kernel's argument (under 4 KiB). A page's piece is between the first and the last one of its group of
+// 2^group_bits pages, where bisection finds it; with large tensors they are mostly the same.
+constexpr uint32_t kPackGroups = 32;
+struct PackSource { uint64_t src; uint32_t bytes; };       // a page's first byte, how many of its 4 KiB are the tensor's
+template <int N>
+struct PackArgs {
+    uint32_t pages, group_bits;
+    uint32_t group[kPackGroups];           // first piece of the group's pages, last piece << 16
+    uint64_t src_pad[N];                   // address of the piece's first byte (48 bits), zero bytes behind its last one << 48
+    uint32_t first_page[N + 1];            // page of the batch's image that the piece begins with; behind the last one: one past its last
 
-    DSLLM_HOST_DEVICE uint64_t src(uint32_t k) const { return src_pad[k] & 0xFFFFFFFFFFFFull; }
-    DSLLM_HOST_DEVICE uint32_t pad(uint32_t k) const { return uint32_t(src_pad[k] >> 48); }
-    DSLLM_HOST_DEVICE bool full() const { return count == uint32_t(kPackBatch) || first_page[count] == kPackBatchPages; }
-    void clear() { count = 0; first_page[0] = 0; }
-    // Takes as much of [addr, addr + nbytes) as there is room for (at least one page unless full()); returns the bytes taken.
-    uint64_t add(uint64_t addr, uint64_t nbytes) {
-        const uint64_t room = kPackBatchPages - first_page[count];
-        uint64_t pages = (nbytes + kPackPage - 1) / kPackPage;
-        uint64_t taken = nbytes;
-        if (pages > room) { pages = room; taken = room * kPackPage; }
-        src_pad[count] = addr | ((pages * kPackPage - taken) << 48);
-        first_page[count + 1] = first_page[count] + uint32_t(pages);
-        count++;
-        return taken;
+    DSLLM_HOST_DEVICE PackSource of(uint32_t page) const {
+        const uint32_t both = group[page >> group_bits];
+        uint32_t lo = both & 0xFFFF, hi = both >> 16;
+        while (lo < hi) {
+            const uint32_t mid = (lo + hi + 1) / 2;
+            if (first_page[mid] <= page) lo = mid;
+            else hi = mid - 1;
+        }
+        const uint64_t from = src_pad[lo];
+        const uint32_t first = first_page[lo], end = first_page[lo + 1];
+        return PackSource{(from & 0xFFFFFFFFFFFFull) + kPackPage * (page - first), uint32_t(kPackPage) - (page + 1 == end ? uint32_t(from >> 48) : 0)};
     }
 };
-static_assert(sizeof(PackBatch) <= 4000, "must fit the kernel argument segment with room to spare");
+static_assert(sizeof(PackArgs<kPackBatch>) <= 4000, "must fit the kernel argument segment with room to spare");
+
+struct PackBatch : PackArgs<kPackBatch> {
+    uint32_t count;
+
+    uint64_t src(uint32_t k) const { return src_pad[k] & 0xFFFFFFFFFFFFull; }
+    uint32_t pad(uint32_t k) const { return uint32_t(src_pad[k] >> 48); }
+    bool full() const { return count == uint32_t(kPackBatch) || pages == kPackBatchPages; }
+    void clear() { count = 0; pages = first_page[0] = 0; }
+    // Takes as much of [addr, addr + nbytes) as there is room for (at least one page unless full()); returns the bytes taken.
+    uint64_t add(uint64_t addr, uint64_t nbytes) {
+        const uint64_t room = kPackBatchPages - pages;
+        uint64_t n = (nbytes + kPackPage - 1) / kPackPage;
+        uint64_t taken = nbytes;
+        if (n > room) { n = room; taken = room * kPackPage; }
+        src_pad[count] = addr | ((n * kPackPage - taken) << 48);
+        pages = first_page[++count] = pages + uint32_t(n);
+        return taken;
+    }
+    // Few pages are one group: their kernel takes less than its launch, and this pass over the list would only make that longer. So
+    // are very large pieces (more than `most_pages_each` in the mean).
+    void make_groups(uint32_t from_pages, uint32_t most_pages_each) {
+        group_bits = 31;
+        group[0] = (count ? count - 1 : 0) << 16;
+        if (pages < from_pages || !count || pages / count > most_pages_each) return;
+        for (group_bits = 0; (pages - 1) >> group_bits >= kPackGroups;) group_bits++;
+        uint32_t k = 0;
+        for (uint32_t g = 0; uint64_t(g) << group_bits < pages; g++) {
+            const uint64_t begin = uint64_t(g) << group_bits, end = begin + (1ull << group_bits);
+            while (first_page[k + 1] <= begin) k++;
+            group[g] = k;
+            while (k + 1 < count && first_page[k + 1] < end) k++;
+            group[g] |= k << 16;
+        }
+    }
+    template <int N>
+    PackArgs<N> shorter() const {          // count is at most N
+        PackArgs<N> a;
+        a.pages = pages;
+        a.group_bits = group_bits;
+        for (uint32_t g = 0; g < kPackGroups; g++) a.group[g] = group[g];
+        for (uint32_t k = 0; k < count; k++) { a.src_pad[k] = src_pad[k]; a.first_page[k] = first_page[k]; }
+        a.first_page[count] = pages;
+        return a;
+    }
+};
 
 // tiles the padded extent of a tensor at data-region offset d0 is cut into (cuts at its start and at every multiple of tile_bytes)
 inline uint64_t tiles_of(uint64_t d0, uint64_t nbytes, uint64_t tile_bytes) {
