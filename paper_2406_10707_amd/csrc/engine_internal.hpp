@@ -135,6 +135,16 @@ constexpr uint64_t kReadPieceBytes = kPieceBytes / 4 < 4096 ? 4096 : kPieceBytes
 // copy, two hide that from each other: 57.0 GB/s to the device in pieces of 4 MiB (one stream 50.4, whole chunks 57.6), 56.4 to the
 // host in parts of 16 MiB (55.1, 57.1).
 constexpr uint64_t kSendBytes = kPieceBytes, kPartBytes = 4 * kPieceBytes;
+// A snapshot's last chunk (its only one, if it has one) goes in up to twelve parts of 2 to 16 MiB, and a part is written in four pieces while the next
+// ones land: what is left behind the last copy is a part of that, shared by the I/O threads. The first part is half as long as the others, as copies of
+// two streams share the link and equal ones land in pairs. Request to committed file, as one copy / in 8 equal parts / in 8 / in 12:
+//   5.5 MB 398, 285, 262, 265 us     21 MB 887, 669, 620, 606     37 MB 1455, 963, 1008, 939     64 MB 2100, 1556, 1584, 1428
+// 107 MB in a chunk of 256 MiB 3323, 2476, 2407, 2284; in two of 64 MiB, where parts of 16 MiB were the rule, 2497, 2245, 2275, 2242.
+constexpr int kFineParts = 12;
+inline uint64_t fine_part_bytes(uint64_t chunk_bytes) {
+    const uint64_t unit = std::max<uint64_t>(kPieceBytes / 4 / kAlign * kAlign, kAlign);
+    return std::min(kPartBytes, std::max(2 * unit, (chunk_bytes / (kFineParts - 1) + unit) / unit * unit));
+}
 // On restore, chunks of at least this size are sent to the device piece by piece, and each is scattered by a launch of its own as soon as it
 // is there. Smaller ones are sent whole and scattered together up to this size: a launch and its wait cost the
 // calling thread as much as the copy of a MiB takes. 250 MiB restored in chunks of 256 KiB 25.2 -> 17.2 ms, of 1 MiB 7.7 -> 6.4
@@ -175,6 +185,7 @@ struct ckpt_ctx {
     std::vector<hipEvent_t> ev_slot;                      // per ring slot: copy into or out of the slot done
     std::vector<std::vector<hipEvent_t>> ev_sent;         // restore in chunks that may be sent on several streams, [dma stream - 1][slot]: the other streams' copies
     std::vector<std::vector<hipEvent_t>> ev_part;         // [chunks from the end][part]: part of one of a snapshot's last chunks
+    std::vector<hipEvent_t> ev_fine;                      // smaller parts of a snapshot's last chunk
     // restore: what the stream had to copy when the slot's chunk was sent (whichever stream that is, if it is always one)
     hipEvent_t sent_event(size_t stream, uint64_t slot) const { return stream == 0 || ev_sent.empty() ? ev_slot[slot] : ev_sent[stream - 1][slot]; }
     bool shares_last_chunks() const { return dma.size() > 1 && cfg.dma_chunk_bytes > dsllm::kPartBytes; }

@@ -6,10 +6,13 @@ using namespace dsllm;
 
 // A data region this small is packed straight into its ring slot over the link: the copy engine's start and the event
 // between kernel and copy cost more than they bring. Request to committed file, staged -> straight: 64 KiB 116 -> 88 us,
-// 1 MiB 156 -> 135, 4 MiB 316 -> 296, 8 MiB 400 -> 385, 16 MiB 586 -> 593 (the kernel's stores reach the copy engines'
+// 1 MiB 156 -> 135, 4 MiB 316 -> 296, 8 MiB 400 -> 385, 16 MiB 586 -> 593 (with neither's file written in parts; the kernel's stores reach the copy engines'
 // rate but hold compute units meanwhile, so the line is drawn where the gain is still several per cent). Not under
 // policy PACK, whose window closes with the pack kernel: writing to device memory ends sooner.
 constexpr uint64_t kStraightBytes = 4ull << 20;
+// Its pieces for the I/O threads: a quarter each, half a MiB at least. As one piece, which one thread writes, and in pieces:
+// 1.7 MB 204 -> 158 us, 3.3 MB 292 -> 205, 4.3 MB 355 -> 250; below a MiB a second thread's waking takes as long as the writing.
+constexpr uint64_t kStraightPieces = 2ull << 20;
 static bool packs_straight_into_ring(const Plan &p, int policy) {
     return policy == CKPT_WINDOW_D2H && p.n_chunks == 1 && p.data_bytes <= kStraightBytes && p.segs.size() == 1 && p.segs[0].kind == CKPT_SEG_STAGED;
 }
@@ -145,9 +148,11 @@ static void submit_one(ckpt_ctx *c, const std::shared_ptr<Snap> &sp) {
         c->slot_state[slot] = SLOT_BUSY;
         return slot;
     };
-    // chunk ch goes to the file; its arrival in `slot` is ev_slot[slot], or part by part the events in `parts`
-    auto hand_to_io = [&](uint64_t ch, uint64_t slot, const hipEvent_t *parts = nullptr) {
-        const uint64_t nbytes = p.chunk_bytes(ch), n_pieces = (nbytes + kPieceBytes - 1) / kPieceBytes;
+    // Chunk ch goes to the file, in four pieces for every part_bytes of it; its arrival in `slot` is ev_slot[slot], or part by part the events
+    // in `parts`. The first part is shorter by `less`.
+    auto hand_to_io = [&](uint64_t ch, uint64_t slot, uint64_t part_bytes = kPartBytes, const hipEvent_t *parts = nullptr, uint64_t less = 0) {
+        const uint64_t piece_bytes = (part_bytes / 4 + kAlign - 1) / kAlign * kAlign;
+        const uint64_t nbytes = p.chunk_bytes(ch), n_pieces = (nbytes + piece_bytes - 1) / piece_bytes;
         {
             std::lock_guard<std::mutex> lk(c->mu);
             c->slot_pieces_left[slot] = uint32_t(n_pieces);
@@ -156,12 +161,12 @@ static void submit_one(ckpt_ctx *c, const std::shared_ptr<Snap> &sp) {
                 job.kind = IoJob::WRITE;
                 job.snap = sp;
                 job.slot = slot;
-                job.slot_off = q * kPieceBytes;
+                job.slot_off = q * piece_bytes;
                 job.file_off = p.header_bytes + ch * CH + job.slot_off;
-                job.nbytes = std::min<uint64_t>(kPieceBytes, nbytes - job.slot_off);
+                job.nbytes = std::min<uint64_t>(piece_bytes, nbytes - job.slot_off);
                 job.last = ch + 1 == p.n_chunks && q == (parts ? n_pieces - 1 : 0);
                 job.ends = ch + 1 == p.n_chunks && (parts || job.last);
-                job.landed = parts ? parts[job.slot_off / kPartBytes] : c->ev_slot[slot];
+                job.landed = parts ? parts[(job.slot_off + less) / part_bytes] : c->ev_slot[slot];
                 c->io_q.push_back(std::move(job));
             }
         }
@@ -188,7 +193,7 @@ static void submit_one(ckpt_ctx *c, const std::shared_ptr<Snap> &sp) {
         if ((e = hipEventRecord(c->ev_slot[slot], c->pack_stream)) != hipSuccess) hip_fail("record", e);
         for (size_t k = 0; k < nk; k++)
             if ((e = hipEventRecord(c->ev_job_tail[k], c->pack_stream)) != hipSuccess) hip_fail("record", e);
-        hand_to_io(0, slot);
+        hand_to_io(0, slot, std::max(p.data_bytes, kStraightPieces));
         all_submitted();
         return;
     }
@@ -240,11 +245,16 @@ static void submit_one(ckpt_ctx *c, const std::shared_ptr<Snap> &sp) {
     // chunks of more than 64 MiB: beside the training step every copy more costs the system runtime some 40 us (1.74 GB in chunks of
     // 256 MiB, the last three in parts: copies at 55.8 GB/s instead of 56.6), and the end is little of the whole there. In chunks of 64 MiB the
     // copies beside the step pay too, 55.3 GB/s instead of 55.9, with the same stall; alone the file is committed sooner, 0.2 GB 4.6 -> 4.1 ms,
-    // 1 GB 20.0 -> 19.6 (in chunks of 256 MiB 22.0 -> 19.8), 1.7 GB 31.9 -> 31.5. Two chunks in parts cost as much as three, one gains nothing.
+    // 1 GB 20.0 -> 19.6 (in chunks of 256 MiB 22.0 -> 19.8), 1.7 GB 31.9 -> 31.5. Two chunks in parts cost as much as three. The last one's parts are
+    // smaller (kFineParts), and so are a single chunk's, whatever its size.
     uint64_t shared = 0;
-    if (c->shares_last_chunks() && p.n_chunks > 1 && (CH <= 4 * kPartBytes || p.n_chunks <= 2 * (nk + 1))) {
+    uint64_t fine_bytes = 0;         // of the last chunk's parts, if they are smaller than the others'
+    if (p.n_chunks == 1 ? !c->ev_fine.empty() : c->shares_last_chunks() && (CH <= 4 * kPartBytes || p.n_chunks <= 2 * (nk + 1))) {
         std::lock_guard<std::mutex> lk(c->mu);
-        if (!c->prev_job || c->prev_job->committed) shared = std::min<uint64_t>(p.n_chunks, nk + 1);
+        if (!c->prev_job || c->prev_job->committed) {
+            shared = std::min<uint64_t>(p.n_chunks, nk + 1);
+            fine_bytes = fine_part_bytes(p.chunk_bytes(p.n_chunks - 1));
+        }
     }
     for (uint64_t sc = 0; sc < std::min<uint64_t>(ahead, p.n_superchunks); sc++) enqueue_pack(sc);
     for (uint64_t sc = 0; sc < p.n_superchunks; sc++) {
@@ -267,9 +277,11 @@ static void submit_one(ckpt_ctx *c, const std::shared_ptr<Snap> &sp) {
             // the chunk's segments: packed bytes out of staging, large tensors out of their own memory,
             // the padding behind those zero-filled here (the slot belongs to this thread until the copy event)
             uint8_t *slot_base = c->ring + slot * CH;
-            const uint64_t part_bytes = in_parts ? kPartBytes : CH;
+            const bool fine = in_parts && ch + 1 == p.n_chunks && fine_bytes < kPartBytes;
+            const uint64_t part_bytes = fine ? fine_bytes : in_parts ? kPartBytes : CH;
+            const uint64_t less = fine ? part_bytes / 2 / kAlign * kAlign : 0;       // by which the first part is shorter than the others
             uint64_t part = 0;
-            const hipEvent_t *parts = in_parts ? c->ev_part[p.n_chunks - 1 - ch].data() : nullptr;
+            const hipEvent_t *parts = fine ? c->ev_fine.data() : in_parts ? c->ev_part[p.n_chunks - 1 - ch].data() : nullptr;
             for (uint64_t j = p.chunk_first_seg[ch]; j < p.chunk_first_seg[ch + 1]; j++) {
                 const ckpt_segment &sg = p.segs[j];
                 const uint64_t at = sg.data_off - ch * CH;
@@ -283,16 +295,16 @@ static void submit_one(ckpt_ctx *c, const std::shared_ptr<Snap> &sp) {
                 const void *src = sg.kind == CKPT_SEG_DIRECT ? reinterpret_cast<const void *>(sg.src)
                                                              : static_cast<const void *>(stage_base + (sg.data_off - sc * SC));
                 for (uint64_t done = 0; done < sg.nbytes;) {
-                    for (; part < (at + done) / part_bytes; part++)      // every copy of an earlier part is enqueued
+                    for (; part < (at + done + less) / part_bytes; part++)      // every copy of an earlier part is enqueued
                         if ((e = hipEventRecord(parts[part], c->dma[(k + part) % nk])) != hipSuccess) hip_fail("record", e);
-                    const uint64_t n = std::min(sg.nbytes - done, (part + 1) * part_bytes - (at + done));
+                    const uint64_t n = std::min(sg.nbytes - done, (part + 1) * part_bytes - less - (at + done));
                     e = hipMemcpyAsync(dst + done, static_cast<const uint8_t *>(src) + done, n, hipMemcpyDeviceToHost, c->dma[(k + part) % nk]);
                     if (e != hipSuccess) hip_fail("hipMemcpyAsync D2H", e);
                     done += n;
                 }
             }
             if (in_parts) {
-                for (; part * part_bytes < p.chunk_bytes(ch); part++)
+                for (; part * part_bytes < p.chunk_bytes(ch) + less; part++)
                     if ((e = hipEventRecord(parts[part], c->dma[(k + part) % nk])) != hipSuccess) hip_fail("record", e);
             } else if ((e = hipEventRecord(c->ev_slot[slot], c->dma[k])) != hipSuccess) hip_fail("record", e);
             const bool last = ch + 1 == p.n_chunks;
@@ -302,7 +314,7 @@ static void submit_one(ckpt_ctx *c, const std::shared_ptr<Snap> &sp) {
             if (last)
                 for (size_t kk = 0; kk < nk; kk++)
                     if ((e = hipEventRecord(c->ev_job_tail[kk], c->dma[kk])) != hipSuccess) hip_fail("record", e);
-            hand_to_io(ch, slot, parts);
+            hand_to_io(ch, slot, in_parts ? part_bytes : kPartBytes, parts, less);
         }
         // The next pack launch goes out one round late, after this super-chunk's copies have been enqueued: its host-side
         // wait is for the copies of the previous super-chunk, and the copy engines have this one's to go on with. The
