@@ -89,7 +89,7 @@ def parse_args():
                          "torch_runtime block of the JSON line. 0: skip")
     ap.add_argument("--pack-only", type=int, default=0,
                     help="N > 0: no snapshot engine, no proxy; N calls of ckpt_pack_image over the whole workload (a launch of its "
-                         "kernel for every 320 tensors) after one 4 GiB launch of the plain copy kernel. For rocprofv3 runs of the pack kernel alone: "
+                         "kernel for up to 1280 tensors) after one 4 GiB launch of the plain copy kernel. For rocprofv3 runs of the pack kernel alone: "
                          "kernel durations and, with --pmc, HBM traffic, the copy kernel being the counters' calibration")
     ap.add_argument("--dump", default="", help="write per-step timings and per-snapshot measurements to this JSON file")
     return ap.parse_args()

@@ -358,7 +358,7 @@ int ckpt_describe_file(const char *path, char *buf, size_t cap, size_t *needed_o
  * only dev_ptr (any byte alignment) and nbytes (> 0) are read; name, dtype and shape are ignored. Tensors
  * and destination must be device memory of the CURRENT device (hipSetDevice), inside their allocations;
  * dev_dst 16-byte aligned, dst_bytes at least the size of the data region; source and destination must
- * not overlap. The descriptors travel in kernel arguments, 320 tensors a launch: nothing is allocated. The call
+ * not overlap. The descriptors travel in kernel arguments, up to 1280 tensors a launch: nothing is allocated. The call
  * enqueues on hip_stream (after whatever is already there) and waits for the stream. CKPT_EINVAL for a bad argument
  * (nothing is launched then), CKPT_EHIP. */
 int ckpt_pack_image(const ckpt_tensor_desc *tensors, size_t n, void *dev_dst, uint64_t dst_bytes, void *hip_stream);

@@ -315,8 +315,9 @@ constexpr uint32_t kMostPagesEach = 4096;
 
 // Writes the pieces of `bt` to `image`, which begins with the page of the batch's first piece. A batch without pieces
 // launches one block of every kernel that finds nothing to do (it makes the runtime load the kernels' code). The arguments
-// have three sizes, as a launch takes the host longer with more bytes of them: 12 tensors 3.4 us with 4 KB, 3.1 with 0.5.
-hipError_t launch_pack_batch(PackBatch &bt, void *image, hipStream_t stream) {
+// have four sizes, as a launch takes the host longer with more bytes of them: 12 tensors 3.4 us with 4 KB, 3.1 with 0.5.
+template <int MOST>
+static hipError_t launch_batch(PackBatchOf<MOST> &bt, void *image, hipStream_t stream) {
     const uint32_t pages = bt.pages;
     uint32_t off_lines = 0;      // pages of tensors that do not start on a 128-byte line
     if (pages >= DSLLM_PACK_RUNS_FROM)
@@ -329,11 +330,16 @@ hipError_t launch_pack_batch(PackBatch &bt, void *image, hipStream_t stream) {
         if (runs) hipLaunchKernelGGL(runs_kernel, dim3((kib + 63) / 64 * 64), dim3(64), 0, stream, args, static_cast<uint8_t *>(image));
         if (in_order) hipLaunchKernelGGL(kernel, dim3(kib), dim3(64), 0, stream, args, static_cast<uint8_t *>(image));
     };
-    if (bt.count <= 32) launch(bt.shorter<32>(), pack_batch_kernel<true, 32>, pack_batch_kernel<false, 32>);
-    if ((bt.count > 32 && bt.count <= 128) || !pages) launch(bt.shorter<128>(), pack_batch_kernel<true, 128>, pack_batch_kernel<false, 128>);
-    if (bt.count > 128 || !pages) launch(static_cast<const PackArgs<kPackBatch> &>(bt), pack_batch_kernel<true, kPackBatch>, pack_batch_kernel<false, kPackBatch>);
+    if (bt.count <= 32) launch(bt.template shorter<32>(), pack_batch_kernel<true, 32>, pack_batch_kernel<false, 32>);
+    if ((bt.count > 32 && bt.count <= 128) || !pages) launch(bt.template shorter<128>(), pack_batch_kernel<true, 128>, pack_batch_kernel<false, 128>);
+    if ((bt.count > 128 && bt.count <= uint32_t(kPackBatch)) || !pages)
+        launch(bt.template shorter<kPackBatch>(), pack_batch_kernel<true, kPackBatch>, pack_batch_kernel<false, kPackBatch>);
+    if constexpr (MOST > kPackBatch)
+        if (bt.count > uint32_t(kPackBatch) || !pages) launch(static_cast<const PackArgs<MOST> &>(bt), pack_batch_kernel<true, MOST>, pack_batch_kernel<false, MOST>);
     return hipGetLastError();
 }
+hipError_t launch_pack_batch(PackBatch &bt, void *image, hipStream_t stream) { return launch_batch(bt, image, stream); }
+hipError_t launch_pack_batch(LongPackBatch &bt, void *image, hipStream_t stream) { return launch_batch(bt, image, stream); }
 
 static inline unsigned grid_for(uint64_t n_tiles) { return unsigned((n_tiles + kWavesPerBlock - 1) / kWavesPerBlock); }
 

@@ -12,6 +12,11 @@
 #include "../../paper_2406_10707_amd/csrc/plan.hpp"
 #include "build_tiles.hpp"
 
+#ifndef EMU_BATCH
+#define EMU_BATCH PackBatch
+#define EMU_PIECES kPackBatch
+#endif
+
 thread_local dim3 threadIdx, blockIdx, blockDim, gridDim;
 ssize_t emu_pwrite(int, const void *, size_t, off_t) { return -1; }   // no file is written here
 
@@ -42,12 +47,12 @@ int main(int argc, char **argv) {
 
     uint8_t *image = static_cast<uint8_t *>(aligned_alloc(4096, data));
     memset(image, 0xCC, data);
-    PackBatch bt;
+    EMU_BATCH bt;
     bt.clear();
     uint8_t *at = image;
     int launches = 0, full_pieces = 0, full_pages = 0;
     auto launch = [&] {
-        full_pieces += bt.count == uint32_t(kPackBatch);
+        full_pieces += bt.count == uint32_t(EMU_PIECES);
         full_pages += bt.first_page[bt.count] == kPackBatchPages;
         launch_pack_batch(bt, at, nullptr);
         at += kPackPage * bt.first_page[bt.count];
