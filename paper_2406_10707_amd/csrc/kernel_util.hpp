@@ -13,18 +13,15 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 // count against two wait counters). Casting to the global address space gives global_load/store.
 #if defined(__HIP_DEVICE_COMPILE__)
 #define DSLLM_GLOBAL __attribute__((address_space(1)))
-// Keeps a loaded 16-byte word whole and in registers of its own. Without it the compiler narrows the
-// two loads of the misaligned path to the dwords the shift uses and packs them into overlapping
-// registers, which forces a wait after every pair of loads.
-#define DSLLM_KEEP_WHOLE(v) asm volatile("" : "+v"(v))
 #else
 #define DSLLM_GLOBAL
-#define DSLLM_KEEP_WHOLE(v) (void)0
 #endif
 __device__ __forceinline__ u32x4 ld16(const u32x4 *p) { return __builtin_nontemporal_load((const u32x4 DSLLM_GLOBAL *)p); }
 typedef u32x4 u32x4_bytealigned __attribute__((aligned(1)));
 // 16 bytes from any byte address; all 16 must lie inside the tensor
 __device__ __forceinline__ u32x4 ld16_unaligned(const uint8_t *p) { return __builtin_nontemporal_load((const u32x4_bytealigned DSLLM_GLOBAL *)p); }
+// 16 bytes to any byte address; all 16 must lie inside the tensor
+__device__ __forceinline__ void st16_unaligned(uint8_t *p, u32x4 v) { __builtin_nontemporal_store(v, (u32x4_bytealigned DSLLM_GLOBAL *)p); }
 __device__ __forceinline__ void st16(u32x4 *p, u32x4 v) { __builtin_nontemporal_store(v, (u32x4 DSLLM_GLOBAL *)p); }
 
 // A value that is the same in every lane of the wavefront, moved to scalar registers. The builtin
