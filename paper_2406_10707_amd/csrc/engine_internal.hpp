@@ -129,6 +129,7 @@ struct IoJob {
 #define DSLLM_PIECE_BYTES (4ull << 20)   // a multiple of 4 KiB
 #endif
 constexpr uint64_t kPieceBytes = DSLLM_PIECE_BYTES;
+static_assert(kPieceBytes > 0 && kPieceBytes % 4096 == 0, "pieces and parts begin on the format's alignment unit (direct I/O)");
 // On restore, where the copy streams take pieces in turn, pieces are a quarter of that, except for direct I/O: the link waits for the
 // first one, and four threads that read 4 MiB each bring none for 0.3 ms and then four at once.
 constexpr uint64_t kReadPieceBytes = kPieceBytes / 4 < 4096 ? 4096 : kPieceBytes / 4 / 4096 * 4096;

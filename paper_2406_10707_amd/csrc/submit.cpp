@@ -148,27 +148,29 @@ static void submit_one(ckpt_ctx *c, const std::shared_ptr<Snap> &sp) {
         c->slot_state[slot] = SLOT_BUSY;
         return slot;
     };
-    // Chunk ch goes to the file, in four pieces for every part_bytes of it; its arrival in `slot` is the event `whole`, or part by part those
-    // in `parts`. The first part is shorter by `less`.
-    auto hand_to_io = [&](uint64_t ch, uint64_t slot, hipEvent_t whole, uint64_t part_bytes = kPartBytes, const hipEvent_t *parts = nullptr, uint64_t less = 0) {
-        const uint64_t piece_bytes = (part_bytes / 4 + kAlign - 1) / kAlign * kAlign;
-        const uint64_t nbytes = p.chunk_bytes(ch), n_pieces = (nbytes + piece_bytes - 1) / piece_bytes;
+    // Chunk ch goes to the file in pieces of at most piece_bytes. Its arrival in `slot` is the event `whole`, or part by part those in
+    // `parts`, the first part shorter by `less` than the part_bytes of the others. A piece ends where its part does: it waits for one event.
+    auto hand_to_io = [&](uint64_t ch, uint64_t slot, hipEvent_t whole, uint64_t piece_bytes = kPieceBytes, uint64_t part_bytes = 0, const hipEvent_t *parts = nullptr, uint64_t less = 0) {
+        const uint64_t nbytes = p.chunk_bytes(ch);
+        uint32_t n_pieces = 0;
         {
             std::lock_guard<std::mutex> lk(c->mu);
-            c->slot_pieces_left[slot] = uint32_t(n_pieces);
-            for (uint64_t q = 0; q < n_pieces; q++) {
+            for (uint64_t at = 0; at < nbytes; n_pieces++) {
+                const uint64_t part = parts ? (at + less) / part_bytes : 0;
                 IoJob job;
                 job.kind = IoJob::WRITE;
                 job.snap = sp;
                 job.slot = slot;
-                job.slot_off = q * piece_bytes;
-                job.file_off = p.header_bytes + ch * CH + job.slot_off;
-                job.nbytes = std::min<uint64_t>(piece_bytes, nbytes - job.slot_off);
-                job.last = ch + 1 == p.n_chunks && q == (parts ? n_pieces - 1 : 0);
+                job.slot_off = at;
+                job.file_off = p.header_bytes + ch * CH + at;
+                job.nbytes = std::min(piece_bytes, (parts ? std::min(nbytes, (part + 1) * part_bytes - less) : nbytes) - at);
+                job.landed = parts ? parts[part] : whole;
+                at += job.nbytes;
+                job.last = ch + 1 == p.n_chunks && (parts ? at == nbytes : job.slot_off == 0);
                 job.ends = ch + 1 == p.n_chunks && (parts || job.last);
-                job.landed = parts ? parts[(job.slot_off + less) / part_bytes] : whole;
                 c->io_q.push_back(std::move(job));
             }
+            c->slot_pieces_left[slot] = n_pieces;
         }
         if (n_pieces == 1) c->cv_io.notify_one();
         else c->cv_io.notify_all();
@@ -193,7 +195,7 @@ static void submit_one(ckpt_ctx *c, const std::shared_ptr<Snap> &sp) {
         if ((e = launch_pack(s->dev_tiles, p.tiles.size(), c->ring + slot * CH, 0, c->pack_stream, c->ev_pack_start[0], c->ev_pack_end[0])) != hipSuccess)
             hip_fail("pack launch", e);
         if ((e = hipEventRecord(c->ev_job_tail[0], c->pack_stream)) != hipSuccess) hip_fail("record", e);
-        hand_to_io(0, slot, c->ev_job_tail[0], std::max(p.data_bytes, kStraightPieces));
+        hand_to_io(0, slot, c->ev_job_tail[0], (std::max(p.data_bytes, kStraightPieces) / 4 + kAlign - 1) / kAlign * kAlign);
         all_submitted();
         return;
     }
@@ -314,7 +316,7 @@ static void submit_one(ckpt_ctx *c, const std::shared_ptr<Snap> &sp) {
             if (last)
                 for (size_t kk = 0; kk < nk; kk++)
                     if ((e = hipEventRecord(c->ev_job_tail[kk], c->dma[kk])) != hipSuccess) hip_fail("record", e);
-            hand_to_io(ch, slot, c->ev_slot[slot], in_parts ? part_bytes : kPartBytes, parts, less);
+            hand_to_io(ch, slot, c->ev_slot[slot], ((in_parts ? part_bytes : kPartBytes) / 4 + kAlign - 1) / kAlign * kAlign, part_bytes, parts, less);
         }
         // The next pack launch goes out one round late, after this super-chunk's copies have been enqueued: its host-side
         // wait is for the copies of the previous super-chunk, and the copy engines have this one's to go on with. The

@@ -4,7 +4,8 @@
 //   restore  a restore hands a chunk's copies to the device while those of the chunk before it are under way, also when the
 //            ring's slots come round again
 //   events   a context has the events that its chunks and streams need
-//   emu_parts <dir> end|restore|events [<chunk bytes> <ring slots>]
+//   one      a shard of one chunk whose copies come late, one after the other: no piece is written before all of it has landed
+//   emu_parts <dir> end|restore|events|one [<chunk bytes> <ring slots>]
 #include <atomic>
 #include <chrono>
 #include <cstdio>
@@ -51,7 +52,7 @@ struct Run {
     ckpt_layout lay;
     hipStream_t compute;
 
-    Run(const std::string &dir, const std::vector<uint64_t> &sizes, uint64_t chunk, uint64_t slots, int io_threads) {
+    Run(const std::string &dir, const std::vector<uint64_t> &sizes, uint64_t chunk, uint64_t slots, int io_threads, int policy = CKPT_WINDOW_D2H) {
         for (uint64_t n : sizes) { t.emplace_back((n + 15) / 16 * 16); shapes.push_back(int64_t(n)); names.push_back("t" + std::to_string(names.size())); }
         std::vector<ckpt_tensor_desc> descs;
         for (size_t k = 0; k < t.size(); k++) {
@@ -67,6 +68,7 @@ struct Run {
         cfg.n_dma_streams = 2;
         cfg.n_io_threads = io_threads;
         cfg.io_mode = CKPT_IO_PWRITE;
+        cfg.window_policy = policy;
         REQUIRE(ckpt_init(&cfg, &ctx) == CKPT_OK);
         REQUIRE(ckpt_register_tensors(ctx, descs.data(), descs.size()) == CKPT_OK);
         REQUIRE(ckpt_get_layout(ctx, &lay) == CKPT_OK);
@@ -187,12 +189,33 @@ static void events(const std::string &dir) {
     REQUIRE(events_of(dir, 40 << 20, 2, 2) - events_of(dir, 16 << 20, 2, 2) == 3 * 3);                           // three chunks, three parts
 }
 
+// Policy PACK: a chunk this small would be packed straight into its slot under the other one. Sizes that leave parts of every
+// length in pages, and pieces that don't divide them.
+static void one_chunk(const std::string &dir, uint64_t chunk) {
+    for (uint64_t pages : {chunk / 4096, chunk / 4096 - 1, chunk / 4096 * 3 / 4, chunk / 8192 + 3, chunk / 16384 + 1}) {
+        Run r(dir, {4096 * pages - 4096 * 2 - 5, 4096, 77}, chunk, 2, 3, CKPT_WINDOW_PACK);
+        REQUIRE(r.lay.n_chunks == 1);
+        for (uint64_t it = 1; it <= 2; it++) {
+            g_emu_copy_hook = [](const void *, size_t, hipMemcpyKind kind, bool starts) {
+                if (kind == hipMemcpyDeviceToHost && starts) std::this_thread::sleep_for(std::chrono::milliseconds(5));
+            };
+            r.snapshot(it);
+            REQUIRE(ckpt_wait_immutable_window_end(r.ctx, r.compute, 0) == CKPT_OK);
+            REQUIRE(ckpt_flush(r.ctx, it) == CKPT_OK);
+            g_emu_copy_hook = nullptr;
+        }
+        r.restored(1);
+        r.restored(2);
+    }
+}
+
 int main(int argc, char **argv) {
     if (argc < 3) return 2;
     const std::string dir = argv[1], what = argv[2];
     if (what == "end") end_of_copies(dir);
     else if (what == "restore" && argc > 4) restore(dir, strtoull(argv[3], nullptr, 10), strtoull(argv[4], nullptr, 10));
     else if (what == "events") events(dir);
+    else if (what == "one" && argc > 3) one_chunk(dir, strtoull(argv[3], nullptr, 10));
     else return 2;
     printf("ok %s\n", what.c_str());
     return 0;

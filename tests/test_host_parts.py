@@ -41,3 +41,11 @@ def test_a_restore_keeps_two_chunks_under_way(emu, tmp_path, chunk, slots):
 
 def test_a_context_has_the_events_that_it_uses(tmp_path_factory, tmp_path):
     _run(_build(tmp_path_factory, "address,undefined"), tmp_path, "events")
+
+
+# pieces whose quarters are whole pages and pieces whose quarters are not, chunks of fewer and of more pages than four times the parts
+@pytest.mark.parametrize("piece", [4096, 8192, 12288, 16384])
+def test_no_piece_is_written_before_it_has_landed(tmp_path_factory, tmp_path, piece):
+    emu = _build(tmp_path_factory, "thread", "-DDSLLM_PIECE_BYTES=%dull" % piece)
+    for chunk in (64 << 10, 256 << 10, 416 << 10):
+        _run(emu, tmp_path, "one", chunk)
