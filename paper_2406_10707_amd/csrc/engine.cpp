@@ -493,9 +493,9 @@ int ckpt_wait_immutable_window_end(ckpt_ctx *c, void *stream, int32_t host_block
         HIP_TRY(c, hipStreamWaitEvent(st, ev, 0));
         if (host_block) HIP_TRY(c, hipEventSynchronize(ev));
     } else {
-        for (size_t k = 0; k < c->tails(sp.get()); k++) HIP_TRY(c, hipStreamWaitEvent(st, c->ev_job_tail[k], 0));
+        for (size_t k = 0; k < c->tails(sp.get()); k++) HIP_TRY(c, hipStreamWaitEvent(st, c->tail(sp.get(), k), 0));
         if (host_block)
-            for (size_t k = 0; k < c->tails(sp.get()); k++) HIP_TRY(c, hipEventSynchronize(c->ev_job_tail[k]));
+            for (size_t k = 0; k < c->tails(sp.get()); k++) HIP_TRY(c, hipEventSynchronize(c->tail(sp.get(), k)));
     }
     std::lock_guard<std::mutex> lk(c->mu);
     sp->window_closed = true;

@@ -97,7 +97,8 @@ struct Snap {
     std::atomic<uint64_t> io_wait_us{0}, io_copy_us{0};   // summed over the I/O threads
     double pack_ms_sum = -1, req_to_d2h_end_ms = -1, d2h_span_ms = -1, req_to_pack_end_ms = -1;
     std::vector<uint8_t> host_capture;      // the host-resident objects as they were when the snapshot was requested
-    bool straight = false;                  // the pack kernel wrote the ring slot: ev_job_tail[0], behind it, is this snapshot's only event
+    bool straight = false;                  // the pack kernel wrote ring slot `straight_slot`: the slot's event, behind it, is this snapshot's only one
+    uint64_t straight_slot = 0;
     bool head_apart = false;                // the first super-chunk was packed in two launches (its first chunk, the rest)
     int policy = CKPT_WINDOW_D2H;           // window policy in force when the snapshot was requested
     int tier2_state = CKPT_TIER2_NONE;      // ckpt_tier2_state
@@ -194,7 +195,10 @@ struct ckpt_ctx {
     std::vector<hipEvent_t> ev_pack_start, ev_pack_end, ev_packed;   // per super-chunk: the kernel's start and end (timing), its completion in the pack stream (ordering)
     std::vector<std::vector<hipEvent_t>> ev_stage_done;   // [stage slot][dma stream]
     std::vector<hipEvent_t> ev_job_tail;                  // per dma stream
-    size_t tails(const Snap *s) const { return s->straight ? 1 : dma.size(); }      // how many of them the snapshot's copies end with
+    // The events that the snapshot's copies end with. A slot's event is not recorded again before the slot has been written; ev_job_tail are
+    // the next snapshot's as soon as the copies are over.
+    size_t tails(const Snap *s) const { return s->straight ? 1 : dma.size(); }
+    hipEvent_t tail(const Snap *s, size_t k) const { return s->straight ? ev_slot[s->straight_slot] : ev_job_tail[k]; }
     hipEvent_t ev_first_copy = nullptr, ev_user = nullptr;
     hipEvent_t ev_packed_head = nullptr;                  // the first chunk of a snapshot is in staging
     hipEvent_t ev_head_end = nullptr, ev_rest_start = nullptr;   // timing of the first super-chunk's two launches, between ev_pack_start[0] and ev_pack_end[0]

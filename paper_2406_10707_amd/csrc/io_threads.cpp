@@ -16,10 +16,10 @@ static void finish_d2h_stats(ckpt_ctx *c, Snap *s) {
         if (parts) add_launch(c->ev_pack_start[0], c->ev_head_end);
         add_launch(parts ? c->ev_rest_start : c->ev_pack_start[i], c->ev_pack_end[i]);
     }
-    const hipEvent_t first_copy = s->straight ? c->ev_pack_start[0] : c->ev_first_copy, packed = s->straight ? c->ev_job_tail[0] : c->ev_packed[n_sc - 1];
+    const hipEvent_t first_copy = s->straight ? c->ev_pack_start[0] : c->ev_first_copy, packed = s->straight ? c->tail(s, 0) : c->ev_packed[n_sc - 1];
     for (size_t k = 0; k < c->tails(s); k++) {
-        if (hipEventElapsedTime(&ms, s->ev_boundary, c->ev_job_tail[k]) == hipSuccess && ms > req_d2h) req_d2h = ms;
-        if (hipEventElapsedTime(&ms, first_copy, c->ev_job_tail[k]) == hipSuccess && ms > span) span = ms;
+        if (hipEventElapsedTime(&ms, s->ev_boundary, c->tail(s, k)) == hipSuccess && ms > req_d2h) req_d2h = ms;
+        if (hipEventElapsedTime(&ms, first_copy, c->tail(s, k)) == hipSuccess && ms > span) span = ms;
     }
     if (hipEventElapsedTime(&ms, s->ev_boundary, packed) == hipSuccess) req_pack = ms;
     std::lock_guard<std::mutex> lk(c->mu);
@@ -119,7 +119,7 @@ void dsllm::io_thread_main(ckpt_ctx *c) {
         if (job.ends && !s->copies_over) {
             bool over = true;
             for (size_t k = 0; over && !s->copies_over && k < c->tails(s); k++) {   // (once another thread has seen it the events may be the next one's)
-                he = job.last ? hipEventSynchronize(c->ev_job_tail[k]) : hipEventQuery(c->ev_job_tail[k]);
+                he = job.last ? hipEventSynchronize(c->tail(s, k)) : hipEventQuery(c->tail(s, k));
                 if (he == hipSuccess) continue;
                 if (job.last) c->fail_snapshot(s, CKPT_EHIP, std::string("tail event: ") + hipGetErrorString(he));
                 else over = false;                 // not yet, or an error that the last piece will report

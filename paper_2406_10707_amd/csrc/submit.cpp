@@ -37,7 +37,7 @@ static void submit_one(ckpt_ctx *c, const std::shared_ptr<Snap> &sp) {
     // one snapshot's copies at a time: the previous one's last copy is over before this one's
     // boundary on the device timeline anyway (the caller closed its window), so this costs nothing there
     if (c->prev_job) {
-        for (size_t k = 0; k < c->tails(c->prev_job.get()); k++) if ((e = hipEventSynchronize(c->ev_job_tail[k])) != hipSuccess) hip_fail("tail sync", e);
+        for (size_t k = 0; k < c->tails(c->prev_job.get()); k++) if ((e = hipEventSynchronize(c->tail(c->prev_job.get(), k))) != hipSuccess) hip_fail("tail sync", e);
         std::unique_lock<std::mutex> lk(c->mu);
         // with retention the previous commit is also what retires an older file into the spare pool this
         // snapshot is about to draw from: wait for it (it follows the last copy by one chunk write)
@@ -192,10 +192,11 @@ static void submit_one(ckpt_ctx *c, const std::shared_ptr<Snap> &sp) {
         // request to committed file 0.46 MB 129..137 -> 110..114 us, 0.5 MB 123..140 -> 105..122, 1.7 MB 140..154 -> 136..148, 3.4 MB even.
         const uint64_t slot = take_slot();
         s->straight = true;
+        s->straight_slot = slot;
         if ((e = launch_pack(s->dev_tiles, p.tiles.size(), c->ring + slot * CH, 0, c->pack_stream, c->ev_pack_start[0], c->ev_pack_end[0])) != hipSuccess)
             hip_fail("pack launch", e);
-        if ((e = hipEventRecord(c->ev_job_tail[0], c->pack_stream)) != hipSuccess) hip_fail("record", e);
-        hand_to_io(0, slot, c->ev_job_tail[0], (std::max(p.data_bytes, kStraightPieces) / 4 + kAlign - 1) / kAlign * kAlign);
+        if ((e = hipEventRecord(c->ev_slot[slot], c->pack_stream)) != hipSuccess) hip_fail("record", e);
+        hand_to_io(0, slot, c->ev_slot[slot], (std::max(p.data_bytes, kStraightPieces) / 4 + kAlign - 1) / kAlign * kAlign);
         all_submitted();
         return;
     }

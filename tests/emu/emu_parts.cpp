@@ -5,7 +5,9 @@
 //            ring's slots come round again
 //   events   a context has the events that its chunks and streams need
 //   one      a shard of one chunk whose copies come late, one after the other: no piece is written before all of it has landed
-//   emu_parts <dir> end|restore|events|one [<chunk bytes> <ring slots>]
+//   straight a shard that is packed straight into its slot and written in pieces, behind a slow sink: the file is committed
+//            while the next snapshot, which the end of these copies has let start, is held on its stream
+//   emu_parts <dir> end|restore|events|one|straight [<chunk bytes> <ring slots>]
 #include <atomic>
 #include <chrono>
 #include <cstdio>
@@ -209,12 +211,46 @@ static void one_chunk(const std::string &dir, uint64_t chunk) {
     }
 }
 
+// One I/O thread, held at its first piece until the next snapshot has been submitted; the next snapshot's stream is held
+// until the first file has been committed.
+static std::atomic<hipStream_t> g_compute{nullptr};
+static std::atomic<bool> g_hold{false}, g_release{false};
+static void straight(const std::string &dir) {
+    Run r(dir, {3 << 20, 400000, 17}, 4 << 20, 3, 1);
+    REQUIRE(r.lay.n_chunks == 1);
+    std::atomic<int> pieces{0};
+    ckpt_stats st;
+    g_before_write = [&](off_t off) {
+        if (off < off_t(r.lay.header_bytes) || g_release) return;
+        if (pieces++ == 0) REQUIRE(comes_true([&] { return ckpt_get_stats(r.ctx, 2, &st) == CKPT_OK && st.host_submit_ms >= 0; }));
+    };
+    r.snapshot(1);
+    REQUIRE(ckpt_wait_immutable_window_end(r.ctx, r.compute, 1) == CKPT_OK);
+    g_compute = r.compute;
+    g_hold = true;
+    g_emu_submit_hook = [](hipStream_t s) {
+        if (s && s != g_compute && g_hold.exchange(false)) s->push([] { comes_true([] { return g_release.load(); }); });
+    };
+    r.snapshot(2);
+    ckpt_stats first;
+    const bool committed = comes_true([&] { return ckpt_get_stats(r.ctx, 1, &first) == CKPT_OK && first.committed; });
+    const bool held = !g_hold && ckpt_get_stats(r.ctx, 2, &st) == CKPT_OK && !st.d2h_done;
+    g_release = true;
+    REQUIRE(committed && held && pieces > 2);
+    g_emu_submit_hook = nullptr;
+    REQUIRE(ckpt_flush(r.ctx, CKPT_ITER_ALL) == CKPT_OK);
+    g_before_write = nullptr;
+    r.restored(1);
+    r.restored(2);
+}
+
 int main(int argc, char **argv) {
     if (argc < 3) return 2;
     const std::string dir = argv[1], what = argv[2];
     if (what == "end") end_of_copies(dir);
     else if (what == "restore" && argc > 4) restore(dir, strtoull(argv[3], nullptr, 10), strtoull(argv[4], nullptr, 10));
     else if (what == "events") events(dir);
+    else if (what == "straight") straight(dir);
     else if (what == "one" && argc > 3) one_chunk(dir, strtoull(argv[3], nullptr, 10));
     else return 2;
     printf("ok %s\n", what.c_str());

@@ -33,6 +33,10 @@ def test_the_end_of_the_copies_is_seen_before_the_last_chunk_is_written(emu, tmp
     _run(emu, tmp_path, "end")
 
 
+def test_a_straight_snapshot_does_not_wait_for_the_next_one(emu, tmp_path):
+    _run(emu, tmp_path, "straight")
+
+
 # chunks sent in pieces, and (more than sixteen pieces) as a whole in between
 @pytest.mark.parametrize("chunk,slots", [(64 << 10, 2), (64 << 10, 3), (128 << 10, 2), (128 << 10, 3), (128 << 10, 20)])
 def test_a_restore_keeps_two_chunks_under_way(emu, tmp_path, chunk, slots):
