@@ -245,12 +245,6 @@ int ckpt_init(const ckpt_config *cfg, ckpt_ctx **out) {
     if (rc.dma_chunk_bytes >= DSLLM_SCATTER_BYTES && !create_events(c->ev_sent, c->dma.size() - 1, c->n_slots)) return cleanup_fail(CKPT_EHIP, hipGetErrorString(e));
     if (c->shares_last_chunks() && !create_events(c->ev_part, c->dma.size() + 1, (rc.dma_chunk_bytes + kPartBytes - 1) / kPartBytes))
         return cleanup_fail(CKPT_EHIP, hipGetErrorString(e));
-    if (c->dma.size() > 1 && rc.dma_chunk_bytes > kPieceBytes) {
-        std::vector<std::vector<hipEvent_t>> fine;
-        const bool made = create_events(fine, 1, kFineParts);
-        c->ev_fine.swap(fine[0]);
-        if (!made) return cleanup_fail(CKPT_EHIP, hipGetErrorString(e));
-    }
     trace("init: slot events created");
     for (int k = 0; k < rc.n_dma_streams; k++) {
         hipEvent_t ev;
@@ -651,7 +645,6 @@ int ckpt_destroy(ckpt_ctx *c) {
     for (auto ev : c->ev_slot) (void)hipEventDestroy(ev);
     for (auto &v : c->ev_sent) for (auto ev : v) (void)hipEventDestroy(ev);
     for (auto &v : c->ev_part) for (auto ev : v) (void)hipEventDestroy(ev);
-    for (auto ev : c->ev_fine) (void)hipEventDestroy(ev);
     for (auto ev : c->ev_pack_start) (void)hipEventDestroy(ev);
     for (auto ev : c->ev_packed) (void)hipEventDestroy(ev);
     for (auto ev : c->ev_pack_end) (void)hipEventDestroy(ev);

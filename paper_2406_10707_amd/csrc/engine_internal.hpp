@@ -138,15 +138,24 @@ constexpr uint64_t kReadPieceBytes = kPieceBytes / 4 < 4096 ? 4096 : kPieceBytes
 // copy, two hide that from each other: 57.0 GB/s to the device in pieces of 4 MiB (one stream 50.4, whole chunks 57.6), 56.4 to the
 // host in parts of 16 MiB (55.1, 57.1).
 constexpr uint64_t kSendBytes = kPieceBytes, kPartBytes = 4 * kPieceBytes;
-// A snapshot's last chunk (its only one, if it has one) goes in up to twelve parts of 2 to 16 MiB, and a part is written in four pieces while the next
-// ones land: what is left behind the last copy is a part of that, shared by the I/O threads. The first part is half as long as the others, as copies of
-// two streams share the link and equal ones land in pairs. Request to committed file, as one copy / in 8 equal parts / in 8 / in 12:
-//   5.5 MB 398, 285, 262, 265 us     21 MB 887, 669, 620, 606     37 MB 1455, 963, 1008, 939     64 MB 2100, 1556, 1584, 1428
-// 107 MB in a chunk of 256 MiB 3323, 2476, 2407, 2284; in two of 64 MiB, where parts of 16 MiB were the rule, 2497, 2245, 2275, 2242.
-constexpr int kFineParts = 12;
-inline uint64_t fine_part_bytes(uint64_t chunk_bytes) {
-    const uint64_t unit = std::max<uint64_t>(kPieceBytes / 4 / kAlign * kAlign, kAlign);
-    return std::min(kPartBytes, std::max(2 * unit, (chunk_bytes / (kFineParts - 1) + unit) / unit * unit));
+// A snapshot's only chunk goes in a copy for every 64 MiB that it has begun, all on one stream, and a copy is written while the next one lands. The
+// caller's update waits for the last of them, and every copy more, with its event, takes 14 us longer: about 1 % here. (On several streams 7 us with the
+// system runtime, where they land one after the other all the same, and 4 with PyTorch's, where two side by side land together.) Window (request to last copy) and request to committed file in us, as one copy / in twelve parts of 2 to 16 MiB / in these:
+//    4.3 MiB  184, 194, 178   363, 241, 265       9.1 MiB  250, 289, 249   461, 331, 397       17 MiB  417, 475, 404   689, 524, 655
+//     33 MiB  713, 777, 719  1231, 852, 1139       70 MiB  1425, 1506, 1441  2316, 1587, 1890   191 MiB  3683, 3777, 3721  6111, 4032, 4495
+// The windows are as long beside a GEMM loop. Parts of 32 MiB: 70 MiB 1466 and 1765.
+constexpr uint64_t kOneChunkStep = 16 * kPieceBytes;
+inline uint64_t one_chunk_part_bytes(uint64_t chunk_bytes) {
+    const uint64_t n = (chunk_bytes + kOneChunkStep - 1) / kOneChunkStep;
+    return ((chunk_bytes + n - 1) / n + kAlign - 1) / kAlign * kAlign;
+}
+// It is written in pieces that the I/O threads share evenly: in pieces of kPieceBytes, 5.3 MiB are two, of which one thread writes the longer one
+// alone (363 us to the committed file, 283 in four). At least half a MiB, for which a second thread's waking pays: 0.7 MiB, packed straight into
+// the ring, 91 us in two pieces, 110 in one; 1.4 MiB 112 in three, 123 in two.
+constexpr uint64_t kLeastPieceBytes = std::min<uint64_t>(512 << 10, kPieceBytes);
+inline uint64_t even_piece_bytes(uint64_t part_bytes, uint64_t threads) {
+    const uint64_t rounds = (part_bytes + threads * kPieceBytes - 1) / (threads * kPieceBytes), n = rounds * threads;
+    return std::max(kLeastPieceBytes, ((part_bytes + n - 1) / n + kAlign - 1) / kAlign * kAlign);
 }
 // On restore, chunks of at least this size are sent to the device piece by piece, and each is scattered by a launch of its own as soon as it
 // is there. Smaller ones are sent whole and scattered together up to this size: a launch and its wait cost the
@@ -188,7 +197,6 @@ struct ckpt_ctx {
     std::vector<hipEvent_t> ev_slot;                      // per ring slot: copy into or out of the slot done
     std::vector<std::vector<hipEvent_t>> ev_sent;         // restore in chunks that may be sent on several streams, [dma stream - 1][slot]: the other streams' copies
     std::vector<std::vector<hipEvent_t>> ev_part;         // [chunks from the end][part]: part of one of a snapshot's last chunks
-    std::vector<hipEvent_t> ev_fine;                      // smaller parts of a snapshot's last chunk
     // restore: what the stream had to copy when the slot's chunk was sent (whichever stream that is, if it is always one)
     hipEvent_t sent_event(size_t stream, uint64_t slot) const { return stream == 0 || ev_sent.empty() ? ev_slot[slot] : ev_sent[stream - 1][slot]; }
     bool shares_last_chunks() const { return dma.size() > 1 && cfg.dma_chunk_bytes > dsllm::kPartBytes; }

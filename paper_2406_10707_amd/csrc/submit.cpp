@@ -10,9 +10,6 @@ using namespace dsllm;
 // rate but hold compute units meanwhile, so the line is drawn where the gain is still several per cent). Not under
 // policy PACK, whose window closes with the pack kernel: writing to device memory ends sooner.
 constexpr uint64_t kStraightBytes = 4ull << 20;
-// Its pieces for the I/O threads: a quarter each, half a MiB at least. As one piece, which one thread writes, and in pieces:
-// 1.7 MB 204 -> 158 us, 3.3 MB 292 -> 205, 4.3 MB 355 -> 250; below a MiB a second thread's waking takes as long as the writing.
-constexpr uint64_t kStraightPieces = 2ull << 20;
 static bool packs_straight_into_ring(const Plan &p, int policy) {
     return policy == CKPT_WINDOW_D2H && p.n_chunks == 1 && p.data_bytes <= kStraightBytes && p.segs.size() == 1 && p.segs[0].kind == CKPT_SEG_STAGED;
 }
@@ -148,22 +145,22 @@ static void submit_one(ckpt_ctx *c, const std::shared_ptr<Snap> &sp) {
         c->slot_state[slot] = SLOT_BUSY;
         return slot;
     };
-    // Chunk ch goes to the file in pieces of at most piece_bytes. Its arrival in `slot` is the event `whole`, or part by part those in
-    // `parts`, the first part shorter by `less` than the part_bytes of the others. A piece ends where its part does: it waits for one event.
-    auto hand_to_io = [&](uint64_t ch, uint64_t slot, hipEvent_t whole, uint64_t piece_bytes = kPieceBytes, uint64_t part_bytes = 0, const hipEvent_t *parts = nullptr, uint64_t less = 0) {
+    // Chunk ch goes to the file in pieces of at most piece_bytes. Its arrival in `slot` is the event `whole`, or part by part of part_bytes
+    // those in `parts`. A piece ends where its part does: it waits for one event.
+    auto hand_to_io = [&](uint64_t ch, uint64_t slot, uint64_t piece_bytes, hipEvent_t whole, uint64_t part_bytes = 0, const hipEvent_t *parts = nullptr) {
         const uint64_t nbytes = p.chunk_bytes(ch);
         uint32_t n_pieces = 0;
         {
             std::lock_guard<std::mutex> lk(c->mu);
             for (uint64_t at = 0; at < nbytes; n_pieces++) {
-                const uint64_t part = parts ? (at + less) / part_bytes : 0;
+                const uint64_t part = parts ? at / part_bytes : 0;
                 IoJob job;
                 job.kind = IoJob::WRITE;
                 job.snap = sp;
                 job.slot = slot;
                 job.slot_off = at;
                 job.file_off = p.header_bytes + ch * CH + at;
-                job.nbytes = std::min(piece_bytes, (parts ? std::min(nbytes, (part + 1) * part_bytes - less) : nbytes) - at);
+                job.nbytes = std::min(piece_bytes, (parts ? std::min(nbytes, (part + 1) * part_bytes) : nbytes) - at);
                 job.landed = parts ? parts[part] : whole;
                 at += job.nbytes;
                 job.last = ch + 1 == p.n_chunks && (parts ? at == nbytes : job.slot_off == 0);
@@ -196,7 +193,7 @@ static void submit_one(ckpt_ctx *c, const std::shared_ptr<Snap> &sp) {
         if ((e = launch_pack(s->dev_tiles, p.tiles.size(), c->ring + slot * CH, 0, c->pack_stream, c->ev_pack_start[0], c->ev_pack_end[0])) != hipSuccess)
             hip_fail("pack launch", e);
         if ((e = hipEventRecord(c->ev_slot[slot], c->pack_stream)) != hipSuccess) hip_fail("record", e);
-        hand_to_io(0, slot, c->ev_slot[slot], (std::max(p.data_bytes, kStraightPieces) / 4 + kAlign - 1) / kAlign * kAlign);
+        hand_to_io(0, slot, even_piece_bytes(p.data_bytes, uint64_t(c->cfg.n_io_threads)), c->ev_slot[slot]);
         all_submitted();
         return;
     }
@@ -248,17 +245,16 @@ static void submit_one(ckpt_ctx *c, const std::shared_ptr<Snap> &sp) {
     // chunks of more than 64 MiB: beside the training step every copy more costs the system runtime some 40 us (1.74 GB in chunks of
     // 256 MiB, the last three in parts: copies at 55.8 GB/s instead of 56.6), and the end is little of the whole there. In chunks of 64 MiB the
     // copies beside the step pay too, 55.3 GB/s instead of 55.9, with the same stall; alone the file is committed sooner, 0.2 GB 4.6 -> 4.1 ms,
-    // 1 GB 20.0 -> 19.6 (in chunks of 256 MiB 22.0 -> 19.8), 1.7 GB 31.9 -> 31.5. Two chunks in parts cost as much as three. The last one's parts are
-    // smaller (kFineParts), and so are a single chunk's, whatever its size.
-    uint64_t shared = 0;
-    uint64_t fine_bytes = 0;         // of the last chunk's parts, if they are smaller than the others'
-    if (p.n_chunks == 1 ? !c->ev_fine.empty() : c->shares_last_chunks() && (CH <= 4 * kPartBytes || p.n_chunks <= 2 * (nk + 1))) {
+    // 1 GB 20.0 -> 19.6 (in chunks of 256 MiB 22.0 -> 19.8), 1.7 GB 31.9 -> 31.5. Two chunks in parts cost as much as three. (Parts of
+    // 2 to 16 MiB of the last chunk alone: 0.1 GB committed 6 % sooner, but a window 3 % longer.) A single chunk has a rule of its own (kOneChunkStep).
+    const bool one = p.n_chunks == 1;
+    const uint64_t part_bytes = one ? one_chunk_part_bytes(p.data_bytes) : kPartBytes;
+    uint64_t shared = 0;             // so many of the last chunks go in parts
+    if (c->shares_last_chunks() && (one ? part_bytes < p.data_bytes : CH <= 4 * kPartBytes || p.n_chunks <= 2 * (nk + 1))) {
         std::lock_guard<std::mutex> lk(c->mu);
-        if (!c->prev_job || c->prev_job->committed) {
-            shared = std::min<uint64_t>(p.n_chunks, nk + 1);
-            fine_bytes = fine_part_bytes(p.chunk_bytes(p.n_chunks - 1));
-        }
+        if (!c->prev_job || c->prev_job->committed) shared = std::min<uint64_t>(p.n_chunks, nk + 1);
     }
+    const uint64_t piece_bytes = one ? even_piece_bytes(shared ? part_bytes : p.data_bytes, uint64_t(c->cfg.n_io_threads)) : kPieceBytes;
     for (uint64_t sc = 0; sc < std::min<uint64_t>(ahead, p.n_superchunks); sc++) enqueue_pack(sc);
     for (uint64_t sc = 0; sc < p.n_superchunks; sc++) {
         const uint64_t stage = sc % c->n_stage;
@@ -280,11 +276,9 @@ static void submit_one(ckpt_ctx *c, const std::shared_ptr<Snap> &sp) {
             // the chunk's segments: packed bytes out of staging, large tensors out of their own memory,
             // the padding behind those zero-filled here (the slot belongs to this thread until the copy event)
             uint8_t *slot_base = c->ring + slot * CH;
-            const bool fine = in_parts && ch + 1 == p.n_chunks && fine_bytes < kPartBytes;
-            const uint64_t part_bytes = fine ? fine_bytes : in_parts ? kPartBytes : CH;
-            const uint64_t less = fine ? part_bytes / 2 / kAlign * kAlign : 0;       // by which the first part is shorter than the others
+            const hipEvent_t *parts = in_parts ? c->ev_part[p.n_chunks - 1 - ch].data() : nullptr;
+            auto stream_of = [&](uint64_t part) { return c->dma[one ? k : (k + part) % nk]; };
             uint64_t part = 0;
-            const hipEvent_t *parts = fine ? c->ev_fine.data() : in_parts ? c->ev_part[p.n_chunks - 1 - ch].data() : nullptr;
             for (uint64_t j = p.chunk_first_seg[ch]; j < p.chunk_first_seg[ch + 1]; j++) {
                 const ckpt_segment &sg = p.segs[j];
                 const uint64_t at = sg.data_off - ch * CH;
@@ -298,17 +292,17 @@ static void submit_one(ckpt_ctx *c, const std::shared_ptr<Snap> &sp) {
                 const void *src = sg.kind == CKPT_SEG_DIRECT ? reinterpret_cast<const void *>(sg.src)
                                                              : static_cast<const void *>(stage_base + (sg.data_off - sc * SC));
                 for (uint64_t done = 0; done < sg.nbytes;) {
-                    for (; part < (at + done + less) / part_bytes; part++)      // every copy of an earlier part is enqueued
-                        if ((e = hipEventRecord(parts[part], c->dma[(k + part) % nk])) != hipSuccess) hip_fail("record", e);
-                    const uint64_t n = std::min(sg.nbytes - done, (part + 1) * part_bytes - less - (at + done));
-                    e = hipMemcpyAsync(dst + done, static_cast<const uint8_t *>(src) + done, n, hipMemcpyDeviceToHost, c->dma[(k + part) % nk]);
+                    for (; in_parts && part < (at + done) / part_bytes; part++)      // every copy of an earlier part is enqueued
+                        if ((e = hipEventRecord(parts[part], stream_of(part))) != hipSuccess) hip_fail("record", e);
+                    const uint64_t n = std::min(sg.nbytes - done, (in_parts ? (part + 1) * part_bytes : CH) - (at + done));
+                    e = hipMemcpyAsync(dst + done, static_cast<const uint8_t *>(src) + done, n, hipMemcpyDeviceToHost, stream_of(part));
                     if (e != hipSuccess) hip_fail("hipMemcpyAsync D2H", e);
                     done += n;
                 }
             }
             if (in_parts) {
-                for (; part * part_bytes < p.chunk_bytes(ch) + less; part++)
-                    if ((e = hipEventRecord(parts[part], c->dma[(k + part) % nk])) != hipSuccess) hip_fail("record", e);
+                for (; part * part_bytes < p.chunk_bytes(ch); part++)
+                    if ((e = hipEventRecord(parts[part], stream_of(part))) != hipSuccess) hip_fail("record", e);
             } else if ((e = hipEventRecord(c->ev_slot[slot], c->dma[k])) != hipSuccess) hip_fail("record", e);
             const bool last = ch + 1 == p.n_chunks;
             if (ch + 1 == c1)
@@ -317,7 +311,7 @@ static void submit_one(ckpt_ctx *c, const std::shared_ptr<Snap> &sp) {
             if (last)
                 for (size_t kk = 0; kk < nk; kk++)
                     if ((e = hipEventRecord(c->ev_job_tail[kk], c->dma[kk])) != hipSuccess) hip_fail("record", e);
-            hand_to_io(ch, slot, c->ev_slot[slot], ((in_parts ? part_bytes : kPartBytes) / 4 + kAlign - 1) / kAlign * kAlign, part_bytes, parts, less);
+            hand_to_io(ch, slot, piece_bytes, c->ev_slot[slot], part_bytes, parts);
         }
         // The next pack launch goes out one round late, after this super-chunk's copies have been enqueued: its host-side
         // wait is for the copies of the previous super-chunk, and the copy engines have this one's to go on with. The

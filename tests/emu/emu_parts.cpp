@@ -4,10 +4,12 @@
 //   restore  a restore hands a chunk's copies to the device while those of the chunk before it are under way, also when the
 //            ring's slots come round again
 //   events   a context has the events that its chunks and streams need
-//   one      a shard of one chunk whose copies come late, one after the other: no piece is written before all of it has landed
+//   one      a shard of one chunk, or two, whose copies come late, one after the other: no piece is written before all of it has landed; a
+//            single chunk has a copy for every sixteen pieces' bytes, each of two chunks one for every four
 //   straight a shard that is packed straight into its slot and written in pieces, behind a slow sink: the file is committed
 //            while the next snapshot, which the end of these copies has let start, is held on its stream
 //   emu_parts <dir> end|restore|events|one|straight [<chunk bytes> <ring slots>]
+#include <algorithm>
 #include <atomic>
 #include <chrono>
 #include <cstdio>
@@ -193,18 +195,24 @@ static void events(const std::string &dir) {
 
 // Policy PACK: a chunk this small would be packed straight into its slot under the other one. Sizes that leave parts of every
 // length in pages, and pieces that don't divide them.
+static std::atomic<int> g_copies_made{0};
 static void one_chunk(const std::string &dir, uint64_t chunk) {
-    for (uint64_t pages : {chunk / 4096, chunk / 4096 - 1, chunk / 4096 * 3 / 4, chunk / 8192 + 3, chunk / 16384 + 1}) {
+    for (uint64_t pages : {chunk / 4096, chunk / 4096 - 1, chunk / 4096 * 3 / 4, chunk / 8192 + 3, chunk / 16384 + 1, chunk / 4096 + 3, chunk / 2048 - 1}) {
         Run r(dir, {4096 * pages - 4096 * 2 - 5, 4096, 77}, chunk, 2, 3, CKPT_WINDOW_PACK);
-        REQUIRE(r.lay.n_chunks == 1);
+        const uint64_t data = 4096 * pages, part = (data > chunk ? 4 : 16) * DSLLM_PIECE_BYTES;
+        REQUIRE(r.lay.data_bytes == data && r.lay.n_chunks == (data + chunk - 1) / chunk);
+        uint64_t copies = 0;
+        for (uint64_t at = 0; at < data; at += chunk) copies += chunk > 4 * DSLLM_PIECE_BYTES ? (std::min(chunk, data - at) + part - 1) / part : 1;
         for (uint64_t it = 1; it <= 2; it++) {
+            g_copies_made = 0;
             g_emu_copy_hook = [](const void *, size_t, hipMemcpyKind kind, bool starts) {
-                if (kind == hipMemcpyDeviceToHost && starts) std::this_thread::sleep_for(std::chrono::milliseconds(5));
+                if (kind == hipMemcpyDeviceToHost && starts) { g_copies_made++; std::this_thread::sleep_for(std::chrono::milliseconds(5)); }
             };
             r.snapshot(it);
             REQUIRE(ckpt_wait_immutable_window_end(r.ctx, r.compute, 0) == CKPT_OK);
             REQUIRE(ckpt_flush(r.ctx, it) == CKPT_OK);
             g_emu_copy_hook = nullptr;
+            REQUIRE(uint64_t(g_copies_made) == copies);
         }
         r.restored(1);
         r.restored(2);

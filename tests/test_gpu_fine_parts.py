@@ -1,6 +1,7 @@
-"""Snapshots of one chunk, whose copies go in up to twelve parts, the first one half as long: around the smallest size that is copied at
-all (4 MiB and a page), where the parts begin to grow with the chunk, and where they reach 16 MiB; and small ones, which the pack kernel stores over the link and
-several I/O threads write. Files against the oracle; a snapshot requested while the one before is still being written takes the other way."""
+"""Snapshots of one chunk: small ones, which the pack kernel stores over the link; from the smallest size that is copied at all (4 MiB and a
+page) up to 64 MiB in one copy; larger ones in a copy for every 64 MiB begun. Pieces that the I/O threads share evenly, one thread and more. Files
+against the oracle; the second snapshot is requested with only stream order between it and the first, whose file may still be on its way (copies are
+then not shared out)."""
 import numpy as np
 import pytest
 
@@ -14,17 +15,23 @@ MIB = 1 << 20
 
 
 @pytest.mark.parametrize("sizes,chunk,options", [
-    ([2 * MIB], 64 * MIB, {}),                                   # straight: one piece more than a quarter each
+    ([2 * MIB], 64 * MIB, {}),                                   # straight: four pieces of half a MiB
     ([2 * MIB + 1, 5], 8 * MIB, {"n_io_threads": 2}),
+    ([700_001], 8 * MIB, {"n_io_threads": 16}),                  # fewer pieces than threads
     ([4 * MIB + 1], 64 * MIB, {}),                               # the smallest copied one
     ([5 * MIB + 4095, 3], 8 * MIB, {"keep_last": 1, "prealloc_files": 2}),
-    ([22 * MIB - 4096], 64 * MIB, {}),                           # eleven times 2 MiB: the last with parts of 2 MiB
+    ([5 * MIB + 4095, 3], 8 * MIB, {"n_io_threads": 1}),
+    ([22 * MIB - 4096], 64 * MIB, {}),
     ([22 * MIB], 64 * MIB, {"n_dma_streams": 3}),
-    ([22 * MIB + 4096, 7], 64 * MIB, {"n_dma_streams": 1}),      # one stream: a single copy
+    ([22 * MIB + 4096, 7], 64 * MIB, {"n_dma_streams": 1}),
     ([9 * MIB + 1, 7, 31 * MIB + 5], 64 * MIB, {"direct_min_bytes": 4 * MIB}),
     ([9 * MIB + 1, 7, 31 * MIB + 5], 64 * MIB, {"window_policy": B.CKPT_WINDOW_PACK, "io_mode": B.CKPT_IO_PWRITE}),
-    ([165 * MIB - 8192], 192 * MIB, {}),                         # eleven times 15 MiB
-    ([165 * MIB], 192 * MIB, {}),                                # parts of 16 MiB, all alike
+    ([64 * MIB], 192 * MIB, {}),                                 # one copy
+    ([64 * MIB + 1], 192 * MIB, {}),                             # two
+    ([64 * MIB + 1], 192 * MIB, {"n_dma_streams": 1}),           # one stream: a single copy
+    ([101 * MIB, 5, 41 * MIB + 77], 192 * MIB, {"direct_min_bytes": 4 * MIB, "n_io_threads": 3}),      # three, cut within both tensors
+    ([165 * MIB - 8192], 192 * MIB, {}),
+    ([165 * MIB], 192 * MIB, {}),
 ])
 def test_snapshots_of_one_chunk(tmp_path, sizes, chunk, options):
     print(f"fine parts {sizes} chunk {chunk} {options}", flush=True)
@@ -38,13 +45,15 @@ def test_snapshots_of_one_chunk(tmp_path, sizes, chunk, options):
     ck.register_tensors(shard.descs())
     assert ck.layout()["n_chunks"] == 1
     shard.fill_device(stream)
-    wants = {}
-    for it in (1, 2):           # the second one is requested as soon as the first one's window has closed
-        shard.update(it, stream)
-        ck.snapshot_async(it, stream.cuda_stream)
+    clones = {}
+    for it in (1, 2):
         ck.wait_immutable_window_end(stream.cuda_stream)
-        stream.synchronize()
-        wants[it] = gu.readback_all(shard)
+        shard.update(it, stream)
+        clones[it] = shard.clone_all(stream)
+        ck.snapshot_async(it, stream.cuda_stream)
+    ck.wait_immutable_window_end(stream.cuda_stream)
+    stream.synchronize()
+    wants = {it: [gu.download(b) for b in bs] for it, bs in clones.items()}
     for it in (1, 2):
         ck.flush(it)
         if it == 2 or not options.get("keep_last"):
