@@ -18,10 +18,19 @@ using namespace dsllm;
 
 namespace {
 
+// Lists of more than kPackBatch tensors go in batches of four times as many with 15.5 KB of arguments: every launch
+// less is some 2 us on the card and up to 5 on the host, and the longer arguments cost 0.1 (320 tensors 9.0 us, 324 9.1). Launches of 320 -> of 1280: 360 tensors
+// 11.6 -> 8.8 us, 592 of 1 MB 12.3 -> 9.5, of 1.74 GB 523 -> 518, 2400 misaligned of 4.3 GB 1378 -> 1365, 16,000 of 5 MB 236 -> 101, of 213 MB
+// 311 -> 188. Large tensors go in launches of 320: those take hundreds of microseconds, and a long sweep in runs is slower by more than a
+// launch. Most of the bytes off the 128-byte lines: 3000 tensors of 1.5 MiB 1481 -> 1480, 1200 of 2 MiB 795 -> 801, of 3 MiB 1180 -> 1195, of 5 MiB 1958 -> 1988,
+// 400 of 17 MiB 2223 -> 2243. On them: 1200 of 3 MiB 1122 -> 1117, of 5 MiB 1847 -> 1840, of 7 MiB 2576 -> 2573, 400 of 9 MiB 1114 -> 1119, of 17 MiB
+// 2084 -> 2094.
+constexpr uint64_t kLongMean = 8ull << 20, kLongMeanOffLines = 2ull << 20;
+
 // What both entry points check before anything is launched: every tensor is device memory of the
 // current GPU and lies inside its allocation, the destination is device memory of the same GPU, 16-byte
-// aligned and large enough. Returns the data-region size and the number of tiles.
-int check_pack_arguments(const ckpt_tensor_desc *tensors, size_t n, const void *dev_dst, uint64_t dst_bytes, uint64_t *n_tiles_out) {
+// aligned and large enough. Returns the number of tiles and whether the list goes in long launches.
+int check_pack_arguments(const ckpt_tensor_desc *tensors, size_t n, const void *dev_dst, uint64_t dst_bytes, uint64_t *n_tiles_out, bool *long_launches) {
     if (!tensors || n == 0 || !dev_dst) return fail(CKPT_EINVAL, "null argument or empty tensor list");
     int dev = 0;
     HIP_TRY(nullptr, hipGetDevice(&dev));
@@ -48,7 +57,7 @@ int check_pack_arguments(const ckpt_tensor_desc *tensors, size_t n, const void *
         return nbytes > uint64_t(base) + span - a ? 2 : 0;
     };
     static const char *const why[] = {"", ": not device memory of the current GPU", ": range runs past its allocation"};
-    uint64_t off = 0, tiles = 0;
+    uint64_t off = 0, tiles = 0, off_lines = 0;
     for (size_t k = 0; k < n; k++) {
         const ckpt_tensor_desc &d = tensors[k];
         if (d.dtype & CKPT_PLACE_HOST) return fail(CKPT_EINVAL, "tensor " + std::to_string(k) + ": host-resident objects cannot be packed on the device");
@@ -56,12 +65,14 @@ int check_pack_arguments(const ckpt_tensor_desc *tensors, size_t n, const void *
         if (int bad = on_this_gpu(d.dev_ptr, d.nbytes)) return fail(CKPT_EINVAL, "tensor " + std::to_string(k) + why[bad]);
         tiles += tiles_of(off, d.nbytes, kTileBytes);
         off += (d.nbytes + kAlign - 1) / kAlign * kAlign;
+        if (uint64_t(d.dev_ptr) % 128) off_lines += d.nbytes;
     }
     if (uint64_t(dev_dst) % 16 != 0) return fail(CKPT_EINVAL, "destination must be 16-byte aligned");
     if (dst_bytes < off) return fail(CKPT_EINVAL, "destination smaller than the data region (" + std::to_string(off) + " bytes)");
     if (int bad = on_this_gpu(dev_dst, off)) return fail(CKPT_EINVAL, std::string("destination") + why[bad]);
     if (tiles > 0xFFFFFFFFull) return fail(CKPT_EINVAL, "more than 2^32 tiles");
     *n_tiles_out = tiles;
+    *long_launches = n > size_t(kPackBatch) && off / n <= (off_lines > off / 2 ? kLongMeanOffLines : kLongMean);
     return CKPT_OK;
 }
 
@@ -89,12 +100,8 @@ int enqueue_batches(const ckpt_tensor_desc *tensors, size_t n, void *dev_dst, hi
     }
     return bt.count ? launch() : CKPT_OK;
 }
-// Lists of more than kPackBatch tensors, which took several launches, go in batches of four times as many with 15.5 KB of arguments: every launch
-// less is some 2 us on the card and up to 5 on the host, and the longer arguments cost 0.1 (320 tensors 9.0 us, 324 9.1). 360 tensors 11.6 -> 8.8 us, 592 of 1 MB 12.3 ->
-// 9.5, of 50 MB 20.2 -> 17.3, of 1.74 GB 525 -> 521, 2400 misaligned of 4.3 GB 1367 -> 1354, 16,000 of 5 MB 236 -> 101, of 213 MB
-// 311 -> 188; 400 of 8.4 GB are even.
-int enqueue_pack_image(const ckpt_tensor_desc *tensors, size_t n, void *dev_dst, hipStream_t stream) {
-    return n > size_t(kPackBatch) ? enqueue_batches<LongPackBatch>(tensors, n, dev_dst, stream) : enqueue_batches<PackBatch>(tensors, n, dev_dst, stream);
+int enqueue_pack_image(const ckpt_tensor_desc *tensors, size_t n, bool long_launches, void *dev_dst, hipStream_t stream) {
+    return long_launches ? enqueue_batches<LongPackBatch>(tensors, n, dev_dst, stream) : enqueue_batches<PackBatch>(tensors, n, dev_dst, stream);
 }
 
 }  // namespace
@@ -112,20 +119,22 @@ extern "C" {
 
 int ckpt_pack_image_noalloc(const ckpt_tensor_desc *tensors, size_t n, void *dev_dst, uint64_t dst_bytes, void *hip_stream) {
     uint64_t n_tiles = 0;
-    int r = check_pack_arguments(tensors, n, dev_dst, dst_bytes, &n_tiles);
+    bool long_launches = false;
+    int r = check_pack_arguments(tensors, n, dev_dst, dst_bytes, &n_tiles, &long_launches);
     if (r) return r;
     if (n_tiles > kNoallocTiles)
         return fail(CKPT_EINVAL, "tensor list needs " + std::to_string(n_tiles) + " tiles, this entry point takes " + std::to_string(kNoallocTiles) +
                                      " (about 4 GiB of data region): use ckpt_pack_image");
-    return enqueue_pack_image(tensors, n, dev_dst, static_cast<hipStream_t>(hip_stream));
+    return enqueue_pack_image(tensors, n, long_launches, dev_dst, static_cast<hipStream_t>(hip_stream));
 }
 
 int ckpt_pack_image(const ckpt_tensor_desc *tensors, size_t n, void *dev_dst, uint64_t dst_bytes, void *hip_stream) {
     uint64_t n_tiles = 0;
-    int r = check_pack_arguments(tensors, n, dev_dst, dst_bytes, &n_tiles);
+    bool long_launches = false;
+    int r = check_pack_arguments(tensors, n, dev_dst, dst_bytes, &n_tiles, &long_launches);
     if (r) return r;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    r = enqueue_pack_image(tensors, n, dev_dst, stream);
+    r = enqueue_pack_image(tensors, n, long_launches, dev_dst, stream);
     hipError_t es = hipStreamSynchronize(stream);
     if (r) return r;
     if (es != hipSuccess) return fail(CKPT_EHIP, std::string("hipStreamSynchronize: ") + hipGetErrorString(es));
