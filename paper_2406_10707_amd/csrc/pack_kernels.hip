@@ -243,13 +243,17 @@ __global__ __launch_bounds__(kBlock) void scatter_kernel(const ckpt_tile *__rest
 #endif
 
 // Groups of pages are made from 4 MiB on: 592 tensors of 50 MB 23.8 -> 20.9 us, 288 of 250 MB 94.9 -> 92.3, 2400 of 4.3 GB (misaligned)
-// 1384 -> 1368; with fewer pages the host takes longer than the kernel (316 tensors of 3.7 MB 4.7 us either way). Not for pieces of
-// more than 16 MiB in the mean: 144 tensors of 11.3 GB take 3369 us without and 3400 with them (why was not established); 72 of 1.9 GB 578 and 575,
-// 400 of 9.7 GB 2879 and 2893.
+// 1384 -> 1368; with fewer pages the host takes longer than the kernel (316 tensors of 3.7 MB 4.7 us either way). Not where more than half of the pages
+// are in large pieces, on which waves that know their piece sooner gain little and make the front of addresses wider (as far as one can
+// tell from outside; in the Adam kernel more waves than the memory needs do the same). In order the line is at 64 MiB, without -> with groups,
+// over two cards: pieces of 4 MiB 1533 -> 1475, 17 MiB 2123 -> 2084 and 2102 -> 2097, 40 MiB 3098 -> 3056 and 3078 -> 3067, 75 MiB
+// 3344 -> 3309, 144 of 32 to 172 MiB 3345 -> 3314 and 3317 -> 3327, 1 GiB 3158 -> 3170 and 3138 -> 3181; bisection of more than 320 pieces always takes longer
+// (one of 4 GB with 1200 of 64 KiB 1324 -> 1313). In runs at 8 MiB: 1 MiB 416 -> 407,
+// 2 MiB 811 -> 799, 6 MiB 1993 -> 1985, 10 MiB even, 17 MiB 2240 -> 2255, 40 MiB 3279 -> 3297; one piece of 8 GB with 1000 of a MiB 3002 -> 3043, of
+// 4 GB with 1200 of 64 KiB 1370 -> 1391.
 #ifndef DSLLM_PACK_GROUPS_FROM
 #define DSLLM_PACK_GROUPS_FROM 1024
 #endif
-constexpr uint32_t kMostPagesEach = 4096;
 
 // Writes the pieces of `bt` to `image`, which begins with the page of the batch's first piece. A batch without pieces
 // launches one block of every kernel that finds nothing to do (it makes the runtime load the kernels' code). The arguments
@@ -257,12 +261,10 @@ constexpr uint32_t kMostPagesEach = 4096;
 template <int MOST>
 static hipError_t launch_batch(PackBatchOf<MOST> &bt, void *image, hipStream_t stream) {
     const uint32_t pages = bt.pages;
-    uint32_t off_lines = 0;      // pages of tensors that do not start on a 128-byte line
-    if (pages >= DSLLM_PACK_RUNS_FROM)
-        for (uint32_t k = 0; k < bt.count; k++)
-            if (bt.src(k) % 128) off_lines += bt.first_page[k + 1] - bt.first_page[k];
-    bt.make_groups(DSLLM_PACK_GROUPS_FROM, kMostPagesEach);
+    const uint32_t off_lines = pages >= DSLLM_PACK_RUNS_FROM ? bt.off_lines : 0;
     const bool runs = off_lines > pages / 2 || !pages, in_order = off_lines <= pages / 2;
+    const bool large = in_order ? bt.in_large > pages / 2 && bt.count <= uint32_t(kPackBatch) : bt.in_large_runs > pages / 2;
+    bt.make_groups(pages >= DSLLM_PACK_GROUPS_FROM && !large);
     auto launch = [&](const auto &args, auto runs_kernel, auto kernel) {
         const unsigned kib = pages ? pages * 4 : 1;
         if (runs) hipLaunchKernelGGL(runs_kernel, dim3((kib + 63) / 64 * 64), dim3(64), 0, stream, args, static_cast<uint8_t *>(image));

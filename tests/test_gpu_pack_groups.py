@@ -1,5 +1,6 @@
 """Lists around the sizes of the pack kernel's arguments (32, 128 and 320 tensors), with few and with enough pages for the
-look-up by groups (1024), one tensor much larger than the others and not, against the oracle's data region."""
+look-up by groups (1024), with too many of them in one tensor (off the lines more than 2048, on them more than 16384), one tensor much larger than the
+others and not, against the oracle's data region."""
 import numpy as np
 import pytest
 
@@ -12,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("n", [1, 32, 33, 128, 129, 320])
-@pytest.mark.parametrize("pages", [1023, 1024, 1025, 2500])
+@pytest.mark.parametrize("pages", [1023, 1024, 1025, 2500, 17500])
 def test_image_around_the_sizes(n, pages):
     print(f"pack groups, {n} tensors, {pages} pages", flush=True)
     for first in (True, False):          # the large tensor at either end of the list
