@@ -106,9 +106,11 @@ __global__ __launch_bounds__(64) void adam_kernel(uint16_t *__restrict__ p, floa
         p[t] = bf16_rne(master[t]);
     }
 }
-// Shared memory of a block that has room for twelve beside each other (160 KiB a compute unit, handed out in pieces of 1280 bytes); only
-// for grids that don't fit the chip's 256 x 32 wave slots at once, as it costs those that do (1 M elements 5.6 -> 6.5 us; 2.5 M 13.6 -> 12.8).
-constexpr unsigned kAdamLds = 12800, kAdamFreeBlocks = 256 * 32;
+// Shared memory of a block that has room for twelve beside each other (160 KiB a compute unit, handed out in pieces of 1280 bytes); only for grids
+// of an eighth more than the chip's 256 x 32 wave slots, as it costs those that fit them at once, and those a little larger where
+// nothing follows: 1 M elements 5.6 -> 6.5 us, one tensor of 2.15 M 14.5 -> 15.8, of 2.25 M 15.8 -> 16.6, of 2.4 M even; twenty of 2.3 M one behind the
+// other 12.6 -> 12.0 each, of 2.5 M 13.7 -> 12.9.
+constexpr unsigned kAdamLds = 12800, kAdamFreeBlocks = 256 * 36;
 
 // ------------------------------------------------------------------ flat-buffer words, copy
 

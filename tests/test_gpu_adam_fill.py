@@ -1,5 +1,5 @@
-"""The Adam step where its blocks are more than the chip has room for at once (2^21 elements: from there on they are
-launched with shared memory that limits how many run beside each other), and its rounding to bf16 in whole quads and in the tail."""
+"""The Adam step where its blocks are more than the chip has room for at once (2^21 elements) and where they are an eighth more (from there
+on they are launched with shared memory that limits how many run beside each other), and its rounding to bf16 in whole quads and in the tail."""
 import numpy as np
 import pytest
 
@@ -20,7 +20,7 @@ def _read(bufs):
     return [gu.download(b).view(dt) for b, dt in zip(bufs, (np.uint16, np.float32, np.float32, np.float32))]
 
 
-@pytest.mark.parametrize("numel", [4 * 64 * 8192, 4 * 64 * 8192 + 1, 4 * 64 * 8192 + 7])
+@pytest.mark.parametrize("numel", [4 * 64 * 8192, 4 * 64 * 8192 + 1, 4 * 64 * 8192 + 7, 4 * 64 * 9216, 4 * 64 * 9216 + 1, 4 * 64 * 9216 + 7])
 def test_adam_around_a_full_chip(numel):
     print(f"adam numel {numel}", flush=True)
     bufs = _bufs(numel)
