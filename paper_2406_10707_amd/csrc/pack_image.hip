@@ -57,7 +57,7 @@ int check_pack_arguments(const ckpt_tensor_desc *tensors, size_t n, const void *
         return nbytes > uint64_t(base) + span - a ? 2 : 0;
     };
     static const char *const why[] = {"", ": not device memory of the current GPU", ": range runs past its allocation"};
-    uint64_t off = 0, tiles = 0, off_lines = 0;
+    uint64_t off = 0, tiles = 0;
     for (size_t k = 0; k < n; k++) {
         const ckpt_tensor_desc &d = tensors[k];
         if (d.dtype & CKPT_PLACE_HOST) return fail(CKPT_EINVAL, "tensor " + std::to_string(k) + ": host-resident objects cannot be packed on the device");
@@ -65,14 +65,19 @@ int check_pack_arguments(const ckpt_tensor_desc *tensors, size_t n, const void *
         if (int bad = on_this_gpu(d.dev_ptr, d.nbytes)) return fail(CKPT_EINVAL, "tensor " + std::to_string(k) + why[bad]);
         tiles += tiles_of(off, d.nbytes, kTileBytes);
         off += (d.nbytes + kAlign - 1) / kAlign * kAlign;
-        if (uint64_t(d.dev_ptr) % 128) off_lines += d.nbytes;
     }
     if (uint64_t(dev_dst) % 16 != 0) return fail(CKPT_EINVAL, "destination must be 16-byte aligned");
     if (dst_bytes < off) return fail(CKPT_EINVAL, "destination smaller than the data region (" + std::to_string(off) + " bytes)");
     if (int bad = on_this_gpu(dev_dst, off)) return fail(CKPT_EINVAL, std::string("destination") + why[bad]);
     if (tiles > 0xFFFFFFFFull) return fail(CKPT_EINVAL, "more than 2^32 tiles");
     *n_tiles_out = tiles;
-    *long_launches = n > size_t(kPackBatch) && off / n <= (off_lines > off / 2 ? kLongMeanOffLines : kLongMean);
+    *long_launches = n > size_t(kPackBatch) && off / n <= kLongMean;
+    if (*long_launches && off / n > kLongMeanOffLines) {
+        uint64_t off_lines = 0;
+        for (size_t k = 0; k < n; k++)
+            if (uint64_t(tensors[k].dev_ptr) % 128) off_lines += tensors[k].nbytes;
+        *long_launches = off_lines <= off / 2;
+    }
     return CKPT_OK;
 }
 

@@ -254,6 +254,7 @@ __global__ __launch_bounds__(kBlock) void scatter_kernel(const ckpt_tile *__rest
 #ifndef DSLLM_PACK_GROUPS_FROM
 #define DSLLM_PACK_GROUPS_FROM 1024
 #endif
+constexpr uint32_t kLargePiece = 16384, kLargePieceRuns = 2048;      // pages: what a launch in order, or in runs, calls a large piece
 
 // Writes the pieces of `bt` to `image`, which begins with the page of the batch's first piece. A batch without pieces
 // launches one block of every kernel that finds nothing to do (it makes the runtime load the kernels' code). The arguments
@@ -261,9 +262,18 @@ __global__ __launch_bounds__(kBlock) void scatter_kernel(const ckpt_tile *__rest
 template <int MOST>
 static hipError_t launch_batch(PackBatchOf<MOST> &bt, void *image, hipStream_t stream) {
     const uint32_t pages = bt.pages;
-    const uint32_t off_lines = pages >= DSLLM_PACK_RUNS_FROM ? bt.off_lines : 0;
+    uint32_t off_lines = 0;                      // pages of pieces that do not start on a 128-byte line
+    uint32_t in_large = 0, in_large_runs = 0;    // of large pieces
+    if (pages >= DSLLM_PACK_RUNS_FROM)
+        for (uint32_t k = 0; k < bt.count; k++) {
+            const uint32_t n = bt.first_page[k + 1] - bt.first_page[k];
+            if (bt.src(k) % 128) off_lines += n;
+            if (n <= kLargePieceRuns) continue;
+            in_large_runs += n;
+            if (n > kLargePiece) in_large += n;
+        }
     const bool runs = off_lines > pages / 2 || !pages, in_order = off_lines <= pages / 2;
-    const bool large = in_order ? bt.in_large > pages / 2 && bt.count <= uint32_t(kPackBatch) : bt.in_large_runs > pages / 2;
+    const bool large = in_order ? in_large > pages / 2 && bt.count <= uint32_t(kPackBatch) : in_large_runs > pages / 2;
     bt.make_groups(pages >= DSLLM_PACK_GROUPS_FROM && !large);
     auto launch = [&](const auto &args, auto runs_kernel, auto kernel) {
         const unsigned kib = pages ? pages * 4 : 1;

@@ -18,7 +18,6 @@ constexpr uint64_t kPackPage = 4096;                  // the file format's align
 #define DSLLM_PACK_BATCH_PAGES (1u << 23)             // 32 GiB of image per launch: a grid has fewer than 2^32 work-items
 #endif
 constexpr uint32_t kPackBatchPages = DSLLM_PACK_BATCH_PAGES;
-constexpr uint32_t kLargePiece = 16384, kLargePieceRuns = 2048;      // pages: what a launch in order, or in runs, calls a large piece
 
 // A list of up to N pieces as a kernel's argument. A page's piece is between the first and the last one of its group of
 // 2^group_bits pages, where bisection finds it; with large tensors they are mostly the same.
@@ -54,12 +53,11 @@ struct PackBatchOf : PackArgs<MOST> {
     using PackArgs<MOST>::src_pad;
     using PackArgs<MOST>::first_page;
     uint32_t count;
-    uint32_t off_lines, in_large, in_large_runs;      // pages of pieces that do not start on a 128-byte line; of large pieces
 
     uint64_t src(uint32_t k) const { return src_pad[k] & 0xFFFFFFFFFFFFull; }
     uint32_t pad(uint32_t k) const { return uint32_t(src_pad[k] >> 48); }
     bool full() const { return count == uint32_t(MOST) || pages == kPackBatchPages; }
-    void clear() { count = off_lines = in_large = in_large_runs = 0; pages = first_page[0] = 0; }
+    void clear() { count = 0; pages = first_page[0] = 0; }
     // Takes as much of [addr, addr + nbytes) as there is room for (at least one page unless full()); returns the bytes taken.
     uint64_t add(uint64_t addr, uint64_t nbytes) {
         const uint64_t room = kPackBatchPages - pages;
@@ -67,9 +65,6 @@ struct PackBatchOf : PackArgs<MOST> {
         uint64_t taken = nbytes;
         if (n > room) { n = room; taken = room * kPackPage; }
         src_pad[count] = addr | ((n * kPackPage - taken) << 48);
-        if (addr % 128) off_lines += uint32_t(n);
-        if (n > kLargePiece) in_large += uint32_t(n);
-        if (n > kLargePieceRuns) in_large_runs += uint32_t(n);
         pages = first_page[++count] = pages + uint32_t(n);
         return taken;
     }
