@@ -3,7 +3,8 @@ before the library, so that the process holds one HIP runtime, PyTorch's).
 
 PyTorch owns the device memory and the stream; the library gets raw pointers and the stream handle.
 A few steps of a toy training loop with snapshots in between, files compared with the CPU oracle on
-clones taken at each boundary, then a restore into overwritten tensors."""
+clones taken at each boundary, then a restore into overwritten tensors; and the pack entry point without allocation
+in a captured graph, whose replays read the tensors as they are then."""
 import sys
 import tempfile
 
@@ -17,6 +18,34 @@ DT = {torch.bfloat16: B.CKPT_BF16, torch.float32: B.CKPT_F32}
 
 def as_bytes(t):
     return t.detach().contiguous().flatten().view(torch.uint8).cpu().numpy()
+
+
+def captured_packs(dev, stream):
+    """Lists whose descriptors fill the kernel arguments of each size (the largest 15.5 KB), one launch and several."""
+    for n in (20, 100, 300, 1000, 1400):
+        print(f"captured pack of {n} tensors", flush=True)
+        arena = torch.randint(0, 256, (n * 5000,), dtype=torch.uint8, device=dev)
+        sizes = [4096 * (k % 2) + 1 + 61 * k % 700 for k in range(n)]
+        descs = [(f"t{k}", B.CKPT_U8, (b,), arena.data_ptr() + 5000 * k + k % 3, b) for k, b in enumerate(sizes)]
+        data = sum(-(-b // 4096) * 4096 for b in sizes)
+        image, eager = (torch.full((data,), 0xEE, dtype=torch.uint8, device=dev) for _ in range(2))
+        graph = torch.cuda.CUDAGraph()
+        stream.synchronize()
+        with torch.cuda.graph(graph, stream=stream):
+            B.pack_image_noalloc(descs, image.data_ptr(), data, stream.cuda_stream)
+        with torch.cuda.stream(stream):
+            for replay in range(4):
+                arena.add_(replay + 1)
+                image.fill_(0xEE)
+                B.pack_image_noalloc(descs, eager.data_ptr(), data, stream.cuda_stream)
+                graph.replay()
+                stream.synchronize()
+                assert torch.equal(image, eager), f"replay {replay}"
+                host, off = as_bytes(image), 0
+                src = as_bytes(arena)
+                for k, b in enumerate(sizes):
+                    assert (host[off:off + b] == src[5000 * k + k % 3:5000 * k + k % 3 + b]).all(), (replay, k)
+                    off += -(-b // 4096) * 4096
 
 
 def main():
@@ -64,6 +93,7 @@ def main():
     stream.synchronize()
     for t, c in zip(state, clones[2]):
         assert torch.equal(t, c)
+    captured_packs(dev, stream)
     ck.destroy()
     print("torch interop ok:", torch.__version__, "hip", torch.version.hip, flush=True)
 
