@@ -187,7 +187,7 @@ __global__ __launch_bounds__(kBlock) void pack_kernel(const ckpt_tile *__restric
 //
 // HBM-bound. What limits a copy here is the order in which requests reach the memory: with one load and one store per
 // lane and blocks that are handed out in address order, the whole chip sweeps source and image in one narrow front.
-// Measured on MI355X, read + write: 6.76 TB/s on 11 GB of large aligned tensors, 6.6 on 1.7 GB in 592 tensors, 6.2 on
+// Measured on MI355X, read + write: 6.76 TB/s on 11 GB of large aligned tensors, 6.7 on 1.7 GB in 592 tensors, 6.3 on
 // 3.7 GB of misaligned fragments, where a wave that walks 32 KiB on its own (pack_kernel, and a kernel that writes its
 // table before it) reaches 5.73, 5.47 and 5.13. More words per lane widen the front and lose (2: 5.3 to 6.1; 4: 5.9 to
 // 6.1), four waves per block lose 5 % on aligned tensors (6.43) and win 1 % on fragments. On small lists the table was
