@@ -89,6 +89,7 @@ struct Snap {
     std::string tmp_path, final_path;
     std::atomic<uint64_t> chunks_left{0};
     std::atomic<bool> copies_over{false};   // one of the I/O threads has seen it
+    std::atomic<int> at_tails{0};           // I/O threads that may be about to ask or wait for the tail events
     hipEvent_t ev_boundary = nullptr;
     bool submitted = false, packs_submitted = false, d2h_done = false, committed = false, window_closed = false;
     Clock::time_point t_request, t_submitted, t_committed, t_first_chunk;

@@ -115,17 +115,21 @@ void dsllm::io_thread_main(ckpt_ctx *c) {
             s->have_first_chunk = true;
         }
         // The first thread to see the end of the copies says so: the next snapshot's submit waits for it, and behind a sink slower than the
-        // link the last chunk is then still to be written.
+        // link the last chunk is then still to be written. It also waits until no thread is in here that found the copies not yet over: the tail
+        // events are its own from then on, and one that asked for them late would wait for the next snapshot's copies.
         if (job.ends && !s->copies_over) {
+            s->at_tails++;
             bool over = true;
-            for (size_t k = 0; over && !s->copies_over && k < c->tails(s); k++) {   // (once another thread has seen it the events may be the next one's)
+            for (size_t k = 0; over && !s->copies_over && k < c->tails(s); k++) {
                 he = job.last ? hipEventSynchronize(c->tail(s, k)) : hipEventQuery(c->tail(s, k));
                 if (he == hipSuccess) continue;
                 if (job.last) c->fail_snapshot(s, CKPT_EHIP, std::string("tail event: ") + hipGetErrorString(he));
                 else over = false;                 // not yet, or an error that the last piece will report
                 (void)hipGetLastError();
             }
+            s->at_tails--;
             if (over && !s->copies_over.exchange(true)) finish_d2h_stats(c, s);
+            else if (s->copies_over) { std::lock_guard<std::mutex> lk(c->mu); c->cv_state.notify_all(); }
         }
         if (s->map) memcpy(s->map + job.file_off, piece, job.nbytes);   // page-cache/tmpfs sink: parallel across threads
         else if (s->fd >= 0) {

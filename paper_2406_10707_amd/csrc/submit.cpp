@@ -38,7 +38,7 @@ static void submit_one(ckpt_ctx *c, const std::shared_ptr<Snap> &sp) {
         std::unique_lock<std::mutex> lk(c->mu);
         // with retention the previous commit is also what retires an older file into the spare pool this
         // snapshot is about to draw from: wait for it (it follows the last copy by one chunk write)
-        c->cv_state.wait(lk, [&] { return c->prev_job->d2h_done && (c->cfg.keep_last == 0 || c->prev_job->committed); });
+        c->cv_state.wait(lk, [&] { return c->prev_job->d2h_done && c->prev_job->at_tails == 0 && (c->cfg.keep_last == 0 || c->prev_job->committed); });
         // a second tier that must receive every snapshot: the previous one has to be on its way there before
         // this one may start (at most one file waits for the slower tier while another is being copied);
         // this is where a slow tier holds training back, through the window wait

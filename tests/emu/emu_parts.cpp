@@ -8,7 +8,9 @@
 //            single chunk has a copy for every sixteen pieces' bytes, each of two chunks one for every four
 //   straight a shard that is packed straight into its slot and written in pieces, behind a slow sink: the file is committed
 //            while the next snapshot, which the end of these copies has let start, is held on its stream
-//   emu_parts <dir> end|restore|events|one|straight [<chunk bytes> <ring slots>]
+//   late     the thread with the last piece is held right before it asks for the end of the copies, and another one says that they are over:
+//            it does not wait for the next snapshot's
+//   emu_parts <dir> end|restore|events|one|straight|late [<chunk bytes> <ring slots>]
 #include <algorithm>
 #include <atomic>
 #include <chrono>
@@ -252,6 +254,69 @@ static void straight(const std::string &dir) {
     r.restored(2);
 }
 
+// Two I/O threads and a last chunk of two parts, the second of two pieces, which a thread each waits for. Both have written a piece of the first
+// snapshot, which tells them from the submit thread. Of an I/O thread's waits one that no write has followed is for the end of the copies.
+static thread_local bool t_io = false, t_waited = false;
+static std::atomic<bool> g_watch{false}, g_at_end{false}, g_said{false};
+static std::atomic<int> g_waits{0};
+static ckpt_ctx *g_ctx;
+static bool submitted(uint64_t it) {
+    ckpt_stats st;
+    return ckpt_get_stats(g_ctx, it, &st) == CKPT_OK && st.host_submit_ms >= 0;
+}
+static void late(const std::string &dir) {
+    const uint64_t piece = DSLLM_PIECE_BYTES, chunk = 8 * piece;
+    Run r(dir, {chunk + 4 * piece + piece + 4096}, chunk, 8, 2, CKPT_WINDOW_PACK);       // 8 pieces, then parts of 4 and of 2
+    REQUIRE(r.lay.n_chunks == 2);
+    g_ctx = r.ctx;
+    std::atomic<int> arrived{0};
+    g_before_write = [&](off_t off) {
+        t_waited = false;
+        if (g_watch && off == off_t(r.lay.header_bytes + chunk + 3 * piece)) comes_true([] { return g_waits >= 13; });    // the last piece goes to this thread
+        if (off < off_t(r.lay.header_bytes) || t_io) return;
+        t_io = true;
+        arrived++;
+        comes_true([&] { return arrived == 2; });
+    };
+    r.snapshot(5);
+    REQUIRE(ckpt_wait_immutable_window_end(r.ctx, r.compute, 0) == CKPT_OK && ckpt_flush(r.ctx, 5) == CKPT_OK && arrived == 2);
+    g_watch = true;
+    g_emu_wait_hook = [] {
+        if (!g_watch || !t_io) return;
+        if (!t_waited) {                       // for a piece
+            t_waited = true;
+            if (++g_waits == 13) comes_true([] { return g_at_end.load(); });        // the last but one
+            return;
+        }
+        g_at_end = true;                       // for the end of the copies
+        g_watch = false;
+        for (int i = 0; i < 300 && !submitted(2); i++) std::this_thread::sleep_for(std::chrono::milliseconds(1));
+        g_said = submitted(2);
+    };
+    g_compute = r.compute;
+    g_emu_copy_hook = [](const void *, size_t n, hipMemcpyKind kind, bool starts) {      // the last part lands when both wait for it
+        if (kind == hipMemcpyDeviceToHost && starts && n == DSLLM_PIECE_BYTES + 4096) comes_true([] { return g_waits >= 14; });
+    };
+    r.snapshot(1);
+    REQUIRE(ckpt_wait_immutable_window_end(r.ctx, r.compute, 1) == CKPT_OK && comes_true([] { return submitted(1); }));
+    g_hold = true;                             // the next snapshot's first stream
+    g_emu_submit_hook = [](hipStream_t s) {
+        if (s && s != g_compute && g_hold.exchange(false)) s->push([] { comes_true([] { return g_release.load(); }); });
+    };
+    r.snapshot(2);
+    ckpt_stats first;
+    const bool committed = comes_true([&] { return ckpt_get_stats(r.ctx, 1, &first) == CKPT_OK && first.committed; });
+    g_release = true;
+    REQUIRE(g_at_end && committed && !g_said);
+    g_emu_submit_hook = nullptr;
+    REQUIRE(ckpt_flush(r.ctx, CKPT_ITER_ALL) == CKPT_OK);
+    g_emu_wait_hook = nullptr;
+    g_emu_copy_hook = nullptr;
+    g_before_write = nullptr;
+    r.restored(1);
+    r.restored(2);
+}
+
 int main(int argc, char **argv) {
     if (argc < 3) return 2;
     const std::string dir = argv[1], what = argv[2];
@@ -259,6 +324,7 @@ int main(int argc, char **argv) {
     else if (what == "restore" && argc > 4) restore(dir, strtoull(argv[3], nullptr, 10), strtoull(argv[4], nullptr, 10));
     else if (what == "events") events(dir);
     else if (what == "straight") straight(dir);
+    else if (what == "late") late(dir);
     else if (what == "one" && argc > 3) one_chunk(dir, strtoull(argv[3], nullptr, 10));
     else return 2;
     printf("ok %s\n", what.c_str());

@@ -191,7 +191,10 @@ inline hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
     });
     return hipSuccess;
 }
+// a test may hold a thread that is about to wait for an event
+inline std::atomic<void (*)()> g_emu_wait_hook{nullptr};
 inline hipError_t hipEventSynchronize(hipEvent_t e) {
+    if (auto hook = g_emu_wait_hook.load()) hook();
     std::unique_lock<std::mutex> lk(e->m);
     const uint64_t gen = e->recorded;       // never recorded: returns at once, like the real call
     e->cv.wait(lk, [&] { return e->completed >= gen; });

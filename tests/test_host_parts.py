@@ -37,6 +37,10 @@ def test_a_straight_snapshot_does_not_wait_for_the_next_one(emu, tmp_path):
     _run(emu, tmp_path, "straight")
 
 
+def test_a_last_piece_does_not_wait_for_the_next_snapshot(tmp_path_factory, tmp_path):
+    _run(_build(tmp_path_factory, "thread", "-DDSLLM_PIECE_BYTES=8192ull", "-DDSLLM_HEAD_APART_TILES=1000000"), tmp_path, "late")
+
+
 # chunks sent in pieces, and (more than sixteen pieces) as a whole in between
 @pytest.mark.parametrize("chunk,slots", [(64 << 10, 2), (64 << 10, 3), (128 << 10, 2), (128 << 10, 3), (128 << 10, 20)])
 def test_a_restore_keeps_two_chunks_under_way(emu, tmp_path, chunk, slots):
